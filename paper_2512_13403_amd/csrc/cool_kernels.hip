@@ -25,8 +25,6 @@ namespace mh {
 namespace {
 
 inline unsigned nblk(long long n) { return (unsigned)((n + 255) / 256); }
-// grid of a grid-stride kernel that ends in one clock atomic per block
-inline unsigned nblk_capped(long long n) { return nblk(n) < 4096u ? nblk(n) : 4096u; }
 
 __device__ __forceinline__ float dpow(float x, float y) { return powf(x, y); }
 __device__ __forceinline__ double dpow(double x, double y) { return pow(x, y); }
@@ -121,9 +119,9 @@ __global__ __launch_bounds__(256) void k_cool_table(T* U, long long N, T gamma, 
   }
   __syncthreads();
   if (threadIdx.x == 0) {
-    atomicMax(&clk->smax, pos_bits(fmax(fmax(sRed[0], sRed[1]), fmax(sRed[2], sRed[3]))));
+    raise_max(&clk->smax, pos_bits(fmax(fmax(sRed[0], sRed[1]), fmax(sRed[2], sRed[3]))));
     if (c.rate)
-      atomicMax(&clk->crate, pos_bits(fmax(fmax(sRate[0], sRate[1]), fmax(sRate[2], sRate[3]))));
+      raise_max(&clk->crate, pos_bits(fmax(fmax(sRate[0], sRate[1]), fmax(sRate[2], sRate[3]))));
   }
   if (bad) {
     atomicAdd(&clk->bad_count, bad);
@@ -242,7 +240,7 @@ __global__ __launch_bounds__(256) void k_cool_rate(const T* __restrict__ U, long
   if ((threadIdx.x & 63) == 0) sRate[threadIdx.x >> 6] = mr;
   __syncthreads();
   if (threadIdx.x == 0)
-    atomicMax(&clk->crate, pos_bits(fmax(fmax(sRate[0], sRate[1]), fmax(sRate[2], sRate[3]))));
+    raise_max(&clk->crate, pos_bits(fmax(fmax(sRate[0], sRate[1]), fmax(sRate[2], sRate[3]))));
 }
 
 }  // namespace
@@ -251,8 +249,8 @@ template <typename T>
 hipError_t launch_cool_table(T* U, const StageGeom& g, T gamma, const double* ih,
                              const CoolTable<T>& c, DevClock* clk, hipStream_t s) {
   const long long N = (long long)g.nx * g.ny * g.nz;
-  hipLaunchKernelGGL((k_cool_table<T>), dim3(nblk_capped(N)), dim3(256), 0, s, U, N, gamma, (T)ih[0],
-                     (T)ih[1], (T)ih[2], c, clk);
+  hipLaunchKernelGGL((k_cool_table<T>), dim3(reduce_blocks(N)), dim3(256), 0, s, U, N, gamma,
+                     (T)ih[0], (T)ih[1], (T)ih[2], c, clk);
   return hipGetLastError();
 }
 
@@ -260,7 +258,8 @@ template <typename T>
 hipError_t launch_cool_rate(const T* U, const StageGeom& g, T gamma, const CoolTable<T>& c,
                             DevClock* clk, hipStream_t s) {
   const long long N = (long long)g.nx * g.ny * g.nz;
-  hipLaunchKernelGGL((k_cool_rate<T>), dim3(nblk_capped(N)), dim3(256), 0, s, U, N, gamma, c, clk);
+  hipLaunchKernelGGL((k_cool_rate<T>), dim3(reduce_blocks(N)), dim3(256), 0, s, U, N, gamma, c,
+                     clk);
   return hipGetLastError();
 }
 

@@ -53,8 +53,6 @@ constexpr int fft_elems() {
 static_assert(fft_elems<double2>() >= 8, "a radix-8 pass needs 8 values per thread");
 
 inline unsigned nblk(long long n) { return (unsigned)((n + 255) / 256); }
-// grid of a grid-stride kernel that ends in one clock atomic per block
-inline unsigned nblk_capped(long long n) { return nblk(n) < 4096u ? nblk(n) : 4096u; }
 
 template <typename T>
 T* P(char* ws, size_t off) {
@@ -410,7 +408,7 @@ __global__ __launch_bounds__(256) void k_accel_sources(T* U, const T* __restrict
   if ((threadIdx.x & 63) == 0) sRed[threadIdx.x >> 6] = m;
   __syncthreads();
   if (threadIdx.x == 0)
-    atomicMax(&clk->smax, pos_bits(fmax(fmax(sRed[0], sRed[1]), fmax(sRed[2], sRed[3]))));
+    raise_max(&clk->smax, pos_bits(fmax(fmax(sRed[0], sRed[1]), fmax(sRed[2], sRed[3]))));
   if (bad) {
     atomicAdd(&clk->bad_count, bad);
     atomicMin(&clk->bad_first, first_bad);
@@ -548,11 +546,11 @@ hipError_t fft_sources(char* ws, const MGLayout& L, const mh_grid_desc& g, bool 
   const long long N = (long long)g.n[0] * g.n[1] * g.n[2];
   const T* acc = P<T>(ws, L.fft_acc);
   if (cool)
-    hipLaunchKernelGGL((k_accel_sources<T, true>), dim3(nblk_capped(N)), dim3(256), 0, s, U, acc, N,
-                       (T)g.gamma, (T)(1.0 / g.h[0]), cp, clk, (int)cfl);
+    hipLaunchKernelGGL((k_accel_sources<T, true>), dim3(reduce_blocks(N)), dim3(256), 0, s, U, acc,
+                       N, (T)g.gamma, (T)(1.0 / g.h[0]), cp, clk, (int)cfl);
   else
-    hipLaunchKernelGGL((k_accel_sources<T, false>), dim3(nblk_capped(N)), dim3(256), 0, s, U, acc, N,
-                       (T)g.gamma, (T)(1.0 / g.h[0]), cp, clk, (int)cfl);
+    hipLaunchKernelGGL((k_accel_sources<T, false>), dim3(reduce_blocks(N)), dim3(256), 0, s, U, acc,
+                       N, (T)g.gamma, (T)(1.0 / g.h[0]), cp, clk, (int)cfl);
   return hipGetLastError();
 }
 

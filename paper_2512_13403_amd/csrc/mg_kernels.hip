@@ -528,7 +528,7 @@ __global__ __launch_bounds__(256) void k_grav_sources(T* U, const T* __restrict_
   if ((threadIdx.x & 63) == 0) sRed[threadIdx.x >> 6] = m;
   __syncthreads();
   if (threadIdx.x == 0)
-    atomicMax(&clk->smax, pos_bits(fmax(fmax(sRed[0], sRed[1]), fmax(sRed[2], sRed[3]))));
+    raise_max(&clk->smax, pos_bits(fmax(fmax(sRed[0], sRed[1]), fmax(sRed[2], sRed[3]))));
   if (bad) {
     atomicAdd(&clk->bad_count, bad);
     atomicMin(&clk->bad_first, first_bad);
@@ -542,8 +542,6 @@ __global__ void k_set_cycles(DevClock* clk, int cycles) {
 inline unsigned nblk(long long n) { return (unsigned)((n + 255) / 256); }
 // a launch over `planes` z-planes of `m` cells each: blockIdx.y is the plane
 inline dim3 plane_grid(long long m, int planes) { return dim3(nblk(m), (unsigned)planes); }
-// grid of a grid-stride kernel that ends in one clock atomic per block
-inline unsigned nblk_capped(long long n) { return nblk(n) < 4096u ? nblk(n) : 4096u; }
 
 // blocks of a two-stage reduction over n values (k_sum_partial's grid)
 inline int sum_blocks(long long n) {
@@ -946,11 +944,11 @@ hipError_t mg_gravity_step(char* ws, MGLayout& L, const mh_grid_desc& g, const m
   if (L.fft) return fft_sources<T>(ws, L, g, cool, last, cp, U, clk, s);
   const T i2h = (T)(1.0 / (2.0 * f.h));
   if (cool)
-    hipLaunchKernelGGL((k_grav_sources<T, true>), dim3(nblk_capped(N)), dim3(256), 0, s, U,
+    hipLaunchKernelGGL((k_grav_sources<T, true>), dim3(reduce_blocks(N)), dim3(256), 0, s, U,
                        P<T>(ws, f.phi[L.cur0]), n, i2h, (T)g.gamma, (T)(1.0 / f.h), cp, clk,
                        (int)last);
   else
-    hipLaunchKernelGGL((k_grav_sources<T, false>), dim3(nblk_capped(N)), dim3(256), 0, s, U,
+    hipLaunchKernelGGL((k_grav_sources<T, false>), dim3(reduce_blocks(N)), dim3(256), 0, s, U,
                        P<T>(ws, f.phi[L.cur0]), n, i2h, (T)g.gamma, (T)(1.0 / f.h), cp, clk,
                        (int)last);
   return hipGetLastError();
@@ -965,7 +963,7 @@ hipError_t mg_kick(char* ws, MGLayout& L, const mh_grid_desc& g, T* U, DevClock*
   const long long N = (long long)f.n * f.n * f.n;
   CoolParams<T> none{};
   if (L.fft) return fft_sources<T>(ws, L, g, false, true, none, U, clk, s);
-  hipLaunchKernelGGL((k_grav_sources<T, false>), dim3(nblk_capped(N)), dim3(256), 0, s, U,
+  hipLaunchKernelGGL((k_grav_sources<T, false>), dim3(reduce_blocks(N)), dim3(256), 0, s, U,
                      P<T>(ws, f.phi[L.cur0]), f.n, (T)(1.0 / (2.0 * f.h)), (T)g.gamma,
                      (T)(1.0 / f.h), none, clk, 1);
   return hipGetLastError();

@@ -97,6 +97,17 @@ __device__ __forceinline__ unsigned long long pos_bits(float v) {
 __device__ __forceinline__ unsigned long long pos_bits(double v) {
   return (unsigned long long)__double_as_longlong(v);
 }
+// Raises *p to at least v (both ordered bit patterns of pos_bits).  Atomics of
+// many workgroups on one address serialise (about 12 ns each: 65 536 of them
+// took 0.6 ms), loads of it do not, and *p only grows inside a kernel, so a
+// workgroup whose value is not above what it reads has nothing to write; one
+// that reads an older, smaller value issues the atomic as before.  A small
+// grid goes straight to the atomic: the load's latency (about 1 us) is then
+// the longer of the two.
+__device__ __forceinline__ void raise_max(unsigned long long* p, unsigned long long v) {
+  if (gridDim.x < 256 || __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < v)
+    atomicMax(p, v);
+}
 __host__ __device__ inline double bits_to_double_f32(unsigned long long b) {
   union { uint32_t u; float f; } c;
   c.u = (uint32_t)b;

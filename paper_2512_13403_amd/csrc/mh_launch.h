@@ -8,6 +8,16 @@
 
 namespace mh {
 
+// workgroups (256 threads) of a grid-stride kernel over n cells that ends in a
+// clock reduction: a cell a thread up to 512 workgroups (two per CU), then four
+// cells a thread up to 2048 (one launch round), so that few workgroups meet at
+// the clock's cache line
+inline unsigned reduce_blocks(long long n) {
+  const long long b1 = (n + 255) / 256, b4 = (n + 1023) / 1024;
+  const long long b = b1 <= 512 ? b1 : (b4 < 512 ? 512 : (b4 < 2048 ? b4 : 2048));
+  return (unsigned)(b < 1 ? 1 : b);
+}
+
 struct StageGeom {
   int nx, ny, nz;
   int bc[3];

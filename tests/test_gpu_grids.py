@@ -1,0 +1,49 @@
+"""Launch shapes: every rule that sizes a grid by the problem is run on both
+sides of its line, against the oracle or against a path that is checked
+against it elsewhere."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2512_13403_amd as mh
+import workloads as wl
+from parity import TOL, as_input, pair, rel_err
+
+pytestmark = pytest.mark.gpu
+
+
+# cells below, at and above 512 workgroups of 256 cells, and above four cells
+# a thread of 512 workgroups
+@pytest.mark.parametrize("shape", [(5, 9, 13), (64, 64, 32), (65, 64, 32), (96, 100, 101)])
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+def test_kept_step_and_signal_speed_over_grid_sizes(shape, dtype):
+    """The grid-stride end of a kept step is bitwise the fused step, and the
+    CFL step that follows is the one of the state it left (the reduced signal
+    speed), which is also what the reduction of a set state gives."""
+    import torch
+
+    nz, ny, nx = shape
+    h = (1.0 / nx, 1.0 / ny, 1.0 / nz)
+    grid = mh.grid_desc(shape, h, dtype=dtype)
+    phys = mh.physics_desc(flags=mh.SRC_FORCING | mh.SRC_COOLING)
+    a, b, c = (mh.Solver(grid, phys) for _ in range(3))
+    U = wl.random_state(shape, seed=3, vmax=0.5)
+    dt = 0.1 / max(shape)
+    a.set_state(U)
+    a.step(1, dt)
+    b.set_state(U)
+    U1, Ub = b.new_state_tensor(), b.new_state_tensor()
+    b.step_keep(dt, U1, Ub)
+    assert torch.equal(a.get_state_device(), b.get_state_device())
+    S = a.get_state().astype(np.float64)
+    v = S[1:4] / S[0]
+    p = (5.0 / 3.0 - 1.0) * (S[4] - 0.5 * S[0] * (v * v).sum(axis=0))
+    cs = np.sqrt(5.0 / 3.0 * p / S[0])
+    want = 0.4 / max(((np.abs(v[k]) + cs) / h[k]).max() for k in range(3))
+    c.set_state(a.get_state_device())
+    # sound speed and velocity each carry a few roundings of the dtype
+    tol = 16 * np.finfo(np.float64 if dtype == "f64" else np.float32).eps
+    for s in (a, b, c):
+        got = float(s.step(1, record=True)[0])
+        assert abs(got - want) <= tol * want
+        assert s.check()[0] == 0
