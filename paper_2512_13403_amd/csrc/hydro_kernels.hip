@@ -784,13 +784,31 @@ __global__ void k_clock_set(DevClock* clk, double t, long long step) {
 
 // ------------------------------------------------------------------ launchers
 
+// Planes per workgroup.  A chunk costs its planes plus about 1.2 planes of
+// prologue (four planes converted and one z face), and a CU works through
+// ceil(workgroups / 256) chunks; in fp32 two workgroups share a CU and cover
+// each other's barriers, so a launch of at most one per CU takes 1.4 times as
+// long per plane (fp64 holds one per CU by its registers).  The chunk that
+// makes the least of this is taken, the longest on a tie.  Against halving the
+// chunk until 4096 workgroups are there, but not below four planes (stage 1 /
+// stage 2, us): 128 x 16 x 16 fp64 21.6 / 26.2 -> 11.1 / 13.7, 64^3 fp32
+// 14.7 / 18.8 -> 11.0 / 14.7, 256^3 fp32 218 / 278 -> 207 / 260 and fp64
+// 573 / 699 -> 523 / 627; 512^3 keeps its 64 planes.
+template <typename T>
 static inline int z_chunk(const StageGeom& g) {
-  // enough workgroups to fill 256 CUs several times over, long z-marches
-  // otherwise (each chunk re-reads 4 planes of prologue)
   const long long tiles_xy = (long long)((g.nx + TX - 1) / TX) * ((g.ny + TY - 1) / TY);
-  int zc = 64;
-  while (zc > 4 && tiles_xy * ((g.nz + zc - 1) / zc) < 4096) zc >>= 1;
-  return zc < g.nz ? zc : g.nz;
+  int best = 1;
+  double least = 1e300;
+  for (int zc = 1; zc <= MAX_ZC && zc <= g.nz; ++zc) {
+    const long long wgs = tiles_xy * ((g.nz + zc - 1) / zc);
+    const long long rounds = (wgs + 255) / 256;
+    const double cost = (sizeof(T) == 4 && rounds == 1 ? 1.4 : (double)rounds) * (zc + 1.2);
+    if (cost <= least) {
+      least = cost;
+      best = zc;
+    }
+  }
+  return best;
 }
 
 template <typename T>
@@ -798,7 +816,7 @@ static void fill_geom(StageArgs<T>& a, const StageGeom& g) {
   a.nx = g.nx; a.ny = g.ny; a.nz = g.nz;
   a.bcx = g.bc[0]; a.bcy = g.bc[1]; a.bcz = g.bc[2];
   a.ncell = (long long)g.nx * g.ny * g.nz;
-  a.zc = z_chunk(g);
+  a.zc = z_chunk<T>(g);
   a.nbx = (g.nx + TX - 1) / TX;
   a.nby = (g.ny + TY - 1) / TY;
   a.nbz = (g.nz + a.zc - 1) / a.zc;

@@ -47,3 +47,20 @@ def test_kept_step_and_signal_speed_over_grid_sizes(shape, dtype):
         got = float(s.step(1, record=True)[0])
         assert abs(got - want) <= tol * want
         assert s.check()[0] == 0
+
+
+# one plane; one tile; a ragged tile pair; chunks of several planes with a
+# remainder (the chunk rule gives 1 to 17 planes here, by dtype)
+@pytest.mark.parametrize("shape", [(1, 3, 5), (2, 8, 64), (7, 9, 65), (37, 121, 190),
+                                   (150, 70, 130)])
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("bc", [(0, 0, 0), (0, 1, 1)])
+def test_steps_over_z_chunks(shape, dtype, bc):
+    nz, ny, nx = shape
+    s, oc = pair(shape, (1.0 / nx, 1.0 / ny, 1.0 / nz), bc, dtype, flags=oracle.SRC_COOLING)
+    Uin = as_input(wl.random_state(shape, seed=4, vmax=0.6), dtype)
+    dt = 0.8 * oracle.cfl_dt(oc, Uin)
+    s.set_state(Uin)
+    s.step(2, dt)
+    ref = oracle.Simulation(oc, Uin).advance(2, dt).U
+    assert rel_err(s.get_state(), ref) < TOL[dtype]
