@@ -787,8 +787,9 @@ __global__ void k_clock_set(DevClock* clk, double t, long long step) {
 // Planes per workgroup.  A chunk costs its planes plus about 1.2 planes of
 // prologue (four planes converted and one z face), and a CU works through
 // ceil(workgroups / 256) chunks; in fp32 two workgroups share a CU and cover
-// each other's barriers, so a launch of at most one per CU takes 1.4 times as
-// long per plane (fp64 holds one per CU by its registers).  The chunk that
+// each other's barriers, so one alone takes 1.4 times as long per plane, which
+// fades over more rounds as the workgroups drift apart (fp64 holds one per CU
+// by its registers).  The chunk that
 // makes the least of this is taken, the longest on a tie.  Against halving the
 // chunk until 4096 workgroups are there, but not below four planes (stage 1 /
 // stage 2, us): 128 x 16 x 16 fp64 21.6 / 26.2 -> 11.1 / 13.7, 64^3 fp32
@@ -802,7 +803,8 @@ static inline int z_chunk(const StageGeom& g) {
   for (int zc = 1; zc <= MAX_ZC && zc <= g.nz; ++zc) {
     const long long wgs = tiles_xy * ((g.nz + zc - 1) / zc);
     const long long rounds = (wgs + 255) / 256;
-    const double cost = (sizeof(T) == 4 && rounds == 1 ? 1.4 : (double)rounds) * (zc + 1.2);
+    const double alone = sizeof(T) == 4 && (rounds & 1) ? 0.4 / (double)(rounds * rounds) : 0.0;
+    const double cost = ((double)rounds + alone) * (zc + 1.2);
     if (cost <= least) {
       least = cost;
       best = zc;
