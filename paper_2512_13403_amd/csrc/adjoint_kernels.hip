@@ -59,12 +59,15 @@ __device__ __forceinline__ void prim_at(const T* __restrict__ U, long long N, lo
 // rho_L(S_L - u_L) - rho_R(S_R - u_R)), so the side, fan and wave-speed
 // branches are the ones the step took; the derivatives use the same
 // reciprocals (dc/dP = g rsq(gP rho) / 2, dc/drho = -c / (2 rho) with
-// 1/rho = gP rsq^2) instead of divisions.
+// 1/rho = gP rsq^2) instead of divisions.  Everything that belongs to the side
+// K the face fell on (its energy, flux and star state) is reversed once, for
+// the selected state, and handed to the left or right adjoint at the end; only
+// the speeds and S* have a reverse on both sides.
 template <typename T>
-__device__ void hllc_reverse(const T (&wl)[5], const T (&wr)[5], T g, T gm1inv, const T (&Fb)[5],
-                             T (&wlb)[5], T (&wrb)[5]) {
-  const T rl = wl[0], ul = wl[1], al = wl[2], bl = wl[3], pl = wl[4];
-  const T rr = wr[0], ur = wr[1], ar = wr[2], br = wr[3], pr = wr[4];
+__device__ __forceinline__ void hllc_reverse(const T (&wl)[5], const T (&wr)[5], T g, T gm1inv,
+                                             const T (&Fb)[5], T (&wlb)[5], T (&wrb)[5]) {
+  const T rl = wl[0], ul = wl[1], pl = wl[4];
+  const T rr = wr[0], ur = wr[1], pr = wr[4];
   const T gpl = g * pl, gpr = g * pr;
   const T rsl = dev_rsq(gpl * rl), rsr = dev_rsq(gpr * rr);
   const T cl = gpl * rsl, cr = gpr * rsr;
@@ -72,20 +75,25 @@ __device__ void hllc_reverse(const T (&wl)[5], const T (&wr)[5], T g, T gm1inv, 
   const bool maxL = (ul + cl) >= (ur + cr);
   const T SL = minL ? ul - cl : ur - cr;
   const T SR = maxL ? ul + cl : ur + cr;
-  const T kl = fmad(ul, ul, fmad(al, al, bl * bl)), kr = fmad(ur, ur, fmad(ar, ar, br * br));
-  const T El = fmad(pl, gm1inv, (T(0.5) * rl) * kl);
-  const T Er = fmad(pr, gm1inv, (T(0.5) * rr) * kr);
   const T dl = rl * (SL - ul), dr = rr * (SR - ur);
   const T num = fmad(-ur, dr, fmad(ul, dl, pr - pl));
   const T iden = dev_rcp(dl - dr);
   const T ss = num * iden;
   const bool left = (SL >= T(0)) || (ss >= T(0));
   const bool fan = (left ? -SL : SR) > T(0);
-  const T rK = left ? rl : rr, uK = left ? ul : ur, aK = left ? al : ar, bK = left ? bl : br;
-  const T pK = left ? pl : pr, EK = left ? El : Er, SK = left ? SL : SR, dK = left ? dl : dr;
+  const T rK = left ? rl : rr, uK = left ? ul : ur, pK = left ? pl : pr;
+  const T aK = left ? wl[2] : wr[2], bK = left ? wl[3] : wr[3];
+  const T SK = left ? SL : SR, dK = left ? dl : dr;
+  const T kK = fmad(uK, uK, fmad(aK, aK, bK * bK));
+  const T EK = fmad(pK, gm1inv, (T(0.5) * rK) * kK);
   const T mK = rK * uK;
 
-  T rKb = 0, uKb = 0, aKb = 0, bKb = 0, pKb = 0, EKb = 0, SKb = 0, dKb = 0, mKb = 0, ssb = 0;
+  // F_K = (mK, mK uK + pK, mK aK, mK bK, uK (EK + pK))
+  T mKb = fmad(Fb[3], bK, fmad(Fb[2], aK, fmad(Fb[1], uK, Fb[0])));
+  T uKb = fmad(Fb[4], EK + pK, Fb[1] * mK);
+  T pKb = fmad(Fb[4], uK, Fb[1]);
+  T aKb = Fb[2] * mK, bKb = Fb[3] * mK, EKb = Fb[4] * uK;
+  T rKb = T(0), SKb = T(0), dKb = T(0), ssb = T(0);
   if (fan) {
     const T q = dev_rcp(SK - ss);
     const T qd = q * dK;
@@ -93,94 +101,66 @@ __device__ void hllc_reverse(const T (&wl)[5], const T (&wr)[5], T g, T gm1inv, 
     const T G4 = fmad(SK - uK, EK, (ss - uK) * H);
     const T s[5] = {qd, qd * ss, qd * aK, qd * bK, q * G4};
     const T UK[5] = {rK, mK, rK * aK, rK * bK, EK};
-    T sb[5], UKb[5];
+    T sb[5];
 #pragma unroll
     for (int f = 0; f < 5; ++f) {
       SKb = fmad(Fb[f], s[f] - UK[f], SKb);
-      sb[f] = SK * Fb[f];
-      UKb[f] = -SK * Fb[f];
+      sb[f] = SK * Fb[f];  // the adjoint of s; that of UK is its negative
     }
     T qb = sb[4] * G4;
     const T G4b = sb[4] * q;
     SKb = fmad(G4b, EK, SKb);
-    uKb = fmad(-G4b, EK, uKb);
-    EKb = fmad(G4b, SK - uK, EKb);
-    ssb = fmad(G4b, H, ssb);
-    uKb = fmad(-G4b, H, uKb);
+    uKb = fmad(-G4b, EK + H, uKb);
+    EKb = fmad(G4b, SK - uK, EKb) - sb[4];
     const T Hb = G4b * (ss - uK);
-    dKb = fmad(Hb, ss, dKb);
-    ssb = fmad(Hb, dK, ssb);
+    dKb = Hb * ss;
+    ssb = fmad(G4b, H, Hb * dK);
     pKb += Hb;
     const T qdb = fmad(sb[3], bK, fmad(sb[2], aK, fmad(sb[1], ss, sb[0])));
     ssb = fmad(sb[1], qd, ssb);
-    aKb = fmad(sb[2], qd, aKb);
-    bKb = fmad(sb[3], qd, bKb);
     qb = fmad(qdb, dK, qb);
     dKb = fmad(qdb, q, dKb);
     const T Zb = -(qb * q) * q;  // q = 1/Z, Z = SK - ss
     SKb += Zb;
     ssb -= Zb;
-    rKb += fmad(UKb[3], bK, fmad(UKb[2], aK, UKb[0]));
-    mKb += UKb[1];
-    aKb = fmad(UKb[2], rK, aKb);
-    bKb = fmad(UKb[3], rK, bKb);
-    EKb += UKb[4];
+    rKb = -fmad(sb[3], bK, fmad(sb[2], aK, sb[0]));
+    mKb -= sb[1];
+    aKb = fmad(sb[2], qd - rK, aKb);
+    bKb = fmad(sb[3], qd - rK, bKb);
   }
-  // F_K = (mK, mK uK + pK, mK aK, mK bK, uK (EK + pK))
-  mKb += fmad(Fb[3], bK, fmad(Fb[2], aK, fmad(Fb[1], uK, Fb[0])));
-  uKb += fmad(Fb[4], EK + pK, Fb[1] * mK);
-  pKb += fmad(Fb[4], uK, Fb[1]);
-  aKb = fmad(Fb[2], mK, aKb);
-  bKb = fmad(Fb[3], mK, bKb);
-  EKb = fmad(Fb[4], uK, EKb);
   rKb = fmad(mKb, uK, rKb);
   uKb = fmad(mKb, rK, uKb);
+  // EK = pK / (g - 1) + rK kK / 2
+  pKb = fmad(EKb, gm1inv, pKb);
+  rKb = fmad(EKb * T(0.5), kK, rKb);
+  const T Er = EKb * rK;
+  uKb = fmad(Er, uK, uKb);
+  aKb = fmad(Er, aK, aKb);
+  bKb = fmad(Er, bK, bKb);
 
-  T rlb = 0, ulb = 0, alb = 0, blb = 0, plb = 0, Elb = 0, SLb = 0, dlb = 0;
-  T rrb = 0, urb = 0, arb = 0, brb = 0, prb = 0, Erb = 0, SRb = 0, drb = 0;
-  if (left) {
-    rlb = rKb; ulb = uKb; alb = aKb; blb = bKb; plb = pKb; Elb = EKb; SLb = SKb; dlb = dKb;
-  } else {
-    rrb = rKb; urb = uKb; arb = aKb; brb = bKb; prb = pKb; Erb = EKb; SRb = SKb; drb = dKb;
-  }
-  // ss = num / den
+  // ss = num / den, den = dl - dr, d_K = rho_K (S_K - u_K)
   const T numb = ssb * iden, denb = -(ssb * ss) * iden;
-  prb += numb;
-  plb -= numb;
-  ulb = fmad(numb, dl, ulb);
-  dlb = fmad(numb, ul, dlb);
-  urb = fmad(-numb, dr, urb);
-  drb = fmad(-numb, ur, drb);
-  dlb += denb;
-  drb -= denb;
-  rlb = fmad(dlb, SL - ul, rlb);
-  SLb = fmad(dlb, rl, SLb);
-  ulb = fmad(-dlb, rl, ulb);
-  rrb = fmad(drb, SR - ur, rrb);
-  SRb = fmad(drb, rr, SRb);
-  urb = fmad(-drb, rr, urb);
-  plb = fmad(Elb, gm1inv, plb);
-  rlb = fmad(Elb * T(0.5), kl, rlb);
-  const T Elr = Elb * rl;
-  ulb = fmad(Elr, ul, ulb);
-  alb = fmad(Elr, al, alb);
-  blb = fmad(Elr, bl, blb);
-  prb = fmad(Erb, gm1inv, prb);
-  rrb = fmad(Erb * T(0.5), kr, rrb);
-  const T Err = Erb * rr;
-  urb = fmad(Err, ur, urb);
-  arb = fmad(Err, ar, arb);
-  brb = fmad(Err, br, brb);
-  T clb = 0, crb = 0;
-  if (minL) { ulb += SLb; clb -= SLb; } else { urb += SLb; crb -= SLb; }
-  if (maxL) { ulb += SRb; clb += SRb; } else { urb += SRb; crb += SRb; }
+  const T dlb = fmad(numb, ul, left ? dKb : T(0)) + denb;
+  const T drb = fmad(-numb, ur, left ? T(0) : dKb) - denb;
+  T plb = (left ? pKb : T(0)) - numb, prb = (left ? T(0) : pKb) + numb;
+  T ulb = fmad(-dlb, rl, fmad(numb, dl, left ? uKb : T(0)));
+  T urb = fmad(-drb, rr, fmad(-numb, dr, left ? T(0) : uKb));
+  T rlb = fmad(dlb, SL - ul, left ? rKb : T(0));
+  T rrb = fmad(drb, SR - ur, left ? T(0) : rKb);
+  const T SLb = fmad(dlb, rl, left ? SKb : T(0));
+  const T SRb = fmad(drb, rr, left ? T(0) : SKb);
+  const T sll = minL ? SLb : T(0), slr = minL ? T(0) : SLb;
+  const T srl = maxL ? SRb : T(0), srr = maxL ? T(0) : SRb;
+  ulb += sll + srl;
+  urb += slr + srr;
+  const T clb = srl - sll, crb = srr - slr;
   // c = sqrt(gP / rho): dc/dP = g rsq / 2, dc/drho = -c / (2 rho), 1/rho = gP rsq^2
   plb = fmad(clb, T(0.5) * g * rsl, plb);
   rlb = fmad(-clb, (T(0.5) * cl) * (gpl * rsl * rsl), rlb);
   prb = fmad(crb, T(0.5) * g * rsr, prb);
   rrb = fmad(-crb, (T(0.5) * cr) * (gpr * rsr * rsr), rrb);
-  wlb[0] = rlb; wlb[1] = ulb; wlb[2] = alb; wlb[3] = blb; wlb[4] = plb;
-  wrb[0] = rrb; wrb[1] = urb; wrb[2] = arb; wrb[3] = brb; wrb[4] = prb;
+  wlb[0] = rlb; wlb[1] = ulb; wlb[2] = left ? aKb : T(0); wlb[3] = left ? bKb : T(0); wlb[4] = plb;
+  wrb[0] = rrb; wrb[1] = urb; wrb[2] = left ? T(0) : aKb; wrb[3] = left ? T(0) : bKb; wrb[4] = prb;
 }
 
 // limited slope phi(a, b) of a run-time limiter with its partials on the
@@ -561,7 +541,39 @@ struct FinishArgs {
   T gm1, beta, c0, c1, c2;
   const T *x0, *x1, *x2;
   T* out;
+  int xv;  // the x that is the v of J^T v itself (0, 1, 2), or -1
 };
+// the same from W and v of the cell in registers
+template <typename T>
+__device__ __forceinline__ void finish_prim(const T (&prim)[5], const T (&vc)[5], const T (&w)[5],
+                                            long long q, long long N, const FinishArgs<T>& fa) {
+  const T ir = dev_rcp(prim[0]);
+  const T vx = prim[1], vy = prim[2], vz = prim[3];
+  const T wr = w[0], wx = w[1], wy = w[2], wz = w[3], wp = w[4];
+  const T gm1 = fa.gm1;
+  T o[5];
+  o[0] = wr - (wx * vx + wy * vy + wz * vz) * ir + wp * gm1 * T(0.5) * (vx * vx + vy * vy + vz * vz);
+  o[1] = wx * ir - wp * gm1 * vx;
+  o[2] = wy * ir - wp * gm1 * vy;
+  o[3] = wz * ir - wp * gm1 * vz;
+  o[4] = wp * gm1;
+#pragma unroll
+  for (int f = 0; f < 5; ++f) o[f] *= fa.beta;
+  if (fa.x0) {
+#pragma unroll
+    for (int f = 0; f < 5; ++f) o[f] += fa.c0 * (fa.xv == 0 ? vc[f] : fa.x0[f * N + q]);
+  }
+  if (fa.x1) {
+#pragma unroll
+    for (int f = 0; f < 5; ++f) o[f] += fa.c1 * (fa.xv == 1 ? vc[f] : fa.x1[f * N + q]);
+  }
+  if (fa.x2) {
+#pragma unroll
+    for (int f = 0; f < 5; ++f) o[f] += fa.c2 * (fa.xv == 2 ? vc[f] : fa.x2[f * N + q]);
+  }
+#pragma unroll
+  for (int f = 0; f < 5; ++f) fa.out[f * N + q] = o[f];
+}
 template <typename T>
 __device__ __forceinline__ void finish_cell(const T* __restrict__ U, const T (&w)[5], long long q,
                                             long long N, const FinishArgs<T>& fa) {
@@ -673,22 +685,51 @@ __global__ __launch_bounds__(256) void k_cell_gather(const T* __restrict__ wbar,
   }
 }
 
+// a difference that is not contracted with the product behind an operand
+template <typename T>
+__device__ __forceinline__ T plain_diff(T a, T b) {
+#pragma clang fp contract(off)
+  return a - b;
+}
+
+// Minmod as a value and the branch it took: fwd (the forward difference a) or
+// bwd (the backward difference b), neither where they disagree in sign -- the
+// selections of minmod_sel.
+template <typename T, int LIM>
+__device__ __forceinline__ T slope_branch(T a, T b, bool& fwd, bool& bwd) {
+  if (LIM == LIM_NONE) {
+    fwd = bwd = false;
+    return T(0);
+  }
+  const bool same = !(a * b <= T(0)), le = fabs(a) <= fabs(b);
+  fwd = same && le;
+  bwd = same && !le;
+  return fwd ? a : (bwd ? b : T(0));
+}
+
+// The fused kernels reverse the slopes per cell, not per face.  With WLb of
+// the face above cell c and WRb of the face below it (W^L = W_c + dW_c/2,
+// W^R = W_c - dW_c/2), the slope's adjoint is dWb = (WLb - WRb)/2 and the
+// cell's own term WLb + WRb; a forward branch (dW_c = W_{c+1} - W_c) adds
+// dWb to cell c + 1 and takes it from c, a backward one adds it to c and takes
+// it from c - 1.  Five sums and two selects per field and face, where the four
+// stencil contributions of a face (slot_contrib) took about thirty.
+
 // J(U)^T v along axis AX = 1 or 2 for periodic boundaries (n >= 4) and the
 // minmod (or first-order) HLLC scheme, face reverse and gather fused: one
 // thread per (x, other) column and segment of `seg` cells along the axis
-// marches the faces c0 - 2 .. c1 in order, reverses each with the arithmetic
-// of k_face_vjp and adds its four stencil contributions (slot_contrib) to a
-// ring of four cell accumulators.  Once face f is done, cell f - 1 has all of
-// its faces (f - 3 .. f, the order in which k_cell_gather sums them, so the
-// result is bitwise the same) and leaves the ring: stored, added to or
-// finished as in k_cell_gather's MODE.  Lanes take consecutive x, so every
-// load and store of a wave is contiguous, and the face records never leave
-// registers (the two-kernel path writes and reads 44 B per face).
+// marches the faces c0 - 2 .. c1 in order, with W of the face's cells and the
+// next one, the slope of the lower cell, and the open sums of two cells in
+// registers.  After face f, cell f - 1 is complete: stored, added to or
+// finished (with W and v from registers) as in k_cell_gather's MODE.  The next
+// cell's U and v are loaded one face ahead.  Lanes take consecutive x, so
+// every load and store of a wave is contiguous.
 template <typename T, int LIM, int AX, int MODE>
 __global__ __launch_bounds__(256) void k_axis_jtv(const T* __restrict__ U, const T* __restrict__ v,
                                                   AxisGeom g, T gamma, T ih, int seg,
                                                   T* __restrict__ Wacc, FinishArgs<T> fa) {
   static_assert(AX == 1 || AX == 2, "columns along y or z");
+  constexpr bool FIN = MODE == GATHER_LAST || MODE == GATHER_FIRST_LAST;
   int d1, d2;
   other_dims<AX>(g, d1, d2);
   const int n = g.n[AX];
@@ -700,174 +741,270 @@ __global__ __launch_bounds__(256) void k_axis_jtv(const T* __restrict__ U, const
   const int o2 = (int)(r % d2), sg = (int)(r / d2);
   const int c0 = sg * seg, c1 = min(c0 + seg, n);
   const long long N = (long long)g.n[0] * g.n[1] * g.n[2];
+  const long long stride = AX == 1 ? (long long)g.n[0] : (long long)g.n[0] * g.n[1];
+  const long long base = cell_of<AX>(g, 0, o1, o2);
   const T gm1 = gamma - T(1);
   const T gm1inv = T(1) / gm1;
   constexpr int vn = 1 + AX, t1 = 1 + (AX + 1) % 3, t2 = 1 + (AX + 2) % 3;
   const int perm[5] = {0, vn, t1, t2, 4};
   auto wrapc = [&](int c) { return c < 0 ? c + n : (c >= n ? c - n : c); };
-  auto load_w = [&](int c, T (&out)[5]) {
-    T wc[5];
-    prim_at(U, N, cell_of<AX>(g, wrapc(c), o1, o2), gm1, wc);
+  // fields in the face frame, (rho, v_n, v_t1, v_t2, P or E)
+  auto load_raw = [&](const T* __restrict__ src, int c, T (&out)[5]) {
+    const T* s = src + base + wrapc(c) * stride;
 #pragma unroll
-    for (int s = 0; s < 5; ++s) out[s] = wc[perm[s]];
+    for (int k = 0; k < 5; ++k) out[k] = s[perm[k] * N];
   };
-  auto load_v = [&](int c, T (&out)[5]) {
-    const long long q = cell_of<AX>(g, wrapc(c), o1, o2);
+  auto prim = [&](const T (&u)[5], T (&w)[5]) {  // to_prim in the face frame
+    T ug[5], wg[5];
 #pragma unroll
-    for (int s = 0; s < 5; ++s) out[s] = v[perm[s] * N + q];
+    for (int k = 0; k < 5; ++k) ug[perm[k]] = u[k];
+    to_prim(ug, gm1, wg);
+#pragma unroll
+    for (int k = 0; k < 5; ++k) w[k] = wg[perm[k]];
   };
-  // stencil of face f: cells f - 1 .. f + 2; v of its left and right cells
-  T w[4][5], vl[5], vr[5];
+  // W of cells f - 1 (finish only), f, f + 1, f + 2; v of f - 1, f, f + 1;
+  // the slope of cell f with its branch
+  T wm[5], w0[5], w1[5], w2[5], vm[5], v0[5], v1[5], dw[5], un[5], vnx[5];
+  bool fwd[5], bwd[5];
+  {
+    T tmp[5];
+    load_raw(U, c0 - 3, tmp);
+    prim(tmp, wm);
+    load_raw(U, c0 - 2, tmp);
+    prim(tmp, w0);
+    load_raw(U, c0 - 1, tmp);
+    prim(tmp, w1);
+    load_raw(U, c0, un);
+    load_raw(v, c0 - 2, v0);
+    load_raw(v, c0 - 1, vnx);
 #pragma unroll
-  for (int k = 0; k < 4; ++k) load_w(c0 - 3 + k, w[k]);
-  load_v(c0 - 2, vl);
-  load_v(c0 - 1, vr);
-  // accumulators of cells f - 1 .. f + 2
-  T acc[4][5];
-#pragma unroll
-  for (int k = 0; k < 4; ++k)
-#pragma unroll
-    for (int s = 0; s < 5; ++s) acc[k][s] = T(0);
-  for (int f = c0 - 2; f <= c1; ++f) {
-    T wl[5], wr[5];
-    int fl = 0;
-#pragma unroll
-    for (int s = 0; s < 5; ++s) {
-      const T a0 = w[2][s] - w[1][s], b0 = w[1][s] - w[0][s];
-      const T a1 = w[3][s] - w[2][s], b1 = w[2][s] - w[1][s];
-      const int s0 = LIM == LIM_NONE ? 0 : minmod_sel(a0, b0);
-      const int s1 = LIM == LIM_NONE ? 0 : minmod_sel(a1, b1);
-      wl[s] = w[1][s] + T(0.5) * sel_value(s0, a0, b0);
-      wr[s] = w[2][s] - T(0.5) * sel_value(s1, a1, b1);
-      fl |= (s0 << (2 * s)) | (s1 << (10 + 2 * s));
+    for (int k = 0; k < 5; ++k) {
+      dw[k] = slope_branch<T, LIM>(plain_diff(w1[k], w0[k]), plain_diff(w0[k], wm[k]), fwd[k],
+                                   bwd[k]);
+      vm[k] = T(0);
     }
-    T Fb[5];
+  }
+  // WRb of the face below cell f, the open sum of cell f - 1, and what cell
+  // f - 1's forward branch adds to cell f
+  T wrp[5], open[5], e1p[5];
 #pragma unroll
-    for (int s = 0; s < 5; ++s) Fb[s] = (vr[s] - vl[s]) * ih;
-    T wlb[5], wrb[5];
+  for (int k = 0; k < 5; ++k) wrp[k] = open[k] = e1p[k] = T(0);
+  for (int f = c0 - 2; f <= c1; ++f) {
+    prim(un, w2);
+#pragma unroll
+    for (int k = 0; k < 5; ++k) v1[k] = vnx[k];
+    if (f < c1) {
+      load_raw(U, f + 3, un);
+      load_raw(v, f + 2, vnx);
+    }
+    T acc[5];
+    const bool emit = f - 1 >= c0;
+    const long long q = base + (long long)(f - 1) * stride;
+    if (emit && (MODE == GATHER_ADD || MODE == GATHER_LAST)) {
+#pragma unroll
+      for (int k = 0; k < 5; ++k) acc[k] = Wacc[perm[k] * N + q];
+    } else {
+#pragma unroll
+      for (int k = 0; k < 5; ++k) acc[k] = T(0);
+    }
+    T wl[5], wr[5], dn[5], Fb[5], wlb[5], wrb[5];
+    bool fwn[5], bwn[5];
+#pragma unroll
+    for (int k = 0; k < 5; ++k) {
+      dn[k] = slope_branch<T, LIM>(plain_diff(w2[k], w1[k]), plain_diff(w1[k], w0[k]), fwn[k],
+                                   bwn[k]);
+      wl[k] = fmad(T(0.5), dw[k], w0[k]);
+      wr[k] = fmad(T(-0.5), dn[k], w1[k]);
+      Fb[k] = (v1[k] - v0[k]) * ih;
+    }
     hllc_reverse<T>(wl, wr, gamma, gm1inv, Fb, wlb, wrb);
+    T done[5];
 #pragma unroll
-    for (int k = 0; k < 4; ++k)
+    for (int k = 0; k < 5; ++k) {
+      const T dwb = T(0.5) * (wlb[k] - wrp[k]);
+      const T e1 = fwd[k] ? dwb : T(0), e2 = bwd[k] ? dwb : T(0);
+      done[k] = open[k] - e2;  // cell f - 1
+      open[k] = ((wlb[k] + wrp[k]) + (e2 - e1)) + e1p[k];
+      e1p[k] = e1;
+      wrp[k] = wrb[k];
+    }
+    if (emit) {
+      if (!FIN) {
 #pragma unroll
-      for (int s = 0; s < 5; ++s) acc[k][s] += slot_contrib<T>(k, fl, s, wlb[s], wrb[s]);
-    // cell f - 1 is complete
-    if (f - 1 >= c0) {
-      const long long q = cell_of<AX>(g, f - 1, o1, o2);
-      if (MODE == GATHER_ADD) {
-#pragma unroll
-        for (int s = 0; s < 5; ++s) Wacc[perm[s] * N + q] += acc[0][s];
-      } else if (MODE == GATHER_FIRST) {
-#pragma unroll
-        for (int s = 0; s < 5; ++s) Wacc[perm[s] * N + q] = acc[0][s];
+        for (int k = 0; k < 5; ++k) Wacc[perm[k] * N + q] = acc[k] + done[k];
       } else {
-        T wc[5];
+        T pg[5], vg[5], wg[5];
 #pragma unroll
-        for (int s = 0; s < 5; ++s)
-          wc[perm[s]] = MODE == GATHER_LAST ? Wacc[perm[s] * N + q] + acc[0][s] : acc[0][s];
-        finish_cell(U, wc, q, N, fa);
+        for (int k = 0; k < 5; ++k) {
+          pg[perm[k]] = wm[k];
+          vg[perm[k]] = vm[k];
+          wg[perm[k]] = acc[k] + done[k];
+        }
+        finish_prim(pg, vg, wg, q, N, fa);
       }
     }
-    if (f == c1) break;
 #pragma unroll
-    for (int s = 0; s < 5; ++s) {
-      acc[0][s] = acc[1][s];
-      acc[1][s] = acc[2][s];
-      acc[2][s] = acc[3][s];
-      acc[3][s] = T(0);
-      w[0][s] = w[1][s];
-      w[1][s] = w[2][s];
-      w[2][s] = w[3][s];
-      vl[s] = vr[s];
+    for (int k = 0; k < 5; ++k) {
+      wm[k] = w0[k];
+      w0[k] = w1[k];
+      w1[k] = w2[k];
+      dw[k] = dn[k];
+      fwd[k] = fwn[k];
+      bwd[k] = bwn[k];
+      vm[k] = v0[k];
+      v0[k] = v1[k];
     }
-    load_w(f + 3, w[3]);
-    load_v(f + 2, vr);
   }
 }
 
 // J(U)^T v along x for periodic boundaries (nx >= 4) and the minmod (or
-// first-order) HLLC scheme, face reverse and gather fused: each wave takes a
-// segment of XSEG = 61 cells of one x row; lane L reverses the face between
-// cells x0 - 2 + L and x0 - 1 + L (the arithmetic of k_face_vjp) and puts its
-// four stencil contributions (slot_contrib) in LDS, and lane L = 2 .. 62
-// sums, for cell x0 + L - 2, the contributions of the faces on lanes L - 2 ..
-// L + 1 in that order (the order of k_cell_gather: bitwise the same result)
-// and stores, adds or finishes it as in k_cell_gather's MODE.  Three faces in
-// 64 are computed twice (by two segments); the face records stay in LDS.
-constexpr int XSEG = 61;
+// first-order) HLLC scheme: a thread per cell c, which reverses the face above
+// it (between c and c + 1).  A workgroup holds `rpb` whole rows (`len` = nx
+// cells each, the ends wrapping inside the row, no face computed twice), or,
+// for rows beyond XROW_MAX, one piece of a row: `cells` cells with three more
+// on either side (`len` = cells + 6), of which the outer ones only lend their
+// state, slope or face.  State, v, the slope, WRb and the slope's
+// contributions pass between neighbours through LDS, and each is computed
+// once, where a lane per face of 61-cell pieces converted every cell four
+// times.
+// The differences are formed with one rounding from the neighbour's factors
+// (velocity m / rho, pressure (g - 1) e), W_{c+1} - W_c = fma(m, 1/rho, -W_c).
+// A cell's backward difference rounds W_{c-1}'s product for the face above it
+// and its own for the face below it, so at a tie the two faces may take
+// different branches; each face's own branch is reversed.
+constexpr int XROW_MAX = 512;
+constexpr int XLDS = 16;  // values per thread in LDS
 
 template <typename T, int LIM, int MODE>
-__global__ __launch_bounds__(256) void k_x_jtv(const T* __restrict__ U, const T* __restrict__ v,
-                                               AxisGeom g, T gamma, T ih, T* __restrict__ Wacc,
-                                               FinishArgs<T> fa) {
-  __shared__ T sc[4][20][64];
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int n = g.n[0];
-  const int nseg = (n + XSEG - 1) / XSEG;
-  const long long wave = (long long)blockIdx.x * 4 + wv;
+__global__ __launch_bounds__(XROW_MAX) void k_x_jtv(const T* __restrict__ U,
+                                                    const T* __restrict__ v, AxisGeom g, T gamma,
+                                                    T ih, int len, int rpb, int cells, int npieces,
+                                                    T* __restrict__ Wacc, FinishArgs<T> fa) {
+  extern __shared__ __align__(16) unsigned char x_jtv_lds[];
+  const int nt = blockDim.x;
+  T* const A = reinterpret_cast<T*>(x_jtv_lds);  // [6][nt]: rho, m, 1/rho, e; then WRb
+  T* const B = A + 6 * nt;                       // [5][nt]: v; then the forward contribution
+  T* const C = B + 5 * nt;                       // [5][nt]: lower-face slope; then the backward one
+  const int n = g.n[0], tid = threadIdx.x;
   const long long nrows = (long long)g.n[1] * g.n[2];
-  const bool active = wave < nrows * nseg;
-  const int sg = (int)(wave % nseg);
-  const long long row = active ? wave / nseg : 0;
-  const int o1 = (int)(row % g.n[1]), o2 = (int)(row / g.n[1]);
-  const int x0 = sg * XSEG;
-  const long long N = (long long)g.n[0] * g.n[1] * g.n[2];
+  const long long N = nrows * n;
+  const bool whole = npieces == 1;
+  const int lr = tid / len, j = tid - lr * len;
+  const long long row =
+      whole ? (long long)blockIdx.x * rpb + lr : (long long)(blockIdx.x / npieces);
+  const int x0 = whole ? 0 : (int)(blockIdx.x % npieces) * cells - 3;
+  const bool active = lr < rpb && row < nrows;
+  // LDS columns of the cells below and above (a piece's end cells stay put)
+  const int tm = j > 0 ? tid - 1 : (whole ? tid + len - 1 : tid);
+  const int tp = j < len - 1 ? tid + 1 : (whole ? tid - (len - 1) : tid);
+  int c = x0 + j;
+  if (!whole) c = c < 0 ? c + n : (c >= n ? c % n : c);
+  const long long q = row * n + c;
   const T gm1 = gamma - T(1);
   const T gm1inv = T(1) / gm1;
-  auto wrapc = [&](int c) {
-    c %= n;
-    return c < 0 ? c + n : c;
-  };
+  const bool own = active && (whole || (j >= 3 && j < 3 + cells && x0 + j < n));
+  // u: rho, m, e with P = (g - 1) e; w the primitives
+  T u[5], ir, w[5], vc[5], dw[5], wp[5], acc[5];
+  bool fwd[5], bwd[5], fwl[5], bwl[5];  // branches at the face above and below
   if (active) {
-    const int f = x0 - 2 + lane;  // the face between cells f and f + 1
-    T w[4][5];
 #pragma unroll
-    for (int k = 0; k < 4; ++k)
-      prim_at(U, N, cell_of<0>(g, wrapc(f - 1 + k), o1, o2), gm1, w[k]);
-    T wl[5], wr[5];
-    int fl = 0;
-#pragma unroll
-    for (int s = 0; s < 5; ++s) {
-      const T a0 = w[2][s] - w[1][s], b0 = w[1][s] - w[0][s];
-      const T a1 = w[3][s] - w[2][s], b1 = w[2][s] - w[1][s];
-      const int s0 = LIM == LIM_NONE ? 0 : minmod_sel(a0, b0);
-      const int s1 = LIM == LIM_NONE ? 0 : minmod_sel(a1, b1);
-      wl[s] = w[1][s] + T(0.5) * sel_value(s0, a0, b0);
-      wr[s] = w[2][s] - T(0.5) * sel_value(s1, a1, b1);
-      fl |= (s0 << (2 * s)) | (s1 << (10 + 2 * s));
+    for (int f = 0; f < 5; ++f) {
+      u[f] = U[f * N + q];
+      vc[f] = v[f * N + q];
+      acc[f] = T(0);
     }
-    const long long ql = cell_of<0>(g, wrapc(f), o1, o2);
-    const long long qr = cell_of<0>(g, wrapc(f + 1), o1, o2);
-    T Fb[5];
+    if (own && (MODE == GATHER_ADD || MODE == GATHER_LAST)) {
 #pragma unroll
-    for (int s = 0; s < 5; ++s) Fb[s] = (v[s * N + qr] - v[s * N + ql]) * ih;
-    T wlb[5], wrb[5];
-    hllc_reverse<T>(wl, wr, gamma, gm1inv, Fb, wlb, wrb);
+      for (int f = 0; f < 5; ++f) acc[f] = Wacc[f * N + q];
+    }
+    to_prim(u, gm1, w);  // the arithmetic of the stage kernels
+    ir = dev_rcp(u[0]);
+    u[4] = fmad(-(T(0.5) * u[0]), fmad(w[1], w[1], fmad(w[2], w[2], w[3] * w[3])), u[4]);
+    A[tid] = u[0];
+    A[5 * nt + tid] = u[4];
+    A[4 * nt + tid] = ir;
 #pragma unroll
-    for (int k = 0; k < 4; ++k)
+    for (int f = 1; f < 4; ++f) A[f * nt + tid] = u[f];
 #pragma unroll
-      for (int s = 0; s < 5; ++s) sc[wv][5 * k + s][lane] = slot_contrib<T>(k, fl, s, wlb[s], wrb[s]);
+    for (int f = 0; f < 5; ++f) B[f * nt + tid] = vc[f];
   }
   __syncthreads();
-  const int c = x0 + lane - 2;
-  if (!active || lane < 2 || lane > 62 || c >= n) return;
-  T acc[5] = {T(0), T(0), T(0), T(0), T(0)};
+  if (active) {
+    const T irp = A[4 * nt + tp], irm = A[4 * nt + tm];
 #pragma unroll
-  for (int m = 0; m < 4; ++m)
-#pragma unroll
-    for (int s = 0; s < 5; ++s) acc[s] += sc[wv][5 * (3 - m) + s][lane - 2 + m];
-  const long long q = cell_of<0>(g, c, o1, o2);
-  if (MODE == GATHER_ADD) {
-#pragma unroll
-    for (int s = 0; s < 5; ++s) Wacc[s * N + q] += acc[s];
-  } else if (MODE == GATHER_FIRST) {
-#pragma unroll
-    for (int s = 0; s < 5; ++s) Wacc[s * N + q] = acc[s];
-  } else {
-    T wc[5];
-#pragma unroll
-    for (int s = 0; s < 5; ++s) wc[s] = MODE == GATHER_LAST ? Wacc[s * N + q] + acc[s] : acc[s];
-    finish_cell(U, wc, q, N, fa);
+    for (int f = 0; f < 5; ++f) {
+      const int k = f == 4 ? 5 : f;
+      const T up = A[k * nt + tp], um = A[k * nt + tm];
+      T a, b, bl;  // forward, and backward as the upper and the lower face take it
+      if (f == 0) {
+        wp[f] = up;
+        a = up - w[f];
+        b = bl = w[f] - um;
+      } else {
+        const T sp = f == 4 ? gm1 : irp, s0 = f == 4 ? gm1 : ir, sm = f == 4 ? gm1 : irm;
+        wp[f] = up * sp;
+        a = fmad(up, sp, -w[f]);
+        b = fmad(-um, sm, w[f]);
+        bl = fmad(u[f], s0, -(um * sm));
+      }
+      dw[f] = slope_branch<T, LIM>(a, b, fwd[f], bwd[f]);
+      C[f * nt + tid] = slope_branch<T, LIM>(a, bl, fwl[f], bwl[f]);
+    }
   }
+  __syncthreads();
+  T wlb[5], wrb[5];
+  if (active) {
+    T wl[5], wr[5], Fb[5];
+#pragma unroll
+    for (int f = 0; f < 5; ++f) {
+      wl[f] = fmad(T(0.5), dw[f], w[f]);
+      wr[f] = fmad(T(-0.5), C[f * nt + tp], wp[f]);
+      Fb[f] = (B[f * nt + tp] - vc[f]) * ih;
+    }
+    hllc_reverse<T>(wl, wr, gamma, gm1inv, Fb, wlb, wrb);
+#pragma unroll
+    for (int f = 0; f < 5; ++f) A[f * nt + tid] = wrb[f];
+  }
+  __syncthreads();
+  T sum[5];
+  if (active) {
+#pragma unroll
+    for (int f = 0; f < 5; ++f) {
+      const T wrp = A[f * nt + tm];
+      const T hl = T(0.5) * wlb[f], hr = T(0.5) * wrp;
+      const T e1 = (fwd[f] ? hl : T(0)) - (fwl[f] ? hr : T(0));
+      const T e2 = (bwd[f] ? hl : T(0)) - (bwl[f] ? hr : T(0));
+      sum[f] = (wlb[f] + wrp) + (e2 - e1);
+      B[f * nt + tid] = e1;
+      C[f * nt + tid] = e2;
+    }
+  }
+  __syncthreads();
+  if (!own) return;
+#pragma unroll
+  for (int f = 0; f < 5; ++f) sum[f] = acc[f] + ((sum[f] + B[f * nt + tm]) - C[f * nt + tp]);
+  if (MODE == GATHER_ADD || MODE == GATHER_FIRST) {
+#pragma unroll
+    for (int f = 0; f < 5; ++f) Wacc[f * N + q] = sum[f];
+  } else {
+    finish_prim(w, vc, sum, q, N, fa);
+  }
+}
+
+// rows per workgroup of k_x_jtv for whole rows of n <= XROW_MAX cells: the
+// count that wastes the fewest lanes of its last wave, near 256 threads
+inline int x_rows_per_block(int n) {
+  int best = 1;
+  double score = -1.0;
+  for (int r = 1; r * n <= XROW_MAX; ++r) {
+    const int t = r * n, w = (t + 63) / 64 * 64;
+    const double s = (double)t / w - 1e-4 * (t < 256 ? 256 - t : t - 256);
+    if (s > score) {
+      score = s;
+      best = r;
+    }
+  }
+  return best;
 }
 
 // out = c0 x0 + c1 x1 + c2 x2 + beta (dW/dU)^T Wacc, W = (rho, v, P) of U
@@ -1135,10 +1272,33 @@ inline unsigned nblk(long long n) { return (unsigned)((n + 255) / 256); }
 
 }  // namespace
 
-// J(U)^T v into out = c0 x0 + c1 x1 + beta J^T v (x0, x1 may be NULL)
-// cells per column segment of the fused march (k_axis_jtv)
-constexpr int ADJ_SEG = 64;
+// Cells per column segment of the fused march: a segment costs its cells plus
+// three faces it shares with its neighbours, and a SIMD works through
+// ceil(waves / 1024) segments of 64 columns; fewer than 2.2 (fp64, which holds
+// two waves by its registers: 1.4) waves leave it waiting on loads, so that
+// shorter segments gain nothing more below that.  Fixed 64-cell segments ran a
+// 32^3 march on four workgroups; one adjoint step from kept stages, fixed ->
+// rule: 64^3 fp32 362 -> 63 us, 128^3 fp32 405 -> 205 us and fp64 593 ->
+// 399 us, 256^3 1.60 ms and 3.1 ms either way.
+template <typename T>
+inline int march_segment(long long columns, int n) {
+  const double least_waves = sizeof(T) == 4 ? 2.2 : 1.4;
+  int best = n;
+  double least = 1e300;
+  for (int nseg = (n + 127) / 128; nseg <= n; ++nseg) {
+    const int seg = (n + nseg - 1) / nseg;
+    const long long threads = columns * ((n + seg - 1) / seg);
+    const double waves = (double)((threads + 65535) / 65536);
+    const double cost = (seg + 3.0) * (waves > least_waves ? waves : least_waves);
+    if (cost < least) {
+      least = cost;
+      best = seg;
+    }
+  }
+  return best;
+}
 
+// J(U)^T v into out = c0 x0 + c1 x1 + beta J^T v (x0, x1 may be NULL)
 template <typename T>
 hipError_t adj_jtv(const AdjointBuffers<T>& B, const StageGeom& geom, int limiter, int riemann,
                    T gamma,
@@ -1147,7 +1307,8 @@ hipError_t adj_jtv(const AdjointBuffers<T>& B, const StageGeom& geom, int limite
   const long long N = (long long)geom.nx * geom.ny * geom.nz;
   const int nn[3] = {geom.nx, geom.ny, geom.nz};
   const bool rt = adj_runtime_scheme(limiter, riemann);
-  const FinishArgs<T> fa{gamma - T(1), beta, c0, c1, c2, x0, x1, x2, out};
+  const FinishArgs<T> fa{gamma - T(1), beta, c0, c1, c2, x0, x1, x2, out,
+                         x0 == v ? 0 : (x1 == v ? 1 : (x2 == v ? 2 : -1))};
   // the axes with fluxes (a periodic axis of one cell has none: its fluxes
   // cancel exactly); the first one's gather stores the W adjoint, the last
   // one's adds the others and finishes the cell
@@ -1198,32 +1359,36 @@ hipError_t adj_jtv(const AdjointBuffers<T>& B, const StageGeom& geom, int limite
       MH_GATHER(AX, false);                                                                   \
     }                                                                                         \
   } while (0)
-    // y and z, periodic with at least four cells, minmod or first order:
-    // the fused column march
+    // periodic with at least four cells, minmod or first order: face reverse
+    // and gather fused, rows along x, column marches along y and z
     const bool march = !rt && geom.bc[ax] == BC_PERIODIC && nn[ax] >= 4;
     if (march && ax == 0) {
-      const long long waves = (N / nn[0]) * ((nn[0] + XSEG - 1) / XSEG);
-      const unsigned blocks = (unsigned)((waves + 3) / 4);
+      const int n = nn[0];
+      const long long rows = N / n;
+      const int npieces = n <= XROW_MAX ? 1 : (n + XROW_MAX - 7) / (XROW_MAX - 6);
+      const int rpb = npieces == 1 ? x_rows_per_block(n) : 1;
+      const int cells = (n + npieces - 1) / npieces;
+      const int len = npieces == 1 ? n : cells + 6;
+      const unsigned threads = (unsigned)((rpb * len + 63) / 64 * 64);
+      const unsigned blocks =
+          (unsigned)(npieces == 1 ? (rows + rpb - 1) / rpb : rows * npieces);
+      const size_t lds = XLDS * threads * sizeof(T);
+#define MH_XJTV_MODE(LM, MODE)                                                                \
+  hipLaunchKernelGGL((k_x_jtv<T, LM, MODE>), dim3(blocks), dim3(threads), lds, s, U, v, ag,   \
+                     gamma, ih, len, rpb, cells, npieces, B.Wacc, fa)
 #define MH_XJTV(LM)                                                                           \
   do {                                                                                        \
-    if (mode == GATHER_ADD)                                                                   \
-      hipLaunchKernelGGL((k_x_jtv<T, LM, GATHER_ADD>), dim3(blocks), dim3(256), 0, s, U, v,  \
-                         ag, gamma, ih, B.Wacc, fa);                                          \
-    else if (mode == GATHER_FIRST)                                                            \
-      hipLaunchKernelGGL((k_x_jtv<T, LM, GATHER_FIRST>), dim3(blocks), dim3(256), 0, s, U, v, \
-                         ag, gamma, ih, B.Wacc, fa);                                          \
-    else if (mode == GATHER_LAST)                                                             \
-      hipLaunchKernelGGL((k_x_jtv<T, LM, GATHER_LAST>), dim3(blocks), dim3(256), 0, s, U, v,  \
-                         ag, gamma, ih, B.Wacc, fa);                                          \
-    else                                                                                      \
-      hipLaunchKernelGGL((k_x_jtv<T, LM, GATHER_FIRST_LAST>), dim3(blocks), dim3(256), 0, s,  \
-                         U, v, ag, gamma, ih, B.Wacc, fa);                                    \
+    if (mode == GATHER_ADD) MH_XJTV_MODE(LM, GATHER_ADD);                                     \
+    else if (mode == GATHER_FIRST) MH_XJTV_MODE(LM, GATHER_FIRST);                            \
+    else if (mode == GATHER_LAST) MH_XJTV_MODE(LM, GATHER_LAST);                              \
+    else MH_XJTV_MODE(LM, GATHER_FIRST_LAST);                                                 \
   } while (0)
       if (limiter == LIM_NONE) MH_XJTV(LIM_NONE);
       else MH_XJTV(LIM_MINMOD);
 #undef MH_XJTV
+#undef MH_XJTV_MODE
     } else if (march) {
-      const int seg = nn[ax] < ADJ_SEG ? nn[ax] : ADJ_SEG;
+      const int seg = march_segment<T>(N / nn[ax], nn[ax]);
       const long long threads = (N / nn[ax]) * ((nn[ax] + seg - 1) / seg);
 #define MH_MARCH(AX, LM)                                                                      \
   do {                                                                                        \

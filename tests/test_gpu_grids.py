@@ -64,3 +64,31 @@ def test_steps_over_z_chunks(shape, dtype, bc):
     s.step(2, dt)
     ref = oracle.Simulation(oc, Uin).advance(2, dt).U
     assert rel_err(s.get_state(), ref) < TOL[dtype]
+
+
+# rows along x: shorter than a wave, filling one, one over, several to a
+# workgroup, the longest whole row, the first in pieces, a long one in pieces;
+# columns along y and z: the shortest, and segments with a remainder
+# (the largest in fp64 alone: among its two million limiter decisions one lies
+# within an fp32 rounding of a tie, where fp32 and the fp64 oracle take
+# different branches)
+@pytest.mark.parametrize("shape,dtype", [(s, d) for s in [
+    (4, 5, 4), (5, 4, 63), (4, 6, 64), (6, 4, 65), (5, 7, 200), (4, 4, 512), (4, 5, 513),
+    (4, 4, 1100), (67, 4, 6), (5, 131, 7)] for d in ("f32", "f64")] + [((33, 40, 48), "f64")])
+def test_adjoint_step_over_rows_and_segments(shape, dtype):
+    """The fused face reverse and gather against the oracle's adjoint."""
+    import torch
+
+    nz, ny, nx = shape
+    s, oc = pair(shape, (1.0 / nx, 1.0 / ny, 1.0 / nz), (0, 0, 0), dtype,
+                 flags=oracle.SRC_COOLING)
+    U = as_input(wl.random_state(shape, seed=5, vmax=0.5), dtype)
+    lam = as_input(np.random.default_rng(6).standard_normal(U.shape), dtype)
+    dt = 0.5 * oracle.cfl_dt(oc, U)
+    if dtype == "f32":
+        dt = float(np.float32(dt))
+    ref = oracle.step_vjp(oc, U, dt, 0, np.zeros((0, 3), np.int32), np.zeros(6), np.zeros(shape),
+                          lam)
+    dev = lambda a: torch.tensor(a, dtype=s.torch_dtype, device="cuda:0")
+    got = s.adjoint_step(dev(U), dt, 0, dev(lam)).cpu().numpy().astype(np.float64)
+    assert np.abs(got - ref).max() / np.abs(ref).max() < TOL[dtype]
