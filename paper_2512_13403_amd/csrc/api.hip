@@ -1059,10 +1059,14 @@ static mh_status adjoint_impl(mh_ctx* c, char* ws, AdjLayout& A, const T* Un, do
   const T gam = (T)g.gamma;
   T* gflux = static_cast<T*>(c->dflux_grad);
   if (g.integrator == MH_RK_EULER) {
-    // lam_n = cur + dt J(U^n)^T cur
+    // lam_n = cur + dt J(U^n)^T cur; the pass reads cur around each cell it
+    // writes, so a result that is to overwrite cur goes by way of lam1
+    T* dst = cur == lam_n ? lam1 : lam_n;
     if (gflux) MH_HIP(c, adj_flux_corr_vjp<T>(cur, geom, g.h, dt, gflux, c->stream));
     MH_HIP(c, adj_jtv<T>(B, geom, lim, g.riemann, gam, g.h, Un, cur, (T)dt, T(1), cur, T(0), nullptr, T(0),
-                         nullptr, lam_n, c->stream));
+                         nullptr, dst, c->stream));
+    if (dst != lam_n)
+      MH_HIP(c, hipMemcpyAsync(lam_n, dst, sbytes, hipMemcpyDeviceToDevice, c->stream));
   } else if (g.integrator == MH_RK_SSP3) {
     // lam2 = 2/3 (cur + dt J(U2)^T cur);  lam1 = 1/4 (lam2 + dt J(U1)^T lam2);
     // lam_n = cur/3 + 3/4 lam2 + lam1 + dt J(U^n)^T lam1

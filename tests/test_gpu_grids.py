@@ -92,3 +92,21 @@ def test_adjoint_step_over_rows_and_segments(shape, dtype):
     dev = lambda a: torch.tensor(a, dtype=s.torch_dtype, device="cuda:0")
     got = s.adjoint_step(dev(U), dt, 0, dev(lam)).cpu().numpy().astype(np.float64)
     assert np.abs(got - ref).max() / np.abs(ref).max() < TOL[dtype]
+
+
+@pytest.mark.parametrize("integrator", [mh.RK_EULER, mh.RK_SSP2, mh.RK_SSP3])
+def test_adjoint_step_in_place(integrator):
+    """lam_n may alias lam_np1: without sources the reverse pass reads the
+    caller's array around each cell, and must not write it before."""
+    import torch
+
+    shape = (20, 24, 72)
+    s = mh.Solver(mh.grid_desc(shape, (1 / 72, 1 / 24, 1 / 20), dtype="f64",
+                               integrator=integrator))
+    U = torch.tensor(wl.random_state(shape, seed=7, vmax=0.5), device="cuda:0")
+    lam = torch.randn(U.shape, dtype=U.dtype, device="cuda:0",
+                      generator=torch.Generator(device="cuda").manual_seed(8))
+    want = s.adjoint_step(U, 1e-3, 0, lam)
+    got = lam.clone()
+    s.adjoint_step(U, 1e-3, 0, got, out=got)
+    assert torch.equal(got, want)
