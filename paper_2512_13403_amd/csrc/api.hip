@@ -24,7 +24,7 @@ constexpr size_t ALIGN = 256;
 inline size_t align_up(size_t x) { return (x + ALIGN - 1) & ~(ALIGN - 1); }
 
 struct Layout {
-  size_t U = 0, U1 = 0, U2 = 0, cool_tab = 0, clk = 0, dtlog = 0, ou_n = 0, ou_ahat = 0, ou_coef = 0, ou_rows = 0;
+  size_t U = 0, U1 = 0, U2 = 0, speed = 0, cool_tab = 0, clk = 0, dtlog = 0, ou_n = 0, ou_ahat = 0, ou_coef = 0, ou_rows = 0;
   size_t tab[3] = {0, 0, 0};
   MGLayout mg;
   size_t total = 0;
@@ -141,6 +141,7 @@ Layout make_layout(const mh_grid_desc* g, const mh_physics_desc* p, int nmodes) 
   if (g->integrator == MH_RK_SSP3) L.U2 = take(5 * N * es);
   if ((p->flags & MH_SRC_COOLING) && p->cool_model == MH_COOL_TABLE)
     L.cool_tab = take(2 * MH_COOL_TABMAX * es);
+  L.speed = take(reduce_blocks((long long)N) * es);
   L.clk = take(sizeof(DevClock));
   L.dtlog = take(DTLOG_CAP * sizeof(double));
   if (p->flags & MH_SRC_FORCING) {
@@ -167,7 +168,10 @@ struct mh_ctx {
   size_t ws_bytes = 0;
   Layout L;
   int nmodes = 0;
-  bool smax_valid = false;
+  // where the CFL signal speed of the state is: nowhere, in the clock (left by
+  // the last kernel of a step), or as partial maxima in the workspace
+  enum Speed { SPEED_NONE, SPEED_CLOCK, SPEED_PART } speed = SPEED_NONE;
+  bool rate_valid = false;  // the clock's cooling rate (tabulated cooling) is the state's
   std::string err;
   // kernel timing (mh_set_timing): event pairs and the kind of each pair
   bool timing = false;
@@ -357,16 +361,53 @@ extern "C" mh_status mh_init(const mh_grid_desc* grid, const mh_physics_desc* ph
   return MH_OK;
 }
 
+// copies the states src[b] (or, with src null, leaves the states in place) into
+// the contexts and measures their CFL signal speeds, one launch for a batch;
+// the contexts share grid and dtype
+template <typename T>
+static hipError_t measure_states(mh_ctx* const* ctxs, int B, const T* const* src, hipStream_t s) {
+  const mh_grid_desc& g = ctxs[0]->g;
+  const StageGeom geom{g.n[0], g.n[1], g.n[2], {g.bc[0], g.bc[1], g.bc[2]}};
+  hipError_t e = hipSuccess;
+  for (int b0 = 0; b0 < B && e == hipSuccess;) {
+    StateBatch<T> sb{};
+    int nb = 0;
+    const mh_grid_desc& g0 = ctxs[b0]->g;
+    const double ih[3] = {1.0 / g0.h[0], 1.0 / g0.h[1], 1.0 / g0.h[2]};
+    // members of one launch also share spacing and gamma
+    for (; b0 + nb < B && nb < STATE_BATCH; ++nb) {
+      mh_ctx* c = ctxs[b0 + nb];
+      if (c->g.gamma != g0.gamma || c->g.h[0] != g0.h[0] || c->g.h[1] != g0.h[1] ||
+          c->g.h[2] != g0.h[2])
+        break;
+      sb.dst[nb] = c->at<T>(c->L.U);
+      sb.src[nb] = src ? src[b0 + nb] : sb.dst[nb];
+      sb.part[nb] = c->at<T>(c->L.speed);
+      c->speed = mh_ctx::SPEED_PART;
+    }
+    e = launch_state_speed<T>(sb, nb, src != nullptr, geom, (T)g0.gamma, ih, s);
+    b0 += nb;
+  }
+  return e;
+}
+
 extern "C" mh_status mh_set_state(mh_ctx* c, const void* U, int where) {
   if (!c) return MH_E_INVALID;
   if (!U || (where != MH_HOST && where != MH_DEVICE))
     return set_err(c, MH_E_INVALID, "mh_set_state: null pointer or bad location");
+  c->rate_valid = false;
+  if (where == MH_DEVICE) {
+    // the copy leaves the state's signal speed as well
+    MH_HIP(c, c->g.dtype == MH_F64 ? measure_states<double>(&c, 1, (const double* const*)&U,
+                                                            c->stream)
+                                   : measure_states<float>(&c, 1, (const float* const*)&U,
+                                                           c->stream));
+    return MH_OK;
+  }
   const size_t bytes = 5 * (size_t)c->cells() * c->esize();
-  MH_HIP(c, hipMemcpyAsync(c->ws + c->L.U, U, bytes,
-                           where == MH_HOST ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice,
-                           c->stream));
-  if (where == MH_HOST) MH_HIP(c, hipStreamSynchronize(c->stream));
-  c->smax_valid = false;
+  MH_HIP(c, hipMemcpyAsync(c->ws + c->L.U, U, bytes, hipMemcpyHostToDevice, c->stream));
+  MH_HIP(c, hipStreamSynchronize(c->stream));
+  c->speed = mh_ctx::SPEED_NONE;
   return MH_OK;
 }
 
@@ -465,16 +506,22 @@ static mh_status step_impl(mh_ctx* c, int32_t nsteps, double dt, double t_stop, 
   pa.sched_stride = sched_stride;
   const bool cfl = !(dt > 0.0) && !dt_sched;
 
-  MH_HIP(c, launch_clock_reset_health(clk, c->stream));
+  if (nsteps == 0) MH_HIP(c, launch_clock_reset_health(clk, c->stream));
   for (int s = 0; s < nsteps; ++s) {
-    if (!c->smax_valid && cfl) {
+    if (cfl && (c->speed == mh_ctx::SPEED_NONE || (table && ctab.rate && !c->rate_valid))) {
       const long tk = time_begin(c, MH_TIME_OTHER);
-      MH_HIP(c, launch_smax<T>(U, geom, (T)g.gamma, ih, clk, c->stream));
-      if (table && ctab.rate)
+      if (c->speed == mh_ctx::SPEED_NONE)
+        MH_HIP(c, measure_states<T>(&c, 1, (const T* const*)nullptr, c->stream));
+      if (table && ctab.rate && !c->rate_valid) {
+        MH_HIP(c, launch_clock_reset_rate(clk, c->stream));
         MH_HIP(c, launch_cool_rate<T>(U, geom, (T)g.gamma, ctab, clk, c->stream));
+      }
       time_end(c, tk);
-      c->smax_valid = true;
     }
+    const bool part = cfl && c->speed == mh_ctx::SPEED_PART;
+    pa.speed_part = part ? c->ws + c->L.speed : nullptr;
+    pa.n_part = part ? (int)reduce_blocks(c->cells()) : 0;
+    pa.reset_health = s == 0;
     pa.log_index = s % DTLOG_CAP;
     long tk = time_begin(c, MH_TIME_PROLOGUE);
     MH_HIP(c, launch_prologue(pa, c->stream));
@@ -561,7 +608,8 @@ static mh_status step_impl(mh_ctx* c, int32_t nsteps, double dt, double t_stop, 
       MH_HIP(c, launch_cool_table<T>(U, geom, (T)g.gamma, ih, ctab, clk, c->stream));
       time_end(c, tk);
     }
-    c->smax_valid = true;
+    c->speed = mh_ctx::SPEED_CLOCK;
+    c->rate_valid = true;
     if (dt_out && ((s + 1) % DTLOG_CAP == 0 || s + 1 == nsteps)) {
       const int n0 = (s / DTLOG_CAP) * DTLOG_CAP;
       MH_HIP(c, hipMemcpyAsync(dt_out + n0, pa.dt_log, (size_t)(s + 1 - n0) * sizeof(double),
@@ -626,21 +674,26 @@ static mh_status corrected_step(mh_ctx* const* ctxs, int B, mh_corr* corr, T* in
       MH_HIP(ctxs[0], hipStreamWaitEvent(main, fork[1 + b], 0));
     }
   }
-  for (int b = 0; b < B; ++b)
-    MH_HIP(ctxs[0], launch_copy(ctxs[b]->ws + ctxs[b]->L.U, in + (size_t)b * bytes / sizeof(T),
-                                bytes, main));
+  std::vector<void*> gathered(B);
+  std::vector<void*> states(B);
+  std::vector<const T*> corrected(B);
+  for (int b = 0; b < B; ++b) {
+    gathered[b] = in + (size_t)b * bytes / sizeof(T);
+    states[b] = ctxs[b]->ws + ctxs[b]->L.U;
+    corrected[b] = out + (size_t)b * bytes / sizeof(T);
+  }
+  MH_HIP(ctxs[0], launch_copies(states.data(), gathered.data(), B, bytes, main));
   MH_HIP(ctxs[0], corr_apply_enqueue(corr, in, out, main));
-  for (int b = 0; b < B; ++b)
-    MH_HIP(ctxs[0], launch_copy(out + (size_t)b * bytes / sizeof(T), ctxs[b]->ws + ctxs[b]->L.U,
-                                bytes, main));
-  if (!dts) {
-    for (int b = 0; b < B; ++b) {
-      mh_ctx* c = ctxs[b];
-      const mh_grid_desc& g = c->g;
-      StageGeom geom{g.n[0], g.n[1], g.n[2], {g.bc[0], g.bc[1], g.bc[2]}};
-      const double ih[3] = {1.0 / g.h[0], 1.0 / g.h[1], 1.0 / g.h[2]};
-      MH_HIP(c, launch_smax<T>(c->at<T>(c->L.U), geom, (T)g.gamma, ih, c->clk(), main));
-    }
+  if (dts) {
+    MH_HIP(ctxs[0], launch_copies((const void* const*)corrected.data(), states.data(), B, bytes,
+                                  main));
+  } else {
+    // the scatter measures the corrected states' signal speeds; a cooling rate
+    // of the uncorrected state limits nothing
+    MH_HIP(ctxs[0], measure_states<T>(ctxs, B, corrected.data(), main));
+    for (int b = 0; b < B; ++b)
+      if (ctxs[b]->cool_table() && ctxs[b]->p.cool_ccool > 0.0)
+        MH_HIP(ctxs[b], launch_clock_reset_rate(ctxs[b]->clk(), main));
   }
   return MH_OK;
 }
@@ -654,16 +707,23 @@ static mh_status step_corrected_impl(mh_ctx* const* ctxs, int B, mh_corr* corr, 
   T* out = in + per;
   MH_HIP(c0, corr_fallbacks_reset(corr));
   for (int b = 0; b < B; ++b) {
-    MH_HIP(c0, launch_sched_reset(ctxs[b]->clk(), c0->stream));
-    if (!dts && !ctxs[b]->smax_valid) {
-      // CFL speed of a state that no step has produced yet
-      mh_ctx* c = ctxs[b];
+    mh_ctx* c = ctxs[b];
+    MH_HIP(c0, launch_sched_reset(c->clk(), c0->stream));
+    if (dts) continue;
+    // every CFL step of the loop (one of them captured) takes its dt from
+    // partial maxima: of a state that no step has produced yet, or the clock's
+    if (c->speed == mh_ctx::SPEED_NONE) {
+      MH_HIP(c, measure_states<T>(&c, 1, (const T* const*)nullptr, c->stream));
+    } else if (c->speed == mh_ctx::SPEED_CLOCK) {
       const mh_grid_desc& g = c->g;
       StageGeom geom{g.n[0], g.n[1], g.n[2], {g.bc[0], g.bc[1], g.bc[2]}};
-      const double ih[3] = {1.0 / g.h[0], 1.0 / g.h[1], 1.0 / g.h[2]};
-      MH_HIP(c, launch_smax<T>(c->at<T>(c->L.U), geom, (T)g.gamma, ih, c->clk(), c->stream));
-      c->smax_valid = true;
+      MH_HIP(c, launch_speed_from_clock<T>(c->clk(), geom, c->at<T>(c->L.speed), c->stream));
+      c->speed = mh_ctx::SPEED_PART;
     }
+    // (the cooling rate of a state set by the caller is not evaluated here)
+    if (c->cool_table() && c->p.cool_ccool > 0.0 && !c->rate_valid)
+      MH_HIP(c, launch_clock_reset_rate(c->clk(), c->stream));
+    c->rate_valid = true;
   }
   if (!graph || nsteps == 0) {
     for (int s = 0; s < nsteps; ++s) {

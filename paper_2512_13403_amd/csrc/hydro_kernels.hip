@@ -685,36 +685,54 @@ __global__ __launch_bounds__(256) void k_stage2_finish(const StageArgs<T> a,
 //   P_{n,c} = Re(B_{n,c} + B_{-n,c}),  Q_{n,c} = Im(B_{n,c} - B_{-n,c}),
 // a_c = P_{0,c} + sum_{n >= 1} (Re X_n P_{n,c} - Im X_n Q_{n,c}).  One thread
 // per (row (y, z), n) writes [n][c][P, Q] of the row's record (6 (R+1) values).
+// The modes, their coefficients and the phase factors of the workgroup's rows
+// are staged in LDS by one round of loads; read per mode from global memory,
+// the chain of dependent loads took 7.7 us for 16 modes at 64^2 rows and 22 us
+// at 512^2 (19 MB written).
+constexpr int ROWS_THREADS = 256;
 template <typename T>
-__global__ __launch_bounds__(256) void k_force_rows(const T* __restrict__ coef,
-                                                    const int* __restrict__ nvec, int nmodes,
-                                                    const T* __restrict__ tabY,
-                                                    const T* __restrict__ tabZ, int ny, int nz,
-                                                    int R, T* __restrict__ rows) {
-  const long long t = (long long)blockIdx.x * 256 + threadIdx.x;
-  if (t >= (long long)ny * nz * (R + 1)) return;
-  const int n = (int)(t % (R + 1));
-  const long long row = t / (R + 1);  // z * ny + y
-  const int y = (int)(row % ny), z = (int)(row / ny);
+__global__ __launch_bounds__(ROWS_THREADS) void k_force_rows(
+    const T* __restrict__ coef, const int* __restrict__ nvec, int nmodes,
+    const T* __restrict__ tabY, const T* __restrict__ tabZ, int ny, int nz, int R,
+    T* __restrict__ rows) {
+  __shared__ T s_coef[6 * MAX_MODES], s_y[2 * ROWS_THREADS], s_z[2 * ROWS_THREADS];
+  __shared__ int s_n[3 * MAX_MODES];
+  const int R1 = R + 1, rpb = ROWS_THREADS / R1;  // rows per workgroup
+  const int lr = threadIdx.x / R1, n = threadIdx.x - lr * R1;
+  const long long row = (long long)blockIdx.x * rpb + lr;  // z * ny + y
+  const bool active = lr < rpb && row < (long long)ny * nz;
+  for (int i = threadIdx.x; i < 6 * nmodes; i += ROWS_THREADS) s_coef[i] = coef[i];
+  for (int i = threadIdx.x; i < 3 * nmodes; i += ROWS_THREADS) s_n[i] = nvec[i];
+  if (active) {
+    const int y = (int)(row % ny), z = (int)(row / ny);
+    const T* ey = tabY + 2 * ((long long)n * ny + y);
+    const T* ez = tabZ + 2 * ((long long)n * nz + z);
+    s_y[2 * threadIdx.x] = ey[0];
+    s_y[2 * threadIdx.x + 1] = ey[1];
+    s_z[2 * threadIdx.x] = ez[0];
+    s_z[2 * threadIdx.x + 1] = ez[1];
+  }
+  __syncthreads();
+  if (!active) return;
   T P[3] = {T(0), T(0), T(0)}, Q[3] = {T(0), T(0), T(0)};
   for (int m = 0; m < nmodes; ++m) {
-    const int nxm = nvec[3 * m];
+    const int nxm = s_n[3 * m];
     if (nxm != n && nxm != -n) continue;
-    const int nym = nvec[3 * m + 1], nzm = nvec[3 * m + 2];
-    const T* ey = tabY + 2 * ((long long)abs(nym) * ny + y);
-    const T* ez = tabZ + 2 * ((long long)abs(nzm) * nz + z);
+    const int nym = s_n[3 * m + 1], nzm = s_n[3 * m + 2];
+    const T* ey = s_y + 2 * (lr * R1 + abs(nym));
+    const T* ez = s_z + 2 * (lr * R1 + abs(nzm));
     const T yr = ey[0], yi = nym < 0 ? -ey[1] : ey[1];
     const T zr = ez[0], zi = nzm < 0 ? -ez[1] : ez[1];
     const T er = yr * zr - yi * zi, ei = yr * zi + yi * zr;
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-      const T cr = coef[6 * m + 2 * c], ci = coef[6 * m + 2 * c + 1];
+      const T cr = s_coef[6 * m + 2 * c], ci = s_coef[6 * m + 2 * c + 1];
       const T br = cr * er - ci * ei, bi = cr * ei + ci * er;
       P[c] += br;
       Q[c] += (nxm == n) ? bi : -bi;
     }
   }
-  T* out = rows + row * 6 * (R + 1) + 6 * n;
+  T* out = rows + row * 6 * R1 + 6 * n;
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
     out[2 * c] = P[c];
@@ -725,9 +743,9 @@ __global__ __launch_bounds__(256) void k_force_rows(const T* __restrict__ coef,
 template <typename T>
 hipError_t launch_force_rows(const T* coef, const int* nvec, int nmodes, const T* tabY,
                              const T* tabZ, int ny, int nz, int R, T* rows, hipStream_t s) {
-  const long long total = (long long)ny * nz * (R + 1);
-  hipLaunchKernelGGL((k_force_rows<T>), dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s,
-                     coef, nvec, nmodes, tabY, tabZ, ny, nz, R, rows);
+  const long long rpb = ROWS_THREADS / (R + 1), nrows = (long long)ny * nz;
+  hipLaunchKernelGGL((k_force_rows<T>), dim3((unsigned)((nrows + rpb - 1) / rpb)),
+                     dim3(ROWS_THREADS), 0, s, coef, nvec, nmodes, tabY, tabZ, ny, nz, R, rows);
   return hipGetLastError();
 }
 
@@ -736,36 +754,64 @@ template hipError_t launch_force_rows<float>(const float*, const int*, int, cons
 template hipError_t launch_force_rows<double>(const double*, const int*, int, const double*,
                                               const double*, int, int, int, double*, hipStream_t);
 
-// CFL signal-speed max of a state (used when no stage-2 epilogue produced it,
-// i.e. right after the state was set).
-template <typename T>
-__global__ __launch_bounds__(256) void k_smax(const T* __restrict__ U, long long N, T gm1, T gamma,
-                                              T ihx, T ihy, T ihz, DevClock* clk) {
+// Signal speed max_a (|v_a| + c)/h_a of states that no stage-2 epilogue left
+// (set by the caller, or corrected), with the copy into place where there is
+// one: batch member blockIdx.y reads src, writes dst (COPY) and the maximum of
+// each workgroup to part, which the next prologue reduces -- no clock to reset
+// before, no atomics.  Bound by memory; VEC cells of 16 bytes per load where
+// the cell count and the addresses allow it.  A copy and a reduction in
+// separate passes took 242 + 146 us at 256^3 fp64.
+template <typename T, int VEC>
+struct alignas(sizeof(T) * VEC) Cells {
+  T v[VEC];
+};
+template <typename T, int VEC, bool COPY>
+__global__ __launch_bounds__(256) void k_state_speed(const StateBatch<T> sb, long long N, T gm1,
+                                                     T gamma, T ihx, T ihy, T ihz) {
+  using V = Cells<T, VEC>;
   __shared__ T sRed[4];
+  const V* __restrict__ src = reinterpret_cast<const V*>(sb.src[blockIdx.y]);
+  V* __restrict__ dst = reinterpret_cast<V*>(sb.dst[blockIdx.y]);
+  const long long NV = N / VEC;
   T smax = T(0);
-  for (long long q = (long long)blockIdx.x * blockDim.x + threadIdx.x; q < N;
+  for (long long q = (long long)blockIdx.x * blockDim.x + threadIdx.x; q < NV;
        q += (long long)gridDim.x * blockDim.x) {
-    T u[5], w[5];
-    load_cell(U, N, q, u);
-    to_prim(u, gm1, w);
-    const T cs = dev_sqrt(gamma * w[4] * dev_rcp(w[0]));
-    smax = fmax(smax, fmax(fmax((fabs(w[1]) + cs) * ihx, (fabs(w[2]) + cs) * ihy),
-                           (fabs(w[3]) + cs) * ihz));
+    V c[5];
+#pragma unroll
+    for (int f = 0; f < 5; ++f) c[f] = src[f * NV + q];
+    if (COPY) {
+#pragma unroll
+      for (int f = 0; f < 5; ++f) dst[f * NV + q] = c[f];
+    }
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) {
+      T u[5], w[5];
+#pragma unroll
+      for (int f = 0; f < 5; ++f) u[f] = c[f].v[i];
+      to_prim(u, gm1, w);
+      const T cs = dev_sqrt(gamma * w[4] * dev_rcp(w[0]));
+      smax = fmax(smax, fmax(fmax((fabs(w[1]) + cs) * ihx, (fabs(w[2]) + cs) * ihy),
+                             (fabs(w[3]) + cs) * ihz));
+    }
   }
   T m = wave_max(smax);
   if ((threadIdx.x & 63) == 0) sRed[threadIdx.x >> 6] = m;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    T bm = fmax(fmax(sRed[0], sRed[1]), fmax(sRed[2], sRed[3]));
-    raise_max(&clk->smax, pos_bits(bm));
-  }
+  if (threadIdx.x == 0)
+    sb.part[blockIdx.y][blockIdx.x] = fmax(fmax(sRed[0], sRed[1]), fmax(sRed[2], sRed[3]));
 }
 
-__global__ void k_clock_reset_smax(DevClock* clk) {
-  if (threadIdx.x == 0) {
-    clk->smax = 0ull;
-    clk->crate = 0ull;
-  }
+// the clock's signal speed as the partials of k_state_speed (a captured step
+// takes its dt from those)
+template <typename T>
+__global__ __launch_bounds__(256) void k_speed_from_clock(const DevClock* clk, int f64, T* part,
+                                                          int n) {
+  const double s = f64 ? bits_to_double_f64(clk->smax) : bits_to_double_f32(clk->smax);
+  for (int i = threadIdx.x; i < n; i += 256) part[i] = (T)s;
+}
+
+__global__ void k_clock_reset_rate(DevClock* clk) {
+  if (threadIdx.x == 0) clk->crate = 0ull;
 }
 
 __global__ void k_clock_reset_health(DevClock* clk) {
@@ -874,12 +920,37 @@ hipError_t launch_stage2_finish(bool cool, StageArgs<T> a, const T* ub, const St
 }
 
 template <typename T>
-hipError_t launch_smax(const T* U, const StageGeom& g, T gamma, const double* ih, DevClock* clk,
-                       hipStream_t s) {
+hipError_t launch_state_speed(const StateBatch<T>& sb, int batch, bool copy, const StageGeom& g,
+                              T gamma, const double* ih, hipStream_t s) {
+  constexpr int VEC = 16 / (int)sizeof(T);
   const long long N = (long long)g.nx * g.ny * g.nz;
-  hipLaunchKernelGGL(k_clock_reset_smax, dim3(1), dim3(64), 0, s, clk);
-  hipLaunchKernelGGL((k_smax<T>), dim3(reduce_blocks(N)), dim3(256), 0, s, U, N, gamma - T(1),
-                     gamma, (T)ih[0], (T)ih[1], (T)ih[2], clk);
+  bool wide = N % VEC == 0;
+  for (int b = 0; b < batch; ++b)
+    wide = wide && (reinterpret_cast<uintptr_t>(sb.src[b]) % 16) == 0 &&
+           (reinterpret_cast<uintptr_t>(sb.dst[b]) % 16) == 0;
+  const dim3 grid(reduce_blocks(N), (unsigned)batch);
+#define MH_SPEED(V, CP)                                                                       \
+  hipLaunchKernelGGL((k_state_speed<T, V, CP>), grid, dim3(256), 0, s, sb, N, gamma - T(1),   \
+                     gamma, (T)ih[0], (T)ih[1], (T)ih[2])
+  if (wide && copy) MH_SPEED(VEC, true);
+  else if (wide) MH_SPEED(VEC, false);
+  else if (copy) MH_SPEED(1, true);
+  else MH_SPEED(1, false);
+#undef MH_SPEED
+  return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_speed_from_clock(const DevClock* clk, const StageGeom& g, T* part,
+                                   hipStream_t s) {
+  const int n = (int)reduce_blocks((long long)g.nx * g.ny * g.nz);
+  hipLaunchKernelGGL((k_speed_from_clock<T>), dim3(1), dim3(256), 0, s, clk,
+                     (int)(sizeof(T) == 8), part, n);
+  return hipGetLastError();
+}
+
+hipError_t launch_clock_reset_rate(DevClock* clk, hipStream_t s) {
+  hipLaunchKernelGGL(k_clock_reset_rate, dim3(1), dim3(64), 0, s, clk);
   return hipGetLastError();
 }
 
@@ -901,9 +972,13 @@ template hipError_t launch_stage2_finish<float>(bool, StageArgs<float>, const fl
                                                 const StageGeom&, hipStream_t);
 template hipError_t launch_stage2_finish<double>(bool, StageArgs<double>, const double*,
                                                  const StageGeom&, hipStream_t);
-template hipError_t launch_smax<float>(const float*, const StageGeom&, float, const double*,
-                                       DevClock*, hipStream_t);
-template hipError_t launch_smax<double>(const double*, const StageGeom&, double, const double*,
-                                        DevClock*, hipStream_t);
+#define MH_SPEED_INST(T)                                                                      \
+  template hipError_t launch_state_speed<T>(const StateBatch<T>&, int, bool, const StageGeom&, \
+                                            T, const double*, hipStream_t);                   \
+  template hipError_t launch_speed_from_clock<T>(const DevClock*, const StageGeom&, T*,       \
+                                                 hipStream_t);
+MH_SPEED_INST(float)
+MH_SPEED_INST(double)
+#undef MH_SPEED_INST
 
 }  // namespace mh

@@ -46,6 +46,16 @@ struct StageArgs {
                    // each cell), or null; run-time-scheme kernel only
 };
 
+// states copied, or measured, together: member b reads src[b] and writes
+// dst[b]; part[b] takes reduce_blocks(cells) maxima of the signal speed
+constexpr int STATE_BATCH = 8;
+template <typename T>
+struct StateBatch {
+  const T* src[STATE_BATCH];
+  T* dst[STATE_BATCH];
+  T* part[STATE_BATCH];
+};
+
 struct OUArgs {
   DevClock* clk;
   double* ahat;    // [M][3][re, im]
@@ -69,6 +79,9 @@ struct PrologueArgs {
   double t_stop;
   int forcing;
   OUArgs ou;
+  const void* speed_part;  // CFL: the signal speed as n_part partial maxima of
+  int n_part;              // the state precision (k_state_speed), or null: the clock's
+  int reset_health;        // clear the counts of unphysical cells
   const double* dt_sched;  // device dt schedule, entry clk->sched_pos * sched_stride (or null)
   long long sched_stride;
 };
@@ -85,8 +98,12 @@ template <typename T>
 hipError_t launch_stage2_finish(bool cool, StageArgs<T> a, const T* ub, const StageGeom& g,
                                 hipStream_t s);
 template <typename T>
-hipError_t launch_smax(const T* U, const StageGeom& g, T gamma, const double* ih, DevClock* clk,
-                       hipStream_t s);
+hipError_t launch_state_speed(const StateBatch<T>& sb, int batch, bool copy, const StageGeom& g,
+                              T gamma, const double* ih, hipStream_t s);
+template <typename T>
+hipError_t launch_speed_from_clock(const DevClock* clk, const StageGeom& g, T* part,
+                                   hipStream_t s);
+hipError_t launch_clock_reset_rate(DevClock* clk, hipStream_t s);
 template <typename T>
 hipError_t launch_cool_table(T* U, const StageGeom& g, T gamma, const double* ih,
                              const CoolTable<T>& c, DevClock* clk, hipStream_t s);
@@ -100,7 +117,8 @@ hipError_t launch_clock_reset_health(DevClock* clk, hipStream_t s);
 hipError_t launch_clock_set(DevClock* clk, double t, long long step, hipStream_t s);
 hipError_t launch_prologue(const PrologueArgs& a, hipStream_t s);
 hipError_t launch_sched_reset(DevClock* clk, hipStream_t s);
-hipError_t launch_copy(const void* src, void* dst, size_t bytes, hipStream_t s);
+hipError_t launch_copies(const void* const* src, void* const* dst, int count, size_t bytes,
+                         hipStream_t s);
 template <typename T>
 hipError_t launch_adam(T* th, T* m, T* v, const T* g, long long count, double lr, double b1,
                        double b2, double eps, long long it, hipStream_t s);

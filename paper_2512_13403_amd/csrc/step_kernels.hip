@@ -7,6 +7,8 @@
 
 namespace mh {
 
+constexpr int PROLOGUE_THREADS = 3 * MAX_MODES;  // a thread per mode and component
+
 // Counter-based normal draws for the OU noise.  SplitMix64 (Steele, Lea &
 // Flood, OOPSLA 2014): output c of the stream seeded with s is
 // mix(s + (c + 1) * 0x9E3779B97F4A7C15).  Two outputs give two uniforms
@@ -34,11 +36,9 @@ __device__ inline void complex_normal(unsigned long long seed, long long group, 
 }
 
 // M eta with M = zeta P + (1 - zeta) C, P = I - n n^T/|n|^2, C = n n^T/|n|^2
-__device__ inline void projected_noise(const OUArgs& a, long long group, int mode,
-                                       double (&out)[3][2]) {
+__device__ inline void project_noise(const OUArgs& a, int mode, const double (&er)[3],
+                                     const double (&ei)[3], double (&out)[3][2]) {
   const int* n = a.nvec + 3 * mode;
-  double er[3], ei[3];
-  for (int c = 0; c < 3; ++c) complex_normal(a.seed, group, mode, c, er[c], ei[c]);
   const double k2 = (double)(n[0] * n[0] + n[1] * n[1] + n[2] * n[2]);
   for (int i = 0; i < 3; ++i) {
     double sr = 0.0, si = 0.0;
@@ -57,8 +57,9 @@ __device__ inline void projected_noise(const OUArgs& a, long long group, int mod
 __global__ void k_ou_init(const OUArgs a) {
   const int m = threadIdx.x;
   if (m < a.nmodes) {
-    double pe[3][2];
-    projected_noise(a, -1, m, pe);
+    double er[3], ei[3], pe[3][2];
+    for (int c = 0; c < 3; ++c) complex_normal(a.seed, -1, m, c, er[c], ei[c]);
+    project_noise(a, m, er, ei, pe);
     for (int c = 0; c < 3; ++c) {
       a.ahat[6 * m + 2 * c] = pe[c][0];
       a.ahat[6 * m + 2 * c + 1] = pe[c][1];
@@ -68,10 +69,33 @@ __global__ void k_ou_init(const OUArgs a) {
 
 // dt of this step, OU update a <- e^{-dt/tau} a + sqrt(1 - e^{-2dt/tau}) M eta,
 // the rms normalisation a_rms / sqrt(2 sum |ahat|^2), and the clock advance.
-__global__ void k_prologue(const PrologueArgs a) {
-  __shared__ double s_dt, s_scale;
+// Latency alone: a serial chain of loads, fp64 transcendentals and barriers
+// that the whole GPU waits for.  So the noise, which does not depend on dt, is
+// drawn first, a thread per mode and component, next to the reduction of the
+// signal speed, and the amplitudes stay in LDS for the normalisation (summed
+// in order by one thread): one wave drawing three components each and reading
+// the amplitudes back took 11.8 us with 16 modes.
+__global__ __launch_bounds__(PROLOGUE_THREADS) void k_prologue(const PrologueArgs a) {
+  __shared__ double s_dt, s_scale, s_speed[PROLOGUE_THREADS / 64];
+  __shared__ double s_er[3 * MAX_MODES], s_ei[3 * MAX_MODES], s_a[6 * MAX_MODES];
   const int t = threadIdx.x;
   DevClock* clk = a.clk;
+  const OUArgs& o = a.ou;
+  const long long step = clk->step;
+  const bool update = a.forcing && step % o.every == 0;
+  if (a.forcing)
+    for (int q = t; q < 6 * o.nmodes; q += PROLOGUE_THREADS) s_a[q] = o.ahat[q];
+  if (a.speed_part) {
+    double m = 0.0;
+    for (int i = t; i < a.n_part; i += PROLOGUE_THREADS)
+      m = fmax(m, a.f64 ? ((const double*)a.speed_part)[i]
+                        : (double)((const float*)a.speed_part)[i]);
+    m = wave_max(m);
+    if ((t & 63) == 0) s_speed[t >> 6] = m;
+  }
+  if (update && t < 3 * o.nmodes)
+    complex_normal(o.seed, step / o.every, t / 3, t % 3, s_er[t], s_ei[t]);
+  __syncthreads();
   if (t == 0) {
     double dt;
     if (a.dt_sched) {
@@ -80,7 +104,11 @@ __global__ void k_prologue(const PrologueArgs a) {
     } else if (a.dt_fixed > 0.0) {
       dt = a.dt_fixed;
     } else {
-      const double smax = a.f64 ? bits_to_double_f64(clk->smax) : bits_to_double_f32(clk->smax);
+      double smax = a.f64 ? bits_to_double_f64(clk->smax) : bits_to_double_f32(clk->smax);
+      if (a.speed_part) {
+        smax = s_speed[0];
+        for (int w = 1; w < PROLOGUE_THREADS / 64; ++w) smax = fmax(smax, s_speed[w]);
+      }
       dt = a.cfl / smax;
       if (a.ccool > 0.0) {
         // cooling-time limit of the tabulated cooling model
@@ -96,46 +124,51 @@ __global__ void k_prologue(const PrologueArgs a) {
   }
   __syncthreads();
   if (a.forcing) {
-    const OUArgs& o = a.ou;
-    const long long step = clk->step;
-    if (step % o.every == 0 && t < o.nmodes) {
+    if (update && t < o.nmodes) {
       const double dte = s_dt * o.every;
       const double f = exp(-dte / o.tau);
       const double g = sqrt(1.0 - exp(-2.0 * dte / o.tau));
-      double pe[3][2];
-      projected_noise(o, step / o.every, t, pe);
+      double er[3], ei[3], pe[3][2];
       for (int c = 0; c < 3; ++c) {
-        o.ahat[6 * t + 2 * c] = f * o.ahat[6 * t + 2 * c] + g * pe[c][0];
-        o.ahat[6 * t + 2 * c + 1] = f * o.ahat[6 * t + 2 * c + 1] + g * pe[c][1];
+        er[c] = s_er[3 * t + c];
+        ei[c] = s_ei[3 * t + c];
       }
+      project_noise(o, t, er, ei, pe);
+      for (int c = 0; c < 3; ++c)
+        for (int q = 0; q < 2; ++q) {
+          const double v = f * s_a[6 * t + 2 * c + q] + g * pe[c][q];
+          s_a[6 * t + 2 * c + q] = v;
+          o.ahat[6 * t + 2 * c + q] = v;
+        }
     }
     __syncthreads();
     if (t == 0) {
       double s = 0.0;
-      for (int q = 0; q < 6 * o.nmodes; ++q) s += o.ahat[q] * o.ahat[q];
+      for (int q = 0; q < 6 * o.nmodes; ++q) s += s_a[q] * s_a[q];
       s_scale = o.arms / sqrt(2.0 * s);
       clk->ou_scale = s_scale;
     }
     __syncthreads();
-    if (t < o.nmodes) {
-      for (int q = 0; q < 6; ++q) {
-        const double v = 2.0 * s_scale * o.ahat[6 * t + q];
-        if (o.f64) ((double*)o.coef)[6 * t + q] = v;
-        else ((float*)o.coef)[6 * t + q] = (float)v;
-      }
+    for (int q = t; q < 6 * o.nmodes; q += PROLOGUE_THREADS) {
+      const double v = 2.0 * s_scale * s_a[q];
+      if (o.f64) ((double*)o.coef)[q] = v;
+      else ((float*)o.coef)[q] = (float)v;
     }
   }
-  __syncthreads();
   if (t == 0) {
     clk->t += s_dt;
-    clk->step += 1;
+    clk->step = step + 1;
     clk->smax = 0ull;
     clk->crate = 0ull;
+    if (a.reset_health) {
+      clk->bad_count = 0ull;
+      clk->bad_first = ~0ull;
+    }
   }
 }
 
 hipError_t launch_prologue(const PrologueArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(k_prologue, dim3(1), dim3(MAX_MODES), 0, s, a);
+  hipLaunchKernelGGL(k_prologue, dim3(1), dim3(PROLOGUE_THREADS), 0, s, a);
   return hipGetLastError();
 }
 
@@ -148,29 +181,43 @@ hipError_t launch_sched_reset(DevClock* clk, hipStream_t s) {
   return hipGetLastError();
 }
 
-// plain device copy in 16-byte words (the corrected step's gathers and
-// scatters, as kernels so that a captured step holds no copy nodes)
-__global__ __launch_bounds__(256) void k_copy16(const uint4* __restrict__ src,
-                                                uint4* __restrict__ dst, size_t n) {
+// plain device copies in 16-byte words, member blockIdx.y (the corrected
+// step's gathers and scatters, as kernels so that a captured step holds no
+// copy nodes, and one launch for a batch)
+struct CopyBatch {
+  const void* src[STATE_BATCH];
+  void* dst[STATE_BATCH];
+};
+__global__ __launch_bounds__(256) void k_copy16(const CopyBatch cb, size_t n) {
+  const uint4* __restrict__ src = (const uint4*)cb.src[blockIdx.y];
+  uint4* __restrict__ dst = (uint4*)cb.dst[blockIdx.y];
   for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256)
     dst[i] = src[i];
 }
-__global__ void k_copy1(const unsigned char* __restrict__ src, unsigned char* __restrict__ dst,
-                        size_t n) {
-  for (size_t i = threadIdx.x; i < n; i += blockDim.x) dst[i] = src[i];
+__global__ void k_copy1(const CopyBatch cb, size_t from, size_t n) {
+  const unsigned char* src = (const unsigned char*)cb.src[blockIdx.y];
+  unsigned char* dst = (unsigned char*)cb.dst[blockIdx.y];
+  for (size_t i = from + threadIdx.x; i < n; i += blockDim.x) dst[i] = src[i];
 }
 
-hipError_t launch_copy(const void* src, void* dst, size_t bytes, hipStream_t s) {
+hipError_t launch_copies(const void* const* src, void* const* dst, int count, size_t bytes,
+                         hipStream_t s) {
   const size_t n16 = bytes / 16;
-  if (n16) {
-    size_t blocks = (n16 + 255) / 256;
-    if (blocks > 4096) blocks = 4096;
-    hipLaunchKernelGGL(k_copy16, dim3((unsigned)blocks), dim3(256), 0, s, (const uint4*)src,
-                       (uint4*)dst, n16);
+  for (int b0 = 0; b0 < count; b0 += STATE_BATCH) {
+    const int nb = count - b0 < STATE_BATCH ? count - b0 : STATE_BATCH;
+    CopyBatch cb{};
+    for (int b = 0; b < nb; ++b) {
+      cb.src[b] = src[b0 + b];
+      cb.dst[b] = dst[b0 + b];
+    }
+    if (n16) {
+      size_t blocks = (n16 + 255) / 256;
+      if (blocks > 4096) blocks = 4096;
+      hipLaunchKernelGGL(k_copy16, dim3((unsigned)blocks, (unsigned)nb), dim3(256), 0, s, cb, n16);
+    }
+    if (bytes % 16)
+      hipLaunchKernelGGL(k_copy1, dim3(1, (unsigned)nb), dim3(64), 0, s, cb, 16 * n16, bytes);
   }
-  if (bytes % 16)
-    hipLaunchKernelGGL(k_copy1, dim3(1), dim3(64), 0, s, (const unsigned char*)src + 16 * n16,
-                       (unsigned char*)dst + 16 * n16, bytes % 16);
   return hipGetLastError();
 }
 

@@ -110,3 +110,76 @@ def test_adjoint_step_in_place(integrator):
     got = lam.clone()
     s.adjoint_step(U, 1e-3, 0, got, out=got)
     assert torch.equal(got, want)
+
+
+# cell counts that load 16 bytes at a time and that do not, by dtype
+@pytest.mark.parametrize("shape", [(5, 9, 13), (3, 6, 11), (6, 8, 16), (40, 64, 96)])
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+def test_set_state_copies_and_measures(shape, dtype):
+    """A device state, aligned or not, and a host state give the same state
+    and the same CFL step."""
+    import torch
+
+    nz, ny, nx = shape
+    grid = mh.grid_desc(shape, (1.0 / nx, 1.0 / ny, 1.0 / nz), dtype=dtype)
+    U = wl.random_state(shape, seed=9, vmax=0.5)
+    s = mh.Solver(grid)
+    s.set_state(U)
+    want = s.get_state_device()
+    s.step(1)  # another state in between, and another signal speed
+    s.set_state(U)
+    dt = float(s.step(1, record=True)[0])
+    room = torch.empty(want.numel() + 1, dtype=want.dtype, device="cuda:0")
+    for off in (0, 1):
+        dev = room[off:off + want.numel()].view(want.shape)
+        dev.copy_(want)
+        s.set_state(dev)
+        assert torch.equal(s.get_state_device(), want)
+        assert float(s.step(1, record=True)[0]) == dt
+
+
+@pytest.mark.parametrize("band", [(1.0, 1.0), (1.0, 2.0), (2.9, 3.0), (7.9, 8.0)])
+@pytest.mark.parametrize("shape", [(6, 7, 9), (17, 30, 70)])
+def test_forcing_rows_over_bands(band, shape):
+    """The forcing's row records for the fewest and most mode indices (rows per
+    workgroup 128 down to 28, a ragged last workgroup) against the oracle."""
+    nz, ny, nx = shape
+    s, oc = pair(shape, (1.0 / nx, 1.0 / ny, 1.0 / nz), (0, 0, 0), "f64",
+                 flags=oracle.SRC_FORCING, ou_seed=11, ou_kmin=band[0], ou_kmax=band[1])
+    U = wl.random_state(shape, seed=10, vmax=0.3)
+    dt = 0.5 * oracle.cfl_dt(oc, U)
+    s.set_state(U)
+    s.step(2, dt)
+    assert rel_err(s.get_state(), oracle.Simulation(oc, U).advance(2, dt).U) < TOL["f64"]
+
+
+@pytest.mark.parametrize("graph", [True, False])
+def test_corrected_steps_beyond_one_launch_batch(graph):
+    """Nine contexts (copies and signal speeds go eight to a launch) with two
+    spacings, CFL steps: bitwise the host-driven loop."""
+    import torch
+
+    n, B, steps = 16, 9, 3
+    mk = lambda: [mh.Solver(mh.grid_desc((n,) * 3, ((1.0 + (b == 5)) / n,) * 3),
+                            mh.physics_desc(flags=mh.SRC_FORCING, ou_seed=b)) for b in range(B)]
+    U = torch.tensor(np.stack([wl.smooth_random_state((n,) * 3, seed=b) for b in range(B)]),
+                     dtype=torch.float32, device="cuda:0")
+    mean = [float(v) for v in U.mean(dim=(0, 2, 3, 4))]
+    std = [float(v) + 1e-3 for v in U.std(dim=(0, 2, 3, 4))]
+    corr = mh.Corrector(mh.corr_desc(n, B, "f32", 5.0 / 3.0, mean, std, (1e-3,) * 5))
+    corr.set_params(wl.corrector_init_params(seed=12, out_scale=1.0).astype(np.float32))
+    a, b = mk(), mk()
+    for s, t, u in zip(a, b, U):
+        s.set_state(u)
+        t.set_state(u)
+    mh.step_corrected(a, corr, steps, use_graph=graph)
+    for _ in range(steps):
+        plain = torch.stack([t.get_state_device() for t in b if t.step(1) is None])
+        out, _, _ = corr.apply(plain)
+        for t, u in zip(b, out):
+            t.set_state(u)
+    for s, t in zip(a, b):
+        assert torch.equal(s.get_state_device(), t.get_state_device())
+    # a CFL step after the corrected ones starts from the corrected states
+    assert [float(s.step(1, record=True)[0]) for s in a] == \
+           [float(t.step(1, record=True)[0]) for t in b]
