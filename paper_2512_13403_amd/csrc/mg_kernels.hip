@@ -16,6 +16,7 @@
 // depend on scheduling.  Every kernel here is memory-bound (about 2 field
 // reads and 1 write per cell per sweep).
 #include <cmath>
+#include <type_traits>
 
 #include "mg.h"
 #include "mh_device.h"
@@ -218,6 +219,247 @@ __global__ __launch_bounds__(256) void k_prolong_add(int nc, const T* __restrict
   phif[q] += e;
 }
 
+// Red-black Gauss-Seidel on tiles: S sweeps (2 S colour passes) of a BX x BY x
+// BZ tile, with the halo that the passes eat up one cell at a time recomputed,
+// so that a sweep reads phi and F once and writes phi once instead of passing
+// over whole cache lines for every colour.  Every cell gets the update of
+// k_rbgs.  Around it, in the same launch: the start from zero (ZERO), the
+// trilinear correction from the coarse level added on loading (PRO), and from
+// the smoothed tile either the restricted residual (RES_COARSE: F_c, averaged
+// over the 8 children) or the block's sum of squared residuals (RES_NORM).
+// phi goes from one buffer to the other, since a tile reads cells that its
+// neighbours write.
+//
+// A thread holds a column of the halo tile along z, phi and F in registers; its
+// z neighbours are its own, the x and y ones come from LDS.  The columns are
+// split by the parity of x + y, each half in its own waves and its own LDS
+// rows, so that a pass updates every second register of a whole wave and
+// consecutive lanes read consecutive words: all addresses are one base plus
+// constants (a thread per cell spent its time on index arithmetic: 18 us a
+// sweep at 128^3 fp64).
+//
+// Two shapes.  MGFine (levels of 96^3 cells and up, bound by the traffic to
+// the last-level cache): 16 x 16 x 8, one sweep a launch.  MGSmall (below,
+// bound by launches and latency): 8^3, both sweeps in one launch.  A V(2,2)
+// cycle at 128^3 fp64 took about 45 launches and 0.30 ms with a launch per
+// colour pass and separate residual, restriction, mean-removal and norm
+// kernels.
+// (The restricted residual's mean is not removed: A phi sums to zero on the
+// periodic grid and F has no mean, so it holds rounding alone; the coarsest
+// solve drops the constant mode.)
+enum : int { RES_NONE = 0, RES_COARSE = 1, RES_NORM = 2 };
+struct MGFine {
+  static constexpr int BX = 16, BY = 16, BZ = 8, S = 1;
+};
+struct MGSmall {
+  static constexpr int BX = 8, BY = 8, BZ = 8, S = 2;
+};
+constexpr int MG_FINE_MIN = 96;    // levels of this many cells per axis: MGFine
+constexpr int MG_TILE_MIN = 16;    // the smallest level smoothed on tiles
+
+template <class C, int RES>
+struct TileShape {
+  static constexpr int H = 2 * C::S + (RES != RES_NONE ? 1 : 0);  // halo of phi
+  static constexpr int EX = C::BX + 2 * H, EY = C::BY + 2 * H, EZ = C::BZ + 2 * H;
+  static constexpr int HX = EX / 2, NC = HX * EY;   // columns of one parity
+  static constexpr int NW = (NC + 63) / 64 * 64;    // threads of one parity
+  static constexpr int NT = 2 * NW;
+};
+
+template <typename T>
+struct TileArgs {
+  int n, ntx, nty;      // cells per axis; tiles along x and y
+  T h2, ih2;
+  const T* phi;         // read (unless ZERO)
+  const T* F;
+  const T* ec;          // PRO: the coarse correction, n / 2 cells per axis
+  T* out;
+  T* Fc;                // RES_COARSE
+  double* partial;      // RES_NORM: one per tile
+};
+
+template <typename T, class C, int RES, bool ZERO, bool PRO>
+__global__ __launch_bounds__((TileShape<C, RES>::NT)) void k_rbgs_tile(const TileArgs<T> a) {
+  using Sh = TileShape<C, RES>;
+  constexpr int BX = C::BX, BY = C::BY, BZ = C::BZ, H = Sh::H;
+  constexpr int EX = Sh::EX, EY = Sh::EY, EZ = Sh::EZ, HX = Sh::HX, NC = Sh::NC, NW = Sh::NW,
+                NT = Sh::NT;
+  constexpr int CH = (H + 1) / 2 + 1;  // coarse halo of the correction
+  constexpr int CX = BX / 2 + 2 * CH, CY = BY / 2 + 2 * CH, CZ = BZ / 2 + 2 * CH;
+  __shared__ T s[EZ * 2 * NC];  // [plane][parity][column]
+  __shared__ T sc[PRO ? CX * CY * CZ : 1];
+  __shared__ double sh[NT / 64];
+  const int n = a.n, tid = threadIdx.x;
+  // each XCD (workgroups are dealt to the 8 in turn) takes a contiguous range
+  // of tiles, whose halos meet in its L2
+  int t = blockIdx.x;
+  if ((gridDim.x & 7) == 0) t = (t & 7) * (gridDim.x >> 3) + (t >> 3);
+  const int tile = t;
+  const int x0 = (t % a.ntx) * BX;
+  t /= a.ntx;
+  const int y0 = (t % a.nty) * BY, z0 = (t / a.nty) * BZ;
+  auto wrapm = [](int i, int m) {
+    i %= m;
+    return i < 0 ? i + m : i;
+  };
+  const int cls = __builtin_amdgcn_readfirstlane(tid / NW), col = tid - cls * NW;
+  const bool active = col < NC;
+  const int jj = col / HX, odd = (jj + cls) & 1, ii = 2 * (col - jj * HX) + odd;
+  const int i = ii - H, j = jj - H;  // from the tile's corner
+  const long long n2 = (long long)n * n;
+  const long long base =
+      active ? (long long)wrapm(y0 + j, n) * n + wrapm(x0 + i, n) : 0;
+  auto plane = [&](int kk) {  // z of plane kk, wrapped once (n >= MG_TILE_MIN)
+    int z = z0 - H + kk;
+    z = z < 0 ? z + n : z;
+    return z >= n ? z - n : z;
+  };
+  T p[EZ], f[EZ];
+  if (active) {
+#pragma unroll
+    for (int kk = 0; kk < EZ; ++kk) p[kk] = ZERO ? T(0) : a.phi[plane(kk) * n2 + base];
+#pragma unroll
+    for (int kk = 1; kk < EZ - 1; ++kk) f[kk] = a.F[plane(kk) * n2 + base];
+  }
+  if (PRO) {
+    const int nc = n >> 1;
+    for (int q = tid; q < CX * CY * CZ; q += NT) {
+      const int I = wrapm(x0 / 2 - CH + q % CX, nc), J = wrapm(y0 / 2 - CH + (q / CX) % CY, nc),
+                K = wrapm(z0 / 2 - CH + q / (CX * CY), nc);
+      sc[q] = a.ec[((long long)K * nc + J) * nc + I];
+    }
+    __syncthreads();
+    if (active) {
+      // per axis 3/4 parent + 1/4 of its neighbour on the child's side: x and
+      // y first, one value per coarse plane
+      const int I = (i >> 1) + CH, J = (j >> 1) + CH;
+      const int I2 = I + ((i & 1) ? 1 : -1), J2 = J + ((j & 1) ? 1 : -1);
+      const T* c00 = sc + J * CX + I;
+      const T* c10 = sc + J * CX + I2;
+      const T* c01 = sc + J2 * CX + I;
+      const T* c11 = sc + J2 * CX + I2;
+      T q[CZ];
+#pragma unroll
+      for (int K = 0; K < CZ; ++K)
+        q[K] = T(0.5625) * c00[K * CX * CY] + T(0.1875) * c10[K * CX * CY] +
+               T(0.1875) * c01[K * CX * CY] + T(0.0625) * c11[K * CX * CY];
+#pragma unroll
+      for (int kk = 0; kk < EZ; ++kk) {
+        constexpr int up = 1, down = -1;
+        const int k = kk - H, K = (k >> 1) + CH, K2 = K + ((k & 1) ? up : down);
+        p[kk] += T(0.75) * q[K] + T(0.25) * q[K2];
+      }
+    }
+  }
+  T* const mine = s + cls * NC + col;
+  const T* const other = s + (1 - cls) * NC + col;
+  if (active) {
+#pragma unroll
+    for (int kk = 0; kk < EZ; ++kk) mine[kk * 2 * NC] = p[kk];
+  }
+  __syncthreads();
+  const T sixth = T(1.0 / 6.0);
+  // the x neighbours sit in the other parity's row at col - 1 + odd and
+  // col + odd, the y neighbours a row below and above at the same place
+  const T* const xl = other - 1 + odd;
+  auto nb = [&](int kk) {
+    const int o = kk * 2 * NC;
+    return xl[o] + xl[o + 1] + other[o - HX] + other[o + HX] + p[kk - 1] + p[kk + 1];
+  };
+  auto inside = [&](int r) {
+    return active && i >= -r && i < BX + r && j >= -r && j < BY + r;
+  };
+  auto colour_pass = [&](auto pass, auto parity) {
+    constexpr int r = H - 1 - decltype(pass)::value;
+    constexpr int first = H - r, last = H + BZ + r;
+    constexpr int k0 = first + ((first + decltype(parity)::value + decltype(pass)::value + H) & 1);
+    if (inside(r)) {
+#pragma unroll
+      for (int kk = k0; kk < last; kk += 2) {
+        p[kk] = (nb(kk) - a.h2 * f[kk]) * sixth;
+        mine[kk * 2 * NC] = p[kk];
+      }
+    }
+  };
+  auto both = [&](auto pass) {
+    // the wave's parity decides which planes hold the colour (the empty asm
+    // statements keep the two bodies apart: merged, they would index the
+    // registers by the parity, from scratch memory)
+    if (cls == 0) {
+      asm volatile("; even columns");
+      colour_pass(pass, std::integral_constant<int, 0>{});
+      asm volatile("; even columns done");
+    } else {
+      asm volatile("; odd columns");
+      colour_pass(pass, std::integral_constant<int, 1>{});
+      asm volatile("; odd columns done");
+    }
+    __syncthreads();
+  };
+  both(std::integral_constant<int, 0>{});
+  both(std::integral_constant<int, 1>{});
+  if constexpr (C::S == 2) {
+    both(std::integral_constant<int, 2>{});
+    both(std::integral_constant<int, 3>{});
+  }
+  const bool own = inside(0) && x0 + i < n && y0 + j < n;
+  if (own) {
+    T* out = a.out + (long long)(y0 + j) * n + (x0 + i);
+#pragma unroll
+    for (int k = 0; k < BZ; ++k)
+      if (z0 + k < n) out[(z0 + k) * n2] = p[H + k];
+  }
+  if (RES == RES_NORM) {
+    double acc = 0.0;
+    if (own) {
+#pragma unroll
+      for (int k = 0; k < BZ; ++k)
+        if (z0 + k < n) {
+          const double r = (double)(f[H + k] - (nb(H + k) - T(6) * p[H + k]) * a.ih2);
+          acc += r * r;
+        }
+    }
+    acc = wave_tree_sum(acc);
+    if ((tid & 63) == 0) sh[tid >> 6] = acc;
+    __syncthreads();
+    if (tid == 0) {
+      double b = sh[0];
+      for (int w = 1; w < NT / 64; ++w) b += sh[w];
+      a.partial[tile] = b;
+    }
+  }
+  if (RES == RES_COARSE) {
+    // a column's residuals in pairs, then the four columns of a coarse cell
+    T v[BZ / 2];
+    if (inside(0)) {
+#pragma unroll
+      for (int K = 0; K < BZ / 2; ++K) {
+        const int lo = H + 2 * K, hi = lo + 1;
+        v[K] = (f[lo] - (nb(lo) - T(6) * p[lo]) * a.ih2) +
+               (f[hi] - (nb(hi) - T(6) * p[hi]) * a.ih2);
+      }
+    }
+    __syncthreads();
+    if (inside(0)) {
+#pragma unroll
+      for (int K = 0; K < BZ / 2; ++K) mine[K * 2 * NC] = v[K];
+    }
+    __syncthreads();
+    const int nc = n >> 1;
+    for (int q = tid; q < BX * BY * BZ / 8; q += NT) {
+      const int I = q % (BX / 2), J = (q / (BX / 2)) % (BY / 2), K = q / (BX / 2 * (BY / 2));
+      const int gi = x0 / 2 + I, gj = y0 / 2 + J, gk = z0 / 2 + K;
+      if (gi >= nc || gj >= nc || gk >= nc) continue;
+      auto at = [&](int ci, int cj) {
+        return s[(K * 2 + ((ci + cj) & 1)) * NC + (cj + H) * HX + ((ci + H) >> 1)];
+      };
+      const T sum = (at(2 * I, 2 * J) + at(2 * I + 1, 2 * J)) +
+                    (at(2 * I, 2 * J + 1) + at(2 * I + 1, 2 * J + 1));
+      a.Fc[((long long)gk * nc + gj) * nc + gi] = T(0.125) * sum;
+    }
+  }
+}
+
 // coarsest grid: phi = 0, `sweeps` Jacobi sweeps, remove the mean; one
 // workgroup of 256 threads, the whole grid (<= 4096 cells) in LDS
 template <typename T>
@@ -253,31 +495,49 @@ __global__ __launch_bounds__(256) void k_coarse_solve(int n, T h2, const T* __re
 // The bottom of the cycle in one workgroup.  Every level with at most
 // MG_TAIL_MAX_CELLS cells lives in LDS (the levels below a 16^3 level take
 // 4096 + 512 + 64 + ... cells), so the many small launches those levels would
-// cost (sweeps, residual, restriction, mean removal, coarse solve,
-// prolongation) become one.  On entry F of the tail's first level is its
-// restricted, mean-free right-hand side and its phi starts from zero, or from
-// phi0 (`warm`: the second cycle of a W-cycle); on exit phi0 holds the result.
-// Inside, the V- or W-cycle over the tail's levels runs as a loop over an
-// explicit per-level count of the coarse cycles still to do.  The arithmetic
-// of each step is that of the corresponding kernel above; the means are
-// summed with a different fixed tree.
+// cost (sweeps, residual, restriction, coarse solve, prolongation) become one.
+// On entry F of the tail's first level is its restricted right-hand side and
+// its phi starts from zero, or from phi0 (`warm`: the second cycle of a
+// W-cycle); on exit phi0 holds the result.  Inside, the V- or W-cycle over the
+// tail's levels runs as a loop over a per-level count of the coarse cycles
+// still to do.  The arithmetic of each smoothing, restriction and prolongation
+// is that of the corresponding kernel above; the restricted residuals' means,
+// which hold rounding alone, are not removed.
+//
+// Bound by latency and, on its one CU, by instructions: a barrier after every
+// colour, and index arithmetic between them.  So run-time quotients go through
+// fdiv, all addresses are 32-bit LDS offsets, the level table sits in LDS (in
+// the kernel's arguments, indexed by a run-time level, it was copied to
+// scratch memory), and the coarsest level's weighted Jacobi sweeps, a fixed
+// linear map, are applied in the eigenvectors of the periodic Laplacian
+// (tail_direct) where it has at most MG_DIRECT_MAX cells per axis.  With 16^3,
+// 8^3 and 4^3 levels and 200 coarse sweeps: 62 us before.
 constexpr int MG_TAIL_MAX_CELLS = 4096;
 constexpr int MG_TAIL_ALLOC = 4688;  // >= 4096 * 8 / 7: all levels of the tail
 constexpr int MG_TAIL_THREADS = 1024;
+constexpr int MG_TAIL_LEVELS = 5;    // 16, 8, 4, 2, 1
+constexpr int MG_DIRECT_MAX = 8;     // cells per axis of a coarsest level solved directly
 
 template <typename T>
 struct TailArgs {
   int nl;                    // levels in the tail (>= 2)
-  int n[MG_MAX_LEVELS];      // cells per axis
-  T h2[MG_MAX_LEVELS];       // h^2
-  T ih2[MG_MAX_LEVELS];      // 1 / h^2
-  int off[MG_MAX_LEVELS];    // offset of each level in the LDS arrays
+  int n0;                    // cells per axis of the first
+  T h;                       // its spacing
   const T* F0;               // right-hand side of the first level (global)
   T* phi0;                   // its phi (global: read when warm, written)
   int pre, post, csweeps;
   int wcycle;                // 1: two coarse cycles per level (W), 0: one (V)
   int rbgs;                  // smoother: 1 red-black Gauss-Seidel, 0 Jacobi
   int warm;                  // start the first level from phi0
+};
+
+// one level of the tail: phi in LDS at off (Jacobi: ping-pong with off +
+// MG_TAIL_ALLOC), F at off
+template <typename T>
+struct TailLevel {
+  int n, off;
+  float rn;                  // 1 / n
+  T h2, ih2;
 };
 
 // the sum of v over the workgroup, returned to every thread: a fixed tree
@@ -299,16 +559,32 @@ __device__ __forceinline__ double block_sum1024(double v, double* sh) {
   return r;
 }
 
+// q / n for q < 2^20 from rn = 1 / n: (q + 1/2) rn lies at least 1 / (2 n) from
+// an integer, far beyond its rounding.  Three instructions; the division of
+// run-time integers takes about 35
+__device__ __forceinline__ int fdiv(int q, float rn) { return (int)(((float)q + 0.5f) * rn); }
+
+// the sum of the six neighbours of cell q = (i, j, k), in nb6's order
 template <typename T>
-__device__ void tail_sweeps(T* pa, T* pb, const T* ff, int o, int n, T h2, int sweeps, int& cur) {
-  const int N = n * n * n;
+__device__ __forceinline__ T tail_nb6(const T* p, int n, int q, int i, int j, int k) {
+  const int n2 = n * n;
+  const T xm = p[i > 0 ? q - 1 : q + n - 1], xp = p[i < n - 1 ? q + 1 : q - (n - 1)];
+  const T ym = p[j > 0 ? q - n : q + n2 - n], yp = p[j < n - 1 ? q + n : q - (n2 - n)];
+  const T zm = p[k > 0 ? q - n2 : q + (n - 1) * n2], zp = p[k < n - 1 ? q + n2 : q - (n - 1) * n2];
+  return xm + xp + ym + yp + zm + zp;
+}
+
+template <typename T>
+__device__ __forceinline__ void tail_sweeps(T* ph, const T* ff, const TailLevel<T>& L, int sweeps,
+                                            int& cur) {
+  const int n = L.n, N = n * n * n;
   const T w = T(2) / T(3);
   for (int it = 0; it < sweeps; ++it) {
-    const T* src = (cur ? pb : pa) + o;
-    T* dst = (cur ? pa : pb) + o;
+    const T* src = ph + L.off + cur * MG_TAIL_ALLOC;
+    T* dst = ph + L.off + (1 - cur) * MG_TAIL_ALLOC;
     for (int q = threadIdx.x; q < N; q += MG_TAIL_THREADS) {
-      const int i = q % n, j = (q / n) % n, k = q / (n * n);
-      dst[q] = (T(1) - w) * src[q] + (w / T(6)) * (nb6(src, n, i, j, k) - h2 * ff[o + q]);
+      const int r = fdiv(q, L.rn), k = fdiv(r, L.rn), j = r - k * n, i = q - r * n;
+      dst[q] = (T(1) - w) * src[q] + (w / T(6)) * (tail_nb6(src, n, q, i, j, k) - L.h2 * ff[L.off + q]);
     }
     __syncthreads();
     cur ^= 1;
@@ -320,18 +596,20 @@ __device__ void tail_sweeps(T* pa, T* pb, const T* ff, int o, int n, T h2, int s
 // (a wave's LDS accesses complete in program order; the fences only keep the
 // compiler from moving them).  Same arithmetic as tail_sweeps.
 template <typename T>
-__device__ void tail_sweeps_wave(T* pa, T* pb, const T* ff, int o, int n, T h2, int sweeps,
-                                 int& cur) {
-  const int N = n * n * n;
+__device__ __forceinline__ void tail_sweeps_wave(T* ph, const T* ff, const TailLevel<T>& L,
+                                                 int sweeps, int& cur) {
+  const int n = L.n, N = n * n * n;
   const T w = T(2) / T(3);
   if (threadIdx.x < 64) {
     const int q = threadIdx.x;
-    const int i = q % n, j = (q / n) % n, k = q / (n * n);
+    const int r = fdiv(q, L.rn), k = fdiv(r, L.rn), j = r - k * n, i = q - r * n;
     int c = cur;
     for (int it = 0; it < sweeps; ++it) {
-      const T* src = (c ? pb : pa) + o;
-      T* dst = (c ? pa : pb) + o;
-      if (q < N) dst[q] = (T(1) - w) * src[q] + (w / T(6)) * (nb6(src, n, i, j, k) - h2 * ff[o + q]);
+      const T* src = ph + L.off + c * MG_TAIL_ALLOC;
+      T* dst = ph + L.off + (1 - c) * MG_TAIL_ALLOC;
+      if (q < N)
+        dst[q] = (T(1) - w) * src[q] +
+                 (w / T(6)) * (tail_nb6(src, n, q, i, j, k) - L.h2 * ff[L.off + q]);
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -345,104 +623,178 @@ __device__ void tail_sweeps_wave(T* pa, T* pb, const T* ff, int o, int n, T h2, 
 // red-black sweeps of a tail level (n even): per colour, a thread per cell
 // of the colour, the arithmetic of k_rbgs
 template <typename T>
-__device__ void tail_rbgs(T* pa, T* pb, const T* ff, int o, int n, T h2, int sweeps, int cur) {
-  const int nh = n >> 1, Nh = nh * n * n;
-  T* phi = (cur ? pb : pa) + o;
+__device__ __forceinline__ void tail_rbgs(T* ph, const T* ff, const TailLevel<T>& L, int sweeps,
+                                          int cur) {
+  const int n = L.n, nh = n >> 1, Nh = nh * n * n;
+  T* phi = ph + L.off + cur * MG_TAIL_ALLOC;
   for (int it = 0; it < sweeps; ++it)
     for (int colour = 0; colour < 2; ++colour) {
       for (int p = threadIdx.x; p < Nh; p += MG_TAIL_THREADS) {
-        const int r = p / nh, j = r % n, k = r / n;
-        const int i = 2 * (p - r * nh) + ((j + k + colour) & 1);
-        const int q = (k * n + j) * n + i;
-        phi[q] = (nb6(phi, n, i, j, k) - h2 * ff[o + q]) / T(6);
+        const int r = fdiv(p, 2.0f * L.rn), k = fdiv(r, L.rn), j = r - k * n;
+        const int i = 2 * (p - r * nh) + ((j + k + colour) & 1), q = r * n + i;
+        phi[q] = (tail_nb6(phi, n, q, i, j, k) - L.h2 * ff[L.off + q]) * T(1.0 / 6.0);
       }
       __syncthreads();
     }
 }
 
+// `sweeps` weighted Jacobi sweeps from zero on A phi = f, n <= MG_DIRECT_MAX,
+// without the constant mode: with f^ the components of f in the separable
+// eigenvectors Q and Lambda the sum of their eigenvalues (A = -Lambda / h^2),
+// phi^ = -(h^2 / Lambda) (1 - (1 - w Lambda / 6)^sweeps) f^, w = 2/3.  A thread
+// per cell; six passes of n products between a and b, the result in a.
 template <typename T>
-__global__ __launch_bounds__(MG_TAIL_THREADS) void k_mgcycle_tail(TailArgs<T> t) {
-  __shared__ T pa[MG_TAIL_ALLOC], pb[MG_TAIL_ALLOC], ff[MG_TAIL_ALLOC];
-  __shared__ double sh[MG_TAIL_THREADS];
-  int cur[MG_MAX_LEVELS];
-  int todo[MG_MAX_LEVELS];  // coarse cycles of level m + 1 still to run for level m
-  {
-    const int N0 = t.n[0] * t.n[0] * t.n[0];
-    for (int q = threadIdx.x; q < N0; q += MG_TAIL_THREADS) {
-      ff[t.off[0] + q] = t.F0[q];
-      pa[t.off[0] + q] = t.warm ? t.phi0[q] : T(0);
+__device__ __forceinline__ void tail_direct(T* a, T* b, const T* f, const T* Q, const T* lam,
+                                            const TailLevel<T>& L, int sweeps) {
+  const int n = L.n, N = n * n * n, q = threadIdx.x;
+  const int r = fdiv(q, L.rn), k = fdiv(r, L.rn), j = r - k * n, i = q - r * n;
+  const bool on = q < N;
+  // out[.., m, ..] = sum_e Q[m][e] in[.., e, ..], or its transpose
+  auto along = [&](const T* in, T* out, int m, int first, int stride, bool back) {
+    if (on) {
+      T v = T(0);
+      for (int e = 0; e < n; ++e)
+        v += Q[back ? e * MG_DIRECT_MAX + m : m * MG_DIRECT_MAX + e] * in[first + e * stride];
+      out[q] = v;
     }
-    cur[0] = 0;
     __syncthreads();
+  };
+  const int fx = q - i, fy = q - j * n, fz = q - k * n * n;
+  along(f, a, i, fx, 1, false);
+  along(a, b, j, fy, n, false);
+  along(b, a, k, fz, n * n, false);
+  if (on) {
+    const T Lm = lam[i] + lam[j] + lam[k];
+    const bool constant = q == 0;
+    T g = T(1) - (T(2) / T(18)) * Lm, pw = T(1);
+    for (int e = sweeps; e > 0; e >>= 1) {
+      if (e & 1) pw *= g;
+      g *= g;
+    }
+    a[q] = constant ? T(0) : -(L.h2 / Lm) * (T(1) - pw) * a[q];
   }
+  __syncthreads();
+  along(a, b, k, fz, n * n, true);
+  along(b, a, j, fy, n, true);
+  along(a, b, i, fx, 1, true);
+  if (on) a[q] = b[q];
+  __syncthreads();
+}
+
+template <typename T>
+__global__ __launch_bounds__(MG_TAIL_THREADS) void k_mgcycle_tail(const TailArgs<T> t) {
+  __shared__ T ph[2 * MG_TAIL_ALLOC], ff[MG_TAIL_ALLOC];
+  __shared__ T sQ[MG_DIRECT_MAX * MG_DIRECT_MAX], slam[MG_DIRECT_MAX];
+  __shared__ double sh[MG_TAIL_THREADS / 64 + 1];
+  __shared__ TailLevel<T> lev[MG_TAIL_LEVELS];
+  const int nl = t.nl, tid = threadIdx.x;
+  const int nb = t.n0 >> (nl - 1);  // cells per axis of the coarsest level
+  const bool direct = nb <= MG_DIRECT_MAX;
+  if (tid < nl) {
+    int off = 0;
+    for (int m = 0; m < tid; ++m) {
+      const int nm = t.n0 >> m;
+      off += nm * nm * nm;
+    }
+    const int n = t.n0 >> tid;
+    const T h = t.h * (T)(1 << tid);
+    lev[tid] = TailLevel<T>{n, off, 1.0f / (float)n, h * h, T(1) / (h * h)};
+  }
+  if (direct && tid >= 64 && tid < 64 + nb * MG_DIRECT_MAX) {
+    // the real Fourier basis: constant, cos and sin pairs, (-1)^i
+    const int m = (tid - 64) / MG_DIRECT_MAX, i = (tid - 64) % MG_DIRECT_MAX, k = (m + 1) / 2;
+    if (i < nb) {
+      const double th = 2.0 * (double)(k * i % nb) / (double)nb;
+      const double c = sqrt((m == 0 || 2 * k == nb ? 1.0 : 2.0) / (double)nb);
+      sQ[tid - 64] = (T)(c * (m % 2 || m == 0 ? cospi(th) : sinpi(th)));
+      if (i == 0) slam[m] = (T)(2.0 - 2.0 * cospi(2.0 * (double)k / (double)nb));
+    }
+  }
+  {
+    const int N0 = t.n0 * t.n0 * t.n0;
+    for (int q = tid; q < N0; q += MG_TAIL_THREADS) {
+      ff[q] = t.F0[q];
+      ph[q] = t.warm ? t.phi0[q] : T(0);
+    }
+  }
+  __syncthreads();
+  unsigned curs = 0;  // bit m: which phi buffer level m is in
+  unsigned todo = 0;  // bits 2 m, 2 m + 1: coarse cycles of level m + 1 still to run
   auto smooth = [&](int m, int sweeps) {
-    if (t.rbgs) tail_rbgs(pa, pb, ff, t.off[m], t.n[m], t.h2[m], sweeps, cur[m]);
-    else tail_sweeps(pa, pb, ff, t.off[m], t.n[m], t.h2[m], sweeps, cur[m]);
+    int cur = (curs >> m) & 1;
+    const TailLevel<T> L = lev[m];
+    if (t.rbgs) tail_rbgs(ph, ff, L, sweeps, cur);
+    else tail_sweeps(ph, ff, L, sweeps, cur);
+    curs = (curs & ~(1u << m)) | ((unsigned)cur << m);
   };
   int m = 0;
   bool down = true;
   for (;;) {
     if (down) {
-      if (m == t.nl - 1) {
+      const TailLevel<T> L = lev[m];
+      if (m == nl - 1) {
         // coarsest level: phi = 0, Jacobi sweeps, remove the mean (as
         // k_coarse_solve)
-        const int n = t.n[m], N = n * n * n, o = t.off[m];
-        for (int q = threadIdx.x; q < N; q += MG_TAIL_THREADS) pa[o + q] = T(0);
-        cur[m] = 0;
-        __syncthreads();
-        if (N <= 64) tail_sweeps_wave(pa, pb, ff, o, n, t.h2[m], t.csweeps, cur[m]);
-        else tail_sweeps(pa, pb, ff, o, n, t.h2[m], t.csweeps, cur[m]);
-        T* phi = (cur[m] ? pb : pa) + o;
-        double s = 0.0;
-        for (int q = threadIdx.x; q < N; q += MG_TAIL_THREADS) s += (double)phi[q];
-        const double mean = block_sum1024(s, sh) / (double)N;
-        for (int q = threadIdx.x; q < N; q += MG_TAIL_THREADS) phi[q] = phi[q] - (T)mean;
-        __syncthreads();
+        const int N = L.n * L.n * L.n;
+        int cur = 0;
+        if (direct) {
+          tail_direct(ph + L.off, ph + L.off + MG_TAIL_ALLOC, ff + L.off, sQ, slam, L, t.csweeps);
+        } else {
+          for (int q = tid; q < N; q += MG_TAIL_THREADS) ph[L.off + q] = T(0);
+          __syncthreads();
+          if (N <= 64) tail_sweeps_wave(ph, ff, L, t.csweeps, cur);
+          else tail_sweeps(ph, ff, L, t.csweeps, cur);
+          T* phi = ph + L.off + cur * MG_TAIL_ALLOC;
+          double s = 0.0;
+          for (int q = tid; q < N; q += MG_TAIL_THREADS) s += (double)phi[q];
+          const double mean = block_sum1024(s, sh) / (double)N;
+          for (int q = tid; q < N; q += MG_TAIL_THREADS) phi[q] = phi[q] - (T)mean;
+          __syncthreads();
+        }
+        curs = (curs & ~(1u << m)) | ((unsigned)cur << m);
         down = false;
         continue;
       }
-      const int n = t.n[m], o = t.off[m];
       smooth(m, t.pre);
       // restricted residual: F_{m+1} = average over the 8 children of F - A phi
-      const T* phi = (cur[m] ? pb : pa) + o;
-      const int nc = t.n[m + 1], Nc = nc * nc * nc, oc = t.off[m + 1];
-      for (int Q = threadIdx.x; Q < Nc; Q += MG_TAIL_THREADS) {
-        const int I = Q % nc, J = (Q / nc) % nc, K = Q / (nc * nc);
+      const T* phi = ph + L.off + (int)((curs >> m) & 1) * MG_TAIL_ALLOC;
+      const TailLevel<T> Lc = lev[m + 1];
+      const int n = L.n, nc = Lc.n, Nc = nc * nc * nc;
+      for (int Q = tid; Q < Nc; Q += MG_TAIL_THREADS) {
+        const int r = fdiv(Q, Lc.rn), K = fdiv(r, Lc.rn), J = r - K * nc, I = Q - r * nc;
         T sum = T(0);
+#pragma unroll
         for (int c = 0; c < 2; ++c)
+#pragma unroll
           for (int b = 0; b < 2; ++b)
+#pragma unroll
             for (int a = 0; a < 2; ++a) {
               const int i = 2 * I + a, j = 2 * J + b, k = 2 * K + c;
               const int q = (k * n + j) * n + i;
-              sum += ff[o + q] - (nb6(phi, n, i, j, k) - T(6) * phi[q]) * t.ih2[m];
+              sum += ff[L.off + q] - (tail_nb6(phi, n, q, i, j, k) - T(6) * phi[q]) * L.ih2;
             }
-        ff[oc + Q] = T(0.125) * sum;
+        ff[Lc.off + Q] = T(0.125) * sum;
+        ph[Lc.off + Q] = T(0);  // the coarse error starts from zero
       }
+      curs &= ~(2u << m);
       __syncthreads();
-      double s = 0.0;
-      for (int Q = threadIdx.x; Q < Nc; Q += MG_TAIL_THREADS) s += (double)ff[oc + Q];
-      const T mean = (T)(block_sum1024(s, sh) / (double)Nc);
-      for (int Q = threadIdx.x; Q < Nc; Q += MG_TAIL_THREADS) {
-        ff[oc + Q] = ff[oc + Q] - mean;
-        pa[oc + Q] = T(0);  // the coarse error starts from zero
-      }
-      cur[m + 1] = 0;
-      __syncthreads();
-      todo[m] = (t.wcycle && m + 1 < t.nl - 1) ? 2 : 1;
+      todo = (todo & ~(3u << (2 * m))) | ((t.wcycle && m + 1 < nl - 1 ? 2u : 1u) << (2 * m));
       ++m;
     } else {
       if (m == 0) break;
       const int p = m - 1;
-      if (--todo[p] > 0) {
+      todo -= 1u << (2 * p);
+      if ((todo >> (2 * p)) & 3u) {
         down = true;  // the next coarse cycle starts from the current result
         continue;
       }
       // cell-centred trilinear prolongation of the coarse correction, added
-      const int nc = t.n[m], nf = t.n[p], Nf = nf * nf * nf;
-      const T* ec = (cur[m] ? pb : pa) + t.off[m];
-      T* phif = (cur[p] ? pb : pa) + t.off[p];
-      for (int q = threadIdx.x; q < Nf; q += MG_TAIL_THREADS) {
-        const int i = q % nf, j = (q / nf) % nf, k = q / (nf * nf);
+      const TailLevel<T> L = lev[p], Lc = lev[m];
+      const int nf = L.n, nc = Lc.n, Nf = nf * nf * nf;
+      const T* ec = ph + Lc.off + (int)((curs >> m) & 1) * MG_TAIL_ALLOC;
+      T* phif = ph + L.off + (int)((curs >> p) & 1) * MG_TAIL_ALLOC;
+      for (int q = tid; q < Nf; q += MG_TAIL_THREADS) {
+        const int r = fdiv(q, L.rn), k = fdiv(r, L.rn), j = r - k * nf, i = q - r * nf;
         const int I = i >> 1, J = j >> 1, K = k >> 1;
         const int I2 = wrapi(I + ((i & 1) ? 1 : -1), nc);
         const int J2 = wrapi(J + ((j & 1) ? 1 : -1), nc);
@@ -466,9 +818,9 @@ __global__ __launch_bounds__(MG_TAIL_THREADS) void k_mgcycle_tail(TailArgs<T> t)
     }
   }
   {
-    const int N0 = t.n[0] * t.n[0] * t.n[0];
-    const T* phi = (cur[0] ? pb : pa) + t.off[0];
-    for (int q = threadIdx.x; q < N0; q += MG_TAIL_THREADS) t.phi0[q] = phi[q];
+    const int N0 = t.n0 * t.n0 * t.n0;
+    const T* phi = ph + (int)(curs & 1) * MG_TAIL_ALLOC;
+    for (int q = tid; q < N0; q += MG_TAIL_THREADS) t.phi0[q] = phi[q];
   }
 }
 
@@ -593,6 +945,69 @@ void smooth_level(char* ws, MGLevel& lv, int sweeps, int rbgs, int& cur, hipStre
   }
 }
 
+// whether level n is smoothed on tiles: red-black, at least one sweep before
+// and after the coarse correction, and not a small grid
+inline bool tiled_level(int n, const mh_physics_desc& p) {
+  return p.mg_smoother == MH_SMOOTH_RBGS && p.mg_pre >= 1 && p.mg_post >= 1 &&
+         n >= MG_TILE_MIN && n % 2 == 0;
+}
+// tiles of the last of `sweeps` sweeps on a level (the blocks of RES_NORM)
+inline int level_tiles(int n, int sweeps) {
+  static_assert(MGFine::BZ == MGSmall::BZ, "tile depth");
+  const int b = n >= MG_FINE_MIN || sweeps % 2 ? MGFine::BX : MGSmall::BX;
+  const int t = (n + b - 1) / b;
+  return t * t * ((n + MGFine::BZ - 1) / MGFine::BZ);
+}
+
+template <typename T, class C, int RES>
+void launch_tile(const TileArgs<T>& a, bool zero, bool pro, unsigned tiles, hipStream_t s) {
+  const dim3 block(TileShape<C, RES>::NT);
+  if (zero) hipLaunchKernelGGL((k_rbgs_tile<T, C, RES, true, false>), dim3(tiles), block, 0, s, a);
+  else if (pro) hipLaunchKernelGGL((k_rbgs_tile<T, C, RES, false, true>), dim3(tiles), block, 0, s, a);
+  else hipLaunchKernelGGL((k_rbgs_tile<T, C, RES, false, false>), dim3(tiles), block, 0, s, a);
+}
+
+// one launch of C::S sweeps on level lv, from phi[cur] to phi[1 - cur]
+template <typename T, class C>
+void tile_sweeps(char* ws, const MGLevel& lv, const MGLevel* cv, const T* ec, int& cur, bool zero,
+                 int res, double* partial, hipStream_t s) {
+  TileArgs<T> a{};
+  a.n = lv.n;
+  a.ntx = (lv.n + C::BX - 1) / C::BX;
+  a.nty = (lv.n + C::BY - 1) / C::BY;
+  a.h2 = (T)(lv.h * lv.h);
+  a.ih2 = (T)(1.0 / (lv.h * lv.h));
+  a.phi = P<T>(ws, lv.phi[cur]);
+  a.F = P<T>(ws, lv.F);
+  a.ec = ec;
+  a.out = P<T>(ws, lv.phi[1 - cur]);
+  a.Fc = cv ? P<T>(ws, cv->F) : nullptr;
+  a.partial = partial;
+  const unsigned tiles = (unsigned)(a.ntx * a.nty * ((lv.n + C::BZ - 1) / C::BZ));
+  if (res == RES_COARSE) launch_tile<T, C, RES_COARSE>(a, zero, ec != nullptr, tiles, s);
+  else if (res == RES_NORM) launch_tile<T, C, RES_NORM>(a, zero, ec != nullptr, tiles, s);
+  else launch_tile<T, C, RES_NONE>(a, zero, ec != nullptr, tiles, s);
+  cur = 1 - cur;
+}
+
+// `sweeps` sweeps of a tiled level: from zero, or with the correction ec added
+// first, and the residual's `res` form from the last launch.  Small levels take
+// the sweeps in pairs if there are only pairs, else one by one
+template <typename T>
+void smooth_tiles(char* ws, const MGLevel& lv, const MGLevel* cv, const T* ec, int sweeps,
+                  int& cur, bool zero, int res, double* partial, hipStream_t s) {
+  const bool pair = lv.n < MG_FINE_MIN && sweeps % 2 == 0;
+  while (sweeps > 0) {
+    const int left = sweeps - (pair ? 2 : 1);
+    const int r = left == 0 ? res : RES_NONE;
+    if (pair) tile_sweeps<T, MGSmall>(ws, lv, cv, ec, cur, zero, r, partial, s);
+    else tile_sweeps<T, MGFine>(ws, lv, cv, ec, cur, zero, r, partial, s);
+    zero = false;
+    ec = nullptr;
+    sweeps = left;
+  }
+}
+
 // first level handled by the single-workgroup tail: the first one after the
 // fine level with at most MG_TAIL_MAX_CELLS cells that is not the coarsest
 // (nlev when there is none)
@@ -604,45 +1019,51 @@ inline int tail_level(const MGLayout& L) {
   return L.nlev;
 }
 
-// one cycle on level l < l0 from its current phi (lev[l].phi[cur[l]]): pre
-// smoothing, restriction of the residual, the coarse error equation solved by
-// one (V) or two (W) cycles of level l + 1 from zero -- one solve when level
-// l + 1 is the coarsest -- prolongation and correction, post smoothing
+// one cycle on level l < l0 from its current phi (lev[l].phi[cur[l]], or from
+// zero): pre smoothing, restriction of the residual, the coarse error equation
+// solved by one (V) or two (W) cycles of level l + 1 from zero -- one solve
+// when level l + 1 is the coarsest -- prolongation and correction, post
+// smoothing.  With `norm`, a tiled level leaves the block sums of its squared
+// residual in `partial` at the end
 template <typename T>
 hipError_t level_cycle(char* ws, MGLayout& L, const mh_physics_desc& p, int l, int l0,
-                       int* cur, double* partial, double* mean_slot, hipStream_t s) {
+                       int* cur, bool zero, bool norm, double* partial, double* mean_slot,
+                       hipStream_t s) {
   const int nl = L.nlev;
   const int rbgs = p.mg_smoother == MH_SMOOTH_RBGS;
   MGLevel& lv = L.lev[l];
   const long long N = (long long)lv.n * lv.n * lv.n;
-  smooth_level<T>(ws, lv, p.mg_pre, rbgs, cur[l], s);
+  const bool tiled = tiled_level(lv.n, p);
   MGLevel& cv = L.lev[l + 1];
   const long long Nc = (long long)cv.n * cv.n * cv.n;
-  // F_c and its block sums in one pass, then its mean removed
-  const int nbc = sum_blocks(Nc);
-  hipLaunchKernelGGL((k_residual_restrict<T>), dim3(nbc), dim3(256), 0, s, cv.n,
-                     (T)(1.0 / (lv.h * lv.h)), P<T>(ws, lv.phi[cur[l]]), P<T>(ws, lv.F),
-                     P<T>(ws, cv.F), partial);
-  hipLaunchKernelGGL(k_sum_final, dim3(1), dim3(256), 0, s, partial, nbc, 1.0 / (double)Nc,
-                     mean_slot);
-  hipLaunchKernelGGL((k_sub_mean<T>), dim3(nblk(Nc)), dim3(256), 0, s, P<T>(ws, cv.F), Nc,
-                     mean_slot);
-  hipError_t e = hipGetLastError();
+  hipError_t e = hipSuccess;
+  if (tiled) {
+    smooth_tiles<T>(ws, lv, &cv, (const T*)nullptr, p.mg_pre, cur[l], zero, RES_COARSE, partial, s);
+  } else {
+    if (zero)
+      hipLaunchKernelGGL((k_zero<T>), dim3(nblk(N)), dim3(256), 0, s, P<T>(ws, lv.phi[cur[l]]), N);
+    smooth_level<T>(ws, lv, p.mg_pre, rbgs, cur[l], s);
+    // F_c and its block sums in one pass, then its mean removed
+    const int nbc = sum_blocks(Nc);
+    hipLaunchKernelGGL((k_residual_restrict<T>), dim3(nbc), dim3(256), 0, s, cv.n,
+                       (T)(1.0 / (lv.h * lv.h)), P<T>(ws, lv.phi[cur[l]]), P<T>(ws, lv.F),
+                       P<T>(ws, cv.F), partial);
+    hipLaunchKernelGGL(k_sum_final, dim3(1), dim3(256), 0, s, partial, nbc, 1.0 / (double)Nc,
+                       mean_slot);
+    hipLaunchKernelGGL((k_sub_mean<T>), dim3(nblk(Nc)), dim3(256), 0, s, P<T>(ws, cv.F), Nc,
+                       mean_slot);
+  }
+  e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int mu = (p.mg_cycle == MH_MG_W && l + 1 < nl - 1) ? 2 : 1;
   if (l + 1 == l0) {
     TailArgs<T> t{};
     t.nl = nl - l0;
-    int off = 0;
-    for (int m = 0; m < t.nl; ++m) {
-      const MGLevel& tv = L.lev[l0 + m];
-      t.n[m] = tv.n;
-      t.h2[m] = (T)(tv.h * tv.h);
-      t.ih2[m] = (T)(1.0 / (tv.h * tv.h));
-      t.off[m] = off;
-      off += tv.n * tv.n * tv.n;
-    }
-    if (off > MG_TAIL_ALLOC) return hipErrorInvalidValue;
+    t.n0 = cv.n;
+    t.h = (T)cv.h;
+    int cells = 0;
+    for (int m = l0; m < nl; ++m) cells += L.lev[m].n * L.lev[m].n * L.lev[m].n;
+    if (cells > MG_TAIL_ALLOC || t.nl > MG_TAIL_LEVELS) return hipErrorInvalidValue;
     t.F0 = P<T>(ws, cv.F);
     t.phi0 = P<T>(ws, cv.phi[0]);
     t.pre = p.mg_pre;
@@ -661,11 +1082,15 @@ hipError_t level_cycle(char* ws, MGLayout& L, const mh_physics_desc& p, int l, i
                        P<T>(ws, cv.F), P<T>(ws, cv.phi[0]), p.mg_coarse_sweeps);
   } else {
     cur[l + 1] = 0;
-    hipLaunchKernelGGL((k_zero<T>), dim3(nblk(Nc)), dim3(256), 0, s, P<T>(ws, cv.phi[0]), Nc);
     for (int k = 0; k < mu; ++k) {
-      e = level_cycle<T>(ws, L, p, l + 1, l0, cur, partial, mean_slot, s);
+      e = level_cycle<T>(ws, L, p, l + 1, l0, cur, k == 0, false, partial, mean_slot, s);
       if (e != hipSuccess) return e;
     }
+  }
+  if (tiled) {
+    smooth_tiles<T>(ws, lv, nullptr, P<T>(ws, cv.phi[cur[l + 1]]), p.mg_post, cur[l], false,
+                    norm ? RES_NORM : RES_NONE, partial, s);
+    return hipGetLastError();
   }
   hipLaunchKernelGGL((k_prolong_add<T>), plane_grid((long long)lv.n * lv.n, lv.n), dim3(256),
                      0, s, cv.n,
@@ -695,7 +1120,8 @@ hipError_t vcycle(char* ws, MGLayout& L, const mh_physics_desc& p, double* parti
     hipError_t e = remove_mean(P<T>(ws, cv.phi[cur[0]]), N, partial, mean_slot, s);
     if (e != hipSuccess) return e;
   } else {
-    hipError_t e = level_cycle<T>(ws, L, p, 0, tail_level(L), cur, partial, mean_slot, s);
+    hipError_t e =
+        level_cycle<T>(ws, L, p, 0, tail_level(L), cur, false, true, partial, mean_slot, s);
     if (e != hipSuccess) return e;
   }
   L.cur0 = cur[0];
@@ -763,9 +1189,11 @@ size_t mg_layout(const mh_grid_desc* g, const mh_physics_desc* p, size_t off, si
   };
   // levels halve n while n > coarsest and n is even (the rule of mg_validate)
   L = MGLayout();
-  L.partial = take(MG_PARTIALS * sizeof(double));
   int n = g->n[0];
   double h = g->h[0];
+  // block sums: of the capped reductions, or one per tile of the fine level
+  const long long t8 = (n + 7) / 8, tiles = t8 * t8 * t8;
+  L.partial = take((size_t)(tiles > MG_PARTIALS ? tiles : MG_PARTIALS) * sizeof(double));
   if (p->grav_solver == MH_GRAV_FFT) {
     MGLevel& lv = L.lev[L.nlev++];
     const size_t bytes = (size_t)n * n * n * es;
@@ -904,11 +1332,17 @@ hipError_t mg_solve(char* ws, MGLayout& L, const mh_physics_desc& p, DevClock* c
   MG_CHECK(remove_mean(P<T>(ws, f.phi[L.cur0]), N, partial, &clk->mean, s));
   int cycles = 0;
   double prev = INFINITY;
+  // a tiled fine level leaves the block sums of |r|^2 with its last sweep; phi
+  // may then carry a constant, which no operator sees, until the end
+  const bool fused = L.nlev > 1 && tiled_level(n, p);
   for (;;) {
     // |r|^2 without storing r: the sum k_sum_partial would form over it
-    const int nbr = sum_blocks(N);
-    hipLaunchKernelGGL((k_residual_norm2<T>), dim3(nbr), dim3(256), 0, s, n,
-                       (T)(1.0 / (f.h * f.h)), P<T>(ws, f.phi[L.cur0]), P<T>(ws, f.F), partial);
+    int nbr = sum_blocks(N);
+    if (fused && cycles > 0)
+      nbr = level_tiles(n, p.mg_post);
+    else
+      hipLaunchKernelGGL((k_residual_norm2<T>), dim3(nbr), dim3(256), 0, s, n,
+                         (T)(1.0 / (f.h * f.h)), P<T>(ws, f.phi[L.cur0]), P<T>(ws, f.F), partial);
     hipLaunchKernelGGL(k_sum_final, dim3(1), dim3(256), 0, s, partial, nbr, 1.0,
                        &clk->mg_rnorm2);
     double norms[2];
@@ -922,9 +1356,11 @@ hipError_t mg_solve(char* ws, MGLayout& L, const mh_physics_desc& p, DevClock* c
     if (p.mg_tol > 0.0 && rn > MG_STALL * prev) break;
     prev = rn;
     MG_CHECK(run_vcycle<T>(ws, L, p, partial, &clk->mean, s));
-    MG_CHECK(remove_mean(P<T>(ws, f.phi[L.cur0]), N, partial, &clk->mean, s));
+    if (!fused) MG_CHECK(remove_mean(P<T>(ws, f.phi[L.cur0]), N, partial, &clk->mean, s));
     ++cycles;
   }
+  if (fused && cycles > 0)
+    MG_CHECK(remove_mean(P<T>(ws, f.phi[L.cur0]), N, partial, &clk->mean, s));
   hipLaunchKernelGGL(k_set_cycles, dim3(1), dim3(64), 0, s, clk, cycles);
   if (cycles_out) *cycles_out = cycles;
   return hipGetLastError();
