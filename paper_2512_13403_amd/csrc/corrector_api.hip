@@ -16,7 +16,7 @@ constexpr size_t CALIGN = 256;
 inline size_t calign(size_t x) { return (x + CALIGN - 1) & ~(CALIGN - 1); }
 
 struct CorrLayout {
-  size_t theta, m, v, grad, w1, w2, w3, w1t, w2t, w3t, x0, z1, h1, z2, h2, y, gx, dy16, dy32, dz2,
+  size_t theta, m, v, grad, w1, w2, w3, w1t, w2t, w3t, x0, z1, h1, z2, h2, y, gx, dy16, dz2,
       dz1;
   size_t wpart, dpart, loss, counters, cpart, total;
 };
@@ -49,7 +49,6 @@ CorrLayout corr_layout(const mh_corr_desc* d) {
   L.y = take(cells * 16 * 4);
   L.gx = take(cells * 16 * 4);
   L.dy16 = take(cells * 16 * 2);
-  L.dy32 = take(cells * 32 * 2);
   L.dz2 = take(cells * 32 * 2);
   L.dz1 = take(cells * 32 * 2);
   L.wpart = take((size_t)28 * corr_wgrad_groups((long long)cells) * 32 * 32 * 4);
@@ -128,7 +127,7 @@ extern "C" mh_status mh_corr_init(const mh_corr_desc* d, void* workspace, size_t
   auto F = [&](size_t o) { return reinterpret_cast<float*>(w + o); };
   auto H = [&](size_t o) { return reinterpret_cast<unsigned short*>(w + o); };
   c->B = CorrBuffers{F(L.theta), F(L.m), F(L.v), F(L.grad), H(L.w1), H(L.w2), H(L.w3), H(L.w1t),
-                     H(L.w2t), H(L.w3t), H(L.x0), H(L.h1), H(L.h2), H(L.dy16), H(L.dy32),
+                     H(L.w2t), H(L.w3t), H(L.x0), H(L.h1), H(L.h2), H(L.dy16),
                      H(L.dz2), H(L.dz1), F(L.z1), F(L.z2), F(L.y), F(L.gx), F(L.wpart),
                      reinterpret_cast<double*>(w + L.dpart), reinterpret_cast<double*>(w + L.loss),
                      reinterpret_cast<unsigned long long*>(w + L.counters),

@@ -7,21 +7,20 @@
 // cross-correlations of 5 -> 32 -> 32 -> 5 channels.
 //
 // Every convolution is an implicit GEMM on v_mfma_f32_16x16x32_bf16.  A
-// workgroup stages a 16 x 4 x 4 block of cells plus its one-cell periodic halo
-// in LDS (bf16, 32 channels per cell, channels contiguous); each of its four
-// waves owns four rows of 16 cells along x (the MFMA rows) and all output
-// channels (the MFMA columns, 16 per tile).  For each of the 27 taps a wave
-// loads that tap's weight block once and multiplies it into its four rows,
-// whose shifted inputs it reads from LDS, accumulating in fp32.  Activations
-// are stored cell-major with 32 channels (the network input fills 10 of them:
-// each of the 5 standardised fields as two bf16 parts, hi + lo, which meet
-// the same first-layer weights, so the input keeps about 16 bits at no extra
+// persistent workgroup of eight waves holds a layer's weights in LDS and stages
+// 16 x 4 x 8 blocks of cells plus their one-cell periodic halo next to them
+// (bf16, 32 channels per cell, channels contiguous); each wave owns four rows
+// of 16 cells along x (the MFMA columns) and all output channels (the MFMA
+// rows, 16 per tile), accumulating in fp32.  Activations are stored cell-major
+// with 32 channels (the network input fills 10 of them: each of the 5
+// standardised fields as two bf16 parts, hi + lo, which meet the same
+// first-layer weights, so the input keeps about 16 bits at no extra
 // matrix-core work; the last layer's 5 outputs sit in 16).  The same kernel
-// serves the input-gradient pass: there the weights are packed transposed
-// with the taps mirrored, so reading at cell + off_tap applies the transpose
-// of the forward map.  Weight gradients are GEMMs over cells: one workgroup
-// per (tap, chunk of 4096 cells) writes a 32 x 32 partial product, and a
-// second kernel adds the chunks in a fixed order (deterministic).
+// serves the input-gradient pass: there the weights are packed transposed with
+// the taps mirrored, so reading at cell + off_tap applies the transpose of the
+// forward map.  Weight gradients are GEMMs over cells: persistent workgroups
+// write partial products of all taps, and a second kernel adds them in a fixed
+// order (deterministic).
 #include <hip/hip_runtime.h>
 
 #include "mh_corrector.h"
@@ -46,6 +45,14 @@ __device__ __forceinline__ bf16x8 load8(const unsigned short* p) {
   bf16x8 v;
   __builtin_memcpy(&v, p, 16);
   return v;
+}
+
+// four floats as bf16 (round to nearest even), one 8-byte store
+__device__ __forceinline__ void store_bf4(unsigned short* p, const f32x4& v) {
+  __bf16 b[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) b[q] = (__bf16)v[q];
+  __builtin_memcpy(p, b, 8);
 }
 
 __device__ __forceinline__ int wrap(int i, int n) { return i < 0 ? i + n : (i >= n ? i - n : i); }
@@ -97,38 +104,80 @@ struct ResArgs {
   long long n3;  // cells per sample
 };
 
-// Halo tile of the tiled convolution: 16 cells along x (the MFMA rows) by
-// CTY x CTZ rows in (y, z), with a one-cell periodic halo, staged in LDS.
+// Halo tile of the weight gradient: 16 cells along x by CTY x CTZ rows in
+// (y, z), with a one-cell periodic halo, staged in LDS.
 constexpr int CTX = 16, CTY = 4, CTZ = 4;
 constexpr int CHX = CTX + 2, CHY = CTY + 2, CHZ = CTZ + 2, CNH = CHX * CHY * CHZ;
-constexpr int CROWS = CTY * CTZ / 4;  // rows per wave (4 waves)
-constexpr int CPD = 4;                // weight prefetch distance, in taps
 static_assert(CTX * CTY * CTZ == CORR_BLOCK_CELLS, "tile size");
 
 typedef __attribute__((__vector_size__(4 * sizeof(unsigned int)))) unsigned int u32x4;
+
+// Tile of the convolution: 16 cells along x (an MFMA row) by VY x VZ rows in
+// (y, z); a wave per z, which owns its VY rows and all output channels.
+constexpr int VX = 16, VY = 4, VZ = 8, VT = 64 * VZ;
 
 // 16-byte channel chunk c of halo cell (hx, ...) sits in slot c ^ ((hx >> 2) & 3):
 // the 16 lanes of a row read 16 consecutive hx and so 16 distinct bank groups.
 __device__ __forceinline__ int cslot(int h, int hx, int c) { return h * 4 + (c ^ ((hx >> 2) & 3)); }
 
-// out[cell][co] for COT output channels (16 or 32) from in[cell][32] (bf16):
-// per tap, the wave's CROWS rows of 16 cells read their shifted inputs from
-// the LDS tile and multiply them by the tap's 32 x COT weight block (bf16
-// [NT][COT][32]), loaded once per tap and prefetched CPD taps ahead.  NT = 9
-// for an input whose 32 channels already hold the three x neighbours (the
-// first layer: 3 x 10 input parts): the taps then run over (dy, dz) only.
-template <int COT, int EPI, int NT = 27, typename TU = float>
-__global__ __launch_bounds__(256, 3) void k_conv(const unsigned short* __restrict__ in,
-                                              const unsigned short* __restrict__ w,
-                                              const float* __restrict__ bias, int nbias, int n,
-                                              const float* __restrict__ zin,
-                                              float* __restrict__ fout,
-                                              unsigned short* __restrict__ hout, int ntiles,
-                                              ResArgs<TU> ra) {
-  __shared__ u32x4 tile[CNH * 4];
-  constexpr int NLD = (CNH * 4 + 255) / 256;  // 16-byte halo chunks per thread
-  const int ntx = n / CTX, nty = n / CTY, ntz = n / CTZ;
-  // tile t: origin (x0, y0, z0) in sample b, whose first cell is `base`
+// out[cell][co] for COT output channels (16 or 32) from in[cell][CI] (bf16, CI
+// = 32, or 16 with the upper half of the operand zero): an implicit GEMM,
+// weights (bf16 [NT][COT][32]) as the A operand.  NT = 9 for an input whose 32
+// channels already hold the three x neighbours (the first layer: 3 x 10 input
+// parts): the taps then run over (dy, dz) only.
+//
+// A persistent workgroup of eight waves per CU holds all weights in LDS, laid
+// out so that an operand is one 16-byte read of consecutive lanes, next to the
+// tile with its halo.  Per dz a wave takes the nine (three) taps' weights into
+// registers and walks its six halo rows: an input operand is read once and
+// meets the three rows whose stencil holds it, so a tap's MFMA costs half an
+// LDS read of each kind instead of one and a global weight load per wave and
+// tile (at 4 x 64^3 the weights alone were 0.9 GB through L2 per layer).  Every
+// output still adds its taps in the order dz, dy, dx.
+// Matrix cores (3.5 k cycles of a 512-cell tile per wave, two per SIMD), LDS
+// and the GELU of the epilogue (4 k cycles) weigh about the same, so the
+// epilogue of a tile is interleaved with the MFMAs of the next one, whose halo
+// was loaded into registers a tile earlier.  Against four waves on a 16 x 4 x 4
+// tile with the weights read from L2 and the epilogue after the MFMAs, at
+// 4 x 64^3 (us): middle layer with its z stored 105 -> 89, the two
+// input-gradient passes 117 -> 97 and 103, last layer 64 -> 48, input gradient
+// of the first 55 -> 42; the gradient of the last layer's 16 outputs is read as
+// it is instead of from a copy padded to 32 channels (25 us of copying).
+template <int COT, int EPI, int NT, int CI, typename TU = float>
+__global__ __launch_bounds__(VT, 2) void k_conv(const unsigned short* __restrict__ in,
+                                                const unsigned short* __restrict__ w,
+                                                const float* __restrict__ bias, int nbias, int n,
+                                                const float* __restrict__ zin,
+                                                float* __restrict__ fout,
+                                                unsigned short* __restrict__ hout, int ntiles,
+                                                ResArgs<TU> ra) {
+  constexpr int DX = NT == 27 ? 3 : 1;           // x taps
+  constexpr int HX = VX + DX - 1, HY = VY + 2, HZ = VZ + 2, NH = HX * HY * HZ;
+  constexpr int NCO = COT / 16, TZ = 3 * DX;     // channel tiles; taps per dz
+  constexpr int NCH = CI / 8;                    // 16-byte chunks per cell in memory
+  constexpr int RU = HX * NCH;                   // chunks per halo row
+  constexpr int RP = VT / RU;                    // rows staged at a time
+  constexpr int NLD = (HY * HZ + RP - 1) / RP;   // chunks per thread
+  __shared__ u32x4 tile[NH * 4];
+  __shared__ u32x4 wts[NT * COT * 4];
+  __shared__ unsigned rowtab[2][HY * HZ];
+  const int ntx = n / VX, nty = n / VY, ntz = n / VZ;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int row = lane & 15, grp = lane >> 4;
+  // chunk c of (tap, co): lane 16 c + co % 16 of the block (tap, co / 16)
+  for (int g = threadIdx.x; g < NT * COT * 4; g += VT) {
+    const int c = g & 3, co = (g >> 2) % COT, tap = (g >> 2) / COT;
+    u32x4 v;
+    __builtin_memcpy(&v, w + g * 8, 16);
+    wts[(tap * NCO + co / 16) * 64 + c * 16 + co % 16] = v;
+  }
+  if (CI < 32) {  // the channels that are not there
+    for (int g = threadIdx.x; g < NH * (4 - NCH); g += VT) {
+      const int h = g / (4 - NCH), c = NCH + g % (4 - NCH);
+      tile[cslot(h, h % HX, c)] = u32x4{0u, 0u, 0u, 0u};
+    }
+  }
+  // tile t: origin (x0, y0, z0) in the sample whose first cell is `base`
   auto origin = [&](int t, int& x0, int& y0, int& z0, long long& base) {
     const int bx = t % ntx;
     t /= ntx;
@@ -136,163 +185,172 @@ __global__ __launch_bounds__(256, 3) void k_conv(const unsigned short* __restric
     t /= nty;
     const int bz = t % ntz;
     base = (long long)(t / ntz) * n * n * (long long)n;
-    x0 = bx * CTX;
-    y0 = by * CTY;
-    z0 = bz * CTZ;
+    x0 = bx * VX;
+    y0 = by * VY;
+    z0 = bz * VZ;
   };
-  // a persistent workgroup walks the tiles t = blockIdx.x, + gridDim.x, ...;
-  // the halo of its next tile is loaded into registers while the current
-  // tile's outputs are formed and stored, then written to LDS
-  // (the thread index is made opaque where the chunk coordinates are
-  // derived, so that they are recomputed per tile rather than hoisted out of
-  // the tile loop and held in registers)
+  // staging: a thread keeps its place (hx, chunk) in a halo row and takes the
+  // rows lr, lr + RP, ..: a row costs the lookup of its first cell (rowtab, of
+  // the next tile, formed by HY HZ threads) and one address, and its LDS slot
+  // is a constant away from the first
+  const int lr = threadIdx.x / RU, u = threadIdx.x - lr * RU, shx = u / NCH;
+  const bool loads = lr < RP;
+  const int slot0 = cslot(0, shx, u % NCH) + (lr * HX + shx) * 4;
   u32x4 pre[NLD];
-  auto fetch = [&](int t) {
-    int x0, y0, z0;
-    long long base;
-    origin(t, x0, y0, z0, base);
-    unsigned tid = threadIdx.x;
-    asm volatile("" : "+v"(tid));
-    const unsigned short* ib = in + base * 32;
-#pragma unroll
-    for (int k = 0; k < NLD; ++k) {
-      // lanes past the last chunk load the last chunk again (unused): every
-      // load is unconditional
-      const unsigned i = min(tid + 256u * k, (unsigned)(CNH * 4 - 1));
-      const unsigned h = i >> 2, c = i & 3;
-      const unsigned hx = h % CHX, hy = (h / CHX) % CHY, hz = h / (CHX * CHY);
-      const unsigned zy = (unsigned)wrap(z0 - 1 + (int)hz, n) * (unsigned)n +
-                          (unsigned)wrap(y0 - 1 + (int)hy, n);
-      const size_t src = (size_t)zy * (unsigned)n + (unsigned)wrap(x0 - 1 + (int)hx, n);
-      __builtin_memcpy(&pre[k], ib + src * 32 + c * 8, 16);
+  auto rows_of = [&](int t, int buf) {
+    if (threadIdx.x < HY * HZ) {
+      int x0, y0, z0;
+      long long base;
+      origin(t, x0, y0, z0, base);
+      const int hz = threadIdx.x / HY, hy = threadIdx.x - hz * HY;
+      rowtab[buf][threadIdx.x] = (unsigned)wrap(z0 - 1 + hz, n) * (unsigned)n * (unsigned)n +
+                                 (unsigned)wrap(y0 - 1 + hy, n) * (unsigned)n;
     }
   };
-  fetch(blockIdx.x);
-  for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
-    int tid = threadIdx.x;
-    asm volatile("" : "+v"(tid));
-#pragma unroll
-    for (int k = 0; k < NLD; ++k) {
-      const int i = tid + 256 * k;
-      if (i < CNH * 4) {
-        const int h = i >> 2;
-        tile[cslot(h, h % CHX, i & 3)] = pre[k];
-      }
-    }
-    __syncthreads();
+  auto fetch = [&](int t, int buf) {
+    if (!loads) return;
     int x0, y0, z0;
     long long base;
     origin(t, x0, y0, z0, base);
-    const int lane = tid & 63, wave = tid >> 6;  // (tid: opaque, see above)
-    const int row = lane & 15, grp = lane >> 4;
-    // the wave's rows (y0 + r, z0 + wave) for r < CROWS = CTY: the halo slab
-    // hz = wave + 1 + dz starts at wtile; lslot: the lane's slot offset for
-    // dx = -1, 0, 1 (cslot of hx = row + 1 + dx, channel chunk grp)
-    static_assert(CROWS == CTY, "a wave's rows are one z-row of the tile");
-    const u32x4* wtile = tile + ((wave + 1) * CHY) * CHX * 4;
-    int lslot[3];
+    const unsigned short* ib = in + base * CI + (u % NCH) * 8;
+    const unsigned x = (unsigned)wrap(x0 - (DX == 3 ? 1 : 0) + shx, n);
 #pragma unroll
-    for (int d = 0; d < 3; ++d) lslot[d] = cslot(0, row + d, grp) + (row + d) * 4;
-    f32x4 acc[CROWS][COT / 16];
-#pragma unroll
-    for (int r = 0; r < CROWS; ++r)
-#pragma unroll
-      for (int nt = 0; nt < COT / 16; ++nt) acc[r][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    // weights: CPD taps in flight (a register ring), so the load of a tap's
-    // block is issued CPD taps before its MFMAs
-    // (opaque per tile: the weight loads stay inside the tile loop instead of
-    // being hoisted out of it and held, all 27 taps, in registers)
-    const unsigned short* wl = w + row * 32 + 8 * grp;
-    asm volatile("" : "+v"(wl));
-    bf16x8 bq[CPD][COT / 16];
-#pragma unroll
-    for (int p = 0; p < CPD; ++p)
-#pragma unroll
-      for (int nt = 0; nt < COT / 16; ++nt) bq[p][nt] = load8(wl + (p * COT + nt * 16) * 32);
-#pragma unroll
-    for (int tap = 0; tap < NT; ++tap) {
-      bf16x8 bw[COT / 16];
-#pragma unroll
-      for (int nt = 0; nt < COT / 16; ++nt) bw[nt] = bq[tap % CPD][nt];
-      if (tap + CPD < NT) {
-#pragma unroll
-        for (int nt = 0; nt < COT / 16; ++nt)
-          bq[tap % CPD][nt] = load8(wl + ((tap + CPD) * COT + nt * 16) * 32);
-      }
-      // 27 taps (dx, dy, dz); 9 taps (dy, dz) when the x shifts are packed
-      // into the input channels (the first layer)
-      const int dx = NT == 27 ? tap % 3 - 1 : 0;
-      const int dy = NT == 27 ? (tap / 3) % 3 - 1 : tap % 3 - 1;
-      const int dz = NT == 27 ? tap / 9 - 1 : tap / 3 - 1;
-#pragma unroll
-      for (int r = 0; r < CROWS; ++r) {
-        // row r of the wave: hy = r + 1 + dy, hz = wave + 1 + dz; the lane's
-        // part of the slot depends on dx only, the rest is a constant
-        const u32x4 raw = wtile[lslot[dx + 1] + ((dz * CHY + r + 1 + dy) * CHX) * 4];
-        bf16x8 a;
-        __builtin_memcpy(&a, &raw, 16);
-#pragma unroll
-        for (int nt = 0; nt < COT / 16; ++nt)
-          acc[r][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bw[nt], a, acc[r][nt], 0, 0, 0);
-      }
+    for (int k = 0; k < NLD; ++k) {
+      const int rw = lr + RP * k;
+      if (rw < HY * HZ)
+        __builtin_memcpy(&pre[k], ib + (size_t)(rowtab[buf][rw] + x) * CI, 16);
     }
-    // the next tile's loads are in flight during the epilogue
-    if (t + (int)gridDim.x < ntiles) fetch(t + gridDim.x);
-    // the weights are the A operand (rows: output channels) and the shifted
-    // inputs B (columns: the row's 16 cells), so lane (row, grp) holds output
-    // channels nt * 16 + 4 grp .. + 3 of cell x0 + row: four consecutive
-    // channels, written with one vector store per (row, tile)
+  };
+  // bias of the lane's output channels
+  float bv[NCO][4];
 #pragma unroll
-    for (int r = 0; r < CROWS; ++r) {
-      const int j = wave * CROWS + r;
-      const long long cell =
-          base + ((long long)(z0 + j / CTY) * n + (y0 + j % CTY)) * n + x0 + row;
+  for (int nt = 0; nt < NCO; ++nt)
 #pragma unroll
-      for (int nt = 0; nt < COT / 16; ++nt) {
-        const int co = nt * 16 + 4 * grp;
-        const long long o = cell * COT + co;
-        const f32x4 v = acc[r][nt];
-        if (EPI == EPI_GELU) {
-          f32x4 zz;
-          unsigned short hv[4];
+    for (int q = 0; q < 4; ++q) {
+      const int co = nt * 16 + 4 * grp + q;
+      bv[nt][q] = (EPI == EPI_GELU || EPI == EPI_LINEAR || EPI == EPI_RESIDUAL) && co < nbias
+                      ? bias[co] : 0.f;
+    }
+  // outputs of row r, channels 16 nt .. of a finished tile; a lane holds
+  // channels 16 nt + 4 grp .. + 3 of cell x0 + row: one vector store
+  auto finish = [&](const f32x4& v, int r, int nt, long long cell0, int sample) {
+    const long long cell = cell0 + (long long)r * n;
+    const int co = nt * 16 + 4 * grp;
+    const long long o = cell * COT + co;
+    if (EPI == EPI_GELU) {
+      f32x4 zz, hz;
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            zz[q] = v[q] + bias[co + q];
-            hv[q] = f2bf(gelu(zz[q]));
-          }
-          if (fout) *(f32x4*)(fout + o) = zz;
-          *(u16x4*)(hout + o) = u16x4{hv[0], hv[1], hv[2], hv[3]};
-        } else if (EPI == EPI_LINEAR) {
-          f32x4 y;
+      for (int q = 0; q < 4; ++q) {
+        zz[q] = v[q] + bv[nt][q];
+        hz[q] = gelu(zz[q]);
+      }
+      if (fout) *(f32x4*)(fout + o) = zz;
+      store_bf4(hout + o, hz);
+    } else if (EPI == EPI_LINEAR) {
+      f32x4 y;
 #pragma unroll
-          for (int q = 0; q < 4; ++q) y[q] = v[q] + (co + q < nbias ? bias[co + q] : 0.f);
-          *(f32x4*)(fout + o) = y;
-        } else if (EPI == EPI_RESIDUAL) {
-          // lanes of channel groups 0 and 1 hold fields 0-3 and 4; the
-          // arithmetic of k_residual
-          const long long b = cell / ra.n3, q = cell - b * ra.n3;
+      for (int q = 0; q < 4; ++q) y[q] = v[q] + bv[nt][q];
+      *(f32x4*)(fout + o) = y;
+    } else if (EPI == EPI_RESIDUAL) {
+      // lanes of channel groups 0 and 1 hold fields 0-3 and 4; the
+      // arithmetic of k_residual
+      const long long f0 = (long long)sample * 5 * ra.n3 + (cell - (long long)sample * ra.n3);
 #pragma unroll
-          for (int k = 0; k < 4; ++k) {
-            const int c = co + k;
-            if (c < 5) {
-              const float y = v[k] + bias[c];
-              const TU d = (TU)(ra.scale[c] * (double)y);
-              const long long f = (b * 5 + c) * ra.n3 + q;
-              ra.out[f] = ra.U[f] + d;
-            }
-          }
-        } else if (EPI == EPI_GELU_BWD) {
-          const f32x4 zi = *(const f32x4*)(zin + o);
-          unsigned short hv[4];
-#pragma unroll
-          for (int q = 0; q < 4; ++q) hv[q] = f2bf(v[q] * gelu_grad(zi[q]));
-          *(u16x4*)(hout + o) = u16x4{hv[0], hv[1], hv[2], hv[3]};
-        } else {
-          *(f32x4*)(fout + o) = v;
+      for (int k = 0; k < 4; ++k) {
+        const int c = co + k;
+        if (c < 5) {
+          const float y = v[k] + bv[nt][k];
+          const TU d = (TU)(ra.scale[c] * (double)y);
+          ra.out[f0 + c * ra.n3] = ra.U[f0 + c * ra.n3] + d;
         }
       }
+    } else if (EPI == EPI_GELU_BWD) {
+      const f32x4 zi = *(const f32x4*)(zin + o);
+      f32x4 g;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) g[q] = v[q] * gelu_grad(zi[q]);
+      store_bf4(hout + o, g);
+    } else {
+      *(f32x4*)(fout + o) = v;
     }
+  };
+  // the wave's rows (y0 + r, z0 + wave): its halo slab hz = wave + 1 + dz
+  const u32x4* const wtile = tile + (wave * HY) * HX * 4;
+  int lslot[DX];
+#pragma unroll
+  for (int d = 0; d < DX; ++d) lslot[d] = cslot(0, row + d, grp) + (row + d) * 4;
+  f32x4 old[VY][NCO];
+  long long old_cell = -1;  // first cell of the finished tile's rows
+  int old_sample = 0, buf = 0;
+  rows_of(blockIdx.x, 0);
+  __syncthreads();
+  fetch(blockIdx.x, 0);
+  for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
+    const int next = t + (int)gridDim.x;
+    if (loads) {
+#pragma unroll
+      for (int k = 0; k < NLD; ++k)
+        if (lr + RP * k < HY * HZ) tile[slot0 + k * RP * HX * 4] = pre[k];
+    }
+    buf ^= 1;
+    if (next < ntiles) rows_of(next, buf);
+    __syncthreads();
+    if (next < ntiles) fetch(next, buf);
+    f32x4 acc[VY][NCO];
+#pragma unroll
+    for (int r = 0; r < VY; ++r)
+#pragma unroll
+      for (int nt = 0; nt < NCO; ++nt) acc[r][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const bool pending = old_cell >= 0;
+#pragma unroll
+    for (int dz = 0; dz < 3; ++dz) {
+      bf16x8 bw[TZ][NCO];
+#pragma unroll
+      for (int k = 0; k < TZ; ++k)
+#pragma unroll
+        for (int nt = 0; nt < NCO; ++nt) {
+          const u32x4 raw = wts[((dz * TZ + k) * NCO + nt) * 64 + lane];
+          __builtin_memcpy(&bw[k][nt], &raw, 16);
+        }
+#pragma unroll
+      for (int hy = 0; hy < HY; ++hy) {
+#pragma unroll
+        for (int d = 0; d < DX; ++d) {
+          const u32x4 raw = wtile[lslot[d] + ((dz * HY + hy) * HX) * 4];
+          bf16x8 a;
+          __builtin_memcpy(&a, &raw, 16);
+#pragma unroll
+          for (int dy = 0; dy < 3; ++dy) {
+            const int r = hy - dy;
+            if (r < 0 || r >= VY) continue;
+#pragma unroll
+            for (int nt = 0; nt < NCO; ++nt)
+              acc[r][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bw[dy * DX + d][nt], a,
+                                                                   acc[r][nt], 0, 0, 0);
+          }
+        }
+        // a share of the previous tile's epilogue
+        const int step = dz * HY + hy;
+        if (step < VY * NCO && pending)
+          finish(old[step / NCO][step % NCO], step / NCO, step % NCO, old_cell, old_sample);
+      }
+    }
+    int x0, y0, z0;
+    long long base;
+    origin(t, x0, y0, z0, base);
+    old_cell = base + ((long long)(z0 + wave) * n + y0) * n + x0 + row;
+    old_sample = t / (ntx * nty * ntz);
+#pragma unroll
+    for (int r = 0; r < VY; ++r)
+#pragma unroll
+      for (int nt = 0; nt < NCO; ++nt) old[r][nt] = acc[r][nt];
     __syncthreads();  // the tile is read by every wave before the next is stored
+  }
+  if (old_cell >= 0) {
+#pragma unroll
+    for (int r = 0; r < VY; ++r)
+#pragma unroll
+      for (int nt = 0; nt < NCO; ++nt) finish(old[r][nt], r, nt, old_cell, old_sample);
   }
 }
 
@@ -823,18 +881,6 @@ __global__ __launch_bounds__(256) void k_input_grad(const float* __restrict__ gx
   }
 }
 
-// dY of 16 channels -> 32-channel operand layout for the next MFMA pass
-__global__ __launch_bounds__(256) void k_pad16to32(const unsigned short* __restrict__ a, long long cells,
-                                                   unsigned short* __restrict__ b) {
-  const long long cell = (long long)blockIdx.x * 256 + threadIdx.x;
-  if (cell >= cells) return;
-  unsigned short v[32];
-#pragma unroll
-  for (int c = 0; c < 32; ++c) v[c] = c < 16 ? a[cell * 16 + c] : 0;
-#pragma unroll
-  for (int c = 0; c < 32; c += 8) __builtin_memcpy(b + cell * 32 + c, v + c, 16);
-}
-
 __global__ __launch_bounds__(256) void k_dsum(const double* __restrict__ part, int n, double* out) {
   // fixed-order block reduction: strided per-thread sums, then a tree in LDS
   __shared__ double sd[256];
@@ -917,12 +963,15 @@ __global__ __launch_bounds__(256) void k_block_average(const T* __restrict__ fin
 inline unsigned blocks(long long n, int per) { return (unsigned)((n + per - 1) / per); }
 
 inline unsigned conv_grid(int n, int batch) {
-  return (unsigned)((long long)(n / CTX) * (n / CTY) * (n / CTZ) * batch);
+  return (unsigned)((long long)(n / VX) * (n / VY) * (n / VZ) * batch);
 }
 
-// persistent convolution workgroups: three per CU of a 256-CU MI355X (the
-// LDS tile allows three), never more than there are tiles
-inline unsigned conv_wgs(unsigned ntiles) { return ntiles < 768u ? ntiles : 768u; }
+// persistent convolution workgroups: one per CU of a 256-CU MI355X (weights
+// and tile fill the LDS), as many as share the tiles evenly
+inline unsigned conv_wgs(unsigned ntiles) {
+  const unsigned rounds = (ntiles + 255u) / 256u;
+  return (ntiles + rounds - 1u) / rounds;
+}
 
 }  // namespace
 
@@ -947,10 +996,10 @@ hipError_t corr_forward(const CorrBuffers& B, const CorrStats& st, int n, int ba
   const unsigned conv_blocks = conv_grid(n, batch);
   hipLaunchKernelGGL((k_standardize<T>), dim3(blocks(cells, 256)), dim3(256), 0, s, U, n, cells, st,
                      B.x0);
-  hipLaunchKernelGGL((k_conv<32, EPI_GELU, 9>), dim3(conv_wgs(conv_blocks)), dim3(256), 0, s, B.x0, B.w1,
+  hipLaunchKernelGGL((k_conv<32, EPI_GELU, 9, 32>), dim3(conv_wgs(conv_blocks)), dim3(VT), 0, s, B.x0, B.w1,
                      B.theta + CORR_OFF_B1, 32, n, (const float*)nullptr,
                      store_z ? B.z1 : (float*)nullptr, B.h1, (int)conv_blocks, ResArgs<float>{});
-  hipLaunchKernelGGL((k_conv<32, EPI_GELU>), dim3(conv_wgs(conv_blocks)), dim3(256), 0, s, B.h1, B.w2,
+  hipLaunchKernelGGL((k_conv<32, EPI_GELU, 27, 32>), dim3(conv_wgs(conv_blocks)), dim3(VT), 0, s, B.h1, B.w2,
                      B.theta + CORR_OFF_B2, 32, n, (const float*)nullptr,
                      store_z ? B.z2 : (float*)nullptr, B.h2, (int)conv_blocks, ResArgs<float>{});
   if (out && add_u && !store_z) {
@@ -958,12 +1007,12 @@ hipError_t corr_forward(const CorrBuffers& B, const CorrStats& st, int n, int ba
     // not stored)
     ResArgs<T> ra{U, out, {}, (long long)n * n * n};
     for (int c = 0; c < 5; ++c) ra.scale[c] = st.scale[c];
-    hipLaunchKernelGGL((k_conv<16, EPI_RESIDUAL, 27, T>), dim3(conv_wgs(conv_blocks)), dim3(256), 0,
+    hipLaunchKernelGGL((k_conv<16, EPI_RESIDUAL, 27, 32, T>), dim3(conv_wgs(conv_blocks)), dim3(VT), 0,
                        s, B.h2, B.w3, B.theta + CORR_OFF_B3, 5, n, (const float*)nullptr,
                        (float*)nullptr, (unsigned short*)nullptr, (int)conv_blocks, ra);
     return hipGetLastError();
   }
-  hipLaunchKernelGGL((k_conv<16, EPI_LINEAR>), dim3(conv_wgs(conv_blocks)), dim3(256), 0, s, B.h2, B.w3,
+  hipLaunchKernelGGL((k_conv<16, EPI_LINEAR, 27, 32>), dim3(conv_wgs(conv_blocks)), dim3(VT), 0, s, B.h2, B.w3,
                      B.theta + CORR_OFF_B3, 5, n, (const float*)nullptr, B.y,
                      (unsigned short*)nullptr, (int)conv_blocks, ResArgs<float>{});
   if (out)
@@ -999,20 +1048,19 @@ hipError_t corr_backward(const CorrBuffers& B, const CorrStats& st, int n, int b
   hipLaunchKernelGGL((k_loss<T>), dim3(lb), dim3(256), 0, s, U, B.y, tgt, gup, n, cells, st,
                      B.dpart, B.dy16, gU, (int)ident);
   hipLaunchKernelGGL(k_dsum, dim3(1), dim3(256), 0, s, B.dpart, (int)lb, B.loss);
-  hipLaunchKernelGGL(k_pad16to32, dim3(lb), dim3(256), 0, s, B.dy16, cells, B.dy32);
   const int nblk = (int)(cells / (CTX * CTY * CTZ));
   const int nwg = corr_wgrad_groups(cells);
   // layer 3: dW3, db3; dH2 -> dZ2 = dH2 * GELU'(Z2)
   hipLaunchKernelGGL((k_wgrad<16>), dim3(nwg), dim3(256), 0, s, B.dy16, B.h2, n, nblk, B.wpart);
   hipLaunchKernelGGL(k_wgrad_reduce, dim3(blocks(28 * 16 * 32, 64)), dim3(256), 0, s, B.wpart,
                      16, nwg, 5, 32, 0, 0, B.grad + CORR_OFF_W3, B.grad + CORR_OFF_B3);
-  hipLaunchKernelGGL((k_conv<32, EPI_GELU_BWD>), dim3(conv_wgs(conv_blocks)), dim3(256), 0, s, B.dy32, B.w3t,
+  hipLaunchKernelGGL((k_conv<32, EPI_GELU_BWD, 27, 16>), dim3(conv_wgs(conv_blocks)), dim3(VT), 0, s, B.dy16, B.w3t,
                      (const float*)nullptr, 0, n, B.z2, (float*)nullptr, B.dz2, (int)conv_blocks, ResArgs<float>{});
   // layer 2
   hipLaunchKernelGGL((k_wgrad<32>), dim3(nwg), dim3(256), 0, s, B.dz2, B.h1, n, nblk, B.wpart);
   hipLaunchKernelGGL(k_wgrad_reduce, dim3(blocks(28 * 32 * 32, 64)), dim3(256), 0, s,
                      B.wpart, 32, nwg, 32, 32, 0, 0, B.grad + CORR_OFF_W2, B.grad + CORR_OFF_B2);
-  hipLaunchKernelGGL((k_conv<32, EPI_GELU_BWD>), dim3(conv_wgs(conv_blocks)), dim3(256), 0, s, B.dz2, B.w2t,
+  hipLaunchKernelGGL((k_conv<32, EPI_GELU_BWD, 27, 32>), dim3(conv_wgs(conv_blocks)), dim3(VT), 0, s, B.dz2, B.w2t,
                      (const float*)nullptr, 0, n, B.z1, (float*)nullptr, B.dz1, (int)conv_blocks, ResArgs<float>{});
   // layer 1
   hipLaunchKernelGGL((k_wgrad<32, true>), dim3(nwg), dim3(256), 0, s, B.dz1, B.x0, n, nblk,
@@ -1020,7 +1068,7 @@ hipError_t corr_backward(const CorrBuffers& B, const CorrStats& st, int n, int b
   hipLaunchKernelGGL(k_wgrad_reduce, dim3(blocks(28 * 32 * 32, 64)), dim3(256), 0, s,
                      B.wpart, 32, nwg, 32, 5, 1, 1, B.grad + CORR_OFF_W1, B.grad + CORR_OFF_B1);
   if (gU) {
-    hipLaunchKernelGGL((k_conv<16, EPI_RAW>), dim3(conv_wgs(conv_blocks)), dim3(256), 0, s, B.dz1, B.w1t,
+    hipLaunchKernelGGL((k_conv<16, EPI_RAW, 27, 32>), dim3(conv_wgs(conv_blocks)), dim3(VT), 0, s, B.dz1, B.w1t,
                        (const float*)nullptr, 0, n, (const float*)nullptr, B.gx,
                        (unsigned short*)nullptr, (int)conv_blocks, ResArgs<float>{});
     hipLaunchKernelGGL((k_input_grad<T>), dim3(lb), dim3(256), 0, s, B.gx, n, cells, st, gU);
