@@ -653,19 +653,113 @@ extern "C" mh_status mh_step(mh_ctx* c, int32_t nsteps, double dt, double t_stop
 
 // ------------------------------------------------- batched corrected steps
 
+// whether the plain steps of the contexts can share launches: alike but for
+// the seed of the forcing, with nothing outside the step's own kernels
+// (gravity, tabulated cooling, a flux correction, kernel timing)
+static bool steps_together(mh_ctx* const* ctxs, int B) {
+  const mh_ctx* c0 = ctxs[0];
+  for (int b = 0; b < B; ++b) {
+    const mh_ctx* c = ctxs[b];
+    mh_physics_desc p = c->p;
+    p.ou_seed = c0->p.ou_seed;
+    if (memcmp(&c->g, &c0->g, sizeof c->g) != 0 || memcmp(&p, &c0->p, sizeof p) != 0 ||
+        (c->p.flags & MH_SRC_GRAVITY) || c->cool_table() || c->dflux || c->timing)
+      return false;
+  }
+  return true;
+}
+
+// One plain step of every context (steps_together), with the new states going
+// to `in` [B][5][N] instead of the workspaces; dts: this step's row of the
+// schedule is chosen on the device, or null for CFL steps (the signal speeds as
+// partial maxima).  STATE_BATCH contexts share a launch: one small cube fills
+// a part of the GPU, and its step is a chain of four short kernels.  Batched,
+// four forced 64^3 fp32 cubes take their step in 64 us, on parallel branches of
+// a captured graph in 110 to 130 us with the gather of the states.
+template <typename T>
+static mh_status batched_step(mh_ctx* const* ctxs, int B, T* in, const double* dts,
+                              hipStream_t s) {
+  const size_t per = 5 * (size_t)ctxs[0]->cells();
+  for (int b0 = 0; b0 < B; b0 += STATE_BATCH) {
+    mh_ctx* c = ctxs[b0];
+    const int nb = B - b0 < STATE_BATCH ? B - b0 : STATE_BATCH;
+    const mh_grid_desc& g = c->g;
+    const StageGeom geom{g.n[0], g.n[1], g.n[2], {g.bc[0], g.bc[1], g.bc[2]}};
+    const bool force = (c->p.flags & MH_SRC_FORCING) != 0;
+    const bool cool = (c->p.flags & MH_SRC_COOLING) != 0;
+    StepBatch inner{}, last{};
+    for (int b = 0; b < nb; ++b) {
+      mh_ctx* m = ctxs[b0 + b];
+      inner.ws[b] = inner.out[b] = last.ws[b] = m->ws - c->ws;
+      last.out[b] = (long long)(b * per * sizeof(T));
+      inner.seed[b] = last.seed[b] = m->p.ou_seed;
+      m->speed = mh_ctx::SPEED_CLOCK;
+      m->rate_valid = true;
+    }
+    StageArgs<T> a = base_stage_args<T>(c, c->clk(), c->at<T>(c->L.ou_rows));
+    PrologueArgs pa{};
+    pa.clk = c->clk();
+    pa.dt_log = c->at<double>(c->L.dtlog);
+    pa.f64 = g.dtype == MH_F64;
+    pa.cfl = g.cfl;
+    pa.t_stop = INFINITY;
+    pa.forcing = force;
+    if (force) pa.ou = ou_args(c);
+    pa.dt_sched = dts ? dts + b0 : nullptr;
+    pa.sched_stride = B;
+    pa.speed_part = dts ? nullptr : c->ws + c->L.speed;
+    pa.n_part = dts ? 0 : (int)reduce_blocks(c->cells());
+    pa.reset_health = 1;
+    MH_HIP(c, launch_prologue(pa, s, &inner, nb));
+    if (force)
+      MH_HIP(c, launch_force_rows<T>(c->at<T>(c->L.ou_coef), c->at<int>(c->L.ou_n), c->nmodes,
+                                     a.ou_tab[1], a.ou_tab[2], g.n[1], g.n[2], a.ou_R,
+                                     c->at<T>(c->L.ou_rows), s, &inner, nb));
+    T* U = c->at<T>(c->L.U);
+    a.uin = U;
+    if (g.integrator != MH_RK_EULER) {
+      a.uout = c->at<T>(c->L.U1);
+      MH_HIP(c, launch_stage<T>(1, g.limiter, false, false, a, geom, s, &inner, nb));
+      a.uin = a.uout;
+    }
+    a.un = U;
+    if (g.integrator == MH_RK_SSP3) {
+      a.uout = c->at<T>(c->L.U2);
+      a.ca = T(0.75);
+      a.cb = T(0.25);
+      MH_HIP(c, launch_stage<T>(3, g.limiter, false, false, a, geom, s, &inner, nb));
+      a.uin = a.uout;
+      a.ca = T(1.0 / 3.0);
+      a.cb = T(2.0 / 3.0);
+    } else if (g.integrator == MH_RK_EULER) {
+      a.ca = T(0);
+      a.cb = T(1);
+    }
+    a.uout = in + (size_t)b0 * per;
+    MH_HIP(c, launch_stage<T>(2, g.limiter, force, cool, a, geom, s, &last, nb));
+  }
+  return MH_OK;
+}
+
 // One corrected step of the B contexts: each context's plain step, the
 // gather of the B states into `in`, the corrector's batched pass into `out`,
 // the scatter back, and (CFL steps) the signal speed of the corrected states
 // for the next step's dt.  The corrector part runs on `main`; with `fork`
 // events (a captured step) the plain steps run on the contexts' own streams
 // as parallel branches (fork[0] ends the previous work on `main`, fork[1 + b]
-// ends context b's step), otherwise on `main` in turn.
+// ends context b's step), otherwise on `main` in turn; `together`: in common
+// launches that leave the stepped states in `in` (batched_step).
 template <typename T>
 static mh_status corrected_step(mh_ctx* const* ctxs, int B, mh_corr* corr, T* in, T* out,
-                                const double* dts, hipStream_t main, const hipEvent_t* fork) {
+                                const double* dts, hipStream_t main, const hipEvent_t* fork,
+                                bool together) {
   const size_t bytes = 5 * (size_t)ctxs[0]->cells() * sizeof(T);
+  if (together) {
+    mh_status st = batched_step<T>(ctxs, B, in, dts, main);
+    if (st != MH_OK) return st;
+  }
   if (fork) MH_HIP(ctxs[0], hipEventRecord(fork[0], main));
-  for (int b = 0; b < B; ++b) {
+  for (int b = 0; b < B && !together; ++b) {
     if (fork) MH_HIP(ctxs[b], hipStreamWaitEvent(ctxs[b]->stream, fork[0], 0));
     mh_status st = step_impl<T>(ctxs[b], 1, 0.0, INFINITY, nullptr, dts ? dts + b : nullptr, B);
     if (st != MH_OK) return st;
@@ -682,7 +776,8 @@ static mh_status corrected_step(mh_ctx* const* ctxs, int B, mh_corr* corr, T* in
     states[b] = ctxs[b]->ws + ctxs[b]->L.U;
     corrected[b] = out + (size_t)b * bytes / sizeof(T);
   }
-  MH_HIP(ctxs[0], launch_copies(states.data(), gathered.data(), B, bytes, main));
+  if (!together)
+    MH_HIP(ctxs[0], launch_copies(states.data(), gathered.data(), B, bytes, main));
   MH_HIP(ctxs[0], corr_apply_enqueue(corr, in, out, main));
   if (dts) {
     MH_HIP(ctxs[0], launch_copies((const void* const*)corrected.data(), states.data(), B, bytes,
@@ -725,14 +820,21 @@ static mh_status step_corrected_impl(mh_ctx* const* ctxs, int B, mh_corr* corr, 
       MH_HIP(c, launch_clock_reset_rate(c->clk(), c->stream));
     c->rate_valid = true;
   }
-  // (more contexts than one launch batch are not captured: a run with nine
-  // parallel branches once ended in a segmentation fault of a runtime thread,
-  // whose cause is not known; the results are the same)
-  if (!graph || nsteps == 0 || B > STATE_BATCH) {
+  // Contexts that step in common launches need no graph: a corrected step is
+  // then about a dozen launches, enqueued faster than they run, while capturing
+  // and instantiating one costs 0.9 ms a call (eight corrected steps of four
+  // forced 64^3 fp32 cubes: 2.93 ms in common launches,
+  // 4.42 captured).  Others are captured, with a
+  // branch per context, which four 64^3 cubes take a third less time on than in
+  // turn, but not more than eight of them: a run with nine branches once ended
+  // in a segmentation fault of a runtime thread, whose cause is not known.
+  const bool together = steps_together(ctxs, B);
+  if (!graph || nsteps == 0 || together || B > STATE_BATCH) {
     for (int s = 0; s < nsteps; ++s) {
-      mh_status st = corrected_step<T>(ctxs, B, corr, in, out, dts, c0->stream, nullptr);
+      mh_status st = corrected_step<T>(ctxs, B, corr, in, out, dts, c0->stream, nullptr, together);
       if (st != MH_OK) return st;
     }
+    if (graph) MH_HIP(c0, hipStreamSynchronize(c0->stream));
     return MH_OK;
   }
   // One corrected step captured into a graph (kernel nodes only) and replayed
@@ -760,7 +862,7 @@ static mh_status step_corrected_impl(mh_ctx* const* ctxs, int B, mh_corr* corr, 
   mh_status st = MH_OK;
   if (ec == hipSuccess) ec = hipStreamBeginCapture(bs[0], hipStreamCaptureModeThreadLocal);
   if (ec == hipSuccess) {
-    st = corrected_step<T>(ctxs, B, corr, in, out, dts, bs[0], ev.data());
+    st = corrected_step<T>(ctxs, B, corr, in, out, dts, bs[0], ev.data(), false);
     ec = hipStreamEndCapture(bs[0], &gr);
   }
   for (int b = 0; b < B; ++b) {

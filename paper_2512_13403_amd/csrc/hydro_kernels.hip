@@ -299,8 +299,24 @@ __device__ __forceinline__ double from_next_lane(double v) {
 // waves.
 static_assert(TX == 64 && 2 * TY <= TX, "one wave per tile row; the edge wave takes 2 TY x faces");
 
-template <typename T, int STAGE, int LIM, bool FORCE, bool COOL>
-__global__ __launch_bounds__(NTHREADS, sizeof(T) == 4 ? 4 : 2) void k_stage(const StageArgs<T> a) {
+// the arguments of member blockIdx.y of a batch
+template <typename T>
+__device__ __forceinline__ void to_member(StageArgs<T>&, const StepSingle&) {}
+template <typename T>
+__device__ __forceinline__ void to_member(StageArgs<T>& a, const StepBatch& sb) {
+  const long long off = sb.ws[blockIdx.y];
+  a.uin = moved(a.uin, off);
+  a.un = moved(a.un, off);
+  a.uout = moved(a.uout, sb.out[blockIdx.y]);
+  a.clk = moved(a.clk, off);
+  a.ou_rows = moved(a.ou_rows, off);
+}
+__device__ __forceinline__ long long member_offset(const StepSingle&) { return 0; }
+__device__ __forceinline__ long long member_offset(const StepBatch& sb) { return sb.ws[blockIdx.y]; }
+
+template <typename T, int STAGE, int LIM, bool FORCE, bool COOL, typename B>
+__global__ __launch_bounds__(NTHREADS, sizeof(T) == 4 ? 4 : 2) void k_stage(StageArgs<T> a,
+                                                                              const B sb) {
   __shared__ T sW[5][TY + 4][TX + 4];
   __shared__ T sFx[5][TY][TX + 1];
   __shared__ T sFy[5][TY + 1][TX];
@@ -313,9 +329,11 @@ __global__ __launch_bounds__(NTHREADS, sizeof(T) == 4 ? 4 : 2) void k_stage(cons
   // XCD-aware tile order: consecutive hardware workgroups go round-robin to
   // the 8 XCDs, so give each XCD a contiguous range of tiles (x fastest, then
   // y, then z) and the x/y halos of neighbouring tiles stay in one L2.
+  // The members of a batch follow one another along the grid's y.
   const int b = blockIdx.x;
   const int logical = (b & 7) * a.nb_per_xcd + (b >> 3);
   if (logical >= a.nbx * a.nby * a.nbz) return;
+  to_member(a, sb);
   const int bx = logical % a.nbx;
   const int rest = logical / a.nbx;
   const int by = rest % a.nby, bz = rest / a.nby;
@@ -690,18 +708,20 @@ __global__ __launch_bounds__(256) void k_stage2_finish(const StageArgs<T> a,
 // the chain of dependent loads took 7.7 us for 16 modes at 64^2 rows and 22 us
 // at 512^2 (19 MB written).
 constexpr int ROWS_THREADS = 256;
-template <typename T>
+template <typename T, typename B>
 __global__ __launch_bounds__(ROWS_THREADS) void k_force_rows(
     const T* __restrict__ coef, const int* __restrict__ nvec, int nmodes,
     const T* __restrict__ tabY, const T* __restrict__ tabZ, int ny, int nz, int R,
-    T* __restrict__ rows) {
+    T* __restrict__ rows, const B sb) {
   __shared__ T s_coef[6 * MAX_MODES], s_y[2 * ROWS_THREADS], s_z[2 * ROWS_THREADS];
   __shared__ int s_n[3 * MAX_MODES];
   const int R1 = R + 1, rpb = ROWS_THREADS / R1;  // rows per workgroup
   const int lr = threadIdx.x / R1, n = threadIdx.x - lr * R1;
   const long long row = (long long)blockIdx.x * rpb + lr;  // z * ny + y
   const bool active = lr < rpb && row < (long long)ny * nz;
-  for (int i = threadIdx.x; i < 6 * nmodes; i += ROWS_THREADS) s_coef[i] = coef[i];
+  const long long off = member_offset(sb);
+  const T* const mcoef = moved(coef, off);
+  for (int i = threadIdx.x; i < 6 * nmodes; i += ROWS_THREADS) s_coef[i] = mcoef[i];
   for (int i = threadIdx.x; i < 3 * nmodes; i += ROWS_THREADS) s_n[i] = nvec[i];
   if (active) {
     const int y = (int)(row % ny), z = (int)(row / ny);
@@ -732,7 +752,7 @@ __global__ __launch_bounds__(ROWS_THREADS) void k_force_rows(
       Q[c] += (nxm == n) ? bi : -bi;
     }
   }
-  T* out = rows + row * 6 * R1 + 6 * n;
+  T* out = moved(rows, off) + row * 6 * R1 + 6 * n;
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
     out[2 * c] = P[c];
@@ -742,17 +762,25 @@ __global__ __launch_bounds__(ROWS_THREADS) void k_force_rows(
 
 template <typename T>
 hipError_t launch_force_rows(const T* coef, const int* nvec, int nmodes, const T* tabY,
-                             const T* tabZ, int ny, int nz, int R, T* rows, hipStream_t s) {
+                             const T* tabZ, int ny, int nz, int R, T* rows, hipStream_t s,
+                             const StepBatch* sb, int batch) {
   const long long rpb = ROWS_THREADS / (R + 1), nrows = (long long)ny * nz;
-  hipLaunchKernelGGL((k_force_rows<T>), dim3((unsigned)((nrows + rpb - 1) / rpb)),
-                     dim3(ROWS_THREADS), 0, s, coef, nvec, nmodes, tabY, tabZ, ny, nz, R, rows);
+  const dim3 grid((unsigned)((nrows + rpb - 1) / rpb), (unsigned)batch);
+  if (sb)
+    hipLaunchKernelGGL((k_force_rows<T, StepBatch>), grid, dim3(ROWS_THREADS), 0, s, coef, nvec,
+                       nmodes, tabY, tabZ, ny, nz, R, rows, *sb);
+  else
+    hipLaunchKernelGGL((k_force_rows<T, StepSingle>), grid, dim3(ROWS_THREADS), 0, s, coef, nvec,
+                       nmodes, tabY, tabZ, ny, nz, R, rows, StepSingle{});
   return hipGetLastError();
 }
 
 template hipError_t launch_force_rows<float>(const float*, const int*, int, const float*,
-                                             const float*, int, int, int, float*, hipStream_t);
+                                             const float*, int, int, int, float*, hipStream_t,
+                                             const StepBatch*, int);
 template hipError_t launch_force_rows<double>(const double*, const int*, int, const double*,
-                                              const double*, int, int, int, double*, hipStream_t);
+                                              const double*, int, int, int, double*, hipStream_t,
+                                              const StepBatch*, int);
 
 // Signal speed max_a (|v_a| + c)/h_a of states that no stage-2 epilogue left
 // (set by the caller, or corrected), with the copy into place where there is
@@ -842,8 +870,8 @@ __global__ void k_clock_set(DevClock* clk, double t, long long step) {
 // 14.7 / 18.8 -> 11.0 / 14.7, 256^3 fp32 218 / 278 -> 207 / 260 and fp64
 // 573 / 699 -> 523 / 627; 512^3 keeps its 64 planes.
 template <typename T>
-static inline int z_chunk(const StageGeom& g) {
-  const long long tiles_xy = (long long)((g.nx + TX - 1) / TX) * ((g.ny + TY - 1) / TY);
+static inline int z_chunk(const StageGeom& g, int batch) {
+  const long long tiles_xy = (long long)((g.nx + TX - 1) / TX) * ((g.ny + TY - 1) / TY) * batch;
   int best = 1;
   double least = 1e300;
   for (int zc = 1; zc <= MAX_ZC && zc <= g.nz; ++zc) {
@@ -860,11 +888,11 @@ static inline int z_chunk(const StageGeom& g) {
 }
 
 template <typename T>
-static void fill_geom(StageArgs<T>& a, const StageGeom& g) {
+static void fill_geom(StageArgs<T>& a, const StageGeom& g, int batch = 1) {
   a.nx = g.nx; a.ny = g.ny; a.nz = g.nz;
   a.bcx = g.bc[0]; a.bcy = g.bc[1]; a.bcz = g.bc[2];
   a.ncell = (long long)g.nx * g.ny * g.nz;
-  a.zc = z_chunk<T>(g);
+  a.zc = z_chunk<T>(g, batch);
   a.nbx = (g.nx + TX - 1) / TX;
   a.nby = (g.ny + TY - 1) / TY;
   a.nbz = (g.nz + a.zc - 1) / a.zc;
@@ -874,8 +902,15 @@ static void fill_geom(StageArgs<T>& a, const StageGeom& g) {
 
 template <typename T, int LM>
 static void launch_stage_lim(int stage, bool force, bool cool, const StageArgs<T>& a, dim3 grid,
-                             dim3 block, hipStream_t s) {
-#define MH_LAUNCH(ST, FO, CO) hipLaunchKernelGGL((k_stage<T, ST, LM, FO, CO>), grid, block, 0, s, a)
+                             dim3 block, hipStream_t s, const StepBatch* sb) {
+#define MH_LAUNCH(ST, FO, CO)                                                                     \
+  do {                                                                                            \
+    if (sb)                                                                                       \
+      hipLaunchKernelGGL((k_stage<T, ST, LM, FO, CO, StepBatch>), grid, block, 0, s, a, *sb);     \
+    else                                                                                          \
+      hipLaunchKernelGGL((k_stage<T, ST, LM, FO, CO, StepSingle>), grid, block, 0, s, a,          \
+                         StepSingle{});                                                           \
+  } while (0)
   if (stage == 1) MH_LAUNCH(1, false, false);
   else if (stage == 3) MH_LAUNCH(3, false, false);
   else if (force && cool) MH_LAUNCH(2, true, true);
@@ -887,25 +922,25 @@ static void launch_stage_lim(int stage, bool force, bool cool, const StageArgs<T
 
 template <typename T>
 hipError_t launch_stage(int stage, int limiter, bool force, bool cool, StageArgs<T> a,
-                        const StageGeom& g, hipStream_t s) {
+                        const StageGeom& g, hipStream_t s, const StepBatch* sb, int batch) {
   // a lane's offset within a z-plane is a 32-bit byte offset
   if ((unsigned long long)g.nx * (unsigned long long)g.ny * sizeof(T) > 0xffffffffull)
     return hipErrorInvalidValue;
-  fill_geom(a, g);
+  fill_geom(a, g, batch);
   dim3 block(TX, TY);
-  dim3 grid(8 * a.nb_per_xcd);
+  dim3 grid(8 * a.nb_per_xcd, batch);
   // every limiter with HLLC: the specialised kernels; another solver, or a
   // flux-correction field: the kernel that reads them at run time
   if (a.rs != RS_HLLC || a.dflux) limiter = LIM_GENERIC;
-  if (limiter == LIM_NONE) launch_stage_lim<T, LIM_NONE>(stage, force, cool, a, grid, block, s);
+  if (limiter == LIM_NONE) launch_stage_lim<T, LIM_NONE>(stage, force, cool, a, grid, block, s, sb);
   else if (limiter == LIM_VANLEER)
-    launch_stage_lim<T, LIM_VANLEER>(stage, force, cool, a, grid, block, s);
-  else if (limiter == LIM_MC) launch_stage_lim<T, LIM_MC>(stage, force, cool, a, grid, block, s);
+    launch_stage_lim<T, LIM_VANLEER>(stage, force, cool, a, grid, block, s, sb);
+  else if (limiter == LIM_MC) launch_stage_lim<T, LIM_MC>(stage, force, cool, a, grid, block, s, sb);
   else if (limiter == LIM_SUPERBEE)
-    launch_stage_lim<T, LIM_SUPERBEE>(stage, force, cool, a, grid, block, s);
+    launch_stage_lim<T, LIM_SUPERBEE>(stage, force, cool, a, grid, block, s, sb);
   else if (limiter == LIM_GENERIC)
-    launch_stage_lim<T, LIM_GENERIC>(stage, force, cool, a, grid, block, s);
-  else launch_stage_lim<T, LIM_MINMOD>(stage, force, cool, a, grid, block, s);
+    launch_stage_lim<T, LIM_GENERIC>(stage, force, cool, a, grid, block, s, sb);
+  else launch_stage_lim<T, LIM_MINMOD>(stage, force, cool, a, grid, block, s, sb);
   return hipGetLastError();
 }
 
@@ -965,9 +1000,9 @@ hipError_t launch_clock_set(DevClock* clk, double t, long long step, hipStream_t
 }
 
 template hipError_t launch_stage<float>(int, int, bool, bool, StageArgs<float>, const StageGeom&,
-                                        hipStream_t);
+                                       hipStream_t, const StepBatch*, int);
 template hipError_t launch_stage<double>(int, int, bool, bool, StageArgs<double>, const StageGeom&,
-                                         hipStream_t);
+                                        hipStream_t, const StepBatch*, int);
 template hipError_t launch_stage2_finish<float>(bool, StageArgs<float>, const float*,
                                                 const StageGeom&, hipStream_t);
 template hipError_t launch_stage2_finish<double>(bool, StageArgs<double>, const double*,

@@ -52,6 +52,12 @@ __device__ __forceinline__ int bc_map(int i, int n, int bc) {
   return i < 0 ? 0 : n - 1;
 }
 
+// p moved by `bytes` (a multiple of the element size); pointer arithmetic, so
+// that the compiler still knows a kernel argument to point to global memory
+template <typename P> __device__ __forceinline__ P* moved(P* p, long long bytes) {
+  return (P*)((const char*)p + bytes);
+}
+
 template <typename T> __device__ __forceinline__ T dev_rcp(T x);
 template <> __device__ __forceinline__ float dev_rcp<float>(float x) {
   return __builtin_amdgcn_rcpf(x);

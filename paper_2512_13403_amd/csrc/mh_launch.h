@@ -56,6 +56,19 @@ struct StateBatch {
   T* part[STATE_BATCH];
 };
 
+// members of one batched launch of the step's kernels: contexts alike but for
+// the seed of the forcing, so that every workspace pointer of member b lies
+// ws[b] bytes after the first member's; a stage's output `uout` lies out[b]
+// bytes after its own.  The kernels are built for one context (StepSingle) and
+// for a batch: looking up the offsets of a batch of one takes 1 to 2 % of a
+// 64^3 step.
+struct StepBatch {
+  long long ws[STATE_BATCH];
+  long long out[STATE_BATCH];
+  unsigned long long seed[STATE_BATCH];
+};
+struct StepSingle {};
+
 struct OUArgs {
   DevClock* clk;
   double* ahat;    // [M][3][re, im]
@@ -86,12 +99,15 @@ struct PrologueArgs {
   long long sched_stride;
 };
 
+// (sb: the members of a batch of these arguments' contexts, or null)
 template <typename T>
 hipError_t launch_stage(int stage, int limiter, bool force, bool cool, StageArgs<T> a,
-                        const StageGeom& g, hipStream_t s);
+                        const StageGeom& g, hipStream_t s, const StepBatch* sb = nullptr,
+                        int batch = 1);
 template <typename T>
 hipError_t launch_force_rows(const T* coef, const int* nvec, int nmodes, const T* tabY,
-                             const T* tabZ, int ny, int nz, int R, T* rows, hipStream_t s);
+                             const T* tabZ, int ny, int nz, int R, T* rows, hipStream_t s,
+                             const StepBatch* sb = nullptr, int batch = 1);
 // cooling and the CFL / health epilogue of the last stage from its stored
 // state after the forcing kick (a step that keeps that state)
 template <typename T>
@@ -115,7 +131,8 @@ hipError_t launch_cool_rate(const T* U, const StageGeom& g, T gamma, const CoolT
                             DevClock* clk, hipStream_t s);
 hipError_t launch_clock_reset_health(DevClock* clk, hipStream_t s);
 hipError_t launch_clock_set(DevClock* clk, double t, long long step, hipStream_t s);
-hipError_t launch_prologue(const PrologueArgs& a, hipStream_t s);
+hipError_t launch_prologue(const PrologueArgs& a, hipStream_t s, const StepBatch* sb = nullptr,
+                           int batch = 1);
 hipError_t launch_sched_reset(DevClock* clk, hipStream_t s);
 hipError_t launch_copies(const void* const* src, void* const* dst, int count, size_t bytes,
                          hipStream_t s);

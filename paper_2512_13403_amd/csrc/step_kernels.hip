@@ -75,7 +75,24 @@ __global__ void k_ou_init(const OUArgs a) {
 // signal speed, and the amplitudes stay in LDS for the normalisation (summed
 // in order by one thread): one wave drawing three components each and reading
 // the amplitudes back took 11.8 us with 16 modes.
-__global__ __launch_bounds__(PROLOGUE_THREADS) void k_prologue(const PrologueArgs a) {
+// One workgroup per member of a batch.
+__device__ __forceinline__ void to_member(PrologueArgs&, const StepSingle&) {}
+__device__ __forceinline__ void to_member(PrologueArgs& a, const StepBatch& sb) {
+  const long long off = sb.ws[blockIdx.x];
+  a.clk = moved(a.clk, off);
+  a.dt_log = moved(a.dt_log, off);
+  a.speed_part = a.speed_part ? moved(a.speed_part, off) : nullptr;
+  if (a.dt_sched) a.dt_sched += blockIdx.x;
+  if (a.forcing) {
+    a.ou.ahat = moved(a.ou.ahat, off);
+    a.ou.nvec = moved(a.ou.nvec, off);
+    a.ou.coef = moved(a.ou.coef, off);
+    a.ou.seed = sb.seed[blockIdx.x];
+  }
+}
+template <typename B>
+__global__ __launch_bounds__(PROLOGUE_THREADS) void k_prologue(PrologueArgs a, const B sb) {
+  to_member(a, sb);
   __shared__ double s_dt, s_scale, s_speed[PROLOGUE_THREADS / 64];
   __shared__ double s_er[3 * MAX_MODES], s_ei[3 * MAX_MODES], s_a[6 * MAX_MODES];
   const int t = threadIdx.x;
@@ -167,8 +184,13 @@ __global__ __launch_bounds__(PROLOGUE_THREADS) void k_prologue(const PrologueArg
   }
 }
 
-hipError_t launch_prologue(const PrologueArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(k_prologue, dim3(1), dim3(PROLOGUE_THREADS), 0, s, a);
+hipError_t launch_prologue(const PrologueArgs& a, hipStream_t s, const StepBatch* sb, int batch) {
+  if (sb)
+    hipLaunchKernelGGL((k_prologue<StepBatch>), dim3((unsigned)batch), dim3(PROLOGUE_THREADS), 0,
+                       s, a, *sb);
+  else
+    hipLaunchKernelGGL((k_prologue<StepSingle>), dim3(1), dim3(PROLOGUE_THREADS), 0, s, a,
+                       StepSingle{});
   return hipGetLastError();
 }
 

@@ -186,3 +186,49 @@ def test_corrected_steps_beyond_one_launch_batch(graph):
     # a CFL step after the corrected ones starts from the corrected states
     assert [float(s.step(1, record=True)[0]) for s in a] == \
            [float(t.step(1, record=True)[0]) for t in b]
+
+
+@pytest.mark.parametrize("dtype,B,integrator,flags,cfl,alike", [
+    ("f32", 9, mh.RK_SSP2, mh.SRC_FORCING | mh.SRC_COOLING, True, True),
+    ("f64", 2, mh.RK_SSP3, mh.SRC_FORCING, False, True),
+    ("f32", 9, mh.RK_EULER, 0, False, True),
+    ("f64", 1, mh.RK_SSP2, mh.SRC_COOLING, True, True),
+    ("f32", 3, mh.RK_SSP2, mh.SRC_FORCING, True, False),
+])
+@pytest.mark.parametrize("graph", [False, True])
+def test_corrected_steps_in_common_launches(dtype, B, integrator, flags, cfl, alike, graph):
+    """Contexts that differ in the forcing's seed alone step in common launches
+    (eight to a launch), others each by themselves: bitwise the host-driven
+    loop either way, clocks and later steps too."""
+    import torch
+
+    n, steps = 16, 3
+    td = torch.float64 if dtype == "f64" else torch.float32
+    mk = lambda: [mh.Solver(mh.grid_desc((n,) * 3, (1.0 / n,) * 3, dtype=dtype,
+                                         integrator=integrator, cfl=0.2 + (not alike) * 0.05 * b),
+                            mh.physics_desc(flags=flags, ou_seed=3 * b)) for b in range(B)]
+    U = torch.tensor(np.stack([wl.smooth_random_state((n,) * 3, seed=b) for b in range(B)]),
+                     dtype=td, device="cuda:0")
+    mean = [float(v) for v in U.mean(dim=(0, 2, 3, 4))]
+    std = [float(v) + 1e-3 for v in U.std(dim=(0, 2, 3, 4))]
+    corr = mh.Corrector(mh.corr_desc(n, B, dtype, 5.0 / 3.0, mean, std, (1e-3,) * 5))
+    corr.set_params(wl.corrector_init_params(seed=12, out_scale=1.0).astype(np.float32))
+    dts = None if cfl else torch.tensor(1e-3 * (1.0 + np.arange(steps * B).reshape(steps, B) % 4),
+                                        dtype=torch.float64, device="cuda:0")
+    a, b = mk(), mk()
+    for s, t, u in zip(a, b, U):
+        s.set_state(u)
+        t.set_state(u)
+    mh.step_corrected(a, corr, steps, dts, use_graph=graph)
+    for k in range(steps):
+        for q, t in enumerate(b):
+            t.step(1, 0.0 if cfl else float(dts[k, q]))
+        out, _, _ = corr.apply(torch.stack([t.get_state_device() for t in b]))
+        for t, u in zip(b, out):
+            t.set_state(u)
+    for s, t in zip(a, b):
+        assert torch.equal(s.get_state_device(), t.get_state_device())
+        assert s.clock() == t.clock()
+    if cfl:
+        assert [float(s.step(1, record=True)[0]) for s in a] == \
+               [float(t.step(1, record=True)[0]) for t in b]
