@@ -365,7 +365,8 @@ extern "C" mh_status mh_init(const mh_grid_desc* grid, const mh_physics_desc* ph
 // the contexts and measures their CFL signal speeds, one launch for a batch;
 // the contexts share grid and dtype
 template <typename T>
-static hipError_t measure_states(mh_ctx* const* ctxs, int B, const T* const* src, hipStream_t s) {
+static hipError_t measure_states(mh_ctx* const* ctxs, int B, const T* const* src, hipStream_t s,
+                                 Choice choice = Choice{}) {
   const mh_grid_desc& g = ctxs[0]->g;
   const StageGeom geom{g.n[0], g.n[1], g.n[2], {g.bc[0], g.bc[1], g.bc[2]}};
   hipError_t e = hipSuccess;
@@ -385,7 +386,8 @@ static hipError_t measure_states(mh_ctx* const* ctxs, int B, const T* const* src
       sb.part[nb] = c->at<T>(c->L.speed);
       c->speed = mh_ctx::SPEED_PART;
     }
-    e = launch_state_speed<T>(sb, nb, src != nullptr, geom, (T)g0.gamma, ih, s);
+    e = launch_state_speed<T>(sb, nb, src != nullptr, geom, (T)g0.gamma, ih, s, choice);
+    choice.count = 0;
     b0 += nb;
   }
   return e;
@@ -743,7 +745,7 @@ static mh_status batched_step(mh_ctx* const* ctxs, int B, T* in, const double* d
 
 // One corrected step of the B contexts: each context's plain step, the
 // gather of the B states into `in`, the corrector's batched pass into `out`,
-// the scatter back, and (CFL steps) the signal speed of the corrected states
+// the scatter back (of `in` where the correction falls back), and (CFL steps) the signal speed of the corrected states
 // for the next step's dt.  The corrector part runs on `main`; with `fork`
 // events (a captured step) the plain steps run on the contexts' own streams
 // as parallel branches (fork[0] ends the previous work on `main`, fork[1 + b]
@@ -778,14 +780,15 @@ static mh_status corrected_step(mh_ctx* const* ctxs, int B, mh_corr* corr, T* in
   }
   if (!together)
     MH_HIP(ctxs[0], launch_copies(states.data(), gathered.data(), B, bytes, main));
-  MH_HIP(ctxs[0], corr_apply_enqueue(corr, in, out, main));
+  Choice plain{};
+  MH_HIP(ctxs[0], corr_apply_enqueue(corr, in, out, main, &plain));
   if (dts) {
     MH_HIP(ctxs[0], launch_copies((const void* const*)corrected.data(), states.data(), B, bytes,
-                                  main));
+                                  main, plain));
   } else {
     // the scatter measures the corrected states' signal speeds; a cooling rate
     // of the uncorrected state limits nothing
-    MH_HIP(ctxs[0], measure_states<T>(ctxs, B, corrected.data(), main));
+    MH_HIP(ctxs[0], measure_states<T>(ctxs, B, corrected.data(), main, plain));
     for (int b = 0; b < B; ++b)
       if (ctxs[b]->cool_table() && ctxs[b]->p.cool_ccool > 0.0)
         MH_HIP(ctxs[b], launch_clock_reset_rate(ctxs[b]->clk(), main));
@@ -823,11 +826,10 @@ static mh_status step_corrected_impl(mh_ctx* const* ctxs, int B, mh_corr* corr, 
   // Contexts that step in common launches need no graph: a corrected step is
   // then about a dozen launches, enqueued faster than they run, while capturing
   // and instantiating one costs 0.9 ms a call (eight corrected steps of four
-  // forced 64^3 fp32 cubes: 2.93 ms in common launches,
-  // 4.42 captured).  Others are captured, with a
-  // branch per context, which four 64^3 cubes take a third less time on than in
-  // turn, but not more than eight of them: a run with nine branches once ended
-  // in a segmentation fault of a runtime thread, whose cause is not known.
+  // forced 64^3 fp32 cubes: 2.93 ms in common launches, 4.42 captured).  Others
+  // are captured, with a branch per context so that their small kernels overlap,
+  // but not more than eight of them: a run with nine branches once ended in a
+  // segmentation fault of a runtime thread, whose cause is not known.
   const bool together = steps_together(ctxs, B);
   if (!graph || nsteps == 0 || together || B > STATE_BATCH) {
     for (int s = 0; s < nsteps; ++s) {

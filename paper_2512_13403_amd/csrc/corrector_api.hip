@@ -18,7 +18,7 @@ inline size_t calign(size_t x) { return (x + CALIGN - 1) & ~(CALIGN - 1); }
 struct CorrLayout {
   size_t theta, m, v, grad, w1, w2, w3, w1t, w2t, w3t, x0, z1, h1, z2, h2, y, gx, dy16, dz2,
       dz1;
-  size_t wpart, dpart, loss, counters, cpart, total;
+  size_t wpart, dpart, loss, counters, total;
 };
 
 CorrLayout corr_layout(const mh_corr_desc* d) {
@@ -52,16 +52,12 @@ CorrLayout corr_layout(const mh_corr_desc* d) {
   L.dz2 = take(cells * 32 * 2);
   L.dz1 = take(cells * 32 * 2);
   L.wpart = take((size_t)28 * corr_wgrad_groups((long long)cells) * 32 * 32 * 4);
-  // per-block partial sums, or the floor partials (64 blocks per sample) and
-  // the two floor values of each sample after them
-  const size_t nd = std::max((cells + 255) / 256, (size_t)d->batch * (64 * 2 + 2));
-  L.dpart = take(nd * sizeof(double));
+  // per-block partial sums of the loss, or of rho and P for the floor
+  L.dpart = take(2 * ((cells + 255) / 256) * sizeof(double));
   L.loss = take(sizeof(double));
   // [floored cells, non-finite cells] of the last floor, then the number of
   // fallbacks counted by the batched corrected step
   L.counters = take(3 * sizeof(unsigned long long));
-  // per-block floored / non-finite counts of the positivity floor
-  L.cpart = take(2 * ((cells + 255) / 256) * sizeof(unsigned long long));
   L.total = off;
   return L;
 }
@@ -95,6 +91,7 @@ struct mh_corr {
   CorrStats st;
   int it = 0;
   long long cells() const { return (long long)d.batch * d.n * d.n * d.n; }
+  double fallback_limit() const { return d.fallback_frac * (double)cells(); }
 };
 
 #define MH_CHK(call)                           \
@@ -130,8 +127,7 @@ extern "C" mh_status mh_corr_init(const mh_corr_desc* d, void* workspace, size_t
                      H(L.w2t), H(L.w3t), H(L.x0), H(L.h1), H(L.h2), H(L.dy16),
                      H(L.dz2), H(L.dz1), F(L.z1), F(L.z2), F(L.y), F(L.gx), F(L.wpart),
                      reinterpret_cast<double*>(w + L.dpart), reinterpret_cast<double*>(w + L.loss),
-                     reinterpret_cast<unsigned long long*>(w + L.counters),
-                     reinterpret_cast<unsigned long long*>(w + L.cpart)};
+                     reinterpret_cast<unsigned long long*>(w + L.counters)};
   for (int k = 0; k < 5; ++k) {
     c->st.mean[k] = d->mean[k];
     c->st.std[k] = d->std[k];
@@ -178,31 +174,28 @@ extern "C" mh_status mh_corr_get_params(mh_corr* c, float* theta, int where) {
 template <typename T>
 static mh_status apply_impl(mh_corr* c, const T* U, T* out, int64_t* floored, int32_t* fell) {
   if (c->d.mode == MH_CORR_FLUX) {
-    MH_CHK(corr_forward<T>(c->B, c->st, c->d.n, c->d.batch, U, out, false, false, c->stream));
+    MH_CHK(corr_forward<T>(c->B, c->st, c->d.n, c->d.batch, U, out, false, false, c->d.gamma,
+                           c->stream));
     if (floored) *floored = 0;
     if (fell) *fell = 0;
     return MH_OK;
   }
-  MH_CHK(corr_forward<T>(c->B, c->st, c->d.n, c->d.batch, U, out, false, true, c->stream));
-  MH_CHK(corr_floor<T>(c->B, U, out, c->d.n, c->d.batch, c->d.gamma, c->d.floor_rel,
-                       c->d.fallback_frac, c->stream));
+  MH_CHK(corr_forward<T>(c->B, c->st, c->d.n, c->d.batch, U, out, false, true, c->d.gamma,
+                         c->stream));
+  MH_CHK(corr_floor<T>(c->B, out, c->d.n, c->d.batch, c->d.gamma, c->d.floor_rel, c->stream));
+  MH_CHK(corr_fallback<T>(c->B, U, out, c->d.n, c->d.batch, c->fallback_limit(), c->stream));
   if (floored || fell) {
     unsigned long long cnt[2];
     MH_CHK(hipMemcpyAsync(cnt, c->B.counters, sizeof cnt, hipMemcpyDeviceToHost, c->stream));
     MH_CHK(hipStreamSynchronize(c->stream));
     if (floored) *floored = (int64_t)cnt[0];
     if (fell)
-      *fell = (cnt[1] > 0 || (double)cnt[0] > c->d.fallback_frac * (double)c->cells()) ? 1 : 0;
+      *fell = (cnt[1] > 0 || (double)cnt[0] > c->fallback_limit()) ? 1 : 0;
   }
   return MH_OK;
 }
 
 namespace {
-// counters[2] += 1 when the floor just run made the batch fall back
-__global__ void k_fallback_count(unsigned long long* counters, double limit) {
-  if (threadIdx.x == 0 && (counters[1] > 0 || (double)counters[0] > limit)) counters[2] += 1;
-}
-
 __global__ void k_fallback_reset(unsigned long long* counters) {
   if (threadIdx.x == 0) counters[2] = 0;
 }
@@ -216,25 +209,20 @@ bool corr_matches(const mh_corr* c, int n, int batch, int dtype) {
   return c->d.mode == MH_CORR_STATE && c->d.n == n && c->d.batch == batch && c->d.dtype == dtype;
 }
 
-hipError_t corr_apply_enqueue(mh_corr* c, const void* U, void* out, hipStream_t s) {
-  hipError_t e;
-  if (c->d.dtype == MH_F64) {
-    e = corr_forward<double>(c->B, c->st, c->d.n, c->d.batch, (const double*)U, (double*)out,
-                             false, true, s);
-    if (e == hipSuccess)
-      e = corr_floor<double>(c->B, (const double*)U, (double*)out, c->d.n, c->d.batch,
-                             c->d.gamma, c->d.floor_rel, c->d.fallback_frac, s);
-  } else {
-    e = corr_forward<float>(c->B, c->st, c->d.n, c->d.batch, (const float*)U, (float*)out,
-                            false, true, s);
-    if (e == hipSuccess)
-      e = corr_floor<float>(c->B, (const float*)U, (float*)out, c->d.n, c->d.batch, c->d.gamma,
-                            c->d.floor_rel, c->d.fallback_frac, s);
-  }
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_fallback_count, dim3(1), dim3(64), 0, s, c->B.counters,
-                     c->d.fallback_frac * (double)c->cells());
-  return hipGetLastError();
+template <typename T>
+static hipError_t apply_enqueue(mh_corr* c, const T* U, T* out, hipStream_t s) {
+  const hipError_t e = corr_forward<T>(c->B, c->st, c->d.n, c->d.batch, U, out, false, true,
+                                       c->d.gamma, s);
+  return e != hipSuccess
+             ? e
+             : corr_floor<T>(c->B, out, c->d.n, c->d.batch, c->d.gamma, c->d.floor_rel, s);
+}
+
+hipError_t corr_apply_enqueue(mh_corr* c, const void* U, void* out, hipStream_t s,
+                              Choice* choice) {
+  *choice = Choice{c->B.counters, c->fallback_limit(), (const char*)U - (const char*)out, 1};
+  return c->d.dtype == MH_F64 ? apply_enqueue<double>(c, (const double*)U, (double*)out, s)
+                              : apply_enqueue<float>(c, (const float*)U, (float*)out, s);
 }
 
 hipError_t corr_fallbacks_reset(mh_corr* c) {
@@ -263,7 +251,8 @@ extern "C" mh_status mh_corr_apply(mh_corr* c, const void* U, void* U_out, int64
 template <typename T>
 static mh_status backward_impl(mh_corr* c, const T* U, const T* tgt, const T* gup, double* loss,
                                T* gU) {
-  MH_CHK(corr_forward<T>(c->B, c->st, c->d.n, c->d.batch, U, (T*)nullptr, true, true, c->stream));
+  MH_CHK(corr_forward<T>(c->B, c->st, c->d.n, c->d.batch, U, (T*)nullptr, true, true,
+                         c->d.gamma, c->stream));
   MH_CHK(corr_backward<T>(c->B, c->st, c->d.n, c->d.batch, U, tgt, gup, gU,
                           c->d.mode == MH_CORR_STATE, c->stream));
   if (loss && tgt) {

@@ -629,30 +629,95 @@ __global__ __launch_bounds__(256) void k_wgrad_reduce(const float* __restrict__ 
 // c] = hi and x[cell][10 (dx + 1) + 5 + c] = lo of cell x + dx (periodic),
 // channels 30, 31 zero, so the first layer's three x taps meet one 32-wide
 // operand (its K dimension) instead of three mostly zero ones
-template <typename T>
-__global__ __launch_bounds__(256) void k_standardize(const T* __restrict__ U, int n, long long cells,
-                                                     CorrStats st, unsigned short* __restrict__ x) {
-  const long long cell = (long long)blockIdx.x * 256 + threadIdx.x;
-  if (cell >= cells) return;
-  const long long n3 = (long long)n * n * n;
-  const long long b = cell / n3, q = cell % n3;
-  const int ix = (int)(q % n);
-  const long long row = q - ix;
-  unsigned short v[32];
+// A cell is standardised once (five fp64 divisions; 15 with the neighbours
+// done again) and handed to its neighbours through LDS, where the 64 bytes of a
+// cell are also regrouped so that lanes store whole lines; with SUM the same
+// read gives the per-block sums of rho and P of the positivity floor, and the
+// floor's counters are cleared.  Workgroup b of a sample takes its chunks b,
+// b + bps, .. of 256 cells.  4 x 64^3 fp32 (21 MB read, 67 MB written): 30 us
+// and 9 for the sums apart, now 19.
+template <typename T, bool SUM>
+__global__ __launch_bounds__(256) void k_standardize(const T* __restrict__ U, int n, int bps,
+                                                     CorrStats st, unsigned short* __restrict__ x,
+                                                     double gm1, double* __restrict__ part,
+                                                     unsigned long long* __restrict__ counters) {
+  __shared__ unsigned parts[5][256];  // hi | lo << 16 of the chunk's cells
+  __shared__ u32x4 lines[256 * 4];
+  __shared__ double ssum[2][4];
+  const unsigned n3 = (unsigned)n * (unsigned)n * (unsigned)n, tid = threadIdx.x;
+  const long long b = blockIdx.x / bps;
+  const T* const Us = U + b * 5 * n3;
+  auto two_parts = [&](int c, T u) {
+    const float v = (float)(((double)u - st.mean[c]) / st.std[c]);
+    const unsigned short hi = f2bf(v);
+    return (unsigned)hi | ((unsigned)f2bf(v - bf2f(hi)) << 16);
+  };
+  double sr = 0.0, sp = 0.0;
+  for (unsigned q0 = (blockIdx.x % bps) * 256u; q0 < n3; q0 += bps * 256u) {
+    const unsigned q = q0 + tid, ix = q % (unsigned)n;
+    T u[5];
+    unsigned own[5], word[3][5];
 #pragma unroll
-  for (int c = 0; c < 32; ++c) v[c] = 0;
-#pragma unroll
-  for (int d = 0; d < 3; ++d) {
-    const int xs = ix + d - 1 < 0 ? n - 1 : (ix + d - 1 >= n ? 0 : ix + d - 1);
+    for (int c = 0; c < 5; ++c) u[c] = Us[(long long)c * n3 + q];
 #pragma unroll
     for (int c = 0; c < 5; ++c) {
-      const float s = (float)(((double)U[(b * 5 + c) * n3 + row + xs] - st.mean[c]) / st.std[c]);
-      v[10 * d + c] = f2bf(s);
-      v[10 * d + 5 + c] = f2bf(s - bf2f(v[10 * d + c]));
+      own[c] = two_parts(c, u[c]);
+      parts[c][tid] = own[c];
+    }
+    if (SUM) {
+      const double rho = (double)u[0], mx = (double)u[1], my = (double)u[2], mz = (double)u[3];
+      sr += rho;
+      sp += gm1 * ((double)u[4] - 0.5 * (mx * mx + my * my + mz * mz) / rho);
+    }
+    __syncthreads();
+    // x neighbours: of this chunk, or (rows that cross its ends) formed here
+    const unsigned ql = ix == 0 ? q + n - 1 : q - 1, qr = ix == (unsigned)n - 1 ? q + 1 - n : q + 1;
+#pragma unroll
+    for (int c = 0; c < 5; ++c) {
+      word[0][c] = ql - q0 < 256u ? parts[c][ql - q0] : two_parts(c, Us[(long long)c * n3 + ql]);
+      word[1][c] = own[c];
+      word[2][c] = qr - q0 < 256u ? parts[c][qr - q0] : two_parts(c, Us[(long long)c * n3 + qr]);
+    }
+    unsigned short v[32];
+    v[30] = v[31] = 0;
+#pragma unroll
+    for (int d = 0; d < 3; ++d)
+#pragma unroll
+      for (int c = 0; c < 5; ++c) {
+        v[10 * d + c] = (unsigned short)word[d][c];
+        v[10 * d + 5 + c] = (unsigned short)(word[d][c] >> 16);
+      }
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      u32x4 w;
+      __builtin_memcpy(&w, v + 8 * c, 16);
+      lines[tid * 4 + (c ^ ((tid >> 2) & 3))] = w;
+    }
+    __syncthreads();
+    unsigned short* const xo = x + (b * n3 + q0) * 32;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const unsigned i = k * 256 + tid, cell = i >> 2;
+      const u32x4 w = lines[cell * 4 + ((i & 3) ^ ((cell >> 2) & 3))];
+      __builtin_memcpy(xo + i * 8, &w, 16);
     }
   }
+  if (SUM) {
 #pragma unroll
-  for (int c = 0; c < 32; c += 8) __builtin_memcpy(x + cell * 32 + c, v + c, 16);
+    for (int o = 32; o > 0; o >>= 1) {
+      sr += __shfl_xor(sr, o, 64);
+      sp += __shfl_xor(sp, o, 64);
+    }
+    if ((tid & 63) == 0) {
+      ssum[0][tid >> 6] = sr;
+      ssum[1][tid >> 6] = sp;
+    }
+    __syncthreads();
+    if (tid < 2) {
+      part[2 * blockIdx.x + tid] = (ssum[tid][0] + ssum[tid][1]) + (ssum[tid][2] + ssum[tid][3]);
+      if (blockIdx.x == 0) counters[tid] = 0;
+    }
+  }
 }
 
 // U' = U + scale * y (y: [cell][16] fp32, first 5 channels)
@@ -671,119 +736,72 @@ __global__ __launch_bounds__(256) void k_residual(const T* __restrict__ U, const
   }
 }
 
-// per-sample sums of rho and P of the uncorrected state (two-stage, fixed order)
+// positivity floor: rho >= f <rho>, then P >= f <P> by raising E at fixed m;
+// counts floored and non-finite cells.  Each workgroup adds the partial sums of
+// its sample (k_standardize; at most 1024, in the same order everywhere) for the
+// two floor values, works through the sample's chunks like k_standardize, and
+// adds its counts to the counters where there are any: one launch of 8 us
+// instead of four (9 + 8 + 6 + 6 us at 4 x 64^3).
 template <typename T>
-__global__ __launch_bounds__(256) void k_rho_p_partial(const T* __restrict__ U, long long n3, double gm1,
-                                                       int blocks_per_sample, double* __restrict__ part) {
-  __shared__ double sr[256], sp[256];
-  const int b = blockIdx.x / blocks_per_sample, blk = blockIdx.x % blocks_per_sample;
-  double r = 0.0, p = 0.0;
-  for (long long q = (long long)blk * 256 + threadIdx.x; q < n3; q += (long long)blocks_per_sample * 256) {
-    const double rho = (double)U[(b * 5) * n3 + q];
-    const double mx = (double)U[(b * 5 + 1) * n3 + q], my = (double)U[(b * 5 + 2) * n3 + q],
-                 mz = (double)U[(b * 5 + 3) * n3 + q], E = (double)U[(b * 5 + 4) * n3 + q];
-    r += rho;
-    p += gm1 * (E - 0.5 * (mx * mx + my * my + mz * mz) / rho);
+__global__ __launch_bounds__(256) void k_floor(T* __restrict__ U, unsigned n3, int bps, double gm1,
+                                               double frel, const double* __restrict__ part,
+                                               int parts, unsigned long long* __restrict__ counters) {
+  __shared__ double ssum[2][256];
+  __shared__ unsigned scount[2][4];
+  const unsigned tid = threadIdx.x;
+  const long long b = blockIdx.x / bps;
+  double sr = 0.0, sp = 0.0;
+  for (int i = tid; i < parts; i += 256) {
+    sr += part[2 * (b * parts + i)];
+    sp += part[2 * (b * parts + i) + 1];
   }
-  sr[threadIdx.x] = r;
-  sp[threadIdx.x] = p;
+  ssum[0][tid] = sr;
+  ssum[1][tid] = sp;
   __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if (threadIdx.x < s) {
-      sr[threadIdx.x] += sr[threadIdx.x + s];
-      sp[threadIdx.x] += sp[threadIdx.x + s];
+  for (unsigned s = 128; s > 0; s >>= 1) {
+    if (tid < s) {
+      ssum[0][tid] += ssum[0][tid + s];
+      ssum[1][tid] += ssum[1][tid + s];
     }
     __syncthreads();
   }
-  if (threadIdx.x == 0) {
-    part[2 * blockIdx.x] = sr[0];
-    part[2 * blockIdx.x + 1] = sp[0];
-  }
-}
-
-// positivity floor: rho >= f <rho>, then P >= f <P> by raising E at fixed m;
-// counts floored and non-finite cells
-// the floor values of each sample, frel times the mean density and pressure,
-// from the k_rho_p_partial sums (one thread per sample, partials added in
-// block order): ref[2 b] = rho floor, ref[2 b + 1] = pressure floor
-__global__ __launch_bounds__(64) void k_floor_ref(const double* __restrict__ part,
-                                                  int blocks_per_sample, int batch, long long n3,
-                                                  double frel, double* __restrict__ ref) {
-  const int b = blockIdx.x * 64 + threadIdx.x;
-  if (b >= batch) return;
-  double sr = 0.0, sp = 0.0;
-  for (int k = 0; k < blocks_per_sample; ++k) {
-    sr += part[2 * (b * blocks_per_sample + k)];
-    sp += part[2 * (b * blocks_per_sample + k) + 1];
-  }
-  ref[2 * b] = frel * sr / (double)n3;
-  ref[2 * b + 1] = frel * sp / (double)n3;
-}
-
-template <typename T>
-__global__ __launch_bounds__(256) void k_floor(T* __restrict__ U, long long n3, long long cells, double gm1,
-                                               const double* __restrict__ ref,
-                                               unsigned long long* __restrict__ cpart) {
-  const long long cell = (long long)blockIdx.x * 256 + threadIdx.x;
-  bool fl = false, bad = false;
-  if (cell < cells) {
-    const long long b = cell / n3, q = cell % n3;
-    const double rf = ref[2 * b], pf = ref[2 * b + 1];
-    T* u = U + b * 5 * n3 + q;
+  const double rf = frel * ssum[0][0] / (double)n3, pf = frel * ssum[1][0] / (double)n3;
+  unsigned nf = 0, nb = 0;  // of the wave
+  for (unsigned q0 = (blockIdx.x % bps) * 256u; q0 < n3; q0 += bps * 256u) {
+    T* u = U + b * 5 * n3 + q0 + tid;
+    const long long N = n3;
+    bool fl = false;
     double rho = (double)u[0];
+    const double mx = (double)u[N], my = (double)u[2 * N], mz = (double)u[3 * N];
+    double E = (double)u[4 * N];
     if (rho < rf) {
       rho = rf;
       u[0] = (T)rf;
       fl = true;
     }
-    const double mx = (double)u[n3], my = (double)u[2 * n3], mz = (double)u[3 * n3];
     const double ek = 0.5 * (mx * mx + my * my + mz * mz) / rho;
-    const double p = gm1 * ((double)u[4 * n3] - ek);
+    const double p = gm1 * (E - ek);
     if (p < pf) {
-      u[4 * n3] = (T)(ek + pf / gm1);
+      const T e = (T)(ek + pf / gm1);
+      u[4 * N] = e;
+      E = (double)e;
       fl = true;
     }
-    bad = !(isfinite(rho) && isfinite(mx) && isfinite(my) && isfinite(mz) &&
-            isfinite((double)u[4 * n3]));
+    const bool bad =
+        !(isfinite(rho) && isfinite(mx) && isfinite(my) && isfinite(mz) && isfinite(E));
+    nf += __popcll(__ballot(fl));
+    nb += __popcll(__ballot(bad));
   }
-  // the block's counts, without atomics (a mostly floored state would
-  // serialise them on two addresses); k_count_sum adds the blocks
-  __shared__ unsigned long long sc[2][4];
-  const unsigned long long nf = __popcll(__ballot(fl)), nb = __popcll(__ballot(bad));
-  if ((threadIdx.x & 63) == 0) {
-    sc[0][threadIdx.x >> 6] = nf;
-    sc[1][threadIdx.x >> 6] = nb;
+  if ((tid & 63) == 0) {
+    scount[0][tid >> 6] = nf;
+    scount[1][tid >> 6] = nb;
   }
   __syncthreads();
-  if (threadIdx.x < 2)
-    cpart[2 * blockIdx.x + threadIdx.x] =
-        sc[threadIdx.x][0] + sc[threadIdx.x][1] + sc[threadIdx.x][2] + sc[threadIdx.x][3];
-}
-
-// counters[k] = sum over blocks of cpart[2 b + k] (fixed order)
-__global__ __launch_bounds__(256) void k_count_sum(const unsigned long long* __restrict__ cpart,
-                                                   int nblocks,
-                                                   unsigned long long* __restrict__ counters) {
-  __shared__ unsigned long long s[2][256];
-  unsigned long long a = 0, b = 0;
-  for (int i = threadIdx.x; i < nblocks; i += 256) {
-    a += cpart[2 * i];
-    b += cpart[2 * i + 1];
+  if (tid < 2) {
+    const unsigned c = scount[tid][0] + scount[tid][1] + scount[tid][2] + scount[tid][3];
+    if (c) atomicAdd(counters + tid, (unsigned long long)c);
   }
-  s[0][threadIdx.x] = a;
-  s[1][threadIdx.x] = b;
-  __syncthreads();
-  for (int st = 128; st > 0; st >>= 1) {
-    if (threadIdx.x < st) {
-      s[0][threadIdx.x] += s[0][threadIdx.x + st];
-      s[1][threadIdx.x] += s[1][threadIdx.x + st];
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x < 2) counters[threadIdx.x] = s[threadIdx.x][0];
 }
-
-
 
 // fallback on the device: when any value was non-finite or more than `limit`
 // cells were floored, out = U (the plain state); counters as k_floor left them
@@ -962,6 +980,16 @@ __global__ __launch_bounds__(256) void k_block_average(const T* __restrict__ fin
 
 inline unsigned blocks(long long n, int per) { return (unsigned)((n + per - 1) / per); }
 
+// workgroups per sample of the chunked elementwise kernels: one per 256 cells
+// (n^3 is a multiple of 4096), at most `most`
+inline int sample_groups(int n, int most) {
+  const long long chunks = (long long)n * n * n / 256;
+  return (int)(chunks < most ? chunks : most);
+}
+// workgroups per sample of k_standardize with sums: their number is what every
+// workgroup of k_floor adds up
+inline int sum_groups(int n) { return sample_groups(n, 1024); }
+
 inline unsigned conv_grid(int n, int batch) {
   return (unsigned)((long long)(n / VX) * (n / VY) * (n / VZ) * batch);
 }
@@ -991,11 +1019,17 @@ hipError_t corr_pack_weights(const CorrBuffers& B, hipStream_t s) {
 
 template <typename T>
 hipError_t corr_forward(const CorrBuffers& B, const CorrStats& st, int n, int batch, const T* U,
-                        T* out, bool store_z, bool add_u, hipStream_t s) {
+                        T* out, bool store_z, bool add_u, double gamma, hipStream_t s) {
   const long long cells = (long long)batch * n * n * n;
   const unsigned conv_blocks = conv_grid(n, batch);
-  hipLaunchKernelGGL((k_standardize<T>), dim3(blocks(cells, 256)), dim3(256), 0, s, U, n, cells, st,
-                     B.x0);
+  if (out && add_u && !store_z) {
+    hipLaunchKernelGGL((k_standardize<T, true>), dim3(batch * sum_groups(n)), dim3(256), 0, s, U, n,
+                       sum_groups(n), st, B.x0, gamma - 1.0, B.dpart, B.counters);
+  } else {
+    const int bps = sample_groups(n, 1 << 20);
+    hipLaunchKernelGGL((k_standardize<T, false>), dim3((unsigned)batch * bps), dim3(256), 0, s, U, n,
+                       bps, st, B.x0, 0.0, (double*)nullptr, (unsigned long long*)nullptr);
+  }
   hipLaunchKernelGGL((k_conv<32, EPI_GELU, 9, 32>), dim3(conv_wgs(conv_blocks)), dim3(VT), 0, s, B.x0, B.w1,
                      B.theta + CORR_OFF_B1, 32, n, (const float*)nullptr,
                      store_z ? B.z1 : (float*)nullptr, B.h1, (int)conv_blocks, ResArgs<float>{});
@@ -1022,20 +1056,21 @@ hipError_t corr_forward(const CorrBuffers& B, const CorrStats& st, int n, int ba
 }
 
 template <typename T>
-hipError_t corr_floor(const CorrBuffers& B, const T* U, T* out, int n, int batch, double gamma,
-                      double frel, double fallback_frac, hipStream_t s) {
-  const long long n3 = (long long)n * n * n, cells = batch * n3;
-  const int bps = 64;
-  hipLaunchKernelGGL((k_rho_p_partial<T>), dim3(batch * bps), dim3(256), 0, s, U, n3, gamma - 1.0,
-                     bps, B.dpart);
-  double* ref = B.dpart + 2 * batch * bps;
-  hipLaunchKernelGGL(k_floor_ref, dim3(blocks(batch, 64)), dim3(64), 0, s, B.dpart, bps, batch, n3, frel, ref);
-  hipLaunchKernelGGL((k_floor<T>), dim3(blocks(cells, 256)), dim3(256), 0, s, out, n3, cells,
-                     gamma - 1.0, ref, B.cpart);
-  hipLaunchKernelGGL(k_count_sum, dim3(1), dim3(256), 0, s, B.cpart, (int)blocks(cells, 256),
-                     B.counters);
-  hipLaunchKernelGGL((k_fallback<T>), dim3(blocks(5 * cells, 256)), dim3(256), 0, s, U, out,
-                     5 * cells, fallback_frac * (double)cells, B.counters);
+hipError_t corr_floor(const CorrBuffers& B, T* out, int n, int batch, double gamma, double frel,
+                      hipStream_t s) {
+  const unsigned n3 = (unsigned)n * (unsigned)n * (unsigned)n;
+  const int bps = sample_groups(n, batch < 2048 ? 2048 / batch : 1);
+  hipLaunchKernelGGL((k_floor<T>), dim3((unsigned)batch * bps), dim3(256), 0, s, out, n3, bps,
+                     gamma - 1.0, frel, B.dpart, sum_groups(n), B.counters);
+  return hipGetLastError();
+}
+
+template <typename T>
+hipError_t corr_fallback(const CorrBuffers& B, const T* U, T* out, int n, int batch, double limit,
+                         hipStream_t s) {
+  const long long count = 5ll * batch * n * n * n;
+  hipLaunchKernelGGL((k_fallback<T>), dim3(blocks(count, 256)), dim3(256), 0, s, U, out, count,
+                     limit, B.counters);
   return hipGetLastError();
 }
 
@@ -1105,9 +1140,10 @@ hipError_t launch_block_average(const T* fine, int nf, int r, T* coarse, hipStre
 
 #define CORR_INSTANTIATE(T)                                                                       \
   template hipError_t corr_forward<T>(const CorrBuffers&, const CorrStats&, int, int, const T*, T*, \
-                                      bool, bool, hipStream_t);                                   \
-  template hipError_t corr_floor<T>(const CorrBuffers&, const T*, T*, int, int, double, double,    \
-                                    double, hipStream_t);                                         \
+                                      bool, bool, double, hipStream_t);                           \
+  template hipError_t corr_floor<T>(const CorrBuffers&, T*, int, int, double, double, hipStream_t); \
+  template hipError_t corr_fallback<T>(const CorrBuffers&, const T*, T*, int, int, double,        \
+                                       hipStream_t);                                              \
   template hipError_t corr_backward<T>(const CorrBuffers&, const CorrStats&, int, int, const T*,  \
                                        const T*, const T*, T*, bool, hipStream_t);                \
   template hipError_t launch_block_average<T>(const T*, int, int, T*, hipStream_t);

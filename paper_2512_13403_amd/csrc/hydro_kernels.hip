@@ -795,10 +795,12 @@ struct alignas(sizeof(T) * VEC) Cells {
 };
 template <typename T, int VEC, bool COPY>
 __global__ __launch_bounds__(256) void k_state_speed(const StateBatch<T> sb, long long N, T gm1,
-                                                     T gamma, T ihx, T ihy, T ihz) {
+                                                     T gamma, T ihx, T ihy, T ihz,
+                                                     const Choice ch) {
   using V = Cells<T, VEC>;
   __shared__ T sRed[4];
-  const V* __restrict__ src = reinterpret_cast<const V*>(sb.src[blockIdx.y]);
+  const V* __restrict__ src =
+      moved(reinterpret_cast<const V*>(sb.src[blockIdx.y]), COPY && choose(ch) ? ch.alt : 0ll);
   V* __restrict__ dst = reinterpret_cast<V*>(sb.dst[blockIdx.y]);
   const long long NV = N / VEC;
   T smax = T(0);
@@ -956,17 +958,17 @@ hipError_t launch_stage2_finish(bool cool, StageArgs<T> a, const T* ub, const St
 
 template <typename T>
 hipError_t launch_state_speed(const StateBatch<T>& sb, int batch, bool copy, const StageGeom& g,
-                              T gamma, const double* ih, hipStream_t s) {
+                              T gamma, const double* ih, hipStream_t s, const Choice& choice) {
   constexpr int VEC = 16 / (int)sizeof(T);
   const long long N = (long long)g.nx * g.ny * g.nz;
-  bool wide = N % VEC == 0;
+  bool wide = N % VEC == 0 && choice.alt % 16 == 0;
   for (int b = 0; b < batch; ++b)
     wide = wide && (reinterpret_cast<uintptr_t>(sb.src[b]) % 16) == 0 &&
            (reinterpret_cast<uintptr_t>(sb.dst[b]) % 16) == 0;
   const dim3 grid(reduce_blocks(N), (unsigned)batch);
 #define MH_SPEED(V, CP)                                                                       \
   hipLaunchKernelGGL((k_state_speed<T, V, CP>), grid, dim3(256), 0, s, sb, N, gamma - T(1),   \
-                     gamma, (T)ih[0], (T)ih[1], (T)ih[2])
+                     gamma, (T)ih[0], (T)ih[1], (T)ih[2], choice)
   if (wide && copy) MH_SPEED(VEC, true);
   else if (wide) MH_SPEED(VEC, false);
   else if (copy) MH_SPEED(1, true);
@@ -1009,7 +1011,7 @@ template hipError_t launch_stage2_finish<double>(bool, StageArgs<double>, const 
                                                  const StageGeom&, hipStream_t);
 #define MH_SPEED_INST(T)                                                                      \
   template hipError_t launch_state_speed<T>(const StateBatch<T>&, int, bool, const StageGeom&, \
-                                            T, const double*, hipStream_t);                   \
+                                            T, const double*, hipStream_t, const Choice&);                   \
   template hipError_t launch_speed_from_clock<T>(const DevClock*, const StageGeom&, T*,       \
                                                  hipStream_t);
 MH_SPEED_INST(float)

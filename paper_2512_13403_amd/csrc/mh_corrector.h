@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "mh_launch.h"
+
 namespace mh {
 
 // canonical parameter order: W1[32][5][27], b1[32], W2[32][32][27], b2[32],
@@ -35,16 +37,21 @@ struct CorrBuffers {
   float *z1, *z2, *y, *gx, *wpart;
   double *dpart, *loss;
   unsigned long long* counters;  // [floored cells, non-finite cells] of the last floor
-  unsigned long long* cpart;     // their per-block parts
 };
 
 hipError_t corr_pack_weights(const CorrBuffers& B, hipStream_t s);
 template <typename T>
 hipError_t corr_forward(const CorrBuffers& B, const CorrStats& st, int n, int batch, const T* U,
-                        T* out, bool store_z, bool add_u, hipStream_t s);
+                        T* out, bool store_z, bool add_u, double gamma, hipStream_t s);
+// after a corr_forward with out, add_u and no stored z, which leaves the sums
+// of rho and P it needs: floors `out` and counts; then, to be enqueued or done
+// otherwise, out = U if more than `limit` cells were floored or any not finite
 template <typename T>
-hipError_t corr_floor(const CorrBuffers& B, const T* U, T* out, int n, int batch, double gamma,
-                      double frel, double fallback_frac, hipStream_t s);
+hipError_t corr_floor(const CorrBuffers& B, T* out, int n, int batch, double gamma, double frel,
+                      hipStream_t s);
+template <typename T>
+hipError_t corr_fallback(const CorrBuffers& B, const T* U, T* out, int n, int batch, double limit,
+                         hipStream_t s);
 template <typename T>
 hipError_t corr_backward(const CorrBuffers& B, const CorrStats& st, int n, int batch, const T* U,
                          const T* tgt, const T* gup, T* gU, bool ident, hipStream_t s);
@@ -65,9 +72,10 @@ namespace mh {
 hipStream_t corr_stream(const mh_corr* c);
 // a state-mode corrector of this cube size, batch and dtype
 bool corr_matches(const mh_corr* c, int n, int batch, int dtype);
-// mh_corr_apply's correction of the batch U into out (forward, residual,
-// floor, fallback), enqueued on stream s only; counts a fallback on the device
-hipError_t corr_apply_enqueue(mh_corr* c, const void* U, void* out, hipStream_t s);
+// mh_corr_apply's correction of the batch U into out but for the fallback
+// (forward, residual, floor), enqueued on stream s only; *choice takes the
+// fallback's rule for whoever reads `out` next, and counts it
+hipError_t corr_apply_enqueue(mh_corr* c, const void* U, void* out, hipStream_t s, Choice* choice);
 hipError_t corr_fallbacks_reset(mh_corr* c);
 hipError_t corr_fallbacks_read(mh_corr* c, int64_t* count);
 

@@ -56,6 +56,23 @@ struct StateBatch {
   T* part[STATE_BATCH];
 };
 
+// A copy's sources lie `alt` bytes further when counters[1] > 0 or counters[0] >
+// limit (a corrected state that falls back to the plain one); such a choice is
+// counted in counters[2] by launches with count = 1.  counters null: never.
+struct Choice {
+  unsigned long long* counters;
+  double limit;
+  long long alt;
+  int count;
+};
+__device__ __forceinline__ bool choose(const Choice& ch) {
+  if (!ch.counters) return false;
+  const bool fell = ch.counters[1] > 0 || (double)ch.counters[0] > ch.limit;
+  if (fell && ch.count && threadIdx.x == 0 && blockIdx.x == 0 && blockIdx.y == 0)
+    ch.counters[2] += 1;
+  return fell;
+}
+
 // members of one batched launch of the step's kernels: contexts alike but for
 // the seed of the forcing, so that every workspace pointer of member b lies
 // ws[b] bytes after the first member's; a stage's output `uout` lies out[b]
@@ -115,7 +132,8 @@ hipError_t launch_stage2_finish(bool cool, StageArgs<T> a, const T* ub, const St
                                 hipStream_t s);
 template <typename T>
 hipError_t launch_state_speed(const StateBatch<T>& sb, int batch, bool copy, const StageGeom& g,
-                              T gamma, const double* ih, hipStream_t s);
+                              T gamma, const double* ih, hipStream_t s,
+                              const Choice& choice = Choice{});
 template <typename T>
 hipError_t launch_speed_from_clock(const DevClock* clk, const StageGeom& g, T* part,
                                    hipStream_t s);
@@ -134,8 +152,9 @@ hipError_t launch_clock_set(DevClock* clk, double t, long long step, hipStream_t
 hipError_t launch_prologue(const PrologueArgs& a, hipStream_t s, const StepBatch* sb = nullptr,
                            int batch = 1);
 hipError_t launch_sched_reset(DevClock* clk, hipStream_t s);
+// bytes: a multiple of 16
 hipError_t launch_copies(const void* const* src, void* const* dst, int count, size_t bytes,
-                         hipStream_t s);
+                         hipStream_t s, Choice choice = Choice{});
 template <typename T>
 hipError_t launch_adam(T* th, T* m, T* v, const T* g, long long count, double lr, double b1,
                        double b2, double eps, long long it, hipStream_t s);

@@ -210,21 +210,18 @@ struct CopyBatch {
   const void* src[STATE_BATCH];
   void* dst[STATE_BATCH];
 };
-__global__ __launch_bounds__(256) void k_copy16(const CopyBatch cb, size_t n) {
-  const uint4* __restrict__ src = (const uint4*)cb.src[blockIdx.y];
+__global__ __launch_bounds__(256) void k_copy16(const CopyBatch cb, size_t n, const Choice ch) {
+  const uint4* __restrict__ src =
+      moved((const uint4*)cb.src[blockIdx.y], choose(ch) ? ch.alt : 0ll);
   uint4* __restrict__ dst = (uint4*)cb.dst[blockIdx.y];
   for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256)
     dst[i] = src[i];
 }
-__global__ void k_copy1(const CopyBatch cb, size_t from, size_t n) {
-  const unsigned char* src = (const unsigned char*)cb.src[blockIdx.y];
-  unsigned char* dst = (unsigned char*)cb.dst[blockIdx.y];
-  for (size_t i = from + threadIdx.x; i < n; i += blockDim.x) dst[i] = src[i];
-}
 
 hipError_t launch_copies(const void* const* src, void* const* dst, int count, size_t bytes,
-                         hipStream_t s) {
+                         hipStream_t s, Choice choice) {
   const size_t n16 = bytes / 16;
+  if (bytes % 16) return hipErrorInvalidValue;
   for (int b0 = 0; b0 < count; b0 += STATE_BATCH) {
     const int nb = count - b0 < STATE_BATCH ? count - b0 : STATE_BATCH;
     CopyBatch cb{};
@@ -232,13 +229,11 @@ hipError_t launch_copies(const void* const* src, void* const* dst, int count, si
       cb.src[b] = src[b0 + b];
       cb.dst[b] = dst[b0 + b];
     }
-    if (n16) {
-      size_t blocks = (n16 + 255) / 256;
-      if (blocks > 4096) blocks = 4096;
-      hipLaunchKernelGGL(k_copy16, dim3((unsigned)blocks, (unsigned)nb), dim3(256), 0, s, cb, n16);
-    }
-    if (bytes % 16)
-      hipLaunchKernelGGL(k_copy1, dim3(1, (unsigned)nb), dim3(64), 0, s, cb, 16 * n16, bytes);
+    size_t blocks = (n16 + 255) / 256;
+    if (blocks > 4096) blocks = 4096;
+    hipLaunchKernelGGL(k_copy16, dim3((unsigned)blocks, (unsigned)nb), dim3(256), 0, s, cb, n16,
+                       choice);
+    choice.count = 0;
   }
   return hipGetLastError();
 }

@@ -232,3 +232,53 @@ def test_corrected_steps_in_common_launches(dtype, B, integrator, flags, cfl, al
     if cfl:
         assert [float(s.step(1, record=True)[0]) for s in a] == \
                [float(t.step(1, record=True)[0]) for t in b]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("n,B", [(16, 1), (48, 3), (112, 1)])
+def test_corrector_input_and_floor_over_sizes(n, B, dtype):
+    """The network input where rows cross the chunks of 256 cells (n = 48,
+    112): its two bf16 parts exactly.  The floor where a sample has fewer (16)
+    and more chunks (112) than workgroups: the floored state, whose reference
+    sums only differ in their order, the number of floored cells, and the
+    fallback at that number."""
+    import torch
+
+    td = torch.float64 if dtype == "f64" else torch.float32
+    U = torch.tensor(np.stack([wl.smooth_random_state((n,) * 3, seed=7 + b) for b in range(B)]),
+                     dtype=td, device="cuda:0")
+    Ud = U.double().cpu().numpy()
+    mean, std = Ud.mean(axis=(0, 2, 3, 4)), Ud.std(axis=(0, 2, 3, 4)) + 1e-3
+
+    def corrector(frac):
+        c = mh.Corrector(mh.corr_desc(n, B, dtype, 5.0 / 3.0, mean, std, (0.0,) * 5,
+                                      floor_rel=0.9, fallback_frac=frac))
+        c.set_params(wl.corrector_init_params(seed=3, out_scale=1.0).astype(np.float32))
+        return c
+
+    sh = (None, slice(None), None, None, None)
+    x = ((Ud - mean[sh]) / std[sh]).astype(np.float32)
+    hi = torch.tensor(x).to(torch.bfloat16).float().numpy()
+    lo = torch.tensor(x - hi).to(torch.bfloat16).float().numpy()
+    want = np.moveaxis(np.concatenate([hi, lo], axis=1), 1, 4).reshape(-1, 10)
+
+    rho, m, E = Ud[:, 0], Ud[:, 1:4], Ud[:, 4]
+    k = 0.5 * (m ** 2).sum(1)
+    rf = 0.9 * rho.mean(axis=(1, 2, 3), keepdims=True)
+    pf = 0.9 * ((2.0 / 3.0) * (E - k / rho)).mean(axis=(1, 2, 3), keepdims=True)
+    rho1 = np.maximum(rho, rf)
+    low = (2.0 / 3.0) * (E - k / rho1) < pf
+    ref = Ud.copy()
+    ref[:, 0], ref[:, 4] = rho1, np.where(low, k / rho1 + 1.5 * pf, E)
+    count = int(((rho < rf) | low).sum())
+    assert 0 < count < rho.size
+
+    c = corrector(1.0)
+    out, floored, fell = c.apply(U)
+    assert np.array_equal(c.activation(0)[:, :10], want)
+    assert floored == count and not fell
+    # the floor values to rounding: of the state's type where they are stored
+    for o, r in zip(out.double().cpu().numpy(), ref):
+        assert rel_err(o, r) < (1e-12 if dtype == "f64" else 1e-6)
+    out, floored, fell = corrector((count - 0.5) / rho.size).apply(U)
+    assert floored == count and fell and torch.equal(out, U)
