@@ -110,6 +110,27 @@ __device__ __forceinline__ void hllc_flux(const T (&wl)[5], const T (&wr)[5], T 
   const T rK = left ? rl : rr, uK = left ? ul : ur, pK = left ? pl : pr;
   const T aK = left ? wl[t1] : wr[t1], bK = left ? wl[t2] : wr[t2];
   const T SK = left ? SL : SR, dK = left ? dl : dr;
+  if (sizeof(T) == 8) {
+    // the same flux from one state behind the face: (r, u, p, E) of the side,
+    // or of its star region, r* = q d, p* = P + d (S* - v), E* = q ((S - v) E -
+    // P v + p* S*), in F = (r u, r u u + p, r u vt, u (E + p)); 13 instructions
+    // less than the difference form below, which fp32 keeps: its sums decide
+    // limiter and side in the reverse pass, where another rounding of the
+    // states flips some of them and moves gradients by 6e-4
+    const T EK = fmad(pK, gm1inv, (T(0.5) * rK) * fmad(uK, uK, fmad(aK, aK, bK * bK)));
+    const bool fan = (left ? -SL : SR) > T(0);
+    const T q = dev_rcp(SK - sstar);
+    const T ps = fmad(dK, sstar - uK, pK);
+    const T Es = q * fmad(ps, sstar, fmad(SK - uK, EK, -(pK * uK)));
+    const T r = fan ? q * dK : rK, u = fan ? sstar : uK, p = fan ? ps : pK, E = fan ? Es : EK;
+    const T m = r * u;
+    F[0] = m;
+    F[vn] = fmad(m, u, p);
+    F[t1] = m * aK;
+    F[t2] = m * bK;
+    F[4] = u * (E + p);
+    return;
+  }
   // total energy of the selected side only (the other side's is never used)
   const T EK = fmad(pK, gm1inv, (T(0.5) * rK) * fmad(uK, uK, fmad(aK, aK, bK * bK)));
   // inside the star fan: S_L < 0 on the left side, S_R > 0 on the right
@@ -314,9 +335,24 @@ __device__ __forceinline__ void to_member(StageArgs<T>& a, const StepBatch& sb) 
 __device__ __forceinline__ long long member_offset(const StepSingle&) { return 0; }
 __device__ __forceinline__ long long member_offset(const StepBatch& sb) { return sb.ws[blockIdx.y]; }
 
+// Whether a thread reads U(z) again when it updates plane z (an L2 hit, three
+// planes after the first read) instead of carrying U of three planes in
+// registers: the fp64 stages without sources then fit 128 registers and two
+// workgroups share a CU, each covering the other's barriers and loads (256^3
+// periodic minmod, stage 1: 551 -> 481 us).  The last stage does not come down to
+// 128 (741 us read again, 654 from registers), and fp32 holds two workgroups
+// anyway (a few per cent slower read again); the limiters with more live values
+// spill at 128.
+template <typename T, int STAGE, int LIM>
+constexpr bool rereads_u = sizeof(T) == 8 && STAGE != 2 && LIM != LIM_MC && LIM != LIM_SUPERBEE &&
+                           LIM != LIM_GENERIC;
+// waves per SIMD the registers are cut for: two workgroups per CU, or one
+template <typename T, int STAGE, int LIM>
+constexpr int stage_waves = sizeof(T) == 4 || rereads_u<T, STAGE, LIM> ? 4 : 2;
+
 template <typename T, int STAGE, int LIM, bool FORCE, bool COOL, typename B>
-__global__ __launch_bounds__(NTHREADS, sizeof(T) == 4 ? 4 : 2) void k_stage(StageArgs<T> a,
-                                                                              const B sb) {
+__global__ __launch_bounds__(NTHREADS, (stage_waves<T, STAGE, LIM>)) void k_stage(StageArgs<T> a,
+                                                                                  const B sb) {
   __shared__ T sW[5][TY + 4][TX + 4];
   __shared__ T sFx[5][TY][TX + 1];
   __shared__ T sFy[5][TY + 1][TX];
@@ -527,6 +563,7 @@ __global__ __launch_bounds__(NTHREADS, sizeof(T) == 4 ? 4 : 2) void k_stage(Stag
         for (int f = 0; f < 5; ++f) sFx[f][r][xc] = F[f];
       }
     }
+    if (rereads_u<T, STAGE, LIM>) load_lane(a.uin + (long long)z * plane, N, col_b, u[0]);
     T fzp[5], dz2[5];
 #pragma unroll
     for (int f = 0; f < 5; ++f) dz2[f] = limited_slope<T, LIM>(w[1][f], w[2][f], w[3][f], a.lim);
@@ -865,12 +902,13 @@ __global__ void k_clock_set(DevClock* clk, double t, long long step) {
 // ceil(workgroups / 256) chunks; in fp32 two workgroups share a CU and cover
 // each other's barriers, so one alone takes 1.4 times as long per plane, which
 // fades over more rounds as the workgroups drift apart (fp64 holds one per CU
-// by its registers).  The chunk that
+// by the registers of the last stage).  The chunk that
 // makes the least of this is taken, the longest on a tie.  Against halving the
 // chunk until 4096 workgroups are there, but not below four planes (stage 1 /
 // stage 2, us): 128 x 16 x 16 fp64 21.6 / 26.2 -> 11.1 / 13.7, 64^3 fp32
 // 14.7 / 18.8 -> 11.0 / 14.7, 256^3 fp32 218 / 278 -> 207 / 260 and fp64
-// 573 / 699 -> 523 / 627; 512^3 keeps its 64 planes.
+// 573 / 699 -> 523 / 627 (then; 481 / 654 now); 512^3
+// keeps its 64 planes.
 template <typename T>
 static inline int z_chunk(const StageGeom& g, int batch) {
   const long long tiles_xy = (long long)((g.nx + TX - 1) / TX) * ((g.ny + TY - 1) / TY) * batch;
