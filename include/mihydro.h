@@ -499,10 +499,10 @@ mh_status mh_set_potential(mh_ctx *ctx, const void *phi, int where);
  * attached.  Enqueues nothing. */
 mh_status mh_set_flux_correction(mh_ctx *ctx, const void *field, void *grad);
 
-/* Multigrid V-cycles are replayed from HIP graphs captured on first use
- * (one V-cycle is ~60 small launches); enable = 0 launches them kernel by
- * kernel instead.  Default on; results are identical either way.
- * Synchronises. */
+/* Multigrid V-cycles of ~60 small launches (the Jacobi smoother, grids that
+ * are not smoothed on tiles) are replayed from HIP graphs captured on first
+ * use; enable = 0 launches them kernel by kernel, as the others always are.
+ * Default on; results are identical either way.  Synchronises. */
 mh_status mh_set_graphs(mh_ctx *ctx, int enable);
 
 /* Message of the last failed call on ctx (empty string if none). */

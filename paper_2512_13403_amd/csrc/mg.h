@@ -24,17 +24,22 @@ struct MGLevel {
   size_t F;       // right-hand side
 };
 
-// V-cycles replayed from captured HIP graphs: one V-cycle is ~60 small
-// launches, so on a mid-size grid it is launch-bound when issued one kernel
-// at a time.  A cache holds one executable graph per parity of the fine-level
+// V-cycles replayed from captured HIP graphs: off the tiled levels one V-cycle
+// is ~60 small launches, so on a mid-size grid it is launch-bound when issued
+// one kernel at a time.  A cache holds one executable graph per parity of the fine-level
 // ping-pong buffer, valid for one workspace base address (the nodes hold raw
 // pointers); it is captured on a private stream and launched on the caller's.
+// Next to the graphs: two pinned words and events through which the device
+// reports the convergence test of each cycle.
 struct MGGraphCache {
   bool enabled = true;
+  int* done = nullptr;  // pinned [2], written by the test of the even / odd cycles
+  hipEvent_t tested[2] = {nullptr, nullptr};
   hipStream_t cs = nullptr;
   char* ws = nullptr;
   hipGraphExec_t exec[2] = {nullptr, nullptr};
   int cur_after[2] = {0, 0};
+  hipError_t prepare_tests();
   void reset();     // drops the executable graphs (keeps the stream)
   void destroy();   // drops everything
 };
@@ -44,7 +49,7 @@ struct MGLayout {
   MGLevel lev[MG_MAX_LEVELS];
   size_t partial = 0;  // MG_PARTIALS doubles
   int cur0 = 0;        // which fine-level phi buffer holds the solution
-  MGGraphCache* graphs = nullptr;  // not owned; null: launch kernel by kernel
+  MGGraphCache* graphs = nullptr;  // not owned; needed by a multigrid solve
   // spectral solver (grav_solver = MH_GRAV_FFT): level 0 only, plus two
   // complex n^3 work arrays, the twiddles and the acceleration [3][n^3]
   int fft = 0;
@@ -72,8 +77,8 @@ hipError_t fft_gravity_vjp(char* ws, MGLayout& L, double h, double G, const T* U
 // Solves lap(phi) = 4 pi G (rho - <rho>) for the density of U (warm start from
 // the previous solution), then applies the gravity kick and, when `last` (no
 // later kernel in the step), the exact two-branch cooling (if on), the CFL
-// reduction and the health check to U.  Synchronises once per V-cycle to test
-// convergence.
+// reduction and the health check to U.  Waits on the host for the convergence
+// test of every cycle, with the next one queued on a tiled fine level.
 template <typename T>
 hipError_t mg_gravity_step(char* ws, MGLayout& L, const mh_grid_desc& g, const mh_physics_desc& p,
                            const CoolParams<T>& cool, T* U, DevClock* clk, bool last,

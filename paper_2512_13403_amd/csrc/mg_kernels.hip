@@ -80,6 +80,33 @@ __global__ __launch_bounds__(256) void k_sum_final(const double* __restrict__ pa
   if (threadIdx.x == 0) *out = b * scale;
 }
 
+// The convergence test before the first cycle or after the next one, with
+// ||r||^2 = sum(partial[0..nb)): stop when ||r|| <= tol ||F||, when the cycles are used up, or (with a
+// tolerance) when a cycle cut the residual by less than MG_STALL: it has then
+// reached the round-off floor of the precision, which in fp32 lies above the
+// usual tolerances.  The answer stays on the device, where it turns the kernels
+// of cycles queued behind it into returns, and goes to the host (pinned, the
+// word of the cycle's parity).
+__global__ __launch_bounds__(256) void k_converged(const double* __restrict__ partial, int nb,
+                                                   DevClock* clk, int first, int max_cycles,
+                                                   double tol, int* host) {
+  __shared__ double sh[256];
+  if (!first && clk->mg_done) return;
+  const int cycles = first ? 0 : clk->mg_tested + 1;
+  double s = 0.0;
+  for (int i = threadIdx.x; i < nb; i += 256) s += partial[i];
+  const double b = block_sum256(s, sh);
+  if (threadIdx.x == 0) {
+    const double rn = sqrt(b), prev = sqrt(clk->mg_rnorm2);
+    const int done = rn <= tol * sqrt(clk->mg_fnorm2) || cycles >= max_cycles ||
+                     (tol > 0.0 && cycles > 0 && rn > MG_STALL * prev);
+    clk->mg_rnorm2 = b;
+    clk->mg_done = done;
+    clk->mg_tested = cycles;
+    host[cycles & 1] = done;
+  }
+}
+
 // y = scale * (x - *mean)   (in place allowed)
 template <typename T>
 __global__ __launch_bounds__(256) void k_shift_scale(T* y, const T* x, long long n,
@@ -276,6 +303,7 @@ struct TileArgs {
   T* out;
   T* Fc;                // RES_COARSE
   double* partial;      // RES_NORM: one per tile
+  const int* done;      // nothing to do when set (a cycle queued ahead of its test)
 };
 
 template <typename T, class C, int RES, bool ZERO, bool PRO>
@@ -314,6 +342,7 @@ __global__ __launch_bounds__((TileShape<C, RES>::NT)) void k_rbgs_tile(const Til
     z = z < 0 ? z + n : z;
     return z >= n ? z - n : z;
   };
+  if (*a.done) return;
   T p[EZ], f[EZ];
   if (active) {
 #pragma unroll
@@ -529,6 +558,7 @@ struct TailArgs {
   int wcycle;                // 1: two coarse cycles per level (W), 0: one (V)
   int rbgs;                  // smoother: 1 red-black Gauss-Seidel, 0 Jacobi
   int warm;                  // start the first level from phi0
+  const int* done;           // as in TileArgs
 };
 
 // one level of the tail: phi in LDS at off (Jacobi: ping-pong with off +
@@ -687,6 +717,7 @@ __global__ __launch_bounds__(MG_TAIL_THREADS) void k_mgcycle_tail(const TailArgs
   __shared__ T sQ[MG_DIRECT_MAX * MG_DIRECT_MAX], slam[MG_DIRECT_MAX];
   __shared__ double sh[MG_TAIL_THREADS / 64 + 1];
   __shared__ TailLevel<T> lev[MG_TAIL_LEVELS];
+  if (*t.done) return;
   const int nl = t.nl, tid = threadIdx.x;
   const int nb = t.n0 >> (nl - 1);  // cells per axis of the coarsest level
   const bool direct = nb <= MG_DIRECT_MAX;
@@ -970,8 +1001,9 @@ void launch_tile(const TileArgs<T>& a, bool zero, bool pro, unsigned tiles, hipS
 // one launch of C::S sweeps on level lv, from phi[cur] to phi[1 - cur]
 template <typename T, class C>
 void tile_sweeps(char* ws, const MGLevel& lv, const MGLevel* cv, const T* ec, int& cur, bool zero,
-                 int res, double* partial, hipStream_t s) {
+                 int res, double* partial, const int* done, hipStream_t s) {
   TileArgs<T> a{};
+  a.done = done;
   a.n = lv.n;
   a.ntx = (lv.n + C::BX - 1) / C::BX;
   a.nty = (lv.n + C::BY - 1) / C::BY;
@@ -995,13 +1027,13 @@ void tile_sweeps(char* ws, const MGLevel& lv, const MGLevel* cv, const T* ec, in
 // the sweeps in pairs if there are only pairs, else one by one
 template <typename T>
 void smooth_tiles(char* ws, const MGLevel& lv, const MGLevel* cv, const T* ec, int sweeps,
-                  int& cur, bool zero, int res, double* partial, hipStream_t s) {
+                  int& cur, bool zero, int res, double* partial, const int* done, hipStream_t s) {
   const bool pair = lv.n < MG_FINE_MIN && sweeps % 2 == 0;
   while (sweeps > 0) {
     const int left = sweeps - (pair ? 2 : 1);
     const int r = left == 0 ? res : RES_NONE;
-    if (pair) tile_sweeps<T, MGSmall>(ws, lv, cv, ec, cur, zero, r, partial, s);
-    else tile_sweeps<T, MGFine>(ws, lv, cv, ec, cur, zero, r, partial, s);
+    if (pair) tile_sweeps<T, MGSmall>(ws, lv, cv, ec, cur, zero, r, partial, done, s);
+    else tile_sweeps<T, MGFine>(ws, lv, cv, ec, cur, zero, r, partial, done, s);
     zero = false;
     ec = nullptr;
     sweeps = left;
@@ -1027,8 +1059,9 @@ inline int tail_level(const MGLayout& L) {
 // residual in `partial` at the end
 template <typename T>
 hipError_t level_cycle(char* ws, MGLayout& L, const mh_physics_desc& p, int l, int l0,
-                       int* cur, bool zero, bool norm, double* partial, double* mean_slot,
+                       int* cur, bool zero, bool norm, double* partial, DevClock* clk,
                        hipStream_t s) {
+  double* const mean_slot = &clk->mean;
   const int nl = L.nlev;
   const int rbgs = p.mg_smoother == MH_SMOOTH_RBGS;
   MGLevel& lv = L.lev[l];
@@ -1038,7 +1071,8 @@ hipError_t level_cycle(char* ws, MGLayout& L, const mh_physics_desc& p, int l, i
   const long long Nc = (long long)cv.n * cv.n * cv.n;
   hipError_t e = hipSuccess;
   if (tiled) {
-    smooth_tiles<T>(ws, lv, &cv, (const T*)nullptr, p.mg_pre, cur[l], zero, RES_COARSE, partial, s);
+    smooth_tiles<T>(ws, lv, &cv, (const T*)nullptr, p.mg_pre, cur[l], zero, RES_COARSE, partial,
+                    &clk->mg_done, s);
   } else {
     if (zero)
       hipLaunchKernelGGL((k_zero<T>), dim3(nblk(N)), dim3(256), 0, s, P<T>(ws, lv.phi[cur[l]]), N);
@@ -1071,6 +1105,7 @@ hipError_t level_cycle(char* ws, MGLayout& L, const mh_physics_desc& p, int l, i
     t.csweeps = p.mg_coarse_sweeps;
     t.wcycle = p.mg_cycle == MH_MG_W;
     t.rbgs = rbgs;
+    t.done = &clk->mg_done;
     cur[l + 1] = 0;
     for (int k = 0; k < mu; ++k) {
       t.warm = k > 0;
@@ -1083,13 +1118,13 @@ hipError_t level_cycle(char* ws, MGLayout& L, const mh_physics_desc& p, int l, i
   } else {
     cur[l + 1] = 0;
     for (int k = 0; k < mu; ++k) {
-      e = level_cycle<T>(ws, L, p, l + 1, l0, cur, k == 0, false, partial, mean_slot, s);
+      e = level_cycle<T>(ws, L, p, l + 1, l0, cur, k == 0, false, partial, clk, s);
       if (e != hipSuccess) return e;
     }
   }
   if (tiled) {
     smooth_tiles<T>(ws, lv, nullptr, P<T>(ws, cv.phi[cur[l + 1]]), p.mg_post, cur[l], false,
-                    norm ? RES_NORM : RES_NONE, partial, s);
+                    norm ? RES_NORM : RES_NONE, partial, &clk->mg_done, s);
     return hipGetLastError();
   }
   hipLaunchKernelGGL((k_prolong_add<T>), plane_grid((long long)lv.n * lv.n, lv.n), dim3(256),
@@ -1099,10 +1134,17 @@ hipError_t level_cycle(char* ws, MGLayout& L, const mh_physics_desc& p, int l, i
   return hipGetLastError();
 }
 
-// one cycle (V or W) on level 0; phi of level 0 is lev[0].phi[L.cur0]
+inline void converged(DevClock* clk, const mh_physics_desc& p, const double* partial, int nb,
+                      bool first, const MGGraphCache* G, hipStream_t s) {
+  hipLaunchKernelGGL(k_converged, dim3(1), dim3(256), 0, s, partial, nb, clk, (int)first,
+                     p.mg_max_cycles, p.mg_tol, G->done);
+}
+
+// one cycle (V or W) on level 0; phi of level 0 is lev[0].phi[L.cur0].  On a
+// tiled fine level the convergence test follows
 template <typename T>
-hipError_t vcycle(char* ws, MGLayout& L, const mh_physics_desc& p, double* partial,
-                  double* mean_slot, hipStream_t s) {
+hipError_t vcycle(char* ws, MGLayout& L, const mh_physics_desc& p, double* partial, DevClock* clk,
+                  hipStream_t s) {
   const int nl = L.nlev;
   int cur[MG_MAX_LEVELS];
   cur[0] = L.cur0;
@@ -1117,12 +1159,14 @@ hipError_t vcycle(char* ws, MGLayout& L, const mh_physics_desc& p, double* parti
                          P<T>(ws, cv.phi[cur[0]]), P<T>(ws, cv.F), P<T>(ws, cv.phi[1 - cur[0]]));
       cur[0] = 1 - cur[0];
     }
-    hipError_t e = remove_mean(P<T>(ws, cv.phi[cur[0]]), N, partial, mean_slot, s);
+    hipError_t e = remove_mean(P<T>(ws, cv.phi[cur[0]]), N, partial, &clk->mean, s);
     if (e != hipSuccess) return e;
   } else {
     hipError_t e =
-        level_cycle<T>(ws, L, p, 0, tail_level(L), cur, false, true, partial, mean_slot, s);
+        level_cycle<T>(ws, L, p, 0, tail_level(L), cur, false, true, partial, clk, s);
     if (e != hipSuccess) return e;
+    if (tiled_level(L.lev[0].n, p))
+      converged(clk, p, partial, level_tiles(L.lev[0].n, p.mg_post), false, L.graphs, s);
   }
   L.cur0 = cur[0];
   return hipGetLastError();
@@ -1278,15 +1322,33 @@ void MGGraphCache::destroy() {
   reset();
   if (cs) (void)hipStreamDestroy(cs);
   cs = nullptr;
+  for (hipEvent_t& e : tested) {
+    if (e) (void)hipEventDestroy(e);
+    e = nullptr;
+  }
+  if (done) (void)hipHostFree(done);
+  done = nullptr;
 }
 
-// one V-cycle: replayed from the cached graph of the current parity (captured
-// on first use), or launched kernel by kernel when no cache is attached
+hipError_t MGGraphCache::prepare_tests() {
+  hipError_t e = hipSuccess;
+  for (hipEvent_t& ev : tested)
+    if (!ev && e == hipSuccess) e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
+  if (!done && e == hipSuccess) e = hipHostMalloc((void**)&done, 2 * sizeof(int), hipHostMallocDefault);
+  return e;
+}
+
+// One V-cycle.  On a tiled fine level it is launched kernel by kernel: its ten
+// launches are queued a cycle ahead, and between two graphs the GPU waits 13 us
+// (two steps with gravity, us, replayed / launched: 16^3 fp32 454 / 390, 64^3
+// fp64 1521 / 1415, 128^3 fp64 3119 / 3016).  The about 60 launches of the other
+// smoothers, each cycle of which waits for the host, are replayed from the cached
+// graph of the current parity, captured on first use
 template <typename T>
 hipError_t run_vcycle(char* ws, MGLayout& L, const mh_physics_desc& p, double* partial,
-                      double* mean_slot, hipStream_t s) {
+                      DevClock* clk, hipStream_t s) {
   MGGraphCache* G = L.graphs;
-  if (!G || !G->enabled) return vcycle<T>(ws, L, p, partial, mean_slot, s);
+  if (!G->enabled || tiled_level(L.lev[0].n, p)) return vcycle<T>(ws, L, p, partial, clk, s);
   if (G->ws != ws) {
     G->reset();
     G->ws = ws;
@@ -1295,7 +1357,7 @@ hipError_t run_vcycle(char* ws, MGLayout& L, const mh_physics_desc& p, double* p
   if (!G->exec[k]) {
     if (!G->cs) MG_CHECK(hipStreamCreateWithFlags(&G->cs, hipStreamNonBlocking));
     MG_CHECK(hipStreamBeginCapture(G->cs, hipStreamCaptureModeRelaxed));
-    const hipError_t e = vcycle<T>(ws, L, p, partial, mean_slot, G->cs);
+    const hipError_t e = vcycle<T>(ws, L, p, partial, clk, G->cs);
     hipGraph_t graph = nullptr;
     const hipError_t e2 = hipStreamEndCapture(G->cs, &graph);
     G->cur_after[k] = L.cur0;
@@ -1330,34 +1392,46 @@ hipError_t mg_solve(char* ws, MGLayout& L, const mh_physics_desc& p, DevClock* c
   }
   MG_CHECK(sum_to(P<T>(ws, f.F), N, true, partial, 1.0, &clk->mg_fnorm2, s));
   MG_CHECK(remove_mean(P<T>(ws, f.phi[L.cur0]), N, partial, &clk->mean, s));
-  int cycles = 0;
-  double prev = INFINITY;
   // a tiled fine level leaves the block sums of |r|^2 with its last sweep; phi
-  // may then carry a constant, which no operator sees, until the end
+  // may then carry a constant, which no operator sees, until the end.  Its
+  // cycles are queued one ahead of the test that may stop them: the host's way
+  // from one cycle's test to the next cycle's launch took 55 of 200 us a cycle
+  // at 128^3 fp64 (a copy and a synchronisation), and a cycle that turns out not
+  // to be wanted is 45 us of kernels that return.  Nothing unguarded writes
+  // the fine level there.
   const bool fused = L.nlev > 1 && tiled_level(n, p);
-  for (;;) {
-    // |r|^2 without storing r: the sum k_sum_partial would form over it
-    int nbr = sum_blocks(N);
-    if (fused && cycles > 0)
-      nbr = level_tiles(n, p.mg_post);
-    else
+  MGGraphCache* const G = L.graphs;
+  MG_CHECK(G->prepare_tests());
+  int cycles = 0;
+  auto test = [&](int after) {
+    if (!fused || after == 0) {
+      // |r|^2 without storing r: the sum k_sum_partial would form over it
+      const int nbr = sum_blocks(N);
       hipLaunchKernelGGL((k_residual_norm2<T>), dim3(nbr), dim3(256), 0, s, n,
                          (T)(1.0 / (f.h * f.h)), P<T>(ws, f.phi[L.cur0]), P<T>(ws, f.F), partial);
-    hipLaunchKernelGGL(k_sum_final, dim3(1), dim3(256), 0, s, partial, nbr, 1.0,
-                       &clk->mg_rnorm2);
-    double norms[2];
-    MG_CHECK(hipMemcpyAsync(norms, &clk->mg_fnorm2, 2 * sizeof(double), hipMemcpyDeviceToHost, s));
-    MG_CHECK(hipStreamSynchronize(s));
-    const double rn = std::sqrt(norms[1]);
-    if (rn <= p.mg_tol * std::sqrt(norms[0]) || cycles >= p.mg_max_cycles) break;
-    // with a tolerance, a cycle that no longer cuts the residual by MG_STALL
-    // has reached the round-off floor of the precision (in fp32 it lies above
-    // the usual tolerances): stop there rather than run to the cycle cap
-    if (p.mg_tol > 0.0 && rn > MG_STALL * prev) break;
-    prev = rn;
-    MG_CHECK(run_vcycle<T>(ws, L, p, partial, &clk->mean, s));
-    if (!fused) MG_CHECK(remove_mean(P<T>(ws, f.phi[L.cur0]), N, partial, &clk->mean, s));
-    ++cycles;
+      converged(clk, p, partial, nbr, after == 0, G, s);
+    }
+    const hipError_t e = hipGetLastError();
+    return e == hipSuccess ? hipEventRecord(G->tested[after & 1], s) : e;
+  };
+  // a cycle and its test
+  auto cycle = [&]() {
+    hipError_t e = run_vcycle<T>(ws, L, p, partial, clk, s);
+    if (!fused && e == hipSuccess)
+      e = remove_mean(P<T>(ws, f.phi[L.cur0]), N, partial, &clk->mean, s);
+    return e == hipSuccess ? test(cycles + 1) : e;
+  };
+  MG_CHECK(test(0));
+  for (;; ++cycles) {
+    const int cur = L.cur0;
+    const bool ahead = fused && cycles < p.mg_max_cycles;
+    if (ahead) MG_CHECK(cycle());
+    MG_CHECK(hipEventSynchronize(G->tested[cycles & 1]));
+    if (*(volatile int*)(G->done + (cycles & 1))) {
+      L.cur0 = cur;  // the cycle queued ahead leaves everything as it is
+      break;
+    }
+    if (!ahead) MG_CHECK(cycle());
   }
   if (fused && cycles > 0)
     MG_CHECK(remove_mean(P<T>(ws, f.phi[L.cur0]), N, partial, &clk->mean, s));

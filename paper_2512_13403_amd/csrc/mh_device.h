@@ -28,6 +28,8 @@ struct DevClock {
   unsigned long long bad_first;
   double ou_scale;
   int32_t mg_cycles;
+  int32_t mg_done;          // the gravity solve in flight has converged (or stops)
+  int32_t mg_tested;        // cycles of it whose outcome has been tested
   int32_t pad;
   double mg_fnorm2;         // ||F||^2 of the current gravity solve
   double mg_rnorm2;         // ||r||^2 of the last residual

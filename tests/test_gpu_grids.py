@@ -282,3 +282,54 @@ def test_corrector_input_and_floor_over_sizes(n, B, dtype):
         assert rel_err(o, r) < (1e-12 if dtype == "f64" else 1e-6)
     out, floored, fell = corrector((count - 0.5) / rho.size).apply(U)
     assert floored == count and fell and torch.equal(out, U)
+
+
+@pytest.mark.parametrize("n,pre,post,cycle,dtype", [
+    (14, 2, 2, mh.MG_V, "f64"),    # below the tiles
+    (16, 2, 2, mh.MG_V, "f64"), (16, 1, 3, mh.MG_W, "f32"),
+    (18, 2, 1, mh.MG_V, "f64"),    # partial tiles; coarsest level 9^3, no tail
+    (20, 3, 2, mh.MG_V, "f32"), (24, 1, 1, mh.MG_W, "f64"), (40, 2, 2, mh.MG_V, "f64"),
+    (48, 2, 3, mh.MG_W, "f64"),
+    (96, 2, 2, mh.MG_V, "f64"),    # the larger tiles of a fine level
+    (112, 1, 2, mh.MG_V, "f32"),   # ... in part; coarsest level 7^3
+])
+def test_gravity_over_tiles_and_levels(n, pre, post, cycle, dtype):
+    """Steps with self-gravity over the sizes where the multigrid's tiles,
+    levels and sweeps per launch change, converged (a fixed 14 cycles), against
+    the oracle."""
+    s, oc = pair((n,) * 3, (1.0 / n,) * 3, dtype=dtype, flags=oracle.SRC_GRAVITY,
+                 grav_G=wl.JEANS_G, mg_pre=pre, mg_post=post, mg_cycle=cycle, mg_tol=0.0,
+                 mg_max_cycles=14)
+    U = as_input(wl.grf_density_state(n, seed=2), dtype)
+    steps = 2 if n < 64 else 1
+    s.set_state(U)
+    s.step(steps, 1e-3)
+    assert s.mg_cycles() == 14
+    sim = oracle.Simulation(oc, U).advance(steps, 1e-3)
+    assert rel_err(s.get_state(), sim.U) < TOL[dtype]
+
+
+@pytest.mark.parametrize("cycles", [0, 1, 2])
+@pytest.mark.parametrize("smoother", [mh.SMOOTH_RBGS, mh.SMOOTH_JACOBI])
+def test_cycles_queued_ahead_leave_no_trace(cycles, smoother):
+    """A solve that stops at its last cycle, or at a tolerance it meets at once,
+    is the oracle's potential after exactly those cycles: the cycle queued
+    behind the test changes nothing, nor does it in the step after."""
+    n = 32
+    s, oc = pair((n,) * 3, (1.0 / n,) * 3, flags=oracle.SRC_GRAVITY, grav_G=wl.JEANS_G,
+                 mg_tol=0.0, mg_max_cycles=cycles, mg_smoother=smoother)
+    U = wl.grf_density_state(n, seed=4)
+    s.set_state(U)
+    sim = oracle.Simulation(oc, U)
+    for _ in range(2):
+        s.step(1, 1e-3)
+        sim.advance(1, 1e-3)
+        assert s.mg_cycles() == cycles
+        # 200 Jacobi sweeps solve the 4^3 level to rounding, as does the direct solve
+        assert np.abs(s.potential() - sim.phi).max() <= 1e-12 * max(np.abs(sim.phi).max(), 1e-30)
+    loose = mh.Solver(mh.grid_desc((n,) * 3, (1.0 / n,) * 3, dtype="f64"),
+                      mh.physics_desc(flags=mh.SRC_GRAVITY, grav_G=wl.JEANS_G, mg_tol=1e3,
+                                      mg_smoother=smoother))
+    loose.set_state(U)
+    loose.step(1, 1e-3)
+    assert loose.mg_cycles() == 0 and np.abs(loose.potential()).max() == 0.0
