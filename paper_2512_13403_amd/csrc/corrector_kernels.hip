@@ -605,13 +605,15 @@ __global__ __launch_bounds__(256, 2) void k_wgrad(const unsigned short* __restri
 // layer's weights).  The co_real entries after the weights take the bias
 // gradient (slot 27, column 0) into gb.  A block takes 64 consecutive
 // elements of a partial (one per lane, ci fastest, so each load of a wave is
-// 256 contiguous bytes); wave v adds the partials v, v + 4, ... in order, and
-// the four sums are added in a fixed order: the result is deterministic.
-__global__ __launch_bounds__(256) void k_wgrad_reduce(const float* __restrict__ partial, int cot,
-                                                      int nwg, int co_real, int ci_real,
-                                                      int fold, int xpack, float* __restrict__ g,
-                                                      float* __restrict__ gb) {
-  __shared__ float sp[4][64];
+// 256 contiguous bytes); wave v of 16 adds the partials v, v + 16, ... in order,
+// and the sums are added in a fixed order: the result is deterministic.  The
+// 59 MB of partials at 4 x 64^3 (32 channels) took 20 us with four waves to a
+// block, each a chain of 128 additions; 16 take 10.
+constexpr int REDUCE_WAVES = 16;
+__global__ __launch_bounds__(64 * REDUCE_WAVES) void k_wgrad_reduce(
+    const float* __restrict__ partial, int cot, int nwg, int co_real, int ci_real, int fold,
+    int xpack, float* __restrict__ g, float* __restrict__ gb) {
+  __shared__ float sp[REDUCE_WAVES][64];
   const int per = 28 * cot * 32;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int e = blockIdx.x * 64 + lane;
@@ -627,7 +629,7 @@ __global__ __launch_bounds__(256) void k_wgrad_reduce(const float* __restrict__ 
   float acc = 0.f;
   if (need) {
 #pragma unroll 8
-    for (int w = wv; w < nwg; w += 4) {
+    for (int w = wv; w < nwg; w += REDUCE_WAVES) {
       const float* pw = partial + (long long)w * per;
       acc += two ? pw[src] + pw[src + ci_real] : pw[src];
     }
@@ -635,7 +637,9 @@ __global__ __launch_bounds__(256) void k_wgrad_reduce(const float* __restrict__ 
   sp[wv][lane] = acc;
   __syncthreads();
   if (wv == 0 && need) {
-    const float tot = ((sp[0][lane] + sp[1][lane]) + sp[2][lane]) + sp[3][lane];
+    float tot = sp[0][lane];
+#pragma unroll
+    for (int w = 1; w < REDUCE_WAVES; ++w) tot += sp[w][lane];
     if (tap < 27) g[(co * ci_real + ci) * 27 + tap] += tot;
     else gb[co] += tot;
   }
@@ -837,6 +841,15 @@ __global__ __launch_bounds__(256) void k_fill_f32(float* p, int count, float v) 
   if (i < count) p[i] = v;
 }
 
+// the loss's factors per field, divided out on the host: with that, a 16-byte load
+// of y and wave sums instead of a tree of barriers, k_loss takes 37 us at 4 x 64^3
+// fp32 (163 MB) instead of 58
+struct LossFactors {
+  double scale[5];
+  double loss[5];  // w / sigma^2
+  double grad[5];  // 2 w / (sigma^2 cells)
+};
+
 // upstream gradient of the network output: with a target T, the loss
 // L = sum_c w_c mean((U'_c - T_c)^2) / sigma_c^2 (per-block partials) and its
 // gradient 2 w_c (U'_c - T_c) / (sigma_c^2 cells); plus gUc = dL/dU' from the
@@ -846,42 +859,43 @@ template <typename T>
 __global__ __launch_bounds__(256) void k_loss(const T* __restrict__ U, const float* __restrict__ y,
                                               const T* __restrict__ tgt,
                                               const T* __restrict__ gup, int n, long long cells,
-                                              CorrStats st, double* __restrict__ part,
+                                              const LossFactors lf, double* __restrict__ part,
                                               unsigned short* __restrict__ dy,
                                               T* __restrict__ gfull, int ident) {
-  __shared__ double sl[256];
+  __shared__ double sl[4];
   const long long cell = (long long)blockIdx.x * 256 + threadIdx.x;
   double l = 0.0;
   if (cell < cells) {
-    const long long n3 = (long long)n * n * n;
-    const long long b = cell / n3, q = cell % n3;
+    const unsigned n3 = (unsigned)n * (unsigned)n * (unsigned)n;
+    // (a block's cells are of one sample: n^3 is a multiple of 256)
+    const long long b = (long long)blockIdx.x * 256 / n3, q = cell - b * n3;
     unsigned short v[16];
 #pragma unroll
     for (int c = 0; c < 16; ++c) v[c] = 0;
+    float yc[5];
+    *(f32x4*)yc = *(const f32x4*)(y + cell * 16);
+    yc[4] = y[cell * 16 + 4];
 #pragma unroll
     for (int c = 0; c < 5; ++c) {
       double g = 0.0;
       if (tgt) {
-        const double uc = (double)U[(b * 5 + c) * n3 + q] + st.scale[c] * (double)y[cell * 16 + c];
+        const double uc = (double)U[(b * 5 + c) * n3 + q] + lf.scale[c] * (double)yc[c];
         const double d = uc - (double)tgt[(b * 5 + c) * n3 + q];
-        const double s2 = st.std[c] * st.std[c];
-        l += st.lw[c] * d * d / s2;
-        g = 2.0 * st.lw[c] * d / s2 / (double)cells;
+        l += lf.loss[c] * d * d;
+        g = lf.grad[c] * d;
       }
       if (gup) g += (double)gup[(b * 5 + c) * n3 + q];
       if (gfull) gfull[(b * 5 + c) * n3 + q] = ident ? (T)g : T(0);
-      v[c] = f2bf((float)(st.scale[c] * g));
+      v[c] = f2bf((float)(lf.scale[c] * g));
     }
     __builtin_memcpy(dy + cell * 16, v, 16);
     __builtin_memcpy(dy + cell * 16 + 8, v + 8, 16);
   }
-  sl[threadIdx.x] = l;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) l += __shfl_xor(l, o, 64);
+  if ((threadIdx.x & 63) == 0) sl[threadIdx.x >> 6] = l;
   __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if (threadIdx.x < s) sl[threadIdx.x] += sl[threadIdx.x + s];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) part[blockIdx.x] = sl[0];
+  if (threadIdx.x == 0) part[blockIdx.x] = (sl[0] + sl[1]) + (sl[2] + sl[3]);
 }
 
 // the cell's own two parts (channels 10..19 of the x-packed input) in the
@@ -898,13 +912,16 @@ __global__ __launch_bounds__(256) void k_unpack_input(const unsigned short* __re
   for (int c = 0; c < 32; c += 8) __builtin_memcpy(x0 + cell * 32 + c, v + c, 16);
 }
 
+struct InverseStd {
+  double v[5];
+};
 // dL/dU += gx_c / std_c (gU holds the upstream gradient of U', the residual
 // path; gx: [cell][16] fp32, the first layer's transposed convolution of dZ1;
 // the two-part input split and the positivity floor pass the gradient
 // through unchanged)
 template <typename T>
 __global__ __launch_bounds__(256) void k_input_grad(const float* __restrict__ gx, int n,
-                                                    long long cells, CorrStats st,
+                                                    long long cells, const InverseStd is,
                                                     T* __restrict__ gU) {
   const long long cell = (long long)blockIdx.x * 256 + threadIdx.x;
   if (cell >= cells) return;
@@ -913,7 +930,7 @@ __global__ __launch_bounds__(256) void k_input_grad(const float* __restrict__ gx
 #pragma unroll
   for (int c = 0; c < 5; ++c) {
     const long long o = (b * 5 + c) * n3 + q;
-    gU[o] = (T)((double)gU[o] + (double)gx[cell * 16 + c] / st.std[c]);
+    gU[o] = (T)((double)gU[o] + (double)gx[cell * 16 + c] * is.v[c]);
   }
 }
 
@@ -1098,33 +1115,42 @@ hipError_t corr_backward(const CorrBuffers& B, const CorrStats& st, int n, int b
   const long long cells = (long long)batch * n * n * n;
   const unsigned conv_blocks = conv_grid(n, batch);
   const unsigned lb = blocks(cells, 256);
-  hipLaunchKernelGGL((k_loss<T>), dim3(lb), dim3(256), 0, s, U, B.y, tgt, gup, n, cells, st,
+  LossFactors lf;
+  InverseStd is;
+  for (int c = 0; c < 5; ++c) {
+    const double s2 = st.std[c] * st.std[c];
+    lf.scale[c] = st.scale[c];
+    lf.loss[c] = st.lw[c] / s2;
+    lf.grad[c] = 2.0 * st.lw[c] / s2 / (double)cells;
+    is.v[c] = 1.0 / st.std[c];
+  }
+  hipLaunchKernelGGL((k_loss<T>), dim3(lb), dim3(256), 0, s, U, B.y, tgt, gup, n, cells, lf,
                      B.dpart, B.dy16, gU, (int)ident);
   hipLaunchKernelGGL(k_dsum, dim3(1), dim3(256), 0, s, B.dpart, (int)lb, B.loss);
   const int nblk = (int)(cells / (CTX * CTY * CTZ));
   const int nwg = corr_wgrad_groups(cells);
   // layer 3: dW3, db3; dH2 -> dZ2 = dH2 * GELU'(Z2)
   hipLaunchKernelGGL((k_wgrad<16>), dim3(nwg), dim3(256), 0, s, B.dy16, B.h2, n, nblk, B.wpart);
-  hipLaunchKernelGGL(k_wgrad_reduce, dim3(blocks(28 * 16 * 32, 64)), dim3(256), 0, s, B.wpart,
+  hipLaunchKernelGGL(k_wgrad_reduce, dim3(blocks(28 * 16 * 32, 64)), dim3(64 * REDUCE_WAVES), 0, s, B.wpart,
                      16, nwg, 5, 32, 0, 0, B.grad + CORR_OFF_W3, B.grad + CORR_OFF_B3);
   hipLaunchKernelGGL((k_conv<32, EPI_GELU_BWD, 27, 16>), dim3(conv_wgs(conv_blocks)), dim3(VT), 0, s, B.dy16, B.w3t,
                      (const float*)nullptr, 0, n, B.z2, (float*)nullptr, B.dz2, (int)conv_blocks, ResArgs<float>{});
   // layer 2
   hipLaunchKernelGGL((k_wgrad<32>), dim3(nwg), dim3(256), 0, s, B.dz2, B.h1, n, nblk, B.wpart);
-  hipLaunchKernelGGL(k_wgrad_reduce, dim3(blocks(28 * 32 * 32, 64)), dim3(256), 0, s,
+  hipLaunchKernelGGL(k_wgrad_reduce, dim3(blocks(28 * 32 * 32, 64)), dim3(64 * REDUCE_WAVES), 0, s,
                      B.wpart, 32, nwg, 32, 32, 0, 0, B.grad + CORR_OFF_W2, B.grad + CORR_OFF_B2);
   hipLaunchKernelGGL((k_conv<32, EPI_GELU_BWD, 27, 32>), dim3(conv_wgs(conv_blocks)), dim3(VT), 0, s, B.dz2, B.w2t,
                      (const float*)nullptr, 0, n, B.z1, (float*)nullptr, B.dz1, (int)conv_blocks, ResArgs<float>{});
   // layer 1
   hipLaunchKernelGGL((k_wgrad<32, true>), dim3(nwg), dim3(256), 0, s, B.dz1, B.x0, n, nblk,
                      B.wpart);
-  hipLaunchKernelGGL(k_wgrad_reduce, dim3(blocks(28 * 32 * 32, 64)), dim3(256), 0, s,
+  hipLaunchKernelGGL(k_wgrad_reduce, dim3(blocks(28 * 32 * 32, 64)), dim3(64 * REDUCE_WAVES), 0, s,
                      B.wpart, 32, nwg, 32, 5, 1, 1, B.grad + CORR_OFF_W1, B.grad + CORR_OFF_B1);
   if (gU) {
     hipLaunchKernelGGL((k_conv<16, EPI_RAW, 27, 32>), dim3(conv_wgs(conv_blocks)), dim3(VT), 0, s, B.dz1, B.w1t,
                        (const float*)nullptr, 0, n, (const float*)nullptr, B.gx,
                        (unsigned short*)nullptr, (int)conv_blocks, ResArgs<float>{});
-    hipLaunchKernelGGL((k_input_grad<T>), dim3(lb), dim3(256), 0, s, B.gx, n, cells, st, gU);
+    hipLaunchKernelGGL((k_input_grad<T>), dim3(lb), dim3(256), 0, s, B.gx, n, cells, is, gU);
   }
   return hipGetLastError();
 }
