@@ -13,7 +13,7 @@
 // radix-2 or radix-4 pass for the rest of log2(n), each an in-register DFT
 // of the values a thread reads, so a 512-point line takes three passes
 // through LDS and no bit-reversal.  Twiddles exp(-2 pi i t / n), t < n/2,
-// come from fp64 sincospi (a table read through the caches).  The inverse
+// come from fp64 sincospi (a table copied to LDS).  The inverse
 // transform is conj(FFT(conj x)), unscaled; the 1/n^3 is folded into the
 // spectral multipliers.
 //
@@ -43,14 +43,13 @@ struct CplxOf<double> {
   using type = double2;
 };
 
-constexpr int FFT_THREADS = 256;
-// values per thread: 128 bytes (16 in fp32, 8 in fp64), so a workgroup holds
-// 32 KB of whole lines in LDS
+// Values per thread, a radix-8 group, and threads per workgroup: whole lines of
+// 32 KB in LDS either way.  In fp32 512 threads of 8 values, not 256 of 16: eight
+// waves a SIMD instead of four cover the loads and barriers (256^3, us: y pass
+// 84 -> 62, x pass with split output 82 -> 59).
+constexpr int FFT_ELEMS = 8;
 template <typename C>
-constexpr int fft_elems() {
-  return 128 / (int)sizeof(C);
-}
-static_assert(fft_elems<double2>() >= 8, "a radix-8 pass needs 8 values per thread");
+constexpr int fft_threads = sizeof(C) == 8 ? 512 : 256;
 
 inline unsigned nblk(long long n) { return (unsigned)((n + 255) / 256); }
 
@@ -119,31 +118,39 @@ __device__ __forceinline__ void dft_regs(C (&u)[R]) {
   for (int i = 0; i < R; ++i) u[i] = v[i];
 }
 
+// Place of point j of a line in its LDS row, and the pitch of the rows: one
+// element of padding every eight keeps a pass's writes, eight elements apart, on
+// different banks, and four more per row the strided ends of the y and z passes,
+// whose lanes step through lines first.  Unpadded, both met 8- to 16-fold
+// conflicts, which bounded every pass (256^3 fp32, y pass 101 us; 84 padded).
+__device__ __forceinline__ int lds_place(int j) { return j + (j >> 3); }
+__host__ __device__ inline int lds_pitch(int n) { return n + (n >> 3) + 4; }
+
 // One radix-R pass of the self-sorting (Stockham) FFT over the E = lpb n
 // values of the workgroup's lines in LDS, after passes whose radices multiply
 // to p: group i (< n / R) of a line reads x[i + r n / R], multiplies by
 // exp(-2 pi i r k / (R p)) with k = i mod p, transforms them, and writes
 // x'[(i - k) R + k + r p].  All groups are read before any is written (one
-// barrier), so the pass works in place; E / FFT_THREADS <= ELEMS, so every
-// thread holds its values in registers.
-template <typename C, int R, int ELEMS>
-__device__ __forceinline__ void stockham_pass(C* buf, const C* __restrict__ stw, int logn, int E,
-                                              int p) {
-  constexpr int GMAX = ELEMS / R;
+// barrier), so the pass works in place; E / NT <= FFT_ELEMS, so every
+// thread holds its values in registers.  FIRST: p = 1, no twiddles.
+template <typename C, int R, bool FIRST>
+__device__ __forceinline__ void stockham_pass(C* buf, const C* stw, int logn, int E, int p) {
+  constexpr int GMAX = FFT_ELEMS / R, NT = fft_threads<C>;
   constexpr int LR = R == 2 ? 1 : (R == 4 ? 2 : 3);
   const int n = 1 << logn, logm = logn - LR, m = n >> LR, groups = E >> LR;
+  const int pitch = lds_pitch(n);
   C u[GMAX][R];
 #pragma unroll
   for (int gi = 0; gi < GMAX; ++gi) {
-    const int g = threadIdx.x + gi * FFT_THREADS;
+    const int g = threadIdx.x + gi * NT;
     if (g < groups) {
       const int li = g >> logm, i = g & (m - 1), k = i & (p - 1);
-      const C* x = buf + (li << logn);
-      const int step = n / (R * p);
+      const C* x = buf + li * pitch;
+      const int step = FIRST ? 0 : n / (R * p);
 #pragma unroll
       for (int r = 0; r < R; ++r) {
-        C v = x[i + r * m];
-        if (r > 0) {
+        C v = x[lds_place(i + r * m)];
+        if (!FIRST && r > 0) {
           const int t = r * k * step;  // < n: table of the first half, negated above it
           C w = stw[t < n / 2 ? t : t - n / 2];
           if (t >= n / 2) w = C{-w.x, -w.y};
@@ -157,16 +164,38 @@ __device__ __forceinline__ void stockham_pass(C* buf, const C* __restrict__ stw,
   __syncthreads();
 #pragma unroll
   for (int gi = 0; gi < GMAX; ++gi) {
-    const int g = threadIdx.x + gi * FFT_THREADS;
+    const int g = threadIdx.x + gi * NT;
     if (g < groups) {
       const int li = g >> logm, i = g & (m - 1), k = i & (p - 1);
-      C* x = buf + (li << logn);
+      C* x = buf + li * pitch;
       const int j = (i - k) * R + k;
 #pragma unroll
-      for (int r = 0; r < R; ++r) x[j + r * p] = u[gi][r];
+      for (int r = 0; r < R; ++r) x[lds_place(j + r * p)] = u[gi][r];
     }
   }
   __syncthreads();
+}
+
+// all passes of the E values of the workgroup's lines in LDS, with the twiddles
+// in LDS after them
+template <typename C>
+__device__ __forceinline__ void stockham(C* buf, const C* stw, int logn, int E) {
+  int p = 1;
+  if (logn >= 3) {
+    stockham_pass<C, 8, true>(buf, stw, logn, E, 1);
+    p = 8;
+    for (int q = 1; q < logn / 3; ++q) {
+      stockham_pass<C, 8, false>(buf, stw, logn, E, p);
+      p *= 8;
+    }
+  }
+  if (logn % 3 == 1) {
+    if (p == 1) stockham_pass<C, 2, true>(buf, stw, logn, E, p);
+    else stockham_pass<C, 2, false>(buf, stw, logn, E, p);
+  } else if (logn % 3 == 2) {
+    if (p == 1) stockham_pass<C, 4, true>(buf, stw, logn, E, p);
+    else stockham_pass<C, 4, false>(buf, stw, logn, E, p);
+  }
 }
 
 // FFT of 2^loglpb lines per workgroup (unscaled); the inverse is
@@ -175,15 +204,13 @@ __device__ __forceinline__ void stockham_pass(C* buf, const C* __restrict__ stw,
 // the lines in flight at once; the store to the cube is batched the same way.
 // IO selects the ends of a 3D transform: 0 in place on `data`; FFT_REAL_IN
 // reads the real field `rin` (imaginary part 0) and writes `data`;
-// FFT_REAL_OUT reads `data` and writes only the real part, to `rout`;
 // FFT_SPLIT_OUT writes the real part to `rout` and the imaginary part to
 // `rout2` (the inverse transform of two Hermitian spectra packed as A + i B
 // gives the two real fields a + i b); FFT_PAIR_IN reads `rin` + i `rin2` (the
 // transform of two real fields at once, separated by Hermitian symmetry).
-enum : int { FFT_COMPLEX = 0, FFT_REAL_IN = 1, FFT_REAL_OUT = 2, FFT_SPLIT_OUT = 3,
-             FFT_PAIR_IN = 4 };
+enum : int { FFT_COMPLEX = 0, FFT_REAL_IN = 1, FFT_SPLIT_OUT = 2, FFT_PAIR_IN = 3 };
 template <typename T, int AXIS, int IO>
-__global__ __launch_bounds__(FFT_THREADS) void k_fft_lines(typename CplxOf<T>::type* data,
+__global__ __launch_bounds__(fft_threads<typename CplxOf<T>::type>) void k_fft_lines(typename CplxOf<T>::type* data,
                                                            const T* __restrict__ rin,
                                                            const T* __restrict__ rin2,
                                                            T* __restrict__ rout,
@@ -191,23 +218,26 @@ __global__ __launch_bounds__(FFT_THREADS) void k_fft_lines(typename CplxOf<T>::t
                                                            const typename CplxOf<T>::type* tw,
                                                            int logn, int loglpb, int inverse) {
   using C = typename CplxOf<T>::type;
-  constexpr int ELEMS = fft_elems<C>();
+  constexpr int ELEMS = FFT_ELEMS, NT = fft_threads<C>;
   extern __shared__ __align__(16) unsigned char smem_raw[];
   C* buf = reinterpret_cast<C*>(smem_raw);
+  const int pitch = lds_pitch(1 << logn);
+  C* stw = buf + (pitch << loglpb);
+  for (int t = threadIdx.x; t < 1 << (logn - 1); t += NT) stw[t] = tw[t];
   // workgroups are dealt round-robin over the 8 XCDs: give each XCD a
   // contiguous range of line blocks, so that the y and z passes' neighbouring
   // blocks (the next lpb values of x) share that XCD's L2 lines
   unsigned b = blockIdx.x;
   if ((gridDim.x & 7u) == 0) b = (b & 7u) * (gridDim.x >> 3) + (b >> 3);
   const unsigned line0 = b << loglpb;
-  const int E = 1 << (logn + loglpb);  // <= ELEMS * FFT_THREADS (the launch sizes lpb so)
+  const int E = 1 << (logn + loglpb);  // <= ELEMS * NT (the launch sizes lpb so)
   // x axis: consecutive threads walk along a line; y, z: across lines
   auto line_of = [&](int e) { return AXIS == 0 ? e >> logn : e & ((1 << loglpb) - 1); };
   auto point_of = [&](int e) { return AXIS == 0 ? e & ((1 << logn) - 1) : e >> loglpb; };
   C v[ELEMS];
 #pragma unroll
   for (int q = 0; q < ELEMS; ++q) {
-    const int e = threadIdx.x + q * FFT_THREADS;
+    const int e = threadIdx.x + q * NT;
     if (e < E) {
       const unsigned idx = line_elem<AXIS>(logn, line0 + line_of(e), point_of(e));
       if (IO == FFT_REAL_IN) v[q] = C{rin[idx], T(0)};
@@ -217,36 +247,28 @@ __global__ __launch_bounds__(FFT_THREADS) void k_fft_lines(typename CplxOf<T>::t
   }
 #pragma unroll
   for (int q = 0; q < ELEMS; ++q) {
-    const int e = threadIdx.x + q * FFT_THREADS;
+    const int e = threadIdx.x + q * NT;
     if (e < E) {
       C x = v[q];
       if (inverse) x.y = -x.y;
-      buf[(line_of(e) << logn) + point_of(e)] = x;
+      buf[line_of(e) * pitch + lds_place(point_of(e))] = x;
     }
   }
   __syncthreads();
-  int p = 1;
-  for (int q = 0; q < logn / 3; ++q) {
-    stockham_pass<C, 8, ELEMS>(buf, tw, logn, E, p);
-    p *= 8;
-  }
-  if (logn % 3 == 1) stockham_pass<C, 2, ELEMS>(buf, tw, logn, E, p);
-  else if (logn % 3 == 2) stockham_pass<C, 4, ELEMS>(buf, tw, logn, E, p);
+  stockham<C>(buf, stw, logn, E);
 #pragma unroll
   for (int q = 0; q < ELEMS; ++q) {
-    const int e = threadIdx.x + q * FFT_THREADS;
-    if (e < E) v[q] = buf[(line_of(e) << logn) + point_of(e)];
+    const int e = threadIdx.x + q * NT;
+    if (e < E) v[q] = buf[line_of(e) * pitch + lds_place(point_of(e))];
   }
 #pragma unroll
   for (int q = 0; q < ELEMS; ++q) {
-    const int e = threadIdx.x + q * FFT_THREADS;
+    const int e = threadIdx.x + q * NT;
     if (e < E) {
       C x = v[q];
       if (inverse) x.y = -x.y;
       const unsigned idx = line_elem<AXIS>(logn, line0 + line_of(e), point_of(e));
-      if (IO == FFT_REAL_OUT) {
-        rout[idx] = x.x;
-      } else if (IO == FFT_SPLIT_OUT) {
+      if (IO == FFT_SPLIT_OUT) {
         rout[idx] = x.x;
         rout2[idx] = x.y;
       } else {
@@ -258,20 +280,6 @@ __global__ __launch_bounds__(FFT_THREADS) void k_fft_lines(typename CplxOf<T>::t
 
 __device__ __forceinline__ int wavenum(int q, int n) { return q <= n / 2 ? q : q - n; }
 
-// Phi_hat / N = -F_hat / (|kappa|^2 N), 0 at kappa = 0
-template <typename T>
-__global__ __launch_bounds__(256) void k_fft_phi(typename CplxOf<T>::type* c, int n, double tk) {
-  const long long N = (long long)n * n * n;
-  const long long q = (long long)blockIdx.x * 256 + threadIdx.x;
-  if (q >= N) return;
-  const int kx = wavenum((int)(q % n), n), ky = wavenum((int)((q / n) % n), n),
-            kz = wavenum((int)(q / ((long long)n * n)), n);
-  const double k2 = tk * tk * (double)(kx * kx + ky * ky + kz * kz);
-  const T f = k2 > 0.0 ? (T)(-1.0 / (k2 * (double)N)) : T(0);
-  c[q].x *= f;
-  c[q].y *= f;
-}
-
 // derivative wavenumber of index q along an axis (Nyquist -> 0)
 __device__ __forceinline__ double dkappa(int q, int n, double tk) {
   return q == n / 2 ? 0.0 : tk * (double)wavenum(q, n);
@@ -282,26 +290,89 @@ __device__ __forceinline__ int axis_index(long long q, int n) {
   return AXIS == 0 ? (int)(q % n) : (AXIS == 1 ? (int)((q / n) % n) : (int)(q / ((long long)n * n)));
 }
 
-// the four real fields of the solve packed two per complex spectrum: with
-// Phi_hat in c (already divided by N) and a_hat_a = -i kappa~_a Phi_hat,
-// c1 = a_hat_x + i a_hat_y and c (in place) = a_hat_z + i Phi_hat; each of
-// the four spectra is Hermitian (the Nyquist index has kappa~ = 0), so the
-// inverse transforms give a_x + i a_y and a_z + i Phi
+// The middle of the solve on lines along z, whose x and y transforms are done:
+// the z transform, Phi_hat / N = -F_hat / (|kappa|^2 N) (0 at kappa = 0), and the
+// inverse z transforms of the four real fields of the solve packed two per
+// complex spectrum: with a_hat_a = -i kappa~_a Phi_hat, c1 = a_hat_x + i a_hat_y
+// and c (in place) = a_hat_z + i Phi_hat; each of the four spectra is Hermitian
+// (the Nyquist index has kappa~ = 0), so the inverse transforms give a_x + i a_y
+// and a_z + i Phi.  Bound by memory: one cube read and two written, where the
+// forward pass, the two spectral passes and the two inverse z passes in kernels
+// of their own moved three times that (256^3 fp32: 408 us, 151 here).
 template <typename T>
-__global__ __launch_bounds__(256) void k_fft_grad_pairs(typename CplxOf<T>::type* c,
-                                                        typename CplxOf<T>::type* c1, int n,
-                                                        double tk) {
-  const long long N = (long long)n * n * n;
-  const long long q = (long long)blockIdx.x * 256 + threadIdx.x;
-  if (q >= N) return;
-  const T kx = (T)dkappa(axis_index<0>(q, n), n, tk), ky = (T)dkappa(axis_index<1>(q, n), n, tk),
-          kz = (T)dkappa(axis_index<2>(q, n), n, tk);
-  const T re = c[q].x, im = c[q].y;
-  // -i k (re + i im) = (k im, -k re); i (u + i w) = (-w, u)
-  c1[q].x = kx * im + ky * re;
-  c1[q].y = -kx * re + ky * im;
-  c[q].x = kz * im - im;
-  c[q].y = -kz * re + re;
+__global__ __launch_bounds__(fft_threads<typename CplxOf<T>::type>) void k_fft_solve_z(typename CplxOf<T>::type* c,
+                                                             typename CplxOf<T>::type* c1,
+                                                             const typename CplxOf<T>::type* tw,
+                                                             int logn, int loglpb, double tk) {
+  using C = typename CplxOf<T>::type;
+  constexpr int ELEMS = FFT_ELEMS, NT = fft_threads<C>;
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  C* buf = reinterpret_cast<C*>(smem_raw);
+  const int pitch = lds_pitch(1 << logn);
+  C* stw = buf + (pitch << loglpb);
+  for (int t = threadIdx.x; t < 1 << (logn - 1); t += NT) stw[t] = tw[t];
+  unsigned b = blockIdx.x;  // (as in k_fft_lines)
+  if ((gridDim.x & 7u) == 0) b = (b & 7u) * (gridDim.x >> 3) + (b >> 3);
+  const unsigned line0 = b << loglpb;
+  const int n = 1 << logn, E = 1 << (logn + loglpb);
+  auto line_of = [&](int e) { return e & ((1 << loglpb) - 1); };
+  auto point_of = [&](int e) { return e >> loglpb; };
+  auto slot = [&](int e) { return line_of(e) * pitch + lds_place(point_of(e)); };
+  auto elem = [&](int e) { return line_elem<2>(logn, line0 + line_of(e), point_of(e)); };
+  C v[ELEMS];
+#pragma unroll
+  for (int q = 0; q < ELEMS; ++q) {
+    const int e = threadIdx.x + q * NT;
+    if (e < E) v[q] = c[elem(e)];
+  }
+#pragma unroll
+  for (int q = 0; q < ELEMS; ++q) {
+    const int e = threadIdx.x + q * NT;
+    if (e < E) buf[slot(e)] = v[q];
+  }
+  __syncthreads();
+  stockham<C>(buf, stw, logn, E);
+  const double N = (double)n * n * n;
+  // from here on a thread's slots are its own between the transforms; the
+  // inverse is conj(FFT(conj))
+#pragma unroll
+  for (int q = 0; q < ELEMS; ++q) {
+    const int e = threadIdx.x + q * NT;
+    if (e < E) {
+      const int line = (int)(line0 + line_of(e)), ix = line & (n - 1), iy = line >> logn,
+                iz = point_of(e);
+      const int mx = wavenum(ix, n), my = wavenum(iy, n), mz = wavenum(iz, n);
+      const double k2 = tk * tk * (double)(mx * mx + my * my + mz * mz);
+      const T f = k2 > 0.0 ? (T)(-1.0 / (k2 * N)) : T(0);
+      const C F = buf[slot(e)];
+      const T re = F.x * f, im = F.y * f;
+      const T kx = (T)dkappa(ix, n, tk), ky = (T)dkappa(iy, n, tk), kz = (T)dkappa(iz, n, tk);
+      // -i k (re + i im) = (k im, -k re); i (u + i w) = (-w, u)
+      buf[slot(e)] = C{kx * im + ky * re, -(-kx * re + ky * im)};
+      v[q] = C{kz * im - im, -(-kz * re + re)};
+    }
+  }
+  __syncthreads();
+  stockham<C>(buf, stw, logn, E);
+#pragma unroll
+  for (int q = 0; q < ELEMS; ++q) {
+    const int e = threadIdx.x + q * NT;
+    if (e < E) {
+      const C x = buf[slot(e)];
+      c1[elem(e)] = C{x.x, -x.y};
+      buf[slot(e)] = v[q];
+    }
+  }
+  __syncthreads();
+  stockham<C>(buf, stw, logn, E);
+#pragma unroll
+  for (int q = 0; q < ELEMS; ++q) {
+    const int e = threadIdx.x + q * NT;
+    if (e < E) {
+      const C x = buf[slot(e)];
+      c[elem(e)] = C{x.x, -x.y};
+    }
+  }
 }
 
 template <typename T>
@@ -438,51 +509,54 @@ __global__ __launch_bounds__(256) void k_accel_kick_vjp(const T* __restrict__ U,
   lout[4 * N + q] = Eb;
 }
 
-// the three one-axis passes over the n^3 cube c, with the twiddles tw; with
-// rin the x pass reads the real field rin instead of c, with rout the z pass
-// writes only the real part of the result, to rout (c then holds no result)
+// how the lines of an axis are dealt: 2^loglpb of them per workgroup, as many
+// as fit the LDS budget
+template <typename T>
+struct LinePlan {
+  int logn = 0, loglpb = 0;
+  unsigned grid;
+  size_t lds;
+  explicit LinePlan(int n) {
+    using C = typename CplxOf<T>::type;
+    while ((1 << logn) < n) ++logn;
+    const long long lines = (long long)n * n;
+    while (((long long)n << (loglpb + 1)) <= (long long)fft_threads<C> * FFT_ELEMS &&
+           (1ll << (loglpb + 1)) <= lines)
+      ++loglpb;
+    grid = (unsigned)(lines >> loglpb);
+    lds = (((size_t)lds_pitch(n) << loglpb) + n / 2) * sizeof(C);
+  }
+};
+
+// one pass over the n^3 cube c along AXIS (IO: see k_fft_lines)
+template <typename T, int AXIS, int IO>
+hipError_t fft_pass(typename CplxOf<T>::type* c, const typename CplxOf<T>::type* tw, int n,
+                    int inverse, hipStream_t s, const T* rin = nullptr, const T* rin2 = nullptr,
+                    T* rout = nullptr, T* rout2 = nullptr) {
+  const LinePlan<T> lp(n);
+  hipLaunchKernelGGL((k_fft_lines<T, AXIS, IO>), dim3(lp.grid), dim3(fft_threads<typename CplxOf<T>::type>), lp.lds, s, c,
+                     rin, rin2, rout, rout2, tw, lp.logn, lp.loglpb, inverse);
+  return hipGetLastError();
+}
+
 // the three one-axis passes over the n^3 cube c, with the twiddles tw; with
 // rin the x pass reads the real field rin (with rin2 too: rin + i rin2)
-// instead of c, with rout the z pass writes only the real part of the result
-// to rout (with rout2 too: the imaginary part to rout2; c then holds no
-// result)
+// instead of c
 template <typename T>
 hipError_t fft3_raw(typename CplxOf<T>::type* c, const typename CplxOf<T>::type* tw, int n,
-                    int inverse, hipStream_t s, const T* rin = nullptr, T* rout = nullptr,
-                    T* rout2 = nullptr, const T* rin2 = nullptr) {
-  using C = typename CplxOf<T>::type;
-  int logn = 0;
-  while ((1 << logn) < n) ++logn;
-  const long long lines = (long long)n * n;
-  // lines per workgroup: a power of two, as many as fit in the LDS budget
-  int loglpb = 0;
-  while (((long long)n << (loglpb + 1)) <= (long long)FFT_THREADS * fft_elems<C>() &&
-         (1ll << (loglpb + 1)) <= lines)
-    ++loglpb;
-  const unsigned grid = (unsigned)(lines >> loglpb);
-  const size_t lds = (size_t)n * sizeof(C) << loglpb;
-  T* const nul = nullptr;
-  const T* const cnul = nullptr;
-#define MH_LINES(AX, IO, RI, RI2, RO, RO2)                                                   \
-  hipLaunchKernelGGL((k_fft_lines<T, AX, IO>), dim3(grid), dim3(FFT_THREADS), lds, s, c, RI, \
-                     RI2, RO, RO2, tw, logn, loglpb, inverse)
-  if (rin && rin2) MH_LINES(0, FFT_PAIR_IN, rin, rin2, nul, nul);
-  else if (rin) MH_LINES(0, FFT_REAL_IN, rin, cnul, nul, nul);
-  else MH_LINES(0, FFT_COMPLEX, cnul, cnul, nul, nul);
-  MH_LINES(1, FFT_COMPLEX, cnul, cnul, nul, nul);
-  if (rout && rout2) MH_LINES(2, FFT_SPLIT_OUT, cnul, cnul, rout, rout2);
-  else if (rout) MH_LINES(2, FFT_REAL_OUT, cnul, cnul, rout, nul);
-  else MH_LINES(2, FFT_COMPLEX, cnul, cnul, nul, nul);
-#undef MH_LINES
-  return hipGetLastError();
+                    int inverse, hipStream_t s, const T* rin = nullptr, const T* rin2 = nullptr) {
+  hipError_t e = rin && rin2 ? fft_pass<T, 0, FFT_PAIR_IN>(c, tw, n, inverse, s, rin, rin2)
+                 : rin       ? fft_pass<T, 0, FFT_REAL_IN>(c, tw, n, inverse, s, rin)
+                             : fft_pass<T, 0, FFT_COMPLEX>(c, tw, n, inverse, s);
+  if (e == hipSuccess) e = fft_pass<T, 1, FFT_COMPLEX>(c, tw, n, inverse, s);
+  return e == hipSuccess ? fft_pass<T, 2, FFT_COMPLEX>(c, tw, n, inverse, s) : e;
 }
 
 template <typename T>
 hipError_t fft3(char* ws, const MGLayout& L, typename CplxOf<T>::type* c, int inverse,
-                hipStream_t s, const T* rin = nullptr, T* rout = nullptr, T* rout2 = nullptr,
-                const T* rin2 = nullptr) {
+                hipStream_t s, const T* rin = nullptr, const T* rin2 = nullptr) {
   using C = typename CplxOf<T>::type;
-  return fft3_raw<T>(c, P<C>(ws, L.fft_tw), L.lev[0].n, inverse, s, rin, rout, rout2, rin2);
+  return fft3_raw<T>(c, P<C>(ws, L.fft_tw), L.lev[0].n, inverse, s, rin, rin2);
 }
 
 template <typename T>
@@ -526,16 +600,23 @@ hipError_t fft_poisson(char* ws, MGLayout& L, double h, hipStream_t s) {
   T* acc = P<T>(ws, L.fft_acc);
   hipLaunchKernelGGL((k_fft_twiddles<T>), dim3(nblk(n / 2 > 0 ? n / 2 : 1)), dim3(256), 0, s,
                      P<C>(ws, L.fft_tw), n);
-  hipError_t e = fft3<T>(ws, L, c0, 0, s, P<T>(ws, f.F));
+  const C* tw = P<C>(ws, L.fft_tw);
+  hipError_t e = fft_pass<T, 0, FFT_REAL_IN>(c0, tw, n, 0, s, P<T>(ws, f.F));
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((k_fft_phi<T>), dim3(nblk(N)), dim3(256), 0, s, c0, n, tk);
-  // two inverse transforms for the four real outputs (a_x, a_y | a_z, Phi)
-  hipLaunchKernelGGL((k_fft_grad_pairs<T>), dim3(nblk(N)), dim3(256), 0, s, c0, c1, n, tk);
-  e = fft3<T>(ws, L, c1, 1, s, nullptr, acc, acc + N);
+  e = fft_pass<T, 1, FFT_COMPLEX>(c0, tw, n, 0, s);
   if (e != hipSuccess) return e;
-  e = fft3<T>(ws, L, c0, 1, s, nullptr, acc + 2 * N, P<T>(ws, f.phi[L.cur0]));
-  if (e != hipSuccess) return e;
-  return hipGetLastError();
+  const LinePlan<T> lp(n);
+  hipLaunchKernelGGL((k_fft_solve_z<T>), dim3(lp.grid), dim3(fft_threads<typename CplxOf<T>::type>), lp.lds, s, c0, c1, tw,
+                     lp.logn, lp.loglpb, tk);
+  // the rest of the two inverse transforms: a_x + i a_y and a_z + i Phi
+  for (C* c : {c1, c0}) {
+    e = fft_pass<T, 1, FFT_COMPLEX>(c, tw, n, 1, s);
+    if (e != hipSuccess) return e;
+    e = fft_pass<T, 0, FFT_SPLIT_OUT>(c, tw, n, 1, s, nullptr, nullptr, c == c1 ? acc : acc + 2 * N,
+                                      c == c1 ? acc + N : P<T>(ws, f.phi[L.cur0]));
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 // kick (+ cooling if `cool`), CFL and health check with the acceleration of
@@ -572,7 +653,7 @@ hipError_t fft_gravity_vjp(char* ws, MGLayout& L, double h, double G, const T* U
   hipLaunchKernelGGL((k_fft_twiddles<T>), dim3(nblk(n / 2 > 0 ? n / 2 : 1)), dim3(256), 0, s,
                      P<C>(ws, L.fft_tw), n);
   // x and y in one transform (two real fields as re + i im), then z
-  hipError_t e = fft3<T>(ws, L, c1, 0, s, accb, nullptr, nullptr, accb + N);
+  hipError_t e = fft3<T>(ws, L, c1, 0, s, accb, accb + N);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((k_fft_adj_accum_pair<T>), dim3(nblk(N)), dim3(256), 0, s, c1, c0, n, tk,
                      fourpiG);

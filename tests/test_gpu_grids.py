@@ -333,3 +333,42 @@ def test_cycles_queued_ahead_leave_no_trace(cycles, smoother):
     loose.set_state(U)
     loose.step(1, 1e-3)
     assert loose.mg_cycles() == 0 and np.abs(loose.potential()).max() == 0.0
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("n", [2, 4, 8, 16, 32, 64, 128])
+def test_spectral_gravity_over_sizes(n, dtype):
+    """The spectral solve at every kind of radix and fill of a workgroup: the
+    potential of a random density and the kick of a uniform-pressure state at
+    rest, against numpy's transforms."""
+    s = mh.Solver(mh.grid_desc((n,) * 3, (1.0 / n,) * 3, dtype=dtype),
+                  mh.physics_desc(flags=mh.SRC_GRAVITY, grav_G=2.0, grav_solver=mh.GRAV_FFT))
+    rng = np.random.default_rng(n)
+    U = np.zeros((5, n, n, n))
+    U[0] = 1.0 + 0.5 * rng.random((n, n, n))
+    U[4] = 10.0
+    U = as_input(U, dtype)
+    dt = 1e-7
+    s.set_state(U)
+    s.step(1, dt)
+    m = np.fft.fftfreq(n, 1.0 / n)
+    k = 2.0 * np.pi * m
+    k2 = k[:, None, None] ** 2 + k[None, :, None] ** 2 + k[None, None, :] ** 2
+    k2[0, 0, 0] = 1.0
+    # the step hardly moves the gas (dt): the density solved for is the given one
+    ph = -4.0 * np.pi * 2.0 * np.fft.fftn(U[0] - U[0].mean()) / k2
+    ph[0, 0, 0] = 0.0
+    phi = np.fft.ifftn(ph).real
+    kd = np.where(np.abs(m) == n // 2, 0.0, k)  # no derivative at the Nyquist index
+    acc = [np.fft.ifftn(-1j * kx * ph).real
+           for kx in (kd[None, None, :], kd[None, :, None], kd[:, None, None])]
+    scale = np.abs(phi).max()
+    # rounding of log2(n) passes over 3 axes, twice, and of the density (fp32);
+    # the drift of the state over dt (fp64: waves and kick move it by 1e-6)
+    tol = 2e-6 if dtype == "f64" else 2e-5
+    assert np.abs(s.potential() - phi).max() < tol * scale
+    got = s.get_state().astype(np.float64)
+    amax = max(np.abs(a).max() for a in acc)
+    if dtype == "f64" and n > 2:
+        for c in range(3):
+            assert np.abs(got[1 + c] / (U[0] * dt) - acc[c]).max() < 1e-4 * amax
