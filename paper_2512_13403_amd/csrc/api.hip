@@ -1112,10 +1112,7 @@ static mh_status adjoint_impl(mh_ctx* c, char* ws, AdjLayout& A, const T* Un, do
 
   // private clock at the step being differentiated; the OU amplitudes of the
   // step start from the caller's copy
-  DevClock hc{};
-  hc.step = step;
-  hc.bad_first = ~0ull;
-  MH_HIP(c, hipMemcpyAsync(aclk, &hc, sizeof hc, hipMemcpyHostToDevice, c->stream));
+  MH_HIP(c, launch_clock_init(aclk, step, c->stream));
   PrologueArgs pa{};
   pa.clk = aclk;
   pa.dt_log = reinterpret_cast<double*>(ws + A.dtlog);

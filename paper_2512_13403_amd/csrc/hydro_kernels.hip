@@ -895,6 +895,15 @@ __global__ void k_clock_set(DevClock* clk, double t, long long step) {
   }
 }
 
+__global__ void k_clock_init(DevClock* clk, long long step) {
+  if (threadIdx.x == 0) {
+    DevClock c{};
+    c.step = step;
+    c.bad_first = ~0ull;
+    *clk = c;
+  }
+}
+
 // ------------------------------------------------------------------ launchers
 
 // Planes per workgroup.  A chunk costs its planes plus about 1.2 planes of
@@ -1036,6 +1045,11 @@ hipError_t launch_clock_reset_health(DevClock* clk, hipStream_t s) {
 
 hipError_t launch_clock_set(DevClock* clk, double t, long long step, hipStream_t s) {
   hipLaunchKernelGGL(k_clock_set, dim3(1), dim3(64), 0, s, clk, t, step);
+  return hipGetLastError();
+}
+
+hipError_t launch_clock_init(DevClock* clk, long long step, hipStream_t s) {
+  hipLaunchKernelGGL(k_clock_init, dim3(1), dim3(64), 0, s, clk, step);
   return hipGetLastError();
 }
 

@@ -149,6 +149,8 @@ hipError_t launch_cool_rate(const T* U, const StageGeom& g, T gamma, const CoolT
                             DevClock* clk, hipStream_t s);
 hipError_t launch_clock_reset_health(DevClock* clk, hipStream_t s);
 hipError_t launch_clock_set(DevClock* clk, double t, long long step, hipStream_t s);
+// a new clock at t = 0 before step `step`
+hipError_t launch_clock_init(DevClock* clk, long long step, hipStream_t s);
 hipError_t launch_prologue(const PrologueArgs& a, hipStream_t s, const StepBatch* sb = nullptr,
                            int batch = 1);
 hipError_t launch_sched_reset(DevClock* clk, hipStream_t s);
