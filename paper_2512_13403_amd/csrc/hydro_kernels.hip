@@ -110,27 +110,6 @@ __device__ __forceinline__ void hllc_flux(const T (&wl)[5], const T (&wr)[5], T 
   const T rK = left ? rl : rr, uK = left ? ul : ur, pK = left ? pl : pr;
   const T aK = left ? wl[t1] : wr[t1], bK = left ? wl[t2] : wr[t2];
   const T SK = left ? SL : SR, dK = left ? dl : dr;
-  if (sizeof(T) == 8) {
-    // the same flux from one state behind the face: (r, u, p, E) of the side,
-    // or of its star region, r* = q d, p* = P + d (S* - v), E* = q ((S - v) E -
-    // P v + p* S*), in F = (r u, r u u + p, r u vt, u (E + p)); 13 instructions
-    // less than the difference form below, which fp32 keeps: its sums decide
-    // limiter and side in the reverse pass, where another rounding of the
-    // states flips some of them and moves gradients by 6e-4
-    const T EK = fmad(pK, gm1inv, (T(0.5) * rK) * fmad(uK, uK, fmad(aK, aK, bK * bK)));
-    const bool fan = (left ? -SL : SR) > T(0);
-    const T q = dev_rcp(SK - sstar);
-    const T ps = fmad(dK, sstar - uK, pK);
-    const T Es = q * fmad(ps, sstar, fmad(SK - uK, EK, -(pK * uK)));
-    const T r = fan ? q * dK : rK, u = fan ? sstar : uK, p = fan ? ps : pK, E = fan ? Es : EK;
-    const T m = r * u;
-    F[0] = m;
-    F[vn] = fmad(m, u, p);
-    F[t1] = m * aK;
-    F[t2] = m * bK;
-    F[4] = u * (E + p);
-    return;
-  }
   // total energy of the selected side only (the other side's is never used)
   const T EK = fmad(pK, gm1inv, (T(0.5) * rK) * fmad(uK, uK, fmad(aK, aK, bK * bK)));
   // inside the star fan: S_L < 0 on the left side, S_R > 0 on the right
@@ -340,7 +319,7 @@ __device__ __forceinline__ long long member_offset(const StepBatch& sb) { return
 // registers: the fp64 stages without sources then fit 128 registers and two
 // workgroups share a CU, each covering the other's barriers and loads (256^3
 // periodic minmod, stage 1: 551 -> 481 us).  The last stage does not come down to
-// 128 (741 us read again, 654 from registers), and fp32 holds two workgroups
+// 128 (741 us read again, 652 from registers), and fp32 holds two workgroups
 // anyway (a few per cent slower read again); the limiters with more live values
 // spill at 128.
 template <typename T, int STAGE, int LIM>
@@ -830,14 +809,14 @@ template <typename T, int VEC>
 struct alignas(sizeof(T) * VEC) Cells {
   T v[VEC];
 };
-template <typename T, int VEC, bool COPY>
+template <typename T, int VEC, bool COPY, bool CHOOSE>
 __global__ __launch_bounds__(256) void k_state_speed(const StateBatch<T> sb, long long N, T gm1,
                                                      T gamma, T ihx, T ihy, T ihz,
                                                      const Choice ch) {
   using V = Cells<T, VEC>;
   __shared__ T sRed[4];
   const V* __restrict__ src =
-      moved(reinterpret_cast<const V*>(sb.src[blockIdx.y]), COPY && choose(ch) ? ch.alt : 0ll);
+      moved(reinterpret_cast<const V*>(sb.src[blockIdx.y]), CHOOSE && choose(ch) ? ch.alt : 0ll);
   V* __restrict__ dst = reinterpret_cast<V*>(sb.dst[blockIdx.y]);
   const long long NV = N / VEC;
   T smax = T(0);
@@ -916,7 +895,7 @@ __global__ void k_clock_init(DevClock* clk, long long step) {
 // chunk until 4096 workgroups are there, but not below four planes (stage 1 /
 // stage 2, us): 128 x 16 x 16 fp64 21.6 / 26.2 -> 11.1 / 13.7, 64^3 fp32
 // 14.7 / 18.8 -> 11.0 / 14.7, 256^3 fp32 218 / 278 -> 207 / 260 and fp64
-// 573 / 699 -> 523 / 627 (then; 481 / 654 now); 512^3
+// 573 / 699 -> 523 / 627 (before U was read again); 512^3
 // keeps its 64 planes.
 template <typename T>
 static inline int z_chunk(const StageGeom& g, int batch) {
@@ -1013,13 +992,16 @@ hipError_t launch_state_speed(const StateBatch<T>& sb, int batch, bool copy, con
     wide = wide && (reinterpret_cast<uintptr_t>(sb.src[b]) % 16) == 0 &&
            (reinterpret_cast<uintptr_t>(sb.dst[b]) % 16) == 0;
   const dim3 grid(reduce_blocks(N), (unsigned)batch);
-#define MH_SPEED(V, CP)                                                                       \
-  hipLaunchKernelGGL((k_state_speed<T, V, CP>), grid, dim3(256), 0, s, sb, N, gamma - T(1),   \
+#define MH_SPEED(V, CP, CH)                                                                     \
+  hipLaunchKernelGGL((k_state_speed<T, V, CP, CH>), grid, dim3(256), 0, s, sb, N, gamma - T(1), \
                      gamma, (T)ih[0], (T)ih[1], (T)ih[2], choice)
-  if (wide && copy) MH_SPEED(VEC, true);
-  else if (wide) MH_SPEED(VEC, false);
-  else if (copy) MH_SPEED(1, true);
-  else MH_SPEED(1, false);
+  const bool ch = copy && choice.counters;
+  if (wide && ch) MH_SPEED(VEC, true, true);
+  else if (wide && copy) MH_SPEED(VEC, true, false);
+  else if (wide) MH_SPEED(VEC, false, false);
+  else if (ch) MH_SPEED(1, true, true);
+  else if (copy) MH_SPEED(1, true, false);
+  else MH_SPEED(1, false, false);
 #undef MH_SPEED
   return hipGetLastError();
 }
@@ -1063,7 +1045,7 @@ template hipError_t launch_stage2_finish<double>(bool, StageArgs<double>, const 
                                                  const StageGeom&, hipStream_t);
 #define MH_SPEED_INST(T)                                                                      \
   template hipError_t launch_state_speed<T>(const StateBatch<T>&, int, bool, const StageGeom&, \
-                                            T, const double*, hipStream_t, const Choice&);                   \
+                                            T, const double*, hipStream_t, const Choice&);    \
   template hipError_t launch_speed_from_clock<T>(const DevClock*, const StageGeom&, T*,       \
                                                  hipStream_t);
 MH_SPEED_INST(float)
