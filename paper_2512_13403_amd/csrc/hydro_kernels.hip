@@ -434,6 +434,13 @@ __global__ __launch_bounds__(NTHREADS, (stage_waves<T, STAGE, LIM>)) void k_stag
       add_dflux(a.dflux, N, (long long)bc_map(z0 - 1, a.nz, a.bcz) * plane + col, fzm);
   }
 
+  // In fp32 and long chunks (large grids, whose CUs are full all the time) the
+  // waves that carry the tile's edge faces alternate between rows 0, 1 and rows
+  // 2, 3, which sit on different SIMDs: 512^3 forced and cooled, four steps, 18.0
+  // -> 17.4 ms; where a chunk is a few planes this costs up to 1 %, and fp64 does
+  // not gain.
+  const int swing = sizeof(T) == 4 && a.zc >= 32 ? 2 : 0;
+
   T smax = T(0);
   unsigned long long nbad = 0, first_bad = ~0ull;
 
@@ -503,9 +510,10 @@ __global__ __launch_bounds__(NTHREADS, (stage_waves<T, STAGE, LIM>)) void k_stag
 #pragma unroll
       for (int f = 0; f < 5; ++f) sFy[f][ty + 1][tx] = F[f];
       // the tile's edge faces: the TX y faces at y0 - 1/2 by the wave of row
-      // 0; the TY x faces at x0 - 1/2 and the TY at x0 + TX - 1/2 by lanes of
-      // the wave of row 1, so two waves (not every wave) carry the extra flux
-      if (ty == 0) {
+      // `edge`; the TY x faces at x0 - 1/2 and the TY at x0 + TX - 1/2 by lanes
+      // of the next row's, so two waves (not every wave) carry the extra flux
+      const int edge = (2 * (z - z0)) & swing;
+      if (ty == edge) {
 #pragma unroll
         for (int f = 0; f < 5; ++f) {
           c0[f] = sW[f][0][tx + 2];
@@ -521,7 +529,7 @@ __global__ __launch_bounds__(NTHREADS, (stage_waves<T, STAGE, LIM>)) void k_stag
                     F);
 #pragma unroll
         for (int f = 0; f < 5; ++f) sFy[f][0][tx] = F[f];
-      } else if (ty == 1 && tx < 2 * TY) {
+      } else if (ty == edge + 1 && tx < 2 * TY) {
         // lane r < TY: row r's face at x0 - 1/2 (LDS columns 0..3); lane
         // TY + r: its face at x0 + TX - 1/2 (columns TX..TX+3)
         const int r = tx < TY ? tx : tx - TY, xc = tx < TY ? 0 : TX;
