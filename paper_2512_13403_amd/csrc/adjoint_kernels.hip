@@ -5,8 +5,10 @@
 // transposed form, lam^n = (dU^{n+1}/dU^n)^T lam^{n+1}, source by source in
 // reverse order and then through the two RK stages:
 //   lam1 = lam_a/2 + (dt/2) J(U1)^T lam_a,   lam^n = lam_a/2 + lam1 + dt J(U^n)^T lam1.
-// J(U)^T v for L(U) = -sum_a (F_{a,i+1/2} - F_{a,i-1/2}) / h_a runs in two
-// deterministic passes per axis (no floating-point atomics):
+// J(U)^T v for L(U) = -sum_a (F_{a,i+1/2} - F_{a,i-1/2}) / h_a is deterministic
+// (no floating-point atomics).  The periodic minmod (or first-order) HLLC scheme
+// takes one kernel per axis, k_x_jtv and k_axis_jtv; the general path two passes
+// per axis:
 //   k_face_vjp    one thread per face: Fb = (v_right - v_left)/h, the HLLC
 //                 reverse sweep gives the face-state adjoints W^L_b, W^R_b, and
 //                 the minmod selections of the two slopes the face used;

@@ -11,10 +11,12 @@
 // W-cycle (the paper's default, App. C) solves each coarse error equation
 // with two recursive cycles, the second from the first one's result (one
 // solve where the next level is the coarsest).  Means are removed from every
-// restricted right-hand side and from phi after every cycle (gauge <phi> = 0).
+// restricted right-hand side and from phi after every cycle (gauge <phi> = 0);
+// levels smoothed on tiles leave both means in, which no operator sees, until
+// the tail and the end of the solve.
 // All reductions are two-stage with fixed block counts, so results do not
-// depend on scheduling.  Every kernel here is memory-bound (about 2 field
-// reads and 1 write per cell per sweep).
+// depend on scheduling.  The fine level is bound by memory and barriers (about 2
+// field reads and 1 write per cell per sweep), the small ones by latency.
 #include <cmath>
 #include <type_traits>
 

@@ -34,10 +34,13 @@ def _forcing_on(s: Solver) -> bool:
     return bool(s.phys.flags & SRC_FORCING)
 
 
-def _snapshot(s: Solver, t, step: int) -> Checkpoint:
-    """The solver's state at clock (t, step).  The clock is known from the steps
-    taken: reading it back would wait for the GPU at every step (about 45 us,
-    twice the kernels of a 32^3 step)."""
+def _snapshot(s: Solver, t=None, step=None) -> Checkpoint:
+    """The solver's state at clock (t, step), read from the device when no step is
+    given.  The rollout knows its clock from the steps taken: reading it back
+    would wait for the GPU at every step (about 45 us, twice the kernels of a
+    32^3 step)."""
+    if step is None:
+        t, step = s.clock()
     return Checkpoint(s.get_state_device(), s.ou_state() if _forcing_on(s) else None,
                       s.potential_device() if _gravity_on(s) else None, t, step)
 
