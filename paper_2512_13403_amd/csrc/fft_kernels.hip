@@ -207,8 +207,10 @@ __device__ __forceinline__ void stockham(C* buf, const C* stw, int logn, int E) 
 // FFT_SPLIT_OUT writes the real part to `rout` and the imaginary part to
 // `rout2` (the inverse transform of two Hermitian spectra packed as A + i B
 // gives the two real fields a + i b); FFT_PAIR_IN reads `rin` + i `rin2` (the
-// transform of two real fields at once, separated by Hermitian symmetry).
-enum : int { FFT_COMPLEX = 0, FFT_REAL_IN = 1, FFT_SPLIT_OUT = 2, FFT_PAIR_IN = 3 };
+// transform of two real fields at once, separated by Hermitian symmetry);
+// FFT_SHIFTED_IN reads scale (rin - *mean).
+enum : int { FFT_COMPLEX = 0, FFT_REAL_IN = 1, FFT_SPLIT_OUT = 2, FFT_PAIR_IN = 3,
+             FFT_SHIFTED_IN = 4 };
 template <typename T, int AXIS, int IO>
 __global__ __launch_bounds__(fft_threads<typename CplxOf<T>::type>) void k_fft_lines(typename CplxOf<T>::type* data,
                                                            const T* __restrict__ rin,
@@ -216,7 +218,8 @@ __global__ __launch_bounds__(fft_threads<typename CplxOf<T>::type>) void k_fft_l
                                                            T* __restrict__ rout,
                                                            T* __restrict__ rout2,
                                                            const typename CplxOf<T>::type* tw,
-                                                           int logn, int loglpb, int inverse) {
+                                                           int logn, int loglpb, int inverse,
+                                                           const double* mean, double scale) {
   using C = typename CplxOf<T>::type;
   constexpr int ELEMS = FFT_ELEMS, NT = fft_threads<C>;
   extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -241,6 +244,7 @@ __global__ __launch_bounds__(fft_threads<typename CplxOf<T>::type>) void k_fft_l
     if (e < E) {
       const unsigned idx = line_elem<AXIS>(logn, line0 + line_of(e), point_of(e));
       if (IO == FFT_REAL_IN) v[q] = C{rin[idx], T(0)};
+      else if (IO == FFT_SHIFTED_IN) v[q] = C{(T)(scale * ((double)rin[idx] - *mean)), T(0)};
       else if (IO == FFT_PAIR_IN) v[q] = C{rin[idx], rin2[idx]};
       else v[q] = data[idx];
     }
@@ -532,10 +536,11 @@ struct LinePlan {
 template <typename T, int AXIS, int IO>
 hipError_t fft_pass(typename CplxOf<T>::type* c, const typename CplxOf<T>::type* tw, int n,
                     int inverse, hipStream_t s, const T* rin = nullptr, const T* rin2 = nullptr,
-                    T* rout = nullptr, T* rout2 = nullptr) {
+                    T* rout = nullptr, T* rout2 = nullptr, const double* mean = nullptr,
+                    double scale = 0.0) {
   const LinePlan<T> lp(n);
   hipLaunchKernelGGL((k_fft_lines<T, AXIS, IO>), dim3(lp.grid), dim3(fft_threads<typename CplxOf<T>::type>), lp.lds, s, c,
-                     rin, rin2, rout, rout2, tw, lp.logn, lp.loglpb, inverse);
+                     rin, rin2, rout, rout2, tw, lp.logn, lp.loglpb, inverse, mean, scale);
   return hipGetLastError();
 }
 
@@ -586,10 +591,12 @@ size_t fft_layout(int n, size_t off, size_t es, MGLayout& L) {
   return off;
 }
 
-// From F = 4 pi G (rho - <rho>) on level 0: the potential into
-// lev[0].phi[cur0] and the acceleration into fft_acc
+// From F = 4 pi G (rho - <rho>), on level 0 or, with x, formed as scale (x - *mean)
+// by the first pass: the potential into lev[0].phi[cur0] and the acceleration into
+// fft_acc
 template <typename T>
-hipError_t fft_poisson(char* ws, MGLayout& L, double h, hipStream_t s) {
+hipError_t fft_poisson(char* ws, MGLayout& L, double h, hipStream_t s, const T* x,
+                       const double* mean, double scale) {
   using C = typename CplxOf<T>::type;
   const MGLevel& f = L.lev[0];
   const int n = f.n;
@@ -601,7 +608,11 @@ hipError_t fft_poisson(char* ws, MGLayout& L, double h, hipStream_t s) {
   hipLaunchKernelGGL((k_fft_twiddles<T>), dim3(nblk(n / 2 > 0 ? n / 2 : 1)), dim3(256), 0, s,
                      P<C>(ws, L.fft_tw), n);
   const C* tw = P<C>(ws, L.fft_tw);
-  hipError_t e = fft_pass<T, 0, FFT_REAL_IN>(c0, tw, n, 0, s, P<T>(ws, f.F));
+  const T* const none = nullptr;
+  T* const nowhere = nullptr;
+  hipError_t e = x ? fft_pass<T, 0, FFT_SHIFTED_IN>(c0, tw, n, 0, s, x, none, nowhere, nowhere, mean,
+                                                    scale)
+                   : fft_pass<T, 0, FFT_REAL_IN>(c0, tw, n, 0, s, P<T>(ws, f.F));
   if (e != hipSuccess) return e;
   e = fft_pass<T, 1, FFT_COMPLEX>(c0, tw, n, 0, s);
   if (e != hipSuccess) return e;
@@ -668,7 +679,8 @@ hipError_t fft_gravity_vjp(char* ws, MGLayout& L, double h, double G, const T* U
 }
 
 #define FFT_INSTANTIATE(T)                                                                     \
-  template hipError_t fft_poisson<T>(char*, MGLayout&, double, hipStream_t);                  \
+  template hipError_t fft_poisson<T>(char*, MGLayout&, double, hipStream_t, const T*,         \
+                                     const double*, double);                                  \
   template hipError_t fft_sources<T>(char*, const MGLayout&, const mh_grid_desc&, bool, bool, \
                                      const CoolParams<T>&, T*, DevClock*, hipStream_t);       \
   template hipError_t fft_gravity_vjp<T>(char*, MGLayout&, double, double, const T*, T,       \

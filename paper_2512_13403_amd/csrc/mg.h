@@ -66,7 +66,8 @@ size_t mg_phi_offset(const MGLayout& L);
 bool fft_size_ok(int n);
 size_t fft_layout(int n, size_t off, size_t es, MGLayout& L);
 template <typename T>
-hipError_t fft_poisson(char* ws, MGLayout& L, double h, hipStream_t s);
+hipError_t fft_poisson(char* ws, MGLayout& L, double h, hipStream_t s, const T* x = nullptr,
+                       const double* mean = nullptr, double scale = 0.0);
 template <typename T>
 hipError_t fft_sources(char* ws, const MGLayout& L, const mh_grid_desc& g, bool cool, bool cfl,
                        const CoolParams<T>& cp, T* U, DevClock* clk, hipStream_t s);
