@@ -168,9 +168,9 @@ struct mh_ctx {
   size_t ws_bytes = 0;
   Layout L;
   int nmodes = 0;
-  // where the CFL signal speed of the state is: nowhere, in the clock (left by
-  // the last kernel of a step), or as partial maxima in the workspace
-  enum Speed { SPEED_NONE, SPEED_CLOCK, SPEED_PART } speed = SPEED_NONE;
+  // the state's CFL signal speed is on the device: as partial maxima in the
+  // workspace or, left by the last kernel of a step, in the clock, which says where
+  bool speed_valid = false;
   bool rate_valid = false;  // the clock's cooling rate (tabulated cooling) is the state's
   std::string err;
   // kernel timing (mh_set_timing): event pairs and the kind of each pair
@@ -384,7 +384,8 @@ static hipError_t measure_states(mh_ctx* const* ctxs, int B, const T* const* src
       sb.dst[nb] = c->at<T>(c->L.U);
       sb.src[nb] = src ? src[b0 + nb] : sb.dst[nb];
       sb.part[nb] = c->at<T>(c->L.speed);
-      c->speed = mh_ctx::SPEED_PART;
+      sb.clk[nb] = c->clk();
+      c->speed_valid = true;
     }
     e = launch_state_speed<T>(sb, nb, src != nullptr, geom, (T)g0.gamma, ih, s, choice);
     choice.count = 0;
@@ -407,9 +408,12 @@ extern "C" mh_status mh_set_state(mh_ctx* c, const void* U, int where) {
     return MH_OK;
   }
   const size_t bytes = 5 * (size_t)c->cells() * c->esize();
+  c->speed_valid = false;
   MH_HIP(c, hipMemcpyAsync(c->ws + c->L.U, U, bytes, hipMemcpyHostToDevice, c->stream));
+  MH_HIP(c, c->g.dtype == MH_F64
+                ? measure_states<double>(&c, 1, (const double* const*)nullptr, c->stream)
+                : measure_states<float>(&c, 1, (const float* const*)nullptr, c->stream));
   MH_HIP(c, hipStreamSynchronize(c->stream));
-  c->speed = mh_ctx::SPEED_NONE;
   return MH_OK;
 }
 
@@ -507,12 +511,14 @@ static mh_status step_impl(mh_ctx* c, int32_t nsteps, double dt, double t_stop, 
   pa.dt_sched = dt_sched;
   pa.sched_stride = sched_stride;
   const bool cfl = !(dt > 0.0) && !dt_sched;
+  pa.speed_part = cfl ? c->ws + c->L.speed : nullptr;
+  pa.n_part = (int)reduce_blocks(c->cells());
 
   if (nsteps == 0) MH_HIP(c, launch_clock_reset_health(clk, c->stream));
   for (int s = 0; s < nsteps; ++s) {
-    if (cfl && (c->speed == mh_ctx::SPEED_NONE || (table && ctab.rate && !c->rate_valid))) {
+    if (cfl && (!c->speed_valid || (table && ctab.rate && !c->rate_valid))) {
       const long tk = time_begin(c, MH_TIME_OTHER);
-      if (c->speed == mh_ctx::SPEED_NONE)
+      if (!c->speed_valid)
         MH_HIP(c, measure_states<T>(&c, 1, (const T* const*)nullptr, c->stream));
       if (table && ctab.rate && !c->rate_valid) {
         MH_HIP(c, launch_clock_reset_rate(clk, c->stream));
@@ -520,9 +526,6 @@ static mh_status step_impl(mh_ctx* c, int32_t nsteps, double dt, double t_stop, 
       }
       time_end(c, tk);
     }
-    const bool part = cfl && c->speed == mh_ctx::SPEED_PART;
-    pa.speed_part = part ? c->ws + c->L.speed : nullptr;
-    pa.n_part = part ? (int)reduce_blocks(c->cells()) : 0;
     pa.reset_health = s == 0;
     pa.log_index = s % DTLOG_CAP;
     long tk = time_begin(c, MH_TIME_PROLOGUE);
@@ -610,7 +613,7 @@ static mh_status step_impl(mh_ctx* c, int32_t nsteps, double dt, double t_stop, 
       MH_HIP(c, launch_cool_table<T>(U, geom, (T)g.gamma, ih, ctab, clk, c->stream));
       time_end(c, tk);
     }
-    c->speed = mh_ctx::SPEED_CLOCK;
+    c->speed_valid = true;
     c->rate_valid = true;
     if (dt_out && ((s + 1) % DTLOG_CAP == 0 || s + 1 == nsteps)) {
       const int n0 = (s / DTLOG_CAP) * DTLOG_CAP;
@@ -673,8 +676,7 @@ static bool steps_together(mh_ctx* const* ctxs, int B) {
 
 // One plain step of every context (steps_together), with the new states going
 // to `in` [B][5][N] instead of the workspaces; dts: this step's row of the
-// schedule is chosen on the device, or null for CFL steps (the signal speeds as
-// partial maxima).  STATE_BATCH contexts share a launch: one small cube fills
+// schedule is chosen on the device, or null for CFL steps.  STATE_BATCH contexts share a launch: one small cube fills
 // a part of the GPU, and its step is a chain of four short kernels.  Batched,
 // four forced 64^3 fp32 cubes take their step in 64 us, on parallel branches of
 // a captured graph in 110 to 130 us with the gather of the states.
@@ -695,7 +697,7 @@ static mh_status batched_step(mh_ctx* const* ctxs, int B, T* in, const double* d
       inner.ws[b] = inner.out[b] = last.ws[b] = m->ws - c->ws;
       last.out[b] = (long long)(b * per * sizeof(T));
       inner.seed[b] = last.seed[b] = m->p.ou_seed;
-      m->speed = mh_ctx::SPEED_CLOCK;
+      m->speed_valid = true;
       m->rate_valid = true;
     }
     StageArgs<T> a = base_stage_args<T>(c, c->clk(), c->at<T>(c->L.ou_rows));
@@ -710,7 +712,7 @@ static mh_status batched_step(mh_ctx* const* ctxs, int B, T* in, const double* d
     pa.dt_sched = dts ? dts + b0 : nullptr;
     pa.sched_stride = B;
     pa.speed_part = dts ? nullptr : c->ws + c->L.speed;
-    pa.n_part = dts ? 0 : (int)reduce_blocks(c->cells());
+    pa.n_part = (int)reduce_blocks(c->cells());
     pa.reset_health = 1;
     MH_HIP(c, launch_prologue(pa, s, &inner, nb));
     if (force)
@@ -808,16 +810,7 @@ static mh_status step_corrected_impl(mh_ctx* const* ctxs, int B, mh_corr* corr, 
     mh_ctx* c = ctxs[b];
     MH_HIP(c0, launch_sched_reset(c->clk(), c0->stream));
     if (dts) continue;
-    // every CFL step of the loop (one of them captured) takes its dt from
-    // partial maxima: of a state that no step has produced yet, or the clock's
-    if (c->speed == mh_ctx::SPEED_NONE) {
-      MH_HIP(c, measure_states<T>(&c, 1, (const T* const*)nullptr, c->stream));
-    } else if (c->speed == mh_ctx::SPEED_CLOCK) {
-      const mh_grid_desc& g = c->g;
-      StageGeom geom{g.n[0], g.n[1], g.n[2], {g.bc[0], g.bc[1], g.bc[2]}};
-      MH_HIP(c, launch_speed_from_clock<T>(c->clk(), geom, c->at<T>(c->L.speed), c->stream));
-      c->speed = mh_ctx::SPEED_PART;
-    }
+    if (!c->speed_valid) MH_HIP(c, measure_states<T>(&c, 1, (const T* const*)nullptr, c->stream));
     // (the cooling rate of a state set by the caller is not evaluated here)
     if (c->cool_table() && c->p.cool_ccool > 0.0 && !c->rate_valid)
       MH_HIP(c, launch_clock_reset_rate(c->clk(), c->stream));

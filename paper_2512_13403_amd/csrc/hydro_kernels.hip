@@ -810,7 +810,9 @@ template hipError_t launch_force_rows<double>(const double*, const int*, int, co
 // (set by the caller, or corrected), with the copy into place where there is
 // one: batch member blockIdx.y reads src, writes dst (COPY) and the maximum of
 // each workgroup to part, which the next prologue reduces -- no clock to reset
-// before, no atomics.  Bound by memory; VEC cells of 16 bytes per load where
+// before, no atomics.  That they hold the speed is a word in the clock, not the
+// caller's knowledge: a captured step replayed on states of its own then reads
+// the clock's smax, and after another state was set the partials again.  Bound by memory; VEC cells of 16 bytes per load where
 // the cell count and the addresses allow it.  A copy and a reduction in
 // separate passes took 242 + 146 us at 256^3 fp64.
 template <typename T, int VEC>
@@ -851,17 +853,10 @@ __global__ __launch_bounds__(256) void k_state_speed(const StateBatch<T> sb, lon
   T m = wave_max(smax);
   if ((threadIdx.x & 63) == 0) sRed[threadIdx.x >> 6] = m;
   __syncthreads();
-  if (threadIdx.x == 0)
+  if (threadIdx.x == 0) {
     sb.part[blockIdx.y][blockIdx.x] = fmax(fmax(sRed[0], sRed[1]), fmax(sRed[2], sRed[3]));
-}
-
-// the clock's signal speed as the partials of k_state_speed (a captured step
-// takes its dt from those)
-template <typename T>
-__global__ __launch_bounds__(256) void k_speed_from_clock(const DevClock* clk, int f64, T* part,
-                                                          int n) {
-  const double s = f64 ? bits_to_double_f64(clk->smax) : bits_to_double_f32(clk->smax);
-  for (int i = threadIdx.x; i < n; i += 256) part[i] = (T)s;
+    if (blockIdx.x == 0) sb.clk[blockIdx.y]->speed_part = 1;
+  }
 }
 
 __global__ void k_clock_reset_rate(DevClock* clk) {
@@ -1014,15 +1009,6 @@ hipError_t launch_state_speed(const StateBatch<T>& sb, int batch, bool copy, con
   return hipGetLastError();
 }
 
-template <typename T>
-hipError_t launch_speed_from_clock(const DevClock* clk, const StageGeom& g, T* part,
-                                   hipStream_t s) {
-  const int n = (int)reduce_blocks((long long)g.nx * g.ny * g.nz);
-  hipLaunchKernelGGL((k_speed_from_clock<T>), dim3(1), dim3(256), 0, s, clk,
-                     (int)(sizeof(T) == 8), part, n);
-  return hipGetLastError();
-}
-
 hipError_t launch_clock_reset_rate(DevClock* clk, hipStream_t s) {
   hipLaunchKernelGGL(k_clock_reset_rate, dim3(1), dim3(64), 0, s, clk);
   return hipGetLastError();
@@ -1051,13 +1037,11 @@ template hipError_t launch_stage2_finish<float>(bool, StageArgs<float>, const fl
                                                 const StageGeom&, hipStream_t);
 template hipError_t launch_stage2_finish<double>(bool, StageArgs<double>, const double*,
                                                  const StageGeom&, hipStream_t);
-#define MH_SPEED_INST(T)                                                                      \
-  template hipError_t launch_state_speed<T>(const StateBatch<T>&, int, bool, const StageGeom&, \
-                                            T, const double*, hipStream_t, const Choice&);    \
-  template hipError_t launch_speed_from_clock<T>(const DevClock*, const StageGeom&, T*,       \
-                                                 hipStream_t);
-MH_SPEED_INST(float)
-MH_SPEED_INST(double)
-#undef MH_SPEED_INST
+template hipError_t launch_state_speed<float>(const StateBatch<float>&, int, bool,
+                                              const StageGeom&, float, const double*, hipStream_t,
+                                              const Choice&);
+template hipError_t launch_state_speed<double>(const StateBatch<double>&, int, bool,
+                                               const StageGeom&, double, const double*,
+                                               hipStream_t, const Choice&);
 
 }  // namespace mh

@@ -30,7 +30,8 @@ struct DevClock {
   int32_t mg_cycles;
   int32_t mg_done;          // the gravity solve in flight has converged (or stops)
   int32_t mg_tested;        // cycles of it whose outcome has been tested
-  int32_t pad;
+  int32_t speed_part;       // the state's signal speed is in k_state_speed's partial maxima,
+                            // not in smax (set with them, cleared by the next prologue)
   double mg_fnorm2;         // ||F||^2 of the current gravity solve
   double mg_rnorm2;         // ||r||^2 of the last residual
   double mean;              // scratch: mean of a field

@@ -47,13 +47,15 @@ struct StageArgs {
 };
 
 // states copied, or measured, together: member b reads src[b] and writes
-// dst[b]; part[b] takes reduce_blocks(cells) maxima of the signal speed
+// dst[b]; part[b] takes reduce_blocks(cells) maxima of the signal speed, which
+// clk[b] is told of
 constexpr int STATE_BATCH = 8;
 template <typename T>
 struct StateBatch {
   const T* src[STATE_BATCH];
   T* dst[STATE_BATCH];
   T* part[STATE_BATCH];
+  DevClock* clk[STATE_BATCH];
 };
 
 // A copy's sources lie `alt` bytes further when counters[1] > 0 or counters[0] >
@@ -109,8 +111,8 @@ struct PrologueArgs {
   double t_stop;
   int forcing;
   OUArgs ou;
-  const void* speed_part;  // CFL: the signal speed as n_part partial maxima of
-  int n_part;              // the state precision (k_state_speed), or null: the clock's
+  const void* speed_part;  // CFL: the n_part partial maxima of the signal speed, of the state
+  int n_part;              // precision (k_state_speed), read when the clock's word says so
   int reset_health;        // clear the counts of unphysical cells
   const double* dt_sched;  // device dt schedule, entry clk->sched_pos * sched_stride (or null)
   long long sched_stride;
@@ -134,9 +136,6 @@ template <typename T>
 hipError_t launch_state_speed(const StateBatch<T>& sb, int batch, bool copy, const StageGeom& g,
                               T gamma, const double* ih, hipStream_t s,
                               const Choice& choice = Choice{});
-template <typename T>
-hipError_t launch_speed_from_clock(const DevClock* clk, const StageGeom& g, T* part,
-                                   hipStream_t s);
 hipError_t launch_clock_reset_rate(DevClock* clk, hipStream_t s);
 template <typename T>
 hipError_t launch_cool_table(T* U, const StageGeom& g, T gamma, const double* ih,

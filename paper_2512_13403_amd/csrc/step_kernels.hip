@@ -100,9 +100,10 @@ __global__ __launch_bounds__(PROLOGUE_THREADS) void k_prologue(PrologueArgs a, c
   const OUArgs& o = a.ou;
   const long long step = clk->step;
   const bool update = a.forcing && step % o.every == 0;
+  const bool part = a.speed_part && clk->speed_part;
   if (a.forcing)
     for (int q = t; q < 6 * o.nmodes; q += PROLOGUE_THREADS) s_a[q] = o.ahat[q];
-  if (a.speed_part) {
+  if (part) {
     double m = 0.0;
     for (int i = t; i < a.n_part; i += PROLOGUE_THREADS)
       m = fmax(m, a.f64 ? ((const double*)a.speed_part)[i]
@@ -122,7 +123,7 @@ __global__ __launch_bounds__(PROLOGUE_THREADS) void k_prologue(PrologueArgs a, c
       dt = a.dt_fixed;
     } else {
       double smax = a.f64 ? bits_to_double_f64(clk->smax) : bits_to_double_f32(clk->smax);
-      if (a.speed_part) {
+      if (part) {
         smax = s_speed[0];
         for (int w = 1; w < PROLOGUE_THREADS / 64; ++w) smax = fmax(smax, s_speed[w]);
       }
@@ -177,6 +178,7 @@ __global__ __launch_bounds__(PROLOGUE_THREADS) void k_prologue(PrologueArgs a, c
     clk->step = step + 1;
     clk->smax = 0ull;
     clk->crate = 0ull;
+    clk->speed_part = 0;
     if (a.reset_health) {
       clk->bad_count = 0ull;
       clk->bad_first = ~0ull;
