@@ -403,13 +403,13 @@ void mh_corr_destroy(mh_corr *c);
  *             dts[s B + b]; NULL = CFL steps (each context's dt from its own
  *             corrected state).  The clock, OU forcing and the other sources
  *             advance as in mh_step.
- *   use_graph 1: one corrected step may be captured into a HIP graph and
- *             replayed nsteps times (it is when the contexts differ in more
- *             than the seed of their forcing); synchronises at the end;
+ *   use_graph 1: the library may capture a corrected step into a HIP graph
+ *             and replay it (none is at present: contexts that differ in the
+ *             seed of their forcing alone step in common launches, which are
+ *             faster, others one after another); synchronises at the end;
  *             contexts with gravity are rejected in this mode
  *             (MH_E_UNSUPPORTED: the multigrid convergence test reads the
- *             host).  0: launched kernel by kernel.  Both give bitwise the
- *             same states.
+ *             host).  0: only enqueued.  Both give bitwise the same states.
  *   fallbacks optional host pointer: the number of steps whose correction
  *             fell back to the plain states (synchronises).
  * Errors (message in mh_last_error(ctxs[0])): MH_E_INVALID (null pointers,

@@ -747,30 +747,22 @@ static mh_status batched_step(mh_ctx* const* ctxs, int B, T* in, const double* d
 
 // One corrected step of the B contexts: each context's plain step, the
 // gather of the B states into `in`, the corrector's batched pass into `out`,
-// the scatter back (of `in` where the correction falls back), and (CFL steps) the signal speed of the corrected states
-// for the next step's dt.  The corrector part runs on `main`; with `fork`
-// events (a captured step) the plain steps run on the contexts' own streams
-// as parallel branches (fork[0] ends the previous work on `main`, fork[1 + b]
-// ends context b's step), otherwise on `main` in turn; `together`: in common
-// launches that leave the stepped states in `in` (batched_step).
+// the scatter back (of `in` where the correction falls back), and (CFL steps)
+// the signal speed of the corrected states for the next step's dt, on the
+// contexts' common stream `main`.  The plain steps are enqueued in turn, or,
+// `together`, in common launches that leave the stepped states in `in`
+// (batched_step).
 template <typename T>
 static mh_status corrected_step(mh_ctx* const* ctxs, int B, mh_corr* corr, T* in, T* out,
-                                const double* dts, hipStream_t main, const hipEvent_t* fork,
-                                bool together) {
+                                const double* dts, hipStream_t main, bool together) {
   const size_t bytes = 5 * (size_t)ctxs[0]->cells() * sizeof(T);
   if (together) {
     mh_status st = batched_step<T>(ctxs, B, in, dts, main);
     if (st != MH_OK) return st;
   }
-  if (fork) MH_HIP(ctxs[0], hipEventRecord(fork[0], main));
   for (int b = 0; b < B && !together; ++b) {
-    if (fork) MH_HIP(ctxs[b], hipStreamWaitEvent(ctxs[b]->stream, fork[0], 0));
     mh_status st = step_impl<T>(ctxs[b], 1, 0.0, INFINITY, nullptr, dts ? dts + b : nullptr, B);
     if (st != MH_OK) return st;
-    if (fork) {
-      MH_HIP(ctxs[b], hipEventRecord(fork[1 + b], ctxs[b]->stream));
-      MH_HIP(ctxs[0], hipStreamWaitEvent(main, fork[1 + b], 0));
-    }
   }
   std::vector<void*> gathered(B);
   std::vector<void*> states(B);
@@ -800,7 +792,7 @@ static mh_status corrected_step(mh_ctx* const* ctxs, int B, mh_corr* corr, T* in
 
 template <typename T>
 static mh_status step_corrected_impl(mh_ctx* const* ctxs, int B, mh_corr* corr, void* stage,
-                                     int nsteps, const double* dts, bool graph) {
+                                     int nsteps, const double* dts, bool wait) {
   mh_ctx* c0 = ctxs[0];
   const size_t per = 5 * (size_t)c0->cells() * (size_t)B;
   T* in = (T*)stage;
@@ -816,71 +808,19 @@ static mh_status step_corrected_impl(mh_ctx* const* ctxs, int B, mh_corr* corr, 
       MH_HIP(c, launch_clock_reset_rate(c->clk(), c->stream));
     c->rate_valid = true;
   }
-  // Contexts that step in common launches need no graph: a corrected step is
-  // then about a dozen launches, enqueued faster than they run, while capturing
-  // and instantiating one costs 0.9 ms a call (eight corrected steps of four
-  // forced 64^3 fp32 cubes: 2.93 ms in common launches, 4.42 captured).  Others
-  // are captured, with a branch per context so that their small kernels overlap,
-  // but not more than eight of them: a run with nine branches once ended in a
-  // segmentation fault of a runtime thread, whose cause is not known.
+  // No graph either way: a corrected step of contexts that step in common
+  // launches is about a dozen launches, enqueued faster than they run, while
+  // capturing and instantiating one costs 0.9 ms a call (eight corrected steps of
+  // four forced 64^3 fp32 cubes: 2.93 ms in common launches, 4.42 captured).
+  // Contexts that differ step one after the other: captured with a branch each,
+  // a run of nine once ended in a segmentation fault of a runtime thread whose
+  // cause is not known, and fewer branches took the same code.
   const bool together = steps_together(ctxs, B);
-  if (!graph || nsteps == 0 || together || B > STATE_BATCH) {
-    for (int s = 0; s < nsteps; ++s) {
-      mh_status st = corrected_step<T>(ctxs, B, corr, in, out, dts, c0->stream, nullptr, together);
-      if (st != MH_OK) return st;
-    }
-    if (graph) MH_HIP(c0, hipStreamSynchronize(c0->stream));
-    return MH_OK;
+  for (int s = 0; s < nsteps; ++s) {
+    mh_status st = corrected_step<T>(ctxs, B, corr, in, out, dts, c0->stream, together);
+    if (st != MH_OK) return st;
   }
-  // One corrected step captured into a graph (kernel nodes only) and replayed
-  // on the contexts' stream.  The capture records on streams of its own (the
-  // contexts' stream may be the null stream, which cannot capture): the B
-  // plain steps on B branch streams, joined before the corrector, so that the
-  // graph runs them concurrently (one 64^3 step fills a small part of the
-  // GPU).  Nothing runs during the capture.
-  const hipStream_t user = c0->stream;
-  std::vector<hipStream_t> bs(B + 1, nullptr);
-  std::vector<hipEvent_t> ev(B + 1, nullptr);
-  hipError_t ec = hipSuccess;
-  for (int b = 0; b <= B && ec == hipSuccess; ++b) {
-    ec = hipStreamCreateWithFlags(&bs[b], hipStreamNonBlocking);
-    if (ec == hipSuccess) ec = hipEventCreateWithFlags(&ev[b], hipEventDisableTiming);
-  }
-  std::vector<int> timing(B);
-  for (int b = 0; b < B; ++b) {
-    timing[b] = ctxs[b]->timing;
-    ctxs[b]->timing = false;
-    ctxs[b]->stream = bs[1 + b];
-  }
-  hipGraph_t gr = nullptr;
-  hipGraphExec_t ex = nullptr;
-  mh_status st = MH_OK;
-  if (ec == hipSuccess) ec = hipStreamBeginCapture(bs[0], hipStreamCaptureModeThreadLocal);
-  if (ec == hipSuccess) {
-    st = corrected_step<T>(ctxs, B, corr, in, out, dts, bs[0], ev.data(), false);
-    ec = hipStreamEndCapture(bs[0], &gr);
-  }
-  for (int b = 0; b < B; ++b) {
-    ctxs[b]->timing = timing[b];
-    ctxs[b]->stream = user;
-  }
-  for (int b = 0; b <= B; ++b) {
-    if (ev[b]) (void)hipEventDestroy(ev[b]);
-    if (bs[b]) (void)hipStreamDestroy(bs[b]);
-  }
-  if (st != MH_OK) {
-    if (gr) (void)hipGraphDestroy(gr);
-    return st;
-  }
-  MH_HIP(c0, ec);
-  hipError_t e = hipGraphInstantiate(&ex, gr, nullptr, nullptr, 0);
-  for (int s = 0; e == hipSuccess && s < nsteps; ++s) e = hipGraphLaunch(ex, c0->stream);
-  // the executable graph is released once its launches have run
-  const hipError_t es = hipStreamSynchronize(c0->stream);
-  if (ex) (void)hipGraphExecDestroy(ex);
-  (void)hipGraphDestroy(gr);
-  MH_HIP(c0, e);
-  MH_HIP(c0, es);
+  if (wait) MH_HIP(c0, hipStreamSynchronize(c0->stream));
   return MH_OK;
 }
 

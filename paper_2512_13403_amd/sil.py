@@ -229,9 +229,8 @@ def evaluate(trajs, nc: int, res: TrainResult, nsteps: int | None = None) -> dic
     """Plain and corrected coarse rollouts from T_0 of each held-out trajectory
     against its fine run.  The trajectories advance together, one coarse solver
     each; the corrected rollout is one call of the library's corrected step
-    (mh_step_corrected: the plain steps and one batched corrector pass per
-    step, replayed from a captured HIP graph, the step sizes from a device
-    schedule).  Cost = wall clock of the batched rollout (after one untimed
+    (mh_step_corrected: the plain steps in common launches and one batched
+    corrector pass per step, the step sizes from a device schedule).  Cost = wall clock of the batched rollout (after one untimed
     step of each kind); the fine cost is the summed wall clock of the same
     trajectories' fine groups."""
     import torch
@@ -268,8 +267,8 @@ def evaluate(trajs, nc: int, res: TrainResult, nsteps: int | None = None) -> dic
     out = {}
     for mode in ("plain", "corrected"):
         corrected = mode == "corrected"
-        # one untimed step first (code objects loaded, the capture path run
-        # once), then the timed rollout from the start
+        # one untimed step first (code objects loaded), then the timed rollout
+        # from the start
         reset()
         if corrected:
             step_corrected(solvers, corr, 1, dts[0:1].contiguous(), use_graph=True, stage=stage)

@@ -58,3 +58,63 @@ def test_captured_cfl_step_replays_like_plain_steps(dtype, flags, where):
         got, want = s.get_state_device(), plain.get_state_device()
         torch.cuda.synchronize()
         assert torch.equal(got, want), k
+
+
+def corrected_case(B, dtype, kinds, scale, flags=0, **phys):
+    """B solvers at 16^3 (twice, alike pairwise), their states and a corrector;
+    kinds: grid options by member."""
+    import torch
+
+    n = 16
+    td = torch.float64 if dtype == "f64" else torch.float32
+    mk = lambda: [mh.Solver(mh.grid_desc((n,) * 3, (1.0 / n,) * 3, dtype=dtype, **kinds(b)),
+                            mh.physics_desc(flags=flags, ou_seed=3 * b, **phys)) for b in range(B)]
+    U = torch.tensor(np.stack([wl.smooth_random_state((n,) * 3, seed=60 + b) for b in range(B)]),
+                     dtype=td, device="cuda:0")
+    mean = [float(v) for v in U.mean(dim=(0, 2, 3, 4))]
+    std = [float(v) + 1e-3 for v in U.std(dim=(0, 2, 3, 4))]
+    corr = mh.Corrector(mh.corr_desc(n, B, dtype, 5.0 / 3.0, mean, std, (scale,) * 5))
+    corr.set_params(wl.corrector_init_params(seed=12, out_scale=1.0).astype(np.float32))
+    a, b = mk(), mk()
+    for s, t, u in zip(a, b, U):
+        s.set_state(u)
+        t.set_state(u)
+    return a, b, corr
+
+
+def host_driven(solvers, corr, steps, dts):
+    """The corrected steps driven from the host: the reference of mh_step_corrected."""
+    import torch
+
+    for k in range(steps):
+        for q, t in enumerate(solvers):
+            t.step(1, 0.0 if dts is None else float(dts[k, q]))
+        out, _, _ = corr.apply(torch.stack([t.get_state_device() for t in solvers]))
+        for t, u in zip(solvers, out):
+            t.set_state(u)
+
+
+def schedule(steps, B):
+    import torch
+
+    return torch.tensor(1e-3 * (1.0 + np.arange(steps * B).reshape(steps, B) % 4),
+                        dtype=torch.float64, device="cuda:0")
+
+
+@pytest.mark.parametrize("B", [2, 8])
+@pytest.mark.parametrize("cfl", [False, True])
+def test_unlike_contexts_step_without_a_graph(B, cfl):
+    """Contexts that differ in more than the forcing's seed, with use_graph set:
+    bitwise the host-driven loop, clocks too, in two calls."""
+    import torch
+
+    steps = 3
+    a, b, corr = corrected_case(B, "f32", lambda q: dict(cfl=0.2 + 0.02 * q,
+                                                         limiter=q % 2), 1e-3, mh.SRC_FORCING)
+    dts = None if cfl else schedule(steps, B)
+    for _ in range(2):
+        mh.step_corrected(a, corr, steps, dts, use_graph=True)
+        host_driven(b, corr, steps, dts)
+        for s, t in zip(a, b):
+            assert torch.equal(s.get_state_device(), t.get_state_device())
+            assert s.clock() == t.clock()
