@@ -747,14 +747,15 @@ static mh_status batched_step(mh_ctx* const* ctxs, int B, T* in, const double* d
 
 // One corrected step of the B contexts: each context's plain step, the
 // gather of the B states into `in`, the corrector's batched pass into `out`,
-// the scatter back (of `in` where the correction falls back), and (CFL steps)
+// the scatter back (of `in` where the correction falls back), and (`measure`)
 // the signal speed of the corrected states for the next step's dt, on the
 // contexts' common stream `main`.  The plain steps are enqueued in turn, or,
 // `together`, in common launches that leave the stepped states in `in`
 // (batched_step).
 template <typename T>
 static mh_status corrected_step(mh_ctx* const* ctxs, int B, mh_corr* corr, T* in, T* out,
-                                const double* dts, hipStream_t main, bool together) {
+                                const double* dts, hipStream_t main, bool together,
+                                bool measure) {
   const size_t bytes = 5 * (size_t)ctxs[0]->cells() * sizeof(T);
   if (together) {
     mh_status st = batched_step<T>(ctxs, B, in, dts, main);
@@ -776,12 +777,11 @@ static mh_status corrected_step(mh_ctx* const* ctxs, int B, mh_corr* corr, T* in
     MH_HIP(ctxs[0], launch_copies(states.data(), gathered.data(), B, bytes, main));
   Choice plain{};
   MH_HIP(ctxs[0], corr_apply_enqueue(corr, in, out, main, &plain));
-  if (dts) {
+  if (!measure) {
     MH_HIP(ctxs[0], launch_copies((const void* const*)corrected.data(), states.data(), B, bytes,
                                   main, plain));
   } else {
-    // the scatter measures the corrected states' signal speeds; a cooling rate
-    // of the uncorrected state limits nothing
+    // a cooling rate of the uncorrected state limits nothing
     MH_HIP(ctxs[0], measure_states<T>(ctxs, B, corrected.data(), main, plain));
     for (int b = 0; b < B; ++b)
       if (ctxs[b]->cool_table() && ctxs[b]->p.cool_ccool > 0.0)
@@ -817,7 +817,10 @@ static mh_status step_corrected_impl(mh_ctx* const* ctxs, int B, mh_corr* corr, 
   // cause is not known, and fewer branches took the same code.
   const bool together = steps_together(ctxs, B);
   for (int s = 0; s < nsteps; ++s) {
-    mh_status st = corrected_step<T>(ctxs, B, corr, in, out, dts, c0->stream, together);
+    // every CFL step takes its dt from the corrected states' signal speeds, and so
+    // does a CFL step after the last scheduled one
+    mh_status st = corrected_step<T>(ctxs, B, corr, in, out, dts, c0->stream, together,
+                                     !dts || s + 1 == nsteps);
     if (st != MH_OK) return st;
   }
   if (wait) MH_HIP(c0, hipStreamSynchronize(c0->stream));

@@ -73,7 +73,8 @@ def corrected_case(B, dtype, kinds, scale, flags=0, **phys):
                      dtype=td, device="cuda:0")
     mean = [float(v) for v in U.mean(dim=(0, 2, 3, 4))]
     std = [float(v) + 1e-3 for v in U.std(dim=(0, 2, 3, 4))]
-    corr = mh.Corrector(mh.corr_desc(n, B, dtype, 5.0 / 3.0, mean, std, (scale,) * 5))
+    corr = mh.Corrector(mh.corr_desc(n, B, dtype, 5.0 / 3.0, mean, std, (scale,) * 5,
+                                     fallback_frac=1.0))
     corr.set_params(wl.corrector_init_params(seed=12, out_scale=1.0).astype(np.float32))
     a, b = mk(), mk()
     for s, t, u in zip(a, b, U):
@@ -118,3 +119,30 @@ def test_unlike_contexts_step_without_a_graph(B, cfl):
         for s, t in zip(a, b):
             assert torch.equal(s.get_state_device(), t.get_state_device())
             assert s.clock() == t.clock()
+
+
+@pytest.mark.parametrize("alike", [True, False])
+@pytest.mark.parametrize("after", ["step", "corrected"])
+def test_cfl_step_after_scheduled_corrected_steps(alike, after):
+    """The CFL step that follows corrected steps on a schedule is the one of the
+    corrected states, whose signal speed a strong correction moves away from
+    the stepped states'."""
+    import torch
+
+    B, steps = 3, 2
+    a, b, corr = corrected_case(B, "f64", lambda q: dict(cfl=0.2 + (not alike) * 0.05 * q), 0.1,
+                                mh.SRC_FORCING)
+    dts = schedule(steps, B)
+    fell = mh.step_corrected(a, corr, steps, dts, count_fallbacks=True)
+    host_driven(b, corr, steps, dts)
+    assert fell == 0
+    if after == "step":
+        got = [float(s.step(1, record=True)[0]) for s in a]
+        want = [float(t.step(1, record=True)[0]) for t in b]
+        assert got == want
+    else:
+        mh.step_corrected(a, corr, 1)
+        host_driven(b, corr, 1, None)
+    for s, t in zip(a, b):
+        assert s.clock() == t.clock()
+        assert torch.equal(s.get_state_device(), t.get_state_device())
