@@ -698,7 +698,6 @@ static mh_status batched_step(mh_ctx* const* ctxs, int B, T* in, const double* d
       last.out[b] = (long long)(b * per * sizeof(T));
       inner.seed[b] = last.seed[b] = m->p.ou_seed;
       m->speed_valid = true;
-      m->rate_valid = true;
     }
     StageArgs<T> a = base_stage_args<T>(c, c->clk(), c->at<T>(c->L.ou_rows));
     PrologueArgs pa{};
@@ -781,12 +780,11 @@ static mh_status corrected_step(mh_ctx* const* ctxs, int B, mh_corr* corr, T* in
     MH_HIP(ctxs[0], launch_copies((const void* const*)corrected.data(), states.data(), B, bytes,
                                   main, plain));
   } else {
-    // a cooling rate of the uncorrected state limits nothing
     MH_HIP(ctxs[0], measure_states<T>(ctxs, B, corrected.data(), main, plain));
-    for (int b = 0; b < B; ++b)
-      if (ctxs[b]->cool_table() && ctxs[b]->p.cool_ccool > 0.0)
-        MH_HIP(ctxs[b], launch_clock_reset_rate(ctxs[b]->clk(), main));
   }
+  // the clock's cooling rate is the uncorrected state's: the next CFL step
+  // evaluates it anew
+  for (int b = 0; b < B; ++b) ctxs[b]->rate_valid = false;
   return MH_OK;
 }
 
@@ -803,10 +801,6 @@ static mh_status step_corrected_impl(mh_ctx* const* ctxs, int B, mh_corr* corr, 
     MH_HIP(c0, launch_sched_reset(c->clk(), c0->stream));
     if (dts) continue;
     if (!c->speed_valid) MH_HIP(c, measure_states<T>(&c, 1, (const T* const*)nullptr, c->stream));
-    // (the cooling rate of a state set by the caller is not evaluated here)
-    if (c->cool_table() && c->p.cool_ccool > 0.0 && !c->rate_valid)
-      MH_HIP(c, launch_clock_reset_rate(c->clk(), c->stream));
-    c->rate_valid = true;
   }
   // No graph either way: a corrected step of contexts that step in common
   // launches is about a dozen launches, enqueued faster than they run, while

@@ -146,3 +146,29 @@ def test_cfl_step_after_scheduled_corrected_steps(alike, after):
     for s, t in zip(a, b):
         assert s.clock() == t.clock()
         assert torch.equal(s.get_state_device(), t.get_state_device())
+
+
+@pytest.mark.parametrize("cfl", [False, True])
+def test_cooling_limit_of_corrected_states(cfl):
+    """Tabulated cooling with a cooling-time limit: the corrected CFL steps, and
+    the plain one after corrected steps of either kind, are limited by the
+    rate of the state they start from."""
+    import torch
+
+    B, steps = 2, 3
+    table = dict(cool_model=mh.COOL_TABLE, cool_table=wl.synthetic_cie_table(),
+                 **wl.COOLING_TABLE_MODEL)
+    a, b, corr = corrected_case(B, "f64", lambda q: {}, 0.02, mh.SRC_COOLING, cool_ccool=1e-3,
+                                **table)
+    free = mh.Solver(a[0].grid, mh.physics_desc(flags=mh.SRC_COOLING, **table))
+    free.set_state(a[0].get_state_device())
+    dts = None if cfl else schedule(steps, B)
+    mh.step_corrected(a, corr, steps, dts)
+    host_driven(b, corr, steps, dts)
+    for s, t in zip(a, b):
+        assert s.clock() == t.clock()
+        assert torch.equal(s.get_state_device(), t.get_state_device())
+    got = [float(s.step(1, record=True)[0]) for s in a]
+    assert got == [float(t.step(1, record=True)[0]) for t in b]
+    # (the limit is the cooling time's, not the signal speed's)
+    assert got[0] < 0.5 * float(free.step(1, record=True)[0])
