@@ -54,6 +54,31 @@ __device__ __forceinline__ void prim_at(const T* __restrict__ U, long long N, lo
   to_prim(u, gm1, w);
 }
 
+// a difference that is not contracted with the product behind an operand
+template <typename T>
+__device__ __forceinline__ T plain_diff(T a, T b) {
+#pragma clang fp contract(off)
+  return a - b;
+}
+
+// Differences of W for the limiter branches of the face-wise kernels and of the x
+// rows.  The stage kernels subtract rounded values of W, so where velocity or
+// pressure does not change, the slope is exactly zero and the step took no branch,
+// while a difference contracted with the product behind W, fma(m, 1/rho, -W_c),
+// leaves the rounding error of that product, of either sign: both sides of a cell
+// then take a branch, and not the same one.  fp64 subtracts rounded values, as the
+// step does.  fp32 keeps the contracted differences, which decide the near-ties
+// of a varying field as exact arithmetic does more often (gradient of a turbulent
+// 256^3 step against 64 bits: 7.6e-4 off, 7.8e-4 with rounded differences), but
+// takes no branch where W is flat: equal, as rounded, over three cells in a row of
+// which two make one of the slope's differences.  (A single pair of equal
+// neighbours in a varying fp32 field is a coincidence of rounding, about one in
+// 1e5, and decided like the near-ties.)
+__device__ __forceinline__ float branch_diff(float a, float b) { return a - b; }
+__device__ __forceinline__ double branch_diff(double a, double b) { return plain_diff(a, b); }
+template <typename T>
+constexpr bool contracted_branches = sizeof(T) == 4;
+
 // Reverse of the one-sided HLLC assembly of the stage kernel, for face states
 // wl, wr = (rho, v_n, v_t1, v_t2, P) in the face frame.  Fb = dL/dF; writes
 // dL/dwl and dL/dwr.  The forward quantities are recomputed with the stage
@@ -388,6 +413,37 @@ __device__ __forceinline__ void other_dims(const AxisGeom& g, int& d1, int& d2) 
   d2 = AX == 2 ? g.n[1] : g.n[2];
 }
 
+// which slopes of the face's left (k = 0) and right cell are flat (see
+// branch_diff), from W of its four stencil cells, cell i the left one; the cells
+// beyond them are read where one difference alone is zero
+template <typename T, int AX>
+__device__ __forceinline__ void flat_slopes(const T* __restrict__ U, long long N, const AxisGeom& g,
+                                            int i, int o1, int o2, T gm1, const int (&perm)[5],
+                                            const T (&w)[4][5], bool (&flat)[2][5]) {
+  bool below = false, above = false;
+#pragma unroll
+  for (int s = 0; s < 5; ++s) {
+    const bool z0 = w[0][s] == w[1][s], z1 = w[1][s] == w[2][s], z2 = w[2][s] == w[3][s];
+    flat[0][s] = flat[1][s] = z1 && (z0 || z2);
+    below = below || (z0 && !z1);
+    above = above || (z2 && !z1);
+  }
+  if (below) {
+    T t[5];
+    prim_at(U, N, cell_of<AX>(g, bc_map(i - 2, g.n[AX], g.bc), o1, o2), gm1, t);
+#pragma unroll
+    for (int s = 0; s < 5; ++s)
+      flat[0][s] = flat[0][s] || (w[0][s] == w[1][s] && t[perm[s]] == w[0][s]);
+  }
+  if (above) {
+    T t[5];
+    prim_at(U, N, cell_of<AX>(g, bc_map(i + 3, g.n[AX], g.bc), o1, o2), gm1, t);
+#pragma unroll
+    for (int s = 0; s < 5; ++s)
+      flat[1][s] = flat[1][s] || (w[2][s] == w[3][s] && t[perm[s]] == w[3][s]);
+  }
+}
+
 template <typename T, int LIM, int AX>
 __global__ __launch_bounds__(256) void k_face_vjp(const T* __restrict__ U, const T* __restrict__ v,
                                                   AxisGeom g, T gamma, T ih, T* __restrict__ wbar,
@@ -415,12 +471,15 @@ __global__ __launch_bounds__(256) void k_face_vjp(const T* __restrict__ U, const
   }
   T wl[5], wr[5];
   int fl = 0;
+  bool flat[2][5] = {};
+  if (contracted_branches<T> && LIM != LIM_NONE)
+    flat_slopes<T, AX>(U, N, g, i, o1, o2, gm1, perm, w, flat);
 #pragma unroll
   for (int s = 0; s < 5; ++s) {
-    const T a0 = w[2][s] - w[1][s], b0 = w[1][s] - w[0][s];
-    const T a1 = w[3][s] - w[2][s], b1 = w[2][s] - w[1][s];
-    const int s0 = LIM == LIM_NONE ? 0 : minmod_sel(a0, b0);
-    const int s1 = LIM == LIM_NONE ? 0 : minmod_sel(a1, b1);
+    const T a0 = branch_diff(w[2][s], w[1][s]), b0 = branch_diff(w[1][s], w[0][s]);
+    const T a1 = branch_diff(w[3][s], w[2][s]), b1 = branch_diff(w[2][s], w[1][s]);
+    const int s0 = LIM == LIM_NONE || flat[0][s] ? 0 : minmod_sel(a0, b0);
+    const int s1 = LIM == LIM_NONE || flat[1][s] ? 0 : minmod_sel(a1, b1);
     wl[s] = w[1][s] + T(0.5) * sel_value(s0, a0, b0);
     wr[s] = w[2][s] - T(0.5) * sel_value(s1, a1, b1);
     fl |= (s0 << (2 * s)) | (s1 << (10 + 2 * s));
@@ -484,10 +543,15 @@ __global__ __launch_bounds__(256) void k_face_vjp_rt(const T* __restrict__ U,
     for (int s = 0; s < 5; ++s) w[k][s] = wc[perm[s]];
   }
   T wl[5], wr[5], pa0[5], pb0[5], pa1[5], pb1[5];
+  bool flat[2][5] = {};
+  if (contracted_branches<T> && lim != LIM_NONE)
+    flat_slopes<T, AX>(U, N, g, i, o1, o2, gm1, perm, w, flat);
 #pragma unroll
   for (int s = 0; s < 5; ++s) {
-    const T d0 = slope_partials(lim, w[2][s] - w[1][s], w[1][s] - w[0][s], pa0[s], pb0[s]);
-    const T d1 = slope_partials(lim, w[3][s] - w[2][s], w[2][s] - w[1][s], pa1[s], pb1[s]);
+    const T d0 = slope_partials(flat[0][s] ? LIM_NONE : lim, branch_diff(w[2][s], w[1][s]),
+                                branch_diff(w[1][s], w[0][s]), pa0[s], pb0[s]);
+    const T d1 = slope_partials(flat[1][s] ? LIM_NONE : lim, branch_diff(w[3][s], w[2][s]),
+                                branch_diff(w[2][s], w[1][s]), pa1[s], pb1[s]);
     wl[s] = w[1][s] + T(0.5) * d0;
     wr[s] = w[2][s] - T(0.5) * d1;
   }
@@ -687,13 +751,6 @@ __global__ __launch_bounds__(256) void k_cell_gather(const T* __restrict__ wbar,
   }
 }
 
-// a difference that is not contracted with the product behind an operand
-template <typename T>
-__device__ __forceinline__ T plain_diff(T a, T b) {
-#pragma clang fp contract(off)
-  return a - b;
-}
-
 // Minmod as a value and the branch it took: fwd (the forward difference a) or
 // bwd (the backward difference b), neither where they disagree in sign -- the
 // selections of minmod_sel.
@@ -869,11 +926,12 @@ __global__ __launch_bounds__(256) void k_axis_jtv(const T* __restrict__ U, const
 // contributions pass between neighbours through LDS, and each is computed
 // once, where a lane per face of 61-cell pieces converted every cell four
 // times.
-// The differences are formed with one rounding from the neighbour's factors
-// (velocity m / rho, pressure (g - 1) e), W_{c+1} - W_c = fma(m, 1/rho, -W_c).
-// A cell's backward difference rounds W_{c-1}'s product for the face above it
-// and its own for the face below it, so at a tie the two faces may take
-// different branches; each face's own branch is reversed.
+// The differences are branch_diff's: in fp32 formed with one rounding from the
+// neighbour's factors (velocity m / rho, pressure (g - 1) e), W_{c+1} - W_c =
+// fma(m, 1/rho, -W_c).  A cell's backward difference then rounds W_{c-1}'s
+// product for the face above it and its own for the face below it, so at a
+// near-tie the two faces may take different branches; each face's own branch is
+// reversed.
 constexpr int XROW_MAX = 512;
 constexpr int XLDS = 16;  // values per thread in LDS
 
@@ -884,7 +942,7 @@ __global__ __launch_bounds__(XROW_MAX) void k_x_jtv(const T* __restrict__ U,
                                                     T* __restrict__ Wacc, FinishArgs<T> fa) {
   extern __shared__ __align__(16) unsigned char x_jtv_lds[];
   const int nt = blockDim.x;
-  T* const A = reinterpret_cast<T*>(x_jtv_lds);  // [6][nt]: rho, m, 1/rho, e; then WRb
+  T* const A = reinterpret_cast<T*>(x_jtv_lds);  // [6][nt]: rho, m, 1/rho, e (fp64: W); then WRb
   T* const B = A + 6 * nt;                       // [5][nt]: v; then the forward contribution
   T* const C = B + 5 * nt;                       // [5][nt]: lower-face slope; then the backward one
   const int n = g.n[0], tid = threadIdx.x;
@@ -922,35 +980,80 @@ __global__ __launch_bounds__(XROW_MAX) void k_x_jtv(const T* __restrict__ U,
     to_prim(u, gm1, w);  // the arithmetic of the stage kernels
     ir = dev_rcp(u[0]);
     u[4] = fmad(-(T(0.5) * u[0]), fmad(w[1], w[1], fmad(w[2], w[2], w[3] * w[3])), u[4]);
-    A[tid] = u[0];
-    A[5 * nt + tid] = u[4];
-    A[4 * nt + tid] = ir;
+    if constexpr (contracted_branches<T>) {
+      A[tid] = u[0];
+      A[5 * nt + tid] = u[4];
+      A[4 * nt + tid] = ir;
 #pragma unroll
-    for (int f = 1; f < 4; ++f) A[f * nt + tid] = u[f];
+      for (int f = 1; f < 4; ++f) A[f * nt + tid] = u[f];
+    } else {
+#pragma unroll
+      for (int f = 0; f < 5; ++f) A[f * nt + tid] = w[f];
+    }
 #pragma unroll
     for (int f = 0; f < 5; ++f) B[f * nt + tid] = vc[f];
   }
   __syncthreads();
   if (active) {
-    const T irp = A[4 * nt + tp], irm = A[4 * nt + tm];
+    if constexpr (contracted_branches<T>) {
+      const T irp = A[4 * nt + tp], irm = A[4 * nt + tm];
+      T a[5], b[5], bl[5];  // forward, and backward as the upper and the lower face take it
+      bool zp[5], zm[5], flat[5], above = false, below = false;
 #pragma unroll
-    for (int f = 0; f < 5; ++f) {
-      const int k = f == 4 ? 5 : f;
-      const T up = A[k * nt + tp], um = A[k * nt + tm];
-      T a, b, bl;  // forward, and backward as the upper and the lower face take it
-      if (f == 0) {
-        wp[f] = up;
-        a = up - w[f];
-        b = bl = w[f] - um;
-      } else {
-        const T sp = f == 4 ? gm1 : irp, s0 = f == 4 ? gm1 : ir, sm = f == 4 ? gm1 : irm;
-        wp[f] = up * sp;
-        a = fmad(up, sp, -w[f]);
-        b = fmad(-um, sm, w[f]);
-        bl = fmad(u[f], s0, -(um * sm));
+      for (int f = 0; f < 5; ++f) {
+        const int k = f == 4 ? 5 : f;
+        const T up = A[k * nt + tp], um = A[k * nt + tm];
+        T wm;
+        if (f == 0) {
+          wp[f] = up;
+          wm = um;
+          a[f] = up - w[f];
+          b[f] = bl[f] = w[f] - um;
+        } else {
+          const T sp = f == 4 ? gm1 : irp, s0 = f == 4 ? gm1 : ir, sm = f == 4 ? gm1 : irm;
+          wp[f] = up * sp;
+          wm = um * sm;
+          a[f] = fmad(up, sp, -w[f]);
+          b[f] = fmad(-um, sm, w[f]);
+          bl[f] = fmad(u[f], s0, -wm);
+        }
+        zp[f] = wp[f] == w[f];
+        zm[f] = w[f] == wm;
+        flat[f] = zp[f] && zm[f];
+        above = above || (zp[f] && !zm[f]);
+        below = below || (zm[f] && !zp[f]);
       }
-      dw[f] = slope_branch<T, LIM>(a, b, fwd[f], bwd[f]);
-      C[f * nt + tid] = slope_branch<T, LIM>(a, bl, fwl[f], bwl[f]);
+      if (LIM != LIM_NONE && (above || below)) {
+        // equal on one side alone (w[f] on that side): the cell beyond decides
+        const auto in_row = [&](int i) { return i < 0 ? i + n : (i >= n ? i - n : i); };
+        T t[5];
+        if (above) {
+          prim_at(U, N, row * n + in_row(c + 2), gm1, t);
+#pragma unroll
+          for (int f = 0; f < 5; ++f) flat[f] = flat[f] || (zp[f] && t[f] == w[f]);
+        }
+        if (below) {
+          prim_at(U, N, row * n + in_row(c - 2), gm1, t);
+#pragma unroll
+          for (int f = 0; f < 5; ++f) flat[f] = flat[f] || (zm[f] && t[f] == w[f]);
+        }
+      }
+#pragma unroll
+      for (int f = 0; f < 5; ++f) {
+        // a flat slope: a zero, which slope_branch gives no branch
+        dw[f] = slope_branch<T, LIM>(flat[f] ? T(0) : a[f], b[f], fwd[f], bwd[f]);
+        C[f * nt + tid] = slope_branch<T, LIM>(flat[f] ? T(0) : a[f], bl[f], fwl[f], bwl[f]);
+      }
+    } else {
+#pragma unroll
+      for (int f = 0; f < 5; ++f) {
+        wp[f] = A[f * nt + tp];
+        dw[f] = slope_branch<T, LIM>(plain_diff(wp[f], w[f]), plain_diff(w[f], A[f * nt + tm]),
+                                     fwd[f], bwd[f]);
+        fwl[f] = fwd[f];
+        bwl[f] = bwd[f];
+        C[f * nt + tid] = dw[f];
+      }
     }
   }
   __syncthreads();
