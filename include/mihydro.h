@@ -174,8 +174,9 @@ mh_status mh_init(const mh_grid_desc *grid, const mh_physics_desc *phys, void *w
                   size_t workspace_bytes, void *stream, mh_ctx **out);
 
 /* Copies a state [5][nz][ny][nx] of the context's dtype into the context.
- * where = MH_HOST (synchronises) or MH_DEVICE (device pointer, asynchronous;
- * the source must stay valid until the stream reaches this copy). */
+ * where = MH_HOST (synchronises) or MH_DEVICE (device pointer, of this or
+ * another GPU, asynchronous; the source must stay valid until the stream
+ * reaches this copy). */
 mh_status mh_set_state(mh_ctx *ctx, const void *U, int where);
 
 /* Copies the current state out; MH_HOST synchronises. */

@@ -166,6 +166,7 @@ struct mh_ctx {
   hipStream_t stream = nullptr;
   char* ws = nullptr;
   size_t ws_bytes = 0;
+  int device = -1;  // of the workspace
   Layout L;
   int nmodes = 0;
   // the state's CFL signal speed is on the device: as partial maxima in the
@@ -337,6 +338,9 @@ extern "C" mh_status mh_init(const mh_grid_desc* grid, const mh_physics_desc* ph
   c->stream = (hipStream_t)stream;
   c->ws = (char*)workspace;
   c->ws_bytes = workspace_bytes;
+  hipPointerAttribute_t at{};
+  if (hipPointerGetAttributes(&at, workspace) == hipSuccess) c->device = at.device;
+  else (void)hipGetLastError();
   c->L = L;
   c->L.mg.graphs = &c->mg_graphs;
   c->nmodes = nm;
@@ -394,26 +398,44 @@ static hipError_t measure_states(mh_ctx* const* ctxs, int B, const T* const* src
   return e;
 }
 
+// whether a kernel on the context's device may read `bytes` at p as values of
+// `align` bytes: aligned, and inside one allocation of that device
+static bool kernel_readable(const mh_ctx* c, const void* p, size_t bytes, size_t align) {
+  if ((uintptr_t)p % align != 0) return false;
+  hipPointerAttribute_t at{};
+  hipDeviceptr_t base = nullptr;
+  size_t size = 0;
+  if (hipPointerGetAttributes(&at, p) != hipSuccess || at.type != hipMemoryTypeDevice ||
+      at.device != c->device ||
+      hipMemGetAddressRange(&base, &size, const_cast<void*>(p)) != hipSuccess) {
+    (void)hipGetLastError();  // a failed look-up is not the next launch's error
+    return false;
+  }
+  const size_t off = (size_t)((const char*)p - (const char*)base);
+  return off <= size && bytes <= size - off;
+}
+
 extern "C" mh_status mh_set_state(mh_ctx* c, const void* U, int where) {
   if (!c) return MH_E_INVALID;
   if (!U || (where != MH_HOST && where != MH_DEVICE))
     return set_err(c, MH_E_INVALID, "mh_set_state: null pointer or bad location");
-  c->rate_valid = false;
-  if (where == MH_DEVICE) {
-    // the copy leaves the state's signal speed as well
-    MH_HIP(c, c->g.dtype == MH_F64 ? measure_states<double>(&c, 1, (const double* const*)&U,
-                                                            c->stream)
-                                   : measure_states<float>(&c, 1, (const float* const*)&U,
-                                                           c->stream));
-    return MH_OK;
-  }
   const size_t bytes = 5 * (size_t)c->cells() * c->esize();
-  c->speed_valid = false;
-  MH_HIP(c, hipMemcpyAsync(c->ws + c->L.U, U, bytes, hipMemcpyHostToDevice, c->stream));
+  // the state's signal speed is measured with the copy, or after the runtime's
+  // copy: from the host, and of what a kernel here could not read or should not
+  // read blindly (another GPU's memory, pinned or managed memory, an array that
+  // ends before the state does), which the runtime copies or refuses
+  const bool direct = where == MH_DEVICE && kernel_readable(c, U, bytes, c->esize());
+  c->rate_valid = false;
+  if (!direct) {
+    c->speed_valid = false;
+    MH_HIP(c, hipMemcpyAsync(c->ws + c->L.U, U, bytes,
+                             where == MH_HOST ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice,
+                             c->stream));
+  }
   MH_HIP(c, c->g.dtype == MH_F64
-                ? measure_states<double>(&c, 1, (const double* const*)nullptr, c->stream)
-                : measure_states<float>(&c, 1, (const float* const*)nullptr, c->stream));
-  MH_HIP(c, hipStreamSynchronize(c->stream));
+                ? measure_states<double>(&c, 1, direct ? (const double* const*)&U : nullptr, c->stream)
+                : measure_states<float>(&c, 1, direct ? (const float* const*)&U : nullptr, c->stream));
+  if (where == MH_HOST) MH_HIP(c, hipStreamSynchronize(c->stream));
   return MH_OK;
 }
 

@@ -172,3 +172,77 @@ def test_cooling_limit_of_corrected_states(cfl):
     assert got == [float(t.step(1, record=True)[0]) for t in b]
     # (the limit is the cooling time's, not the signal speed's)
     assert got[0] < 0.5 * float(free.step(1, record=True)[0])
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("source", ["tensor", "pinned", "byte offset", "last bytes", "other gpu"])
+def test_set_state_from_any_device_memory(source, dtype):
+    """mh_set_state(MH_DEVICE) takes what the runtime's copy takes: the state and
+    its CFL step are those of the same values set from a tensor."""
+    import ctypes
+
+    import torch
+
+    if source == "other gpu" and torch.cuda.device_count() < 2:
+        pytest.skip("one GPU")
+    shape = (6, 10, 24)
+    s = mh.Solver(mh.grid_desc(shape, (1.0 / 24, 0.1, 1.0 / 6), dtype=dtype))
+    host = torch.tensor(wl.random_state(shape, seed=31, vmax=0.5), dtype=s.torch_dtype)
+    s.set_state(host.to("cuda:0"))
+    want = s.get_state_device()
+    dt = float(s.step(1, record=True)[0])
+    if source == "pinned":
+        keep = host.pin_memory()
+        ptr = keep.data_ptr()
+    elif source == "byte offset":  # not a multiple of the value's size
+        raw = torch.frombuffer(bytearray(host.numpy().tobytes()), dtype=torch.uint8)
+        keep = torch.empty(raw.numel() + 1, dtype=torch.uint8, device="cuda:0")
+        keep[1:].copy_(raw)
+        ptr = keep.data_ptr() + 1
+    elif source == "last bytes":  # the end of an allocation of its own (over 10 MiB)
+        keep = torch.empty(12 * 2 ** 20 // host.element_size(), dtype=host.dtype, device="cuda:0")
+        keep[-host.numel():].copy_(host.reshape(-1))
+        ptr = keep.data_ptr() + (keep.numel() - host.numel()) * host.element_size()
+    else:
+        keep = host.to("cuda:1" if source == "other gpu" else "cuda:0")
+        torch.cuda.synchronize(keep.device)
+        ptr = keep.data_ptr()
+    torch.cuda.synchronize()
+    assert s.lib.mh_set_state(s.ctx, ctypes.c_void_p(ptr), mh.DEVICE) == mh.OK
+    assert torch.equal(s.get_state_device(), want)
+    assert float(s.step(1, record=True)[0]) == dt
+
+
+def test_set_state_inside_a_capture():
+    """A captured set_state and CFL step: every replay starts from what the tensor
+    holds then."""
+    import torch
+
+    shape = (6, 10, 24)
+    grid = mh.grid_desc(shape, (1.0 / 24, 0.1, 1.0 / 6))
+    U = [torch.tensor(wl.random_state(shape, seed=41 + k, vmax=0.3 * (k + 1)),
+                      dtype=torch.float32, device="cuda:0") for k in range(3)]
+    plain = mh.Solver(grid)
+    side = torch.cuda.Stream()
+    room = U[0].clone()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        s = mh.Solver(grid)
+    s.set_state(room)
+    s.step(1)
+    side.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=side):
+        s.set_state(room)
+        s.step(1)
+    for k in (1, 0, 2, 1):
+        room.copy_(U[k])
+        torch.cuda.synchronize()
+        with torch.cuda.stream(side):
+            g.replay()
+        plain.set_state(U[k])
+        plain.step(1)
+        torch.cuda.synchronize()
+        got, want = s.get_state_device(), plain.get_state_device()
+        torch.cuda.synchronize()
+        assert torch.equal(got, want), k
