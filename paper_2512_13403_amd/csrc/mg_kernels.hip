@@ -984,6 +984,10 @@ inline bool tiled_level(int n, const mh_physics_desc& p) {
   return p.mg_smoother == MH_SMOOTH_RBGS && p.mg_pre >= 1 && p.mg_post >= 1 &&
          n >= MG_TILE_MIN && n % 2 == 0;
 }
+// the same of the fine level: where it is not itself the coarsest grid
+inline bool tiled_fine(const MGLayout& L, const mh_physics_desc& p) {
+  return L.nlev > 1 && tiled_level(L.lev[0].n, p);
+}
 // tiles of the last of `sweeps` sweeps on a level (the blocks of RES_NORM)
 inline int level_tiles(int n, int sweeps) {
   static_assert(MGFine::BZ == MGSmall::BZ, "tile depth");
@@ -1167,7 +1171,7 @@ hipError_t vcycle(char* ws, MGLayout& L, const mh_physics_desc& p, double* parti
     hipError_t e =
         level_cycle<T>(ws, L, p, 0, tail_level(L), cur, false, true, partial, clk, s);
     if (e != hipSuccess) return e;
-    if (tiled_level(L.lev[0].n, p))
+    if (tiled_fine(L, p))
       converged(clk, p, partial, level_tiles(L.lev[0].n, p.mg_post), false, L.graphs, s);
   }
   L.cur0 = cur[0];
@@ -1344,13 +1348,14 @@ hipError_t MGGraphCache::prepare_tests() {
 // launches are queued a cycle ahead, and between two graphs the GPU waits 13 us
 // (two steps with gravity, us, replayed / launched: 16^3 fp32 454 / 390, 64^3
 // fp64 1521 / 1415, 128^3 fp64 3119 / 3016).  The about 60 launches of the other
-// smoothers, each cycle of which waits for the host, are replayed from the cached
-// graph of the current parity, captured on first use
+// smoothers, or the coarse sweeps of a cube that is its own coarsest grid, each
+// cycle of which waits for the host, are replayed from the cached graph of the
+// current parity, captured on first use
 template <typename T>
 hipError_t run_vcycle(char* ws, MGLayout& L, const mh_physics_desc& p, double* partial,
                       DevClock* clk, hipStream_t s) {
   MGGraphCache* G = L.graphs;
-  if (!G->enabled || tiled_level(L.lev[0].n, p)) return vcycle<T>(ws, L, p, partial, clk, s);
+  if (!G->enabled || tiled_fine(L, p)) return vcycle<T>(ws, L, p, partial, clk, s);
   if (G->ws != ws) {
     G->reset();
     G->ws = ws;
@@ -1401,7 +1406,7 @@ hipError_t mg_solve(char* ws, MGLayout& L, const mh_physics_desc& p, DevClock* c
   // at 128^3 fp64 (a copy and a synchronisation), and a cycle that turns out not
   // to be wanted is 45 us of kernels that return.  Nothing unguarded writes
   // the fine level there.
-  const bool fused = L.nlev > 1 && tiled_level(n, p);
+  const bool fused = tiled_fine(L, p);
   MGGraphCache* const G = L.graphs;
   MG_CHECK(G->prepare_tests());
   int cycles = 0;
