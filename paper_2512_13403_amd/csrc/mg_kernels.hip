@@ -42,6 +42,19 @@ __device__ __forceinline__ T nb6(const T* __restrict__ p, int n, int i, int j, i
          p[(long long)kp * n2 + (long long)j * n + i];
 }
 
+// x / 6 as a division rounds it: the product with the rounded 1/6 and one correction
+// by its exact remainder (Markstein's final step), three instructions where a
+// division takes about ten, and twice that in fp64.  The product alone is off by up
+// to an ulp, always to the same side, which the sweeps accumulate: the fp32
+// potential of a white-noise density after 14 cycles was 2.3e-6 (96^3) and 5.7e-6
+// (160^3) off instead of 0.8e-6 and 0.3e-6, and the residual at its floor a quarter
+// higher.  The correction costs 0.6 % of a 128^3 fp64 step.
+template <typename T>
+__device__ __forceinline__ T sixth(T x) {
+  const T q = x * T(1.0 / 6.0);
+  return fmad(fmad(T(-6), q, x), T(1.0 / 6.0), q);
+}
+
 // a fixed tree inside each wave: lane l adds lane l + s for s = 32, 16, ...,
 // 1 (lane 0 holds the wave's sum)
 __device__ __forceinline__ double wave_tree_sum(double v) {
@@ -389,7 +402,6 @@ __global__ __launch_bounds__((TileShape<C, RES>::NT)) void k_rbgs_tile(const Til
     for (int kk = 0; kk < EZ; ++kk) mine[kk * 2 * NC] = p[kk];
   }
   __syncthreads();
-  const T sixth = T(1.0 / 6.0);
   // the x neighbours sit in the other parity's row at col - 1 + odd and
   // col + odd, the y neighbours a row below and above at the same place
   const T* const xl = other - 1 + odd;
@@ -407,7 +419,7 @@ __global__ __launch_bounds__((TileShape<C, RES>::NT)) void k_rbgs_tile(const Til
     if (inside(r)) {
 #pragma unroll
       for (int kk = k0; kk < last; kk += 2) {
-        p[kk] = (nb(kk) - a.h2 * f[kk]) * sixth;
+        p[kk] = sixth(nb(kk) - a.h2 * f[kk]);
         mine[kk * 2 * NC] = p[kk];
       }
     }
@@ -664,7 +676,7 @@ __device__ __forceinline__ void tail_rbgs(T* ph, const T* ff, const TailLevel<T>
       for (int p = threadIdx.x; p < Nh; p += MG_TAIL_THREADS) {
         const int r = fdiv(p, 2.0f * L.rn), k = fdiv(r, L.rn), j = r - k * n;
         const int i = 2 * (p - r * nh) + ((j + k + colour) & 1), q = r * n + i;
-        phi[q] = (tail_nb6(phi, n, q, i, j, k) - L.h2 * ff[L.off + q]) * T(1.0 / 6.0);
+        phi[q] = sixth(tail_nb6(phi, n, q, i, j, k) - L.h2 * ff[L.off + q]);
       }
       __syncthreads();
     }
