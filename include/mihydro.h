@@ -467,11 +467,12 @@ mh_status mh_fft3(void *data, int32_t n, int32_t dtype, int32_t inverse, void *w
  * a device index of 64 or more). */
 mh_status mh_fft3_noalloc(void *data, int32_t n, int32_t dtype, int32_t inverse, void *stream);
 
-/* Kernel timing with HIP events.  While enabled, mh_step records an event pair
- * on the context stream around every kernel launch it makes, by kind:
+/* Kernel timing with HIP events.  While enabled, mh_step and mh_set_state record
+ * an event pair on the context stream around every kernel launch they make, by kind:
  *   MH_TIME_STAGE1, MH_TIME_STAGE2 (the fused stage kernels),
- *   MH_TIME_PROLOGUE (per-step dt / OU kernel), MH_TIME_OTHER (CFL reduction
- *   after set_state, multigrid and gravity kernels, bookkeeping).
+ *   MH_TIME_PROLOGUE (per-step dt / OU kernel), MH_TIME_OTHER (the CFL
+ *   reduction of a set state, which also copies a device state; multigrid and
+ *   gravity kernels, bookkeeping).
  * mh_get_timing synchronises, returns per kind the summed milliseconds and
  * the number of timed launches (arrays of MH_TIME_KINDS), and clears the
  * records.  At most 65536 launches are timed between two reads; later ones

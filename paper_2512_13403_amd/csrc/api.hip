@@ -432,9 +432,11 @@ extern "C" mh_status mh_set_state(mh_ctx* c, const void* U, int where) {
                              where == MH_HOST ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice,
                              c->stream));
   }
+  const long tk = time_begin(c, MH_TIME_OTHER);
   MH_HIP(c, c->g.dtype == MH_F64
                 ? measure_states<double>(&c, 1, direct ? (const double* const*)&U : nullptr, c->stream)
                 : measure_states<float>(&c, 1, direct ? (const float* const*)&U : nullptr, c->stream));
+  time_end(c, tk);
   if (where == MH_HOST) MH_HIP(c, hipStreamSynchronize(c->stream));
   return MH_OK;
 }

@@ -246,3 +246,23 @@ def test_set_state_inside_a_capture():
         got, want = s.get_state_device(), plain.get_state_device()
         torch.cuda.synchronize()
         assert torch.equal(got, want), k
+
+
+@pytest.mark.parametrize("where", ["device", "host"])
+def test_timing_includes_the_reduction_of_a_set_state(where):
+    """The signal speed of a set state is a timed launch of kind MH_TIME_OTHER, once
+    a state, wherever it is measured."""
+    import torch
+
+    shape = (16, 16, 64)
+    s = mh.Solver(mh.grid_desc(shape, (1.0 / 64, 1.0 / 16, 1.0 / 16)))
+    U = wl.random_state(shape, seed=3, vmax=0.5).astype(np.float32)
+    if where == "device":
+        U = torch.tensor(U, device="cuda:0")
+    s.set_timing(True)
+    for _ in range(2):
+        s.set_state(U)
+        s.step(2)
+    ms, launches = s.timing()
+    assert launches[mh.TIME_OTHER] == 2 and ms[mh.TIME_OTHER] > 0.0
+    assert list(launches[[mh.TIME_STAGE1, mh.TIME_STAGE2, mh.TIME_PROLOGUE]]) == [4, 4, 4]
