@@ -553,13 +553,16 @@ __global__ __launch_bounds__(256) void k_coarse_solve(int n, T h2, const T* __re
 // the kernel's arguments, indexed by a run-time level, it was copied to
 // scratch memory), and the coarsest level's weighted Jacobi sweeps, a fixed
 // linear map, are applied in the eigenvectors of the periodic Laplacian
-// (tail_direct) where it has at most MG_DIRECT_MAX cells per axis.  With 16^3,
-// 8^3 and 4^3 levels and 200 coarse sweeps: 62 us before.
+// (tail_direct; the tail's first level has at most 16 cells per axis and is not
+// the coarsest, which so has at most eight).  With 16^3, 8^3 and 4^3 levels and
+// 200 coarse sweeps: 62 us before.
 constexpr int MG_TAIL_MAX_CELLS = 4096;
 constexpr int MG_TAIL_ALLOC = 4688;  // >= 4096 * 8 / 7: all levels of the tail
 constexpr int MG_TAIL_THREADS = 1024;
 constexpr int MG_TAIL_LEVELS = 5;    // 16, 8, 4, 2, 1
-constexpr int MG_DIRECT_MAX = 8;     // cells per axis of a coarsest level solved directly
+constexpr int MG_DIRECT_MAX = 8;     // cells per axis of the coarsest level, at most
+static_assert(8 * MG_DIRECT_MAX * MG_DIRECT_MAX * MG_DIRECT_MAX >= MG_TAIL_MAX_CELLS,
+              "half the cells per axis of the tail's first level are solved directly");
 
 template <typename T>
 struct TailArgs {
@@ -583,25 +586,6 @@ struct TailLevel {
   float rn;                  // 1 / n
   T h2, ih2;
 };
-
-// the sum of v over the workgroup, returned to every thread: a fixed tree
-// inside each wave, then the same over the 16 wave sums
-__device__ __forceinline__ double block_sum1024(double v, double* sh) {
-  static_assert(MG_TAIL_THREADS == 1024, "16 waves");
-  const int t = threadIdx.x;
-  v = wave_tree_sum(v);
-  if ((t & 63) == 0) sh[t >> 6] = v;
-  __syncthreads();
-  if (t < 64) {
-    double w = t < 16 ? sh[t] : 0.0;
-    for (int s = 8; s > 0; s >>= 1) w += __shfl_down(w, s, 64);
-    if (t == 0) sh[16] = w;
-  }
-  __syncthreads();
-  const double r = sh[16];
-  __syncthreads();
-  return r;
-}
 
 // q / n for q < 2^20 from rn = 1 / n: (q + 1/2) rn lies at least 1 / (2 n) from
 // an integer, far beyond its rounding.  Three instructions; the division of
@@ -633,35 +617,6 @@ __device__ __forceinline__ void tail_sweeps(T* ph, const T* ff, const TailLevel<
     __syncthreads();
     cur ^= 1;
   }
-}
-
-// The same sweeps on a level of at most 64 cells (the coarsest level): one
-// wave, a cell per lane, so no workgroup barrier is needed between sweeps
-// (a wave's LDS accesses complete in program order; the fences only keep the
-// compiler from moving them).  Same arithmetic as tail_sweeps.
-template <typename T>
-__device__ __forceinline__ void tail_sweeps_wave(T* ph, const T* ff, const TailLevel<T>& L,
-                                                 int sweeps, int& cur) {
-  const int n = L.n, N = n * n * n;
-  const T w = T(2) / T(3);
-  if (threadIdx.x < 64) {
-    const int q = threadIdx.x;
-    const int r = fdiv(q, L.rn), k = fdiv(r, L.rn), j = r - k * n, i = q - r * n;
-    int c = cur;
-    for (int it = 0; it < sweeps; ++it) {
-      const T* src = ph + L.off + c * MG_TAIL_ALLOC;
-      T* dst = ph + L.off + (1 - c) * MG_TAIL_ALLOC;
-      if (q < N)
-        dst[q] = (T(1) - w) * src[q] +
-                 (w / T(6)) * (tail_nb6(src, n, q, i, j, k) - L.h2 * ff[L.off + q]);
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      c ^= 1;
-    }
-  }
-  __syncthreads();
-  cur ^= sweeps & 1;
 }
 
 // red-black sweeps of a tail level (n even): per colour, a thread per cell
@@ -729,12 +684,10 @@ template <typename T>
 __global__ __launch_bounds__(MG_TAIL_THREADS) void k_mgcycle_tail(const TailArgs<T> t) {
   __shared__ T ph[2 * MG_TAIL_ALLOC], ff[MG_TAIL_ALLOC];
   __shared__ T sQ[MG_DIRECT_MAX * MG_DIRECT_MAX], slam[MG_DIRECT_MAX];
-  __shared__ double sh[MG_TAIL_THREADS / 64 + 1];
   __shared__ TailLevel<T> lev[MG_TAIL_LEVELS];
   if (*t.done) return;
   const int nl = t.nl, tid = threadIdx.x;
   const int nb = t.n0 >> (nl - 1);  // cells per axis of the coarsest level
-  const bool direct = nb <= MG_DIRECT_MAX;
   if (tid < nl) {
     int off = 0;
     for (int m = 0; m < tid; ++m) {
@@ -745,7 +698,7 @@ __global__ __launch_bounds__(MG_TAIL_THREADS) void k_mgcycle_tail(const TailArgs
     const T h = t.h * (T)(1 << tid);
     lev[tid] = TailLevel<T>{n, off, 1.0f / (float)n, h * h, T(1) / (h * h)};
   }
-  if (direct && tid >= 64 && tid < 64 + nb * MG_DIRECT_MAX) {
+  if (tid >= 64 && tid < 64 + nb * MG_DIRECT_MAX) {
     // the real Fourier basis: constant, cos and sin pairs, (-1)^i
     const int m = (tid - 64) / MG_DIRECT_MAX, i = (tid - 64) % MG_DIRECT_MAX, k = (m + 1) / 2;
     if (i < nb) {
@@ -778,25 +731,9 @@ __global__ __launch_bounds__(MG_TAIL_THREADS) void k_mgcycle_tail(const TailArgs
     if (down) {
       const TailLevel<T> L = lev[m];
       if (m == nl - 1) {
-        // coarsest level: phi = 0, Jacobi sweeps, remove the mean (as
-        // k_coarse_solve)
-        const int N = L.n * L.n * L.n;
-        int cur = 0;
-        if (direct) {
-          tail_direct(ph + L.off, ph + L.off + MG_TAIL_ALLOC, ff + L.off, sQ, slam, L, t.csweeps);
-        } else {
-          for (int q = tid; q < N; q += MG_TAIL_THREADS) ph[L.off + q] = T(0);
-          __syncthreads();
-          if (N <= 64) tail_sweeps_wave(ph, ff, L, t.csweeps, cur);
-          else tail_sweeps(ph, ff, L, t.csweeps, cur);
-          T* phi = ph + L.off + cur * MG_TAIL_ALLOC;
-          double s = 0.0;
-          for (int q = tid; q < N; q += MG_TAIL_THREADS) s += (double)phi[q];
-          const double mean = block_sum1024(s, sh) / (double)N;
-          for (int q = tid; q < N; q += MG_TAIL_THREADS) phi[q] = phi[q] - (T)mean;
-          __syncthreads();
-        }
-        curs = (curs & ~(1u << m)) | ((unsigned)cur << m);
+        // coarsest level: what Jacobi sweeps from zero give, without the mean
+        tail_direct(ph + L.off, ph + L.off + MG_TAIL_ALLOC, ff + L.off, sQ, slam, L, t.csweeps);
+        curs &= ~(1u << m);
         down = false;
         continue;
       }
@@ -1008,17 +945,26 @@ inline int level_tiles(int n, int sweeps) {
   return t * t * ((n + MGFine::BZ - 1) / MGFine::BZ);
 }
 
+// (sweeps from zero come before the coarse correction and end in its right-hand
+// side, sweeps with the correction end in the norm)
 template <typename T, class C, int RES>
-void launch_tile(const TileArgs<T>& a, bool zero, bool pro, unsigned tiles, hipStream_t s) {
+hipError_t launch_tile(const TileArgs<T>& a, bool zero, bool pro, unsigned tiles, hipStream_t s) {
   const dim3 block(TileShape<C, RES>::NT);
-  if (zero) hipLaunchKernelGGL((k_rbgs_tile<T, C, RES, true, false>), dim3(tiles), block, 0, s, a);
-  else if (pro) hipLaunchKernelGGL((k_rbgs_tile<T, C, RES, false, true>), dim3(tiles), block, 0, s, a);
-  else hipLaunchKernelGGL((k_rbgs_tile<T, C, RES, false, false>), dim3(tiles), block, 0, s, a);
+  if ((zero && (pro || RES == RES_NORM)) || (pro && RES == RES_COARSE)) return hipErrorInvalidValue;
+  if constexpr (RES != RES_NORM)
+    if (zero)
+      hipLaunchKernelGGL((k_rbgs_tile<T, C, RES, true, false>), dim3(tiles), block, 0, s, a);
+  if constexpr (RES != RES_COARSE)
+    if (pro)
+      hipLaunchKernelGGL((k_rbgs_tile<T, C, RES, false, true>), dim3(tiles), block, 0, s, a);
+  if (!zero && !pro)
+    hipLaunchKernelGGL((k_rbgs_tile<T, C, RES, false, false>), dim3(tiles), block, 0, s, a);
+  return hipGetLastError();
 }
 
 // one launch of C::S sweeps on level lv, from phi[cur] to phi[1 - cur]
 template <typename T, class C>
-void tile_sweeps(char* ws, const MGLevel& lv, const MGLevel* cv, const T* ec, int& cur, bool zero,
+hipError_t tile_sweeps(char* ws, const MGLevel& lv, const MGLevel* cv, const T* ec, int& cur, bool zero,
                  int res, double* partial, const int* done, hipStream_t s) {
   TileArgs<T> a{};
   a.done = done;
@@ -1034,28 +980,31 @@ void tile_sweeps(char* ws, const MGLevel& lv, const MGLevel* cv, const T* ec, in
   a.Fc = cv ? P<T>(ws, cv->F) : nullptr;
   a.partial = partial;
   const unsigned tiles = (unsigned)(a.ntx * a.nty * ((lv.n + C::BZ - 1) / C::BZ));
-  if (res == RES_COARSE) launch_tile<T, C, RES_COARSE>(a, zero, ec != nullptr, tiles, s);
-  else if (res == RES_NORM) launch_tile<T, C, RES_NORM>(a, zero, ec != nullptr, tiles, s);
-  else launch_tile<T, C, RES_NONE>(a, zero, ec != nullptr, tiles, s);
   cur = 1 - cur;
+  if (res == RES_COARSE) return launch_tile<T, C, RES_COARSE>(a, zero, ec != nullptr, tiles, s);
+  if (res == RES_NORM) return launch_tile<T, C, RES_NORM>(a, zero, ec != nullptr, tiles, s);
+  return launch_tile<T, C, RES_NONE>(a, zero, ec != nullptr, tiles, s);
 }
 
 // `sweeps` sweeps of a tiled level: from zero, or with the correction ec added
 // first, and the residual's `res` form from the last launch.  Small levels take
 // the sweeps in pairs if there are only pairs, else one by one
 template <typename T>
-void smooth_tiles(char* ws, const MGLevel& lv, const MGLevel* cv, const T* ec, int sweeps,
+hipError_t smooth_tiles(char* ws, const MGLevel& lv, const MGLevel* cv, const T* ec, int sweeps,
                   int& cur, bool zero, int res, double* partial, const int* done, hipStream_t s) {
   const bool pair = lv.n < MG_FINE_MIN && sweeps % 2 == 0;
   while (sweeps > 0) {
     const int left = sweeps - (pair ? 2 : 1);
     const int r = left == 0 ? res : RES_NONE;
-    if (pair) tile_sweeps<T, MGSmall>(ws, lv, cv, ec, cur, zero, r, partial, done, s);
-    else tile_sweeps<T, MGFine>(ws, lv, cv, ec, cur, zero, r, partial, done, s);
+    const hipError_t e =
+        pair ? tile_sweeps<T, MGSmall>(ws, lv, cv, ec, cur, zero, r, partial, done, s)
+             : tile_sweeps<T, MGFine>(ws, lv, cv, ec, cur, zero, r, partial, done, s);
+    if (e != hipSuccess) return e;
     zero = false;
     ec = nullptr;
     sweeps = left;
   }
+  return hipSuccess;
 }
 
 // first level handled by the single-workgroup tail: the first one after the
@@ -1089,8 +1038,9 @@ hipError_t level_cycle(char* ws, MGLayout& L, const mh_physics_desc& p, int l, i
   const long long Nc = (long long)cv.n * cv.n * cv.n;
   hipError_t e = hipSuccess;
   if (tiled) {
-    smooth_tiles<T>(ws, lv, &cv, (const T*)nullptr, p.mg_pre, cur[l], zero, RES_COARSE, partial,
-                    &clk->mg_done, s);
+    e = smooth_tiles<T>(ws, lv, &cv, (const T*)nullptr, p.mg_pre, cur[l], zero, RES_COARSE, partial,
+                        &clk->mg_done, s);
+    if (e != hipSuccess) return e;
   } else {
     if (zero)
       hipLaunchKernelGGL((k_zero<T>), dim3(nblk(N)), dim3(256), 0, s, P<T>(ws, lv.phi[cur[l]]), N);
@@ -1141,9 +1091,8 @@ hipError_t level_cycle(char* ws, MGLayout& L, const mh_physics_desc& p, int l, i
     }
   }
   if (tiled) {
-    smooth_tiles<T>(ws, lv, nullptr, P<T>(ws, cv.phi[cur[l + 1]]), p.mg_post, cur[l], false,
-                    norm ? RES_NORM : RES_NONE, partial, &clk->mg_done, s);
-    return hipGetLastError();
+    return smooth_tiles<T>(ws, lv, nullptr, P<T>(ws, cv.phi[cur[l + 1]]), p.mg_post, cur[l], false,
+                           norm ? RES_NORM : RES_NONE, partial, &clk->mg_done, s);
   }
   hipLaunchKernelGGL((k_prolong_add<T>), plane_grid((long long)lv.n * lv.n, lv.n), dim3(256),
                      0, s, cv.n,
