@@ -940,6 +940,7 @@ __global__ __launch_bounds__(XROW_MAX) void k_x_jtv(const T* __restrict__ U,
                                                     const T* __restrict__ v, AxisGeom g, T gamma,
                                                     T ih, int len, int rpb, int cells, int npieces,
                                                     T* __restrict__ Wacc, FinishArgs<T> fa) {
+  static_assert(MODE == GATHER_FIRST || MODE == GATHER_FIRST_LAST, "x is the first axis, if any");
   extern __shared__ __align__(16) unsigned char x_jtv_lds[];
   const int nt = blockDim.x;
   T* const A = reinterpret_cast<T*>(x_jtv_lds);  // [6][nt]: rho, m, 1/rho, e (fp64: W); then WRb
@@ -964,18 +965,13 @@ __global__ __launch_bounds__(XROW_MAX) void k_x_jtv(const T* __restrict__ U,
   const T gm1inv = T(1) / gm1;
   const bool own = active && (whole || (j >= 3 && j < 3 + cells && x0 + j < n));
   // u: rho, m, e with P = (g - 1) e; w the primitives
-  T u[5], ir, w[5], vc[5], dw[5], wp[5], acc[5];
+  T u[5], ir, w[5], vc[5], dw[5], wp[5];
   bool fwd[5], bwd[5], fwl[5], bwl[5];  // branches at the face above and below
   if (active) {
 #pragma unroll
     for (int f = 0; f < 5; ++f) {
       u[f] = U[f * N + q];
       vc[f] = v[f * N + q];
-      acc[f] = T(0);
-    }
-    if (own && (MODE == GATHER_ADD || MODE == GATHER_LAST)) {
-#pragma unroll
-      for (int f = 0; f < 5; ++f) acc[f] = Wacc[f * N + q];
     }
     to_prim(u, gm1, w);  // the arithmetic of the stage kernels
     ir = dev_rcp(u[0]);
@@ -1087,8 +1083,8 @@ __global__ __launch_bounds__(XROW_MAX) void k_x_jtv(const T* __restrict__ U,
   __syncthreads();
   if (!own) return;
 #pragma unroll
-  for (int f = 0; f < 5; ++f) sum[f] = acc[f] + ((sum[f] + B[f * nt + tm]) - C[f * nt + tp]);
-  if (MODE == GATHER_ADD || MODE == GATHER_FIRST) {
+  for (int f = 0; f < 5; ++f) sum[f] = (sum[f] + B[f * nt + tm]) - C[f * nt + tp];
+  if (MODE == GATHER_FIRST) {
 #pragma unroll
     for (int f = 0; f < 5; ++f) Wacc[f * N + q] = sum[f];
   } else {
@@ -1483,9 +1479,7 @@ hipError_t adj_jtv(const AdjointBuffers<T>& B, const StageGeom& geom, int limite
                      gamma, ih, len, rpb, cells, npieces, B.Wacc, fa)
 #define MH_XJTV(LM)                                                                           \
   do {                                                                                        \
-    if (mode == GATHER_ADD) MH_XJTV_MODE(LM, GATHER_ADD);                                     \
-    else if (mode == GATHER_FIRST) MH_XJTV_MODE(LM, GATHER_FIRST);                            \
-    else if (mode == GATHER_LAST) MH_XJTV_MODE(LM, GATHER_LAST);                              \
+    if (mode == GATHER_FIRST) MH_XJTV_MODE(LM, GATHER_FIRST);                                 \
     else MH_XJTV_MODE(LM, GATHER_FIRST_LAST);                                                 \
   } while (0)
       if (limiter == LIM_NONE) MH_XJTV(LIM_NONE);
