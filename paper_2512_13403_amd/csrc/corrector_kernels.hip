@@ -373,8 +373,7 @@ __global__ __launch_bounds__(VT, 2) void k_conv(const unsigned short* __restrict
 }
 
 // Weight gradient of one layer, dW[tap][co][ci] = sum over cells of
-// dz[cell][co] x[cell + off_tap][ci], on the same 16 x 4 x 4 halo tiles as
-// k_conv.  A persistent workgroup takes every gridDim.x-th block of cells; per
+// dz[cell][co] x[cell + off_tap][ci], on 16 x 4 x 4 halo tiles.  A persistent workgroup takes every gridDim.x-th block of cells; per
 // block it stages the layer input with its halo and the block's output
 // gradients in LDS, both channel-major (each channel's x rows contiguous), so
 // that every MFMA operand of a lane -- 8 consecutive cells of one channel --

@@ -47,7 +47,7 @@ struct MGGraphCache {
 struct MGLayout {
   int nlev = 0;
   MGLevel lev[MG_MAX_LEVELS];
-  size_t partial = 0;  // MG_PARTIALS doubles
+  size_t partial = 0;  // block sums: MG_PARTIALS doubles, or one per 8^3 tile of the fine level
   int cur0 = 0;        // which fine-level phi buffer holds the solution
   MGGraphCache* graphs = nullptr;  // not owned; needed by a multigrid solve
   // spectral solver (grav_solver = MH_GRAV_FFT): level 0 only, plus two

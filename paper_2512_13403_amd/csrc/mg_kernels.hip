@@ -1274,9 +1274,6 @@ hipError_t mg_set_guess(char* ws, MGLayout& L, const T* phi0, hipStream_t s) {
   return hipGetLastError();
 }
 
-// V-cycles on A phi = F (F already mean-free on the fine level) from the
-// current guess until ||F - A phi||_2 <= tol ||F||_2 or max_cycles cycles;
-// the mean of phi is removed before the first and after every cycle.
 void MGGraphCache::reset() {
   for (int k = 0; k < 2; ++k) {
     if (exec[k]) (void)hipGraphExecDestroy(exec[k]);
@@ -1344,6 +1341,10 @@ hipError_t run_vcycle(char* ws, MGLayout& L, const mh_physics_desc& p, double* p
   return hipSuccess;
 }
 
+// Cycles on A phi = F (F already mean-free on the fine level) from the current
+// guess until ||F - A phi||_2 <= tol ||F||_2, max_cycles cycles or the stall of
+// k_converged; the mean of phi is removed before the first cycle and after the
+// last (after every one where the fine level is not smoothed on tiles).
 template <typename T>
 hipError_t mg_solve(char* ws, MGLayout& L, const mh_physics_desc& p, DevClock* clk, int* cycles_out,
                     hipStream_t s) {
