@@ -54,6 +54,20 @@ __device__ __forceinline__ void prim_at(const T* __restrict__ U, long long N, lo
   to_prim(u, gm1, w);
 }
 
+// the same as the products of to_prim, W = x y: rho 1, m (1/rho), e (g - 1)
+template <typename T>
+__device__ __forceinline__ void prim_factors_at(const T* __restrict__ U, long long N, long long q,
+                                                T gm1, T (&x)[5], T (&y)[5]) {
+  T u[5], w[5];
+#pragma unroll
+  for (int f = 0; f < 5; ++f) x[f] = u[f] = U[f * N + q];
+  to_prim(u, gm1, w);
+  y[0] = T(1);
+  y[1] = y[2] = y[3] = dev_rcp(u[0]);
+  x[4] = fmad(-(T(0.5) * u[0]), fmad(w[1], w[1], fmad(w[2], w[2], w[3] * w[3])), u[4]);
+  y[4] = gm1;
+}
+
 // a difference that is not contracted with the product behind an operand
 template <typename T>
 __device__ __forceinline__ T plain_diff(T a, T b) {
@@ -73,9 +87,9 @@ __device__ __forceinline__ T plain_diff(T a, T b) {
 // takes no branch where W is flat: equal, as rounded, over three cells in a row of
 // which two make one of the slope's differences.  (A single pair of equal
 // neighbours in a varying fp32 field is a coincidence of rounding, about one in
-// 1e5, and decided like the near-ties.)
-__device__ __forceinline__ float branch_diff(float a, float b) { return a - b; }
-__device__ __forceinline__ double branch_diff(double a, double b) { return plain_diff(a, b); }
+// 1e5, and decided like the near-ties.)  Which product is contracted is written out,
+// not left to the compiler, whose choice changes with the code around it: in the
+// lowest of a face's three differences the lower cell's, in the others the upper's.
 template <typename T>
 constexpr bool contracted_branches = sizeof(T) == 4;
 
@@ -413,8 +427,44 @@ __device__ __forceinline__ void other_dims(const AxisGeom& g, int& d1, int& d2) 
   d2 = AX == 2 ? g.n[1] : g.n[2];
 }
 
+// W of a face's four stencil cells i - 1 .. i + 2 in the face frame, and the three
+// differences between them
+template <typename T>
+struct FaceStencil {
+  T w[4][5], dm[5], dc[5], dp[5];
+};
+template <typename T, int AX>
+__device__ __forceinline__ void face_stencil(const T* __restrict__ U, long long N,
+                                             const AxisGeom& g, int i, int o1, int o2, T gm1,
+                                             const int (&perm)[5], FaceStencil<T>& st) {
+  T x[4][5], y[4][5];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    T xc[5], yc[5];
+    prim_factors_at(U, N, cell_of<AX>(g, bc_map(i - 1 + k, g.n[AX], g.bc), o1, o2), gm1, xc, yc);
+#pragma unroll
+    for (int s = 0; s < 5; ++s) {
+      x[k][s] = xc[perm[s]];
+      y[k][s] = yc[perm[s]];
+      st.w[k][s] = x[k][s] * y[k][s];
+    }
+  }
+#pragma unroll
+  for (int s = 0; s < 5; ++s) {
+    if constexpr (contracted_branches<T>) {
+      st.dm[s] = fmad(-x[0][s], y[0][s], st.w[1][s]);
+      st.dc[s] = fmad(x[2][s], y[2][s], -st.w[1][s]);
+      st.dp[s] = fmad(x[3][s], y[3][s], -st.w[2][s]);
+    } else {
+      st.dm[s] = plain_diff(st.w[1][s], st.w[0][s]);
+      st.dc[s] = plain_diff(st.w[2][s], st.w[1][s]);
+      st.dp[s] = plain_diff(st.w[3][s], st.w[2][s]);
+    }
+  }
+}
+
 // which slopes of the face's left (k = 0) and right cell are flat (see
-// branch_diff), from W of its four stencil cells, cell i the left one; the cells
+// contracted_branches), from W of its four stencil cells, cell i the left one; the cells
 // beyond them are read where one difference alone is zero
 template <typename T, int AX>
 __device__ __forceinline__ void flat_slopes(const T* __restrict__ U, long long N, const AxisGeom& g,
@@ -461,28 +511,29 @@ __global__ __launch_bounds__(256) void k_face_vjp(const T* __restrict__ U, const
   const T gm1inv = T(1) / gm1;
   constexpr int vn = 1 + AX, t1 = 1 + (AX + 1) % 3, t2 = 1 + (AX + 2) % 3;
   const int perm[5] = {0, vn, t1, t2, 4};
-  T w[4][5];
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    T wc[5];
-    prim_at(U, N, cell_of<AX>(g, bc_map(i - 1 + k, n, g.bc), o1, o2), gm1, wc);
-#pragma unroll
-    for (int s = 0; s < 5; ++s) w[k][s] = wc[perm[s]];
-  }
+  FaceStencil<T> st;
+  face_stencil<T, AX>(U, N, g, i, o1, o2, gm1, perm, st);
+  const T(&w)[4][5] = st.w;
   T wl[5], wr[5];
   int fl = 0;
-  bool flat[2][5] = {};
-  if (contracted_branches<T> && LIM != LIM_NONE)
-    flat_slopes<T, AX>(U, N, g, i, o1, o2, gm1, perm, w, flat);
 #pragma unroll
   for (int s = 0; s < 5; ++s) {
-    const T a0 = branch_diff(w[2][s], w[1][s]), b0 = branch_diff(w[1][s], w[0][s]);
-    const T a1 = branch_diff(w[3][s], w[2][s]), b1 = branch_diff(w[2][s], w[1][s]);
-    const int s0 = LIM == LIM_NONE || flat[0][s] ? 0 : minmod_sel(a0, b0);
-    const int s1 = LIM == LIM_NONE || flat[1][s] ? 0 : minmod_sel(a1, b1);
+    const T a0 = st.dc[s], b0 = st.dm[s], a1 = st.dp[s], b1 = st.dc[s];
+    const int s0 = LIM == LIM_NONE ? 0 : minmod_sel(a0, b0);
+    const int s1 = LIM == LIM_NONE ? 0 : minmod_sel(a1, b1);
     wl[s] = w[1][s] + T(0.5) * sel_value(s0, a0, b0);
     wr[s] = w[2][s] - T(0.5) * sel_value(s1, a1, b1);
     fl |= (s0 << (2 * s)) | (s1 << (10 + 2 * s));
+  }
+  if (contracted_branches<T> && LIM != LIM_NONE) {
+    bool flat[2][5];
+    flat_slopes<T, AX>(U, N, g, i, o1, o2, gm1, perm, w, flat);
+#pragma unroll
+    for (int s = 0; s < 5; ++s) {
+      if (flat[0][s]) wl[s] = w[1][s];
+      if (flat[1][s]) wr[s] = w[2][s];
+      fl &= ~((flat[0][s] ? 3 << (2 * s) : 0) | (flat[1][s] ? 3 << (10 + 2 * s) : 0));
+    }
   }
   // Fb = (v of the face's right cell - v of its left cell) / h, real cells only
   const bool has_right = g.bc == BC_PERIODIC || i + 1 <= n - 1;
@@ -534,26 +585,31 @@ __global__ __launch_bounds__(256) void k_face_vjp_rt(const T* __restrict__ U,
   const T gm1inv = T(1) / gm1;
   constexpr int vn = 1 + AX, t1 = 1 + (AX + 1) % 3, t2 = 1 + (AX + 2) % 3;
   const int perm[5] = {0, vn, t1, t2, 4};
-  T w[4][5];
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    T wc[5];
-    prim_at(U, N, cell_of<AX>(g, bc_map(i - 1 + k, n, g.bc), o1, o2), gm1, wc);
-#pragma unroll
-    for (int s = 0; s < 5; ++s) w[k][s] = wc[perm[s]];
-  }
+  FaceStencil<T> st;
+  face_stencil<T, AX>(U, N, g, i, o1, o2, gm1, perm, st);
+  const T(&w)[4][5] = st.w;
   T wl[5], wr[5], pa0[5], pb0[5], pa1[5], pb1[5];
-  bool flat[2][5] = {};
-  if (contracted_branches<T> && lim != LIM_NONE)
-    flat_slopes<T, AX>(U, N, g, i, o1, o2, gm1, perm, w, flat);
 #pragma unroll
   for (int s = 0; s < 5; ++s) {
-    const T d0 = slope_partials(flat[0][s] ? LIM_NONE : lim, branch_diff(w[2][s], w[1][s]),
-                                branch_diff(w[1][s], w[0][s]), pa0[s], pb0[s]);
-    const T d1 = slope_partials(flat[1][s] ? LIM_NONE : lim, branch_diff(w[3][s], w[2][s]),
-                                branch_diff(w[2][s], w[1][s]), pa1[s], pb1[s]);
+    const T d0 = slope_partials(lim, st.dc[s], st.dm[s], pa0[s], pb0[s]);
+    const T d1 = slope_partials(lim, st.dp[s], st.dc[s], pa1[s], pb1[s]);
     wl[s] = w[1][s] + T(0.5) * d0;
     wr[s] = w[2][s] - T(0.5) * d1;
+  }
+  if (contracted_branches<T> && lim != LIM_NONE) {
+    bool flat[2][5];
+    flat_slopes<T, AX>(U, N, g, i, o1, o2, gm1, perm, w, flat);
+#pragma unroll
+    for (int s = 0; s < 5; ++s) {
+      if (flat[0][s]) {
+        wl[s] = w[1][s];
+        pa0[s] = pb0[s] = T(0);
+      }
+      if (flat[1][s]) {
+        wr[s] = w[2][s];
+        pa1[s] = pb1[s] = T(0);
+      }
+    }
   }
   const bool has_right = g.bc == BC_PERIODIC || i + 1 <= n - 1;
   const bool has_left = g.bc == BC_PERIODIC || i >= 0;
@@ -926,7 +982,7 @@ __global__ __launch_bounds__(256) void k_axis_jtv(const T* __restrict__ U, const
 // contributions pass between neighbours through LDS, and each is computed
 // once, where a lane per face of 61-cell pieces converted every cell four
 // times.
-// The differences are branch_diff's: in fp32 formed with one rounding from the
+// In fp32 the limiter's differences are formed with one rounding from the
 // neighbour's factors (velocity m / rho, pressure (g - 1) e), W_{c+1} - W_c =
 // fma(m, 1/rho, -W_c).  A cell's backward difference then rounds W_{c-1}'s
 // product for the face above it and its own for the face below it, so at a
