@@ -463,34 +463,31 @@ __device__ __forceinline__ void face_stencil(const T* __restrict__ U, long long 
   }
 }
 
+// whether any two neighbours of the stencil are equal in any field, without which no
+// slope is flat
+template <typename T>
+__device__ __forceinline__ bool any_equal(const T (&w)[4][5]) {
+  bool e = false;
+#pragma unroll
+  for (int s = 0; s < 5; ++s)
+    e = e || w[0][s] == w[1][s] || w[1][s] == w[2][s] || w[2][s] == w[3][s];
+  return e;
+}
 // which slopes of the face's left (k = 0) and right cell are flat (see
-// contracted_branches), from W of its four stencil cells, cell i the left one; the cells
-// beyond them are read where one difference alone is zero
+// contracted_branches), from W of its four stencil cells, cell i the left one, and of
+// the cells beyond them
 template <typename T, int AX>
 __device__ __forceinline__ void flat_slopes(const T* __restrict__ U, long long N, const AxisGeom& g,
                                             int i, int o1, int o2, T gm1, const int (&perm)[5],
                                             const T (&w)[4][5], bool (&flat)[2][5]) {
-  bool below = false, above = false;
+  T lo[5], hi[5];
+  prim_at(U, N, cell_of<AX>(g, bc_map(i - 2, g.n[AX], g.bc), o1, o2), gm1, lo);
+  prim_at(U, N, cell_of<AX>(g, bc_map(i + 3, g.n[AX], g.bc), o1, o2), gm1, hi);
 #pragma unroll
   for (int s = 0; s < 5; ++s) {
     const bool z0 = w[0][s] == w[1][s], z1 = w[1][s] == w[2][s], z2 = w[2][s] == w[3][s];
-    flat[0][s] = flat[1][s] = z1 && (z0 || z2);
-    below = below || (z0 && !z1);
-    above = above || (z2 && !z1);
-  }
-  if (below) {
-    T t[5];
-    prim_at(U, N, cell_of<AX>(g, bc_map(i - 2, g.n[AX], g.bc), o1, o2), gm1, t);
-#pragma unroll
-    for (int s = 0; s < 5; ++s)
-      flat[0][s] = flat[0][s] || (w[0][s] == w[1][s] && t[perm[s]] == w[0][s]);
-  }
-  if (above) {
-    T t[5];
-    prim_at(U, N, cell_of<AX>(g, bc_map(i + 3, g.n[AX], g.bc), o1, o2), gm1, t);
-#pragma unroll
-    for (int s = 0; s < 5; ++s)
-      flat[1][s] = flat[1][s] || (w[2][s] == w[3][s] && t[perm[s]] == w[3][s]);
+    flat[0][s] = (z1 && (z0 || z2)) || (z0 && lo[perm[s]] == w[0][s]);
+    flat[1][s] = (z1 && (z0 || z2)) || (z2 && hi[perm[s]] == w[3][s]);
   }
 }
 
@@ -525,7 +522,7 @@ __global__ __launch_bounds__(256) void k_face_vjp(const T* __restrict__ U, const
     wr[s] = w[2][s] - T(0.5) * sel_value(s1, a1, b1);
     fl |= (s0 << (2 * s)) | (s1 << (10 + 2 * s));
   }
-  if (contracted_branches<T> && LIM != LIM_NONE) {
+  if (contracted_branches<T> && LIM != LIM_NONE && any_equal(w)) {
     bool flat[2][5];
     flat_slopes<T, AX>(U, N, g, i, o1, o2, gm1, perm, w, flat);
 #pragma unroll
@@ -596,7 +593,7 @@ __global__ __launch_bounds__(256) void k_face_vjp_rt(const T* __restrict__ U,
     wl[s] = w[1][s] + T(0.5) * d0;
     wr[s] = w[2][s] - T(0.5) * d1;
   }
-  if (contracted_branches<T> && lim != LIM_NONE) {
+  if (contracted_branches<T> && lim != LIM_NONE && any_equal(w)) {
     bool flat[2][5];
     flat_slopes<T, AX>(U, N, g, i, o1, o2, gm1, perm, w, flat);
 #pragma unroll
@@ -1050,7 +1047,7 @@ __global__ __launch_bounds__(XROW_MAX) void k_x_jtv(const T* __restrict__ U,
     if constexpr (contracted_branches<T>) {
       const T irp = A[4 * nt + tp], irm = A[4 * nt + tm];
       T a[5], b[5], bl[5];  // forward, and backward as the upper and the lower face take it
-      bool zp[5], zm[5], flat[5], above = false, below = false;
+      bool equal = false;
 #pragma unroll
       for (int f = 0; f < 5; ++f) {
         const int k = f == 4 ? 5 : f;
@@ -1069,32 +1066,27 @@ __global__ __launch_bounds__(XROW_MAX) void k_x_jtv(const T* __restrict__ U,
           b[f] = fmad(-um, sm, w[f]);
           bl[f] = fmad(u[f], s0, -wm);
         }
-        zp[f] = wp[f] == w[f];
-        zm[f] = w[f] == wm;
-        flat[f] = zp[f] && zm[f];
-        above = above || (zp[f] && !zm[f]);
-        below = below || (zm[f] && !zp[f]);
+        equal = equal || wp[f] == w[f] || wm == w[f];
       }
-      if (LIM != LIM_NONE && (above || below)) {
-        // equal on one side alone (w[f] on that side): the cell beyond decides
-        const auto in_row = [&](int i) { return i < 0 ? i + n : (i >= n ? i - n : i); };
-        T t[5];
-        if (above) {
-          prim_at(U, N, row * n + in_row(c + 2), gm1, t);
+      if (LIM != LIM_NONE && equal) {
+        // (rare, and so read again:) the slope is flat where W is equal on both
+        // sides, or on one and in the cell beyond; its zero is given no branch
+        T t[4][5];
+        const int at[4] = {c - 2, c - 1, c + 1, c + 2};
 #pragma unroll
-          for (int f = 0; f < 5; ++f) flat[f] = flat[f] || (zp[f] && t[f] == w[f]);
-        }
-        if (below) {
-          prim_at(U, N, row * n + in_row(c - 2), gm1, t);
+        for (int k = 0; k < 4; ++k)
+          prim_at(U, N, row * n + (at[k] < 0 ? at[k] + n : (at[k] >= n ? at[k] - n : at[k])), gm1,
+                  t[k]);
 #pragma unroll
-          for (int f = 0; f < 5; ++f) flat[f] = flat[f] || (zm[f] && t[f] == w[f]);
+        for (int f = 0; f < 5; ++f) {
+          const bool zm = t[1][f] == w[f], zp = t[2][f] == w[f];
+          if ((zm && zp) || (zm && t[0][f] == w[f]) || (zp && t[3][f] == w[f])) a[f] = T(0);
         }
       }
 #pragma unroll
       for (int f = 0; f < 5; ++f) {
-        // a flat slope: a zero, which slope_branch gives no branch
-        dw[f] = slope_branch<T, LIM>(flat[f] ? T(0) : a[f], b[f], fwd[f], bwd[f]);
-        C[f * nt + tid] = slope_branch<T, LIM>(flat[f] ? T(0) : a[f], bl[f], fwl[f], bwl[f]);
+        dw[f] = slope_branch<T, LIM>(a[f], b[f], fwd[f], bwd[f]);
+        C[f * nt + tid] = slope_branch<T, LIM>(a[f], bl[f], fwl[f], bwl[f]);
       }
     } else {
 #pragma unroll
