@@ -1071,17 +1071,22 @@ __global__ __launch_bounds__(XROW_MAX) void k_x_jtv(const T* __restrict__ U,
       if (LIM != LIM_NONE && equal) {
         // (rare, and so read again:) the slope is flat where W is equal on both
         // sides, or on one and in the cell beyond; its zero is given no branch
-        T t[4][5];
-        const int at[4] = {c - 2, c - 1, c + 1, c + 2};
+        // (one cell after another: its registers are the whole kernel's)
+        unsigned same[4];  // by cell, bit f: equal to this cell's
+#pragma unroll 1
+        for (int k = 0; k < 4; ++k) {
+          const int at = c + (k < 2 ? k - 2 : k - 1);
+          T t[5];
+          prim_at(U, N, row * n + (at < 0 ? at + n : (at >= n ? at - n : at)), gm1, t);
+          unsigned m = 0;
 #pragma unroll
-        for (int k = 0; k < 4; ++k)
-          prim_at(U, N, row * n + (at[k] < 0 ? at[k] + n : (at[k] >= n ? at[k] - n : at[k])), gm1,
-                  t[k]);
-#pragma unroll
-        for (int f = 0; f < 5; ++f) {
-          const bool zm = t[1][f] == w[f], zp = t[2][f] == w[f];
-          if ((zm && zp) || (zm && t[0][f] == w[f]) || (zp && t[3][f] == w[f])) a[f] = T(0);
+          for (int f = 0; f < 5; ++f) m |= (t[f] == w[f] ? 1u : 0u) << f;
+          same[k] = m;
         }
+        const unsigned flat = (same[1] & (same[2] | same[0])) | (same[2] & same[3]);
+#pragma unroll
+        for (int f = 0; f < 5; ++f)
+          if ((flat >> f) & 1u) a[f] = T(0);
       }
 #pragma unroll
       for (int f = 0; f < 5; ++f) {
