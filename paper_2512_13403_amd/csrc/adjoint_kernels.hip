@@ -84,14 +84,20 @@ __device__ __forceinline__ T plain_diff(T a, T b) {
 // step does.  fp32 keeps the contracted differences, which decide the near-ties
 // of a varying field as exact arithmetic does more often (gradient of a turbulent
 // 256^3 step against 64 bits: 7.6e-4 off, 7.8e-4 with rounded differences), but
-// takes no branch where W is flat: equal, as rounded, over three cells in a row of
-// which two make one of the slope's differences.  (A single pair of equal
-// neighbours in a varying fp32 field is a coincidence of rounding, about one in
-// 1e5, and decided like the near-ties.)  Which product is contracted is written out,
+// takes no branch where W is flat: where one of the slope's two differences is zero,
+// as rounded, and so is another at most two further (plateaus and their ends, pairs
+// of equal cells).  (A single pair of equal neighbours in a varying fp32 field is a
+// coincidence of rounding, about one in 1e5, and decided like the near-ties.)  Which product is contracted is written out,
 // not left to the compiler, whose choice changes with the code around it: in the
 // lowest of a face's three differences the lower cell's, in the others the upper's.
 template <typename T>
 constexpr bool contracted_branches = sizeof(T) == 4;
+// The fields (a bit each) whose slope is flat, from the zero differences z: bits
+// 5 (k + 3) .. of the difference between cells k and k + 1 of the slope's, k = -3 .. 2
+__device__ __forceinline__ unsigned flat_fields(unsigned z) {
+  const auto d = [&](int k) { return (z >> (5 * (k + 3))) & 31u; };
+  return (d(0) & (d(-2) | d(-1) | d(1) | d(2))) | (d(-1) & (d(-3) | d(-2) | d(0) | d(1)));
+}
 
 // Reverse of the one-sided HLLC assembly of the stage kernel, for face states
 // wl, wr = (rho, v_n, v_t1, v_t2, P) in the face frame.  Fb = dL/dF; writes
@@ -473,22 +479,28 @@ __device__ __forceinline__ bool any_equal(const T (&w)[4][5]) {
     e = e || w[0][s] == w[1][s] || w[1][s] == w[2][s] || w[2][s] == w[3][s];
   return e;
 }
-// which slopes of the face's left (k = 0) and right cell are flat (see
-// contracted_branches), from W of its four stencil cells, cell i the left one, and of
-// the cells beyond them
+// the face-frame fields whose slope in cell i (flat[0]) or i + 1 (flat[1]) is flat
+// (flat_fields), cell i the left one of the face
 template <typename T, int AX>
 __device__ __forceinline__ void flat_slopes(const T* __restrict__ U, long long N, const AxisGeom& g,
                                             int i, int o1, int o2, T gm1, const int (&perm)[5],
-                                            const T (&w)[4][5], bool (&flat)[2][5]) {
-  T lo[5], hi[5];
-  prim_at(U, N, cell_of<AX>(g, bc_map(i - 2, g.n[AX], g.bc), o1, o2), gm1, lo);
-  prim_at(U, N, cell_of<AX>(g, bc_map(i + 3, g.n[AX], g.bc), o1, o2), gm1, hi);
+                                            unsigned (&flat)[2]) {
+  unsigned long long z = 0;
+  T below[5] = {};
+#pragma unroll 1
+  for (int k = -3; k <= 4; ++k) {
+    T t[5];
+    prim_at(U, N, cell_of<AX>(g, bc_map(i + k, g.n[AX], g.bc), o1, o2), gm1, t);
+    unsigned m = 0;
 #pragma unroll
-  for (int s = 0; s < 5; ++s) {
-    const bool z0 = w[0][s] == w[1][s], z1 = w[1][s] == w[2][s], z2 = w[2][s] == w[3][s];
-    flat[0][s] = (z1 && (z0 || z2)) || (z0 && lo[perm[s]] == w[0][s]);
-    flat[1][s] = (z1 && (z0 || z2)) || (z2 && hi[perm[s]] == w[3][s]);
+    for (int s = 0; s < 5; ++s) {
+      m |= (t[perm[s]] == below[s] ? 1u : 0u) << s;
+      below[s] = t[perm[s]];
+    }
+    if (k > -3) z |= (unsigned long long)m << (5 * (k + 2));
   }
+  flat[0] = flat_fields((unsigned)z & 0x3fffffffu);
+  flat[1] = flat_fields((unsigned)(z >> 5));
 }
 
 template <typename T, int LIM, int AX>
@@ -523,13 +535,14 @@ __global__ __launch_bounds__(256) void k_face_vjp(const T* __restrict__ U, const
     fl |= (s0 << (2 * s)) | (s1 << (10 + 2 * s));
   }
   if (contracted_branches<T> && LIM != LIM_NONE && any_equal(w)) {
-    bool flat[2][5];
-    flat_slopes<T, AX>(U, N, g, i, o1, o2, gm1, perm, w, flat);
+    unsigned flat[2];
+    flat_slopes<T, AX>(U, N, g, i, o1, o2, gm1, perm, flat);
 #pragma unroll
     for (int s = 0; s < 5; ++s) {
-      if (flat[0][s]) wl[s] = w[1][s];
-      if (flat[1][s]) wr[s] = w[2][s];
-      fl &= ~((flat[0][s] ? 3 << (2 * s) : 0) | (flat[1][s] ? 3 << (10 + 2 * s) : 0));
+      const bool f0 = (flat[0] >> s) & 1u, f1 = (flat[1] >> s) & 1u;
+      if (f0) wl[s] = w[1][s];
+      if (f1) wr[s] = w[2][s];
+      fl &= ~((f0 ? 3 << (2 * s) : 0) | (f1 ? 3 << (10 + 2 * s) : 0));
     }
   }
   // Fb = (v of the face's right cell - v of its left cell) / h, real cells only
@@ -594,15 +607,15 @@ __global__ __launch_bounds__(256) void k_face_vjp_rt(const T* __restrict__ U,
     wr[s] = w[2][s] - T(0.5) * d1;
   }
   if (contracted_branches<T> && lim != LIM_NONE && any_equal(w)) {
-    bool flat[2][5];
-    flat_slopes<T, AX>(U, N, g, i, o1, o2, gm1, perm, w, flat);
+    unsigned flat[2];
+    flat_slopes<T, AX>(U, N, g, i, o1, o2, gm1, perm, flat);
 #pragma unroll
     for (int s = 0; s < 5; ++s) {
-      if (flat[0][s]) {
+      if ((flat[0] >> s) & 1u) {
         wl[s] = w[1][s];
         pa0[s] = pb0[s] = T(0);
       }
-      if (flat[1][s]) {
+      if ((flat[1] >> s) & 1u) {
         wr[s] = w[2][s];
         pa1[s] = pb1[s] = T(0);
       }
@@ -1069,21 +1082,24 @@ __global__ __launch_bounds__(XROW_MAX) void k_x_jtv(const T* __restrict__ U,
         equal = equal || wp[f] == w[f] || wm == w[f];
       }
       if (LIM != LIM_NONE && equal) {
-        // (rare, and so read again:) the slope is flat where W is equal on both
-        // sides, or on one and in the cell beyond; its zero is given no branch
-        // (one cell after another: its registers are the whole kernel's)
-        unsigned same[4];  // by cell, bit f: equal to this cell's
+        // (rare, and so read again, one cell after another: its registers are the
+        // whole kernel's)  A flat slope's zero is given no branch.
+        unsigned z = 0;
+        T below[5] = {};
 #pragma unroll 1
-        for (int k = 0; k < 4; ++k) {
-          const int at = c + (k < 2 ? k - 2 : k - 1);
+        for (int k = -3; k <= 3; ++k) {
+          const int at = c + k;
           T t[5];
           prim_at(U, N, row * n + (at < 0 ? at + n : (at >= n ? at - n : at)), gm1, t);
           unsigned m = 0;
 #pragma unroll
-          for (int f = 0; f < 5; ++f) m |= (t[f] == w[f] ? 1u : 0u) << f;
-          same[k] = m;
+          for (int f = 0; f < 5; ++f) {
+            m |= (t[f] == below[f] ? 1u : 0u) << f;
+            below[f] = t[f];
+          }
+          if (k > -3) z |= m << (5 * (k + 2));
         }
-        const unsigned flat = (same[1] & (same[2] | same[0])) | (same[2] & same[3]);
+        const unsigned flat = flat_fields(z);
 #pragma unroll
         for (int f = 0; f < 5; ++f)
           if ((flat >> f) & 1u) a[f] = T(0);
