@@ -1359,6 +1359,11 @@ hipError_t mg_solve(char* ws, MGLayout& L, const mh_physics_desc& p, DevClock* c
     if (cycles_out) *cycles_out = 0;
     return hipGetLastError();
   }
+  // the host waits for every test: there is nothing to capture (the null stream
+  // cannot be captured, and is not asked)
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (s) MG_CHECK(hipStreamIsCapturing(s, &capture));
+  if (capture != hipStreamCaptureStatusNone) return hipErrorStreamCaptureUnsupported;
   MG_CHECK(sum_to(P<T>(ws, f.F), N, true, partial, 1.0, &clk->mg_fnorm2, s));
   MG_CHECK(remove_mean(P<T>(ws, f.phi[L.cur0]), N, partial, &clk->mean, s));
   // a tiled fine level leaves the block sums of |r|^2 with its last sweep; phi

@@ -266,3 +266,46 @@ def test_timing_includes_the_reduction_of_a_set_state(where):
     ms, launches = s.timing()
     assert launches[mh.TIME_OTHER] == 2 and ms[mh.TIME_OTHER] > 0.0
     assert list(launches[[mh.TIME_STAGE1, mh.TIME_STAGE2, mh.TIME_PROLOGUE]]) == [4, 4, 4]
+
+
+@pytest.mark.parametrize("solver", [mh.GRAV_MG, mh.GRAV_FFT])
+def test_multigrid_is_refused_inside_a_capture(solver):
+    """The multigrid solve waits for its convergence tests on the host, so a captured
+    step with it is refused, and the solver steps on afterwards; the spectral
+    solve is captured."""
+    import torch
+
+    n = 16
+    grid = mh.grid_desc((n,) * 3, (1.0 / n,) * 3)
+    phys = mh.physics_desc(flags=mh.SRC_GRAVITY, grav_G=2.0, mg_tol=1e-5, grav_solver=solver)
+    U = torch.tensor(wl.grf_density_state(n, seed=5), dtype=torch.float32, device="cuda:0")
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    plain = mh.Solver(grid, phys)
+    with torch.cuda.stream(side):
+        s = mh.Solver(grid, phys)
+    for t in (s, plain):
+        t.set_state(U)
+        t.step(1, 1e-3)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    refused = False
+    with torch.cuda.graph(g, stream=side):
+        try:
+            s.step(1, 1e-3)
+        except mh.MHError:
+            refused = True
+    assert refused == (solver == mh.GRAV_MG)
+    s.set_state(plain.get_state_device())
+    s.set_potential(plain.potential_device())
+    for k in range(3):
+        if refused:
+            s.step(1, 1e-3)
+        else:
+            with torch.cuda.stream(side):
+                g.replay()
+        plain.step(1, 1e-3)
+        torch.cuda.synchronize()
+        got, want = s.get_state_device(), plain.get_state_device()
+        torch.cuda.synchronize()
+        assert torch.equal(got, want), k
